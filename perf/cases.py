@@ -318,3 +318,165 @@ def tolerance(case):
     if case["kind"] == "optimizer":
         return {"rel": 1e-4, "max": 1e-2}
     return {"rel": 1e-2, "max": 0.4}
+
+
+# ---- the same results in binary64, in plain torch, from the inputs that `prepare` makes
+
+def _exact_place(hist, S):
+    """Slots of the classes by popularity: floors, then shrink the most / grow the least rounded up."""
+    pop = [max(int(h), 0) for h in hist]
+    P = sum(pop)
+    if P == 0:
+        pop, P = [1] * len(pop), len(pop)
+    n = [max(1, p * S // P) for p in pop]
+    diff = [c * P - p * S for c, p in zip(n, pop)]
+    while sum(n) > S:
+        i = max((i for i in range(len(n)) if n[i] > 1), key=lambda i: (diff[i], -i))
+        n[i] -= 1
+        diff[i] -= P
+    while sum(n) < S:
+        i = min(range(len(n)), key=lambda i: (diff[i], i))
+        n[i] += 1
+        diff[i] += P
+    return n
+
+
+def _exact_forward(s):
+    c, D, dev = s.case, torch.float64, s.X.device
+    E, k, T, A = c["E"], c["k"], c["T"], c["T"] * c["k"]
+    s.p = torch.softmax(s.logits.to(D), 1)
+    idx = torch.sort(s.logits, dim=1, descending=True, stable=True).indices[:, :k].contiguous()
+    gate = s.p.gather(1, idx)
+    if c["renorm"]:
+        gate = gate / gate.sum(1, keepdim=True)
+    cls = idx.reshape(-1)
+    order = torch.argsort(cls, stable=True)      # rows: assignments by class, in their own order
+    hist = torch.bincount(cls, minlength=E)
+    kept = hist
+    if s.cap:
+        begin = hist.cumsum(0) - hist
+        quota = s.cap * s.counts.to(torch.int64)
+        rank = torch.arange(A, device=dev) - begin[cls[order]]
+        order = order[rank < quota[cls[order]]]
+        kept = torch.minimum(hist, quota)
+    R = order.numel()
+    roa = torch.full((A,), -1, dtype=torch.int64, device=dev)
+    roa[order] = torch.arange(R, device=dev)
+    s.xidx, s.xgate, s.xroa, s.xhist, s.rows = idx, gate, roa.view(T, k), hist.tolist(), kept.tolist()
+    f = c["f"]
+    Xp, UV, H, Yp = (torch.zeros(A, n, dtype=D, device=dev) for n in (c["d"], 2 * f, f, c["d"]))
+    Xp[:R] = s.X.to(D)[order // k]
+    for e, o, n in _classes(s):
+        W1, W2 = _weights(s, e)
+        UV[o:o + n] = Xp[o:o + n] @ W1.t()
+        u, v = UV[o:o + n, :f], UV[o:o + n, f:]
+        H[o:o + n] = u * torch.sigmoid(u) * v
+        Yp[o:o + n] = H[o:o + n] @ W2.t()
+    g = torch.where(s.xroa >= 0, gate, torch.zeros_like(gate))
+    Y = torch.zeros(T, c["d"], dtype=D, device=dev)
+    for j in range(k):
+        Y += g[:, j:j + 1] * Yp[s.xroa[:, j].clamp(min=0)]
+    s.xXp, s.xUV, s.xH, s.xYp = Xp, UV, H, Yp
+    return {"idx": None, "gate": gate, "hist": None, "rows": None, "offsets": None, "Y": Y,
+            "Xp": Xp, "UV": UV, "H": H, "Yp": Yp}
+
+
+def _classes(s):
+    o = 0
+    for e, n in enumerate(s.rows):
+        if n:
+            yield e, o, n
+        o += n
+
+
+def _weights(s, e):
+    q = int(s.first[e])
+    return s.W1[q].double(), s.W2[q].double()
+
+
+def _exact_experts(s, dYp):
+    c, D = s.case, torch.float64
+    E, d, f = c["E"], c["d"], c["f"]
+    dXp = torch.zeros_like(dYp)
+    dW1, dW2 = torch.zeros(E, 2 * f, d, dtype=D, device=dYp.device), torch.zeros(E, d, f, dtype=D, device=dYp.device)
+    for e, o, n in _classes(s):
+        W1, W2 = _weights(s, e)
+        dy, u, v = dYp[o:o + n], s.xUV[o:o + n, :f], s.xUV[o:o + n, f:]
+        dh, sg = dy @ W2, torch.sigmoid(u)
+        duv = torch.cat((dh * v * sg * (1 + u * (1 - sg)), dh * u * sg), 1)
+        dXp[o:o + n] = duv @ W1
+        dW1[e], dW2[e] = duv.t() @ s.xXp[o:o + n], dy.t() @ s.xH[o:o + n]
+    return dXp, dW1, dW2
+
+
+def _exact_backward(s):
+    c, D = s.case, torch.float64
+    dY = s.dY.to(D)
+    dYp, dgate = torch.zeros_like(s.xYp), torch.zeros_like(s.xgate)
+    for j in range(c["k"]):
+        at = s.xroa[:, j]
+        dYp[at] = s.xgate[:, j:j + 1] * dY
+        dgate[:, j] = (dY * s.xYp[at]).sum(1)
+    dXp, dW1, dW2 = _exact_experts(s, dYp)
+    dX = torch.zeros_like(dY)
+    for j in range(c["k"]):
+        dX += dXp[s.xroa[:, j]]
+    ps = s.p.gather(1, s.xidx)
+    if c["renorm"]:
+        dgate = (dgate - (dgate * s.xgate).sum(1, keepdim=True)) / ps.sum(1, keepdim=True)
+    dp = torch.zeros_like(s.p).scatter_(1, s.xidx, dgate)
+    return {"dX": dX, "dlogits": s.p * (dp - (dgate * ps).sum(1, keepdim=True)), "dW1": dW1, "dW2": dW2}
+
+
+def _exact_optimizer(s, hist, dW1, dW2):
+    c, D = s.case, torch.float64
+    E, n1 = c["E"], 2 * c["f"] * c["d"]
+    per = 3 * c["d"] * c["f"] // c["N"]
+    lo = per * s.cfg.shard
+    g = torch.cat((dW1.reshape(E, -1)[:, min(lo, n1):min(lo + per, n1)],
+                   dW2.reshape(E, -1)[:, max(lo - n1, 0):max(lo + per - n1, 0)]), 1).to(D)
+    b1, b2, lr, eps, wd = (float(np.float32(x)) for x in (0.9, 0.999, 1e-4, 1e-8, 0.01))
+    m, v = b1 * s.m.to(D) + (1 - b1) * g, b2 * s.v.to(D) + (1 - b2) * g * g
+    w = s.master.to(D)
+    w = w - lr * (m / (1 - b1 ** s.step) / (torch.sqrt(v / (1 - b2 ** s.step)) + eps) + wd * w)
+    at = torch.repeat_interleave(torch.arange(E), torch.tensor(_exact_place(hist, c["S"]))).to(w.device)
+    W1, W2 = s.W1.to(D), s.W2.to(D)
+    in1 = max(0, min(lo + per, n1) - lo)        # elements of the shard that lie in W1
+    for q, e in enumerate(at.tolist()):         # the slots get the fresh weights rounded to their type
+        fresh = w[e].to(s.W1.dtype).to(D)
+        if in1:
+            W1[q].view(-1)[lo:lo + in1] = fresh[:in1]
+        if in1 < per:
+            W2[q].view(-1)[max(lo - n1, 0):lo + per - n1] = fresh[in1:]
+    return {"placement": None, "master": w, "m": m, "v": v, "W1": W1, "W2": W2}
+
+
+def exact(case, seed):
+    if 8.0 * case["S"] * 3 * case["d"] * case["f"] > 3e10 and case["kind"] != "router":
+        return None         # the slots alone are 30 GB in binary64
+    s = prepare(case, seed)
+    c, D, kind = s.case, torch.float64, case["kind"]
+    if kind == "router":
+        X, Wr, dl = s.X.to(D), s.Wr.to(D), s.dlogits.to(D)
+        dX = dl @ Wr
+        for j in range(c["k"]):
+            dX += s.dXp[s.roa.view(-1, c["k"])[:, j].long()].to(D)
+        return {"logits": X @ Wr.t() + s.b.to(D), "dWr": dl.t() @ X, "db": dl.sum(0), "dX": dX}
+    if kind == "optimizer":
+        return _exact_optimizer(s, s.hist.tolist(), s.dW1, s.dW2)
+    if kind in ("backward", "slots"):       # what the forward saved is given
+        s.rows, s.p = s.hist.tolist(), torch.softmax(s.logits.to(D), 1)
+        s.xidx, s.xgate, s.xroa = s.idx.long(), s.gate.to(D), s.roa.view(-1, c["k"]).long()
+        s.xXp, s.xUV, s.xH, s.xYp = (t.to(D) for t in (s.Xp, s.UV, s.H, s.Yp))
+    if kind == "forward":
+        return _exact_forward(s)
+    if kind == "backward":
+        return _exact_backward(s)
+    if kind == "slots":
+        dXp, dW1, dW2 = _exact_experts(s, s.dYp.to(D))
+        return {"dXp": dXp, "dW1": dW1[s.placement.long()], "dW2": dW2[s.placement.long()]}
+    out = _exact_forward(s)
+    for n in ("Xp", "UV", "H", "Yp"):
+        del out[n]
+    back = _exact_backward(s)
+    return {**out, **back, **_exact_optimizer(s, s.xhist, back["dW1"], back["dW2"])}

@@ -4,7 +4,7 @@
 // weight-gradient GEMM, which sums over every row of a class at once).
 //
 // Six products share one tiled kernel (bf16 inputs, fp32 accumulation on the gfx950
-// MFMA 32x32x16 bf16 instruction; a plain-FMA twin serves fp32 configurations):
+// MFMA 32x32x16 bf16 instruction; kernels on the fp32 MFMA serve fp32 configurations):
 //   FWD1   [u|v] = Xp  * W1^T      + SwiGLU epilogue writing u, v and h = silu(u)*v
 //   FWD2   Yp    = H   * W2^T
 //   BWD_DH dh    = dYp * W2        turned into du, dv from the saved u, v in the epilogue
@@ -795,167 +795,351 @@ __global__ __launch_bounds__(256) void slice_sum_kernel(GemmParams p, int ntx) {
   }
 }
 
-// ---------------------------------------------------------------- fp32 FMA twin
-// Same six products for fp32 activations/weights: 64x64 output tile, 16-deep reduction
-// steps, each thread a 4x4 micro-tile, plain FMAs in fp32.
-// The weight gradients of a small batch are few tiles with long reductions: they also come with
-// a 32x32 tile (2x2 micro-tile) that makes four times as many workgroups.
-constexpr int FK = 16;
+// ---------------------------------------------------------------- fp32 products
+// The same six products for fp32 activations and weights on the fp32 matrix instruction
+// (32x32x2: 64 cycles for 4096 flops per SIMD, twice the rate of plain FMAs).  A wavefront
+// computes 32-row x 32-column blocks; lane l holds row (left) or column (right) l % 32 of an
+// operand, and of every 8 reduction indices the four 4*(l/32) .. +3: both operands agree on that
+// order, so it only permutes the sum.  In the result, lane l holds column l % 32 and its 16
+// registers the rows 8*(r/4) + 4*(l/32) + r%4: stores and the saved u, v are whole 128-byte lines.
+// Two-level summation: every 16 reduction indices are summed in a fresh accumulator and then added,
+// which keeps the rounding error of long reductions (weight gradients) near sqrt(K/16).
+constexpr int F32_CHUNK = 16;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
 
-template <int MODE, int FB>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p) {
-  constexpr int MT = FB / 16;             // micro-tile edge of a thread
-  constexpr int NH = FB * FK / 256;       // elements per operand a thread carries per step
-  static_assert(FB == 64 || (FB == 32 && MODE >= WGRAD2), "32x32 tiles serve the weight gradients");
-  __shared__ float As[FK][FB + 4];
-  __shared__ float Bs[FK][FB + 4];
-  const int tid = threadIdx.x;
-  constexpr bool VARM = MODE <= BWD_DX;
-  int row0, row1, group, kbeg = 0, K;
-  if (VARM) {
-    // fp32 tiles are 64 rows: each 256-row entry of the table is walked in four quarters
-    const int mt = blockIdx.y >> 2;
-    if (mt >= p.tile_map[0]) return;
-    row0 = p.tile_map[4 + 4 * mt] + (blockIdx.y & 3) * FB;
-    row1 = p.tile_map[4 + 4 * mt + 1];
-    if (row0 >= row1) return;
-    row1 = min(row1, row0 + FB);
-    group = p.tile_map[4 + 4 * mt + 2];
-    K = p.K;
-  } else {
-    group = blockIdx.z;
-    row0 = blockIdx.y * FB;
-    row1 = min(p.M, row0 + FB);
-    if (p.per_slot) {
-      kbeg = p.slot_offsets[group];
-      K = p.slot_offsets[group + 1] - kbeg;
+// What both fp32 kernels need to know about a product: its operands, their pitches and extents.
+template <int MODE>
+struct F32Operands {
+  static constexpr bool VARM = MODE <= BWD_DX;
+  static constexpr bool A_KC = VARM;                       // left operand reduction-contiguous
+  static constexpr bool B_KC = MODE == FWD1 || MODE == FWD2;
+  const float* A;    // first tile row (KC) or column 0 of the reduction's first row (KS)
+  const float* B;
+  long long lda, ldb;
+  int row0, row1, group, K;
+
+  // tile `part` of 256 / `rows` parts of a table entry (variable rows), or row tile `part` of a group
+  __device__ __forceinline__ bool init(const GemmParams& p, int rows, int y, int z) {
+    int kbeg = 0;
+    if (VARM) {
+      const int parts = GEMM_BM / rows, mt = y / parts;
+      if (mt >= p.tile_map[0]) return false;
+      row0 = p.tile_map[4 + 4 * mt] + (y % parts) * rows;
+      row1 = p.tile_map[4 + 4 * mt + 1];
+      if (row0 >= row1) return false;
+      row1 = min(row1, row0 + rows);
+      group = p.tile_map[4 + 4 * mt + 2];
+      K = p.K;
     } else {
-      kbeg = p.slot_offsets[p.first_slot[group]];
-      K = p.slot_offsets[p.first_slot[group + 1]] - kbeg;
-    }
-    if (K == 0 && p.skip_empty) return;
-  }
-  const int n0 = blockIdx.x * (MODE == FWD1 ? FB / 2 : FB);
-  const float* A = static_cast<const float*>(p.A);
-  const float* B = static_cast<const float*>(p.B) + (VARM ? (long long)group * p.b_group_stride : 0);
-  const long long d = p.d, f = p.f;
-
-  // element (tile row i, reduction index k) of each operand, or 0 outside
-  auto a_at = [&](int i, int k) -> float {
-    const int r = row0 + i;
-    if (r >= row1 || k >= K) return 0.f;
-    switch (MODE) {
-      case FWD1: return A[r * d + k];
-      case FWD2: return A[r * f + k];
-      case BWD_DH: return A[r * d + k];
-      case BWD_DX: return A[r * 2 * f + k];
-      case WGRAD2: return A[(long long)(kbeg + k) * d + r];
-      default: return A[(long long)(kbeg + k) * 2 * f + r];
-    }
-  };
-  auto b_at = [&](int j, int k) -> float {
-    if (k >= K) return 0.f;
-    switch (MODE) {
-      case FWD1: {  // tile columns 0..31 gate, 32..63 up of hidden units n0..n0+31
-        const int hu = n0 + (j & 31);
-        if (hu >= f) return 0.f;
-        return B[((j >> 5) ? f + hu : hu) * d + k];
+      group = p.per_slot ? z : p.class_order[z];   // long reductions first
+      row0 = y * rows;
+      row1 = min(p.M, row0 + rows);
+      if (p.per_slot) {
+        kbeg = p.slot_offsets[group];
+        K = p.slot_offsets[group + 1] - kbeg;
+      } else {
+        kbeg = p.slot_offsets[p.first_slot[group]];
+        K = p.slot_offsets[p.first_slot[group + 1]] - kbeg;
       }
-      case FWD2: return n0 + j < p.N ? B[(long long)(n0 + j) * f + k] : 0.f;
-      case BWD_DH: return n0 + j < p.N ? B[(long long)k * f + n0 + j] : 0.f;
-      case BWD_DX: return n0 + j < p.N ? B[(long long)k * d + n0 + j] : 0.f;
-      case WGRAD2: return n0 + j < p.N ? B[(long long)(kbeg + k) * f + n0 + j] : 0.f;
-      default: return n0 + j < p.N ? B[(long long)(kbeg + k) * d + n0 + j] : 0.f;
+      if (K == 0 && p.skip_empty) return false;
+    }
+    lda = MODE == FWD2 ? p.f : (MODE == BWD_DX || MODE == WGRAD1) ? 2LL * p.f : p.d;
+    ldb = (MODE == FWD1 || MODE == BWD_DX || MODE == WGRAD1) ? p.d : p.f;
+    A = static_cast<const float*>(p.A) + (VARM ? (long long)row0 * lda : (long long)kbeg * lda + row0);
+    B = static_cast<const float*>(p.B) + (VARM ? (long long)group * p.b_group_stride : (long long)kbeg * ldb);
+    return true;
+  }
+};
+
+// value x (for FWD1 also its up half v) of output element (row, col)
+template <int MODE>
+__device__ __forceinline__ void f32_store(const GemmParams& p, int group, long long row, int col, float x, float v) {
+  const long long f = p.f;
+  if (MODE == FWD1) {
+    float* UVo = static_cast<float*>(p.UVout);
+    UVo[row * 2 * f + col] = x;
+    UVo[row * 2 * f + f + col] = v;
+    static_cast<float*>(p.H)[row * f + col] = silu_f(x) * v;
+  } else if (MODE == FWD2 || MODE == BWD_DX) {
+    static_cast<float*>(p.C)[row * p.N + col] = x;
+  } else if (MODE == BWD_DH) {
+    const float* UVi = static_cast<const float*>(p.UV);
+    const float u = UVi[row * 2 * f + col], vv = UVi[row * 2 * f + f + col];
+    const float sg = sigmoid_f(u);
+    float* Co = static_cast<float*>(p.C);
+    Co[row * 2 * f + col] = x * vv * sg * (1.f + u * (1.f - sg));
+    Co[row * 2 * f + f + col] = x * u * sg;
+  } else {
+    (static_cast<float*>(p.C) + (long long)group * p.c_group_stride)[row * p.N + col] = x;
+  }
+}
+
+// Tile of 64 rows x 64 NBL columns (FWD1: the gate and up columns of 64 hidden units), 32-deep steps
+// through LDS, four wavefronts of 32 x 32 NBL.  The next step's loads sit in registers while the
+// current one feeds the matrix pipes; three to five workgroups share a compute unit and cover each
+// other's barriers.  Rows and columns beyond the tile's extent are clamped to a valid one (they
+// only reach outputs that are never stored), reduction indices beyond K are zeros in both
+// operands.  A wavefront whose outputs all lie outside multiplies nothing.
+// Bound by the matrix pipes once a few workgroups share a unit (E = 24, 9000 rows in 36 slots,
+// d = 328, f = 872: first forward product 160 us, 59 % of the cycles are MFMAs, 13 % of them padding of
+// ragged slots; the plain-FMA kernel took 238, the six products together 1070 -> 700 us).
+constexpr int F32_BM = 64, F32_BK = 32;
+
+template <int MODE, int NBL>
+__global__ __launch_bounds__(256, NBL == 2 ? 3 : 5) void gemm_f32_kernel(GemmParams p) {
+  using Op = F32Operands<MODE>;
+  static_assert(NBL == 2 || (NBL == 1 && MODE != FWD1), "the gate and up columns of a hidden unit go together");
+  constexpr int F32_BN = 64 * NBL, NBP = 2 * NBL;   // tile columns; 16-byte pieces of the right operand per thread
+  constexpr int LDK = F32_BK + 4;              // [row][k]: 16-byte reads of 16 rows hit all 64 banks once
+  constexpr int LDA = F32_BM + 8, LDB = F32_BN + 8;   // [k][row]: rows 4 apart are 32 banks apart
+  __shared__ __attribute__((aligned(16))) float As[Op::A_KC ? F32_BM * LDK : F32_BK * LDA];
+  __shared__ __attribute__((aligned(16))) float Bs[Op::B_KC ? F32_BN * LDK : F32_BK * LDB];
+  Op o;
+  if (!o.init(p, F32_BM, blockIdx.y, blockIdx.z)) return;
+  const int K = o.K, N = MODE == FWD1 ? p.f : p.N;
+  const int n0 = blockIdx.x * (MODE == FWD1 ? F32_BN / 2 : F32_BN);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1, r31 = lane & 31, hw = lane >> 5;
+
+  // 16-byte pieces of a step: 2 of the left operand and 4 of the right one per thread, each at a
+  // wave-uniform base (tile and step) plus a 32-bit byte offset inside the tile (at most 128 rows of
+  // 2^22 elements)
+  unsigned oa[2], ob[NBP];
+  int ka[2], kb[NBP];                            // reduction index of the piece within a step
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int e = tid + 256 * h, c = (e & 15) * 4;
+    ka[h] = Op::A_KC ? (e & 7) * 4 : e >> 4;
+    oa[h] = Op::A_KC ? (unsigned)(min(e >> 3, o.row1 - o.row0 - 1) * (int)o.lda + ka[h]) * 4u
+                     : (unsigned)(ka[h] * (int)o.lda + (c < o.row1 - o.row0 ? c : 0)) * 4u;
+  }
+#pragma unroll
+  for (int h = 0; h < NBP; ++h) {
+    const int e = tid + 256 * h, c = (e & (F32_BN / 4 - 1)) * 4;
+    kb[h] = Op::B_KC ? (e & 7) * 4 : e / (F32_BN / 4);
+    // FWD1: the 64 tile columns of a wavefront are 32 gate and the 32 up columns of the same hidden
+    // units; piece h is a gate column for even h and an up column for odd h
+    const int t = MODE == FWD1 ? (h >> 1) * 32 + ((e >> 3) & 31) : e >> 3;
+    ob[h] = Op::B_KC ? (unsigned)(min(t, N - 1 - n0) * (int)o.ldb + kb[h]) * 4u
+                     : (unsigned)(kb[h] * (int)o.ldb + (n0 + c < N ? c : 0)) * 4u;
+  }
+  const float* const b0 = o.B + (Op::B_KC ? n0 * o.ldb : n0);
+  floatx4 na[2], nb[NBP];
+  auto fetch = [&](int k0) {
+    const bool whole = k0 + F32_BK <= K;
+    const char* const qa = reinterpret_cast<const char*>(o.A + (Op::A_KC ? k0 : k0 * o.lda));
+    const char* const qb = reinterpret_cast<const char*>(b0 + (Op::B_KC ? k0 : k0 * o.ldb));
+    const char* const qu = MODE == FWD1 ? qb + 4LL * p.f * o.ldb : qb;
+    if (whole) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) na[h] = *reinterpret_cast<const floatx4*>(qa + oa[h]);
+#pragma unroll
+      for (int h = 0; h < NBP; ++h) nb[h] = *reinterpret_cast<const floatx4*>((h & 1 ? qu : qb) + ob[h]);
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        na[h] = floatx4{0.f, 0.f, 0.f, 0.f};
+        if (k0 + ka[h] < K) na[h] = *reinterpret_cast<const floatx4*>(qa + oa[h]);
+      }
+#pragma unroll
+      for (int h = 0; h < NBP; ++h) {
+        nb[h] = floatx4{0.f, 0.f, 0.f, 0.f};
+        if (k0 + kb[h] < K) nb[h] = *reinterpret_cast<const floatx4*>((h & 1 ? qu : qb) + ob[h]);
+      }
     }
   };
-  constexpr bool A_KC = VARM, B_KC = MODE == FWD1 || MODE == FWD2;
-
-  float acc[MT][MT] = {};
-  const int ty = tid >> 4, tx = tid & 15;  // rows ty*MT.., cols tx + 16*c (FWD1 pairs gate/up)
-  // each thread carries 4 + 4 elements of a step from memory to LDS; the elements of the next
-  // step are fetched into registers before the current step's FMAs, so their latency hides
-  // behind them.  Operands are walked along their contiguous index for coalescing.
-  float na[NH], nb[NH];
-  auto fetch = [&](int k0) {
+  auto commit = [&]() {
 #pragma unroll
-    for (int h = 0; h < NH; ++h) {
+    for (int h = 0; h < 2; ++h) {
       const int e = tid + 256 * h;
-      const int ai = A_KC ? e / FK : e % FB, ak = A_KC ? e % FK : e / FB;
-      na[h] = a_at(ai, k0 + ak);
-      const int bj = B_KC ? e / FK : e % FB, bk = B_KC ? e % FK : e / FB;
-      nb[h] = b_at(bj, k0 + bk);
+      *reinterpret_cast<floatx4*>(As + (Op::A_KC ? (e >> 3) * LDK + (e & 7) * 4 : (e >> 4) * LDA + (e & 15) * 4)) = na[h];
+    }
+#pragma unroll
+    for (int h = 0; h < NBP; ++h) {
+      const int e = tid + 256 * h;
+      *reinterpret_cast<floatx4*>(Bs + (Op::B_KC ? (e >> 3) * LDK + (e & 7) * 4 : e / (F32_BN / 4) * LDB + (e & (F32_BN / 4 - 1)) * 4)) = nb[h];
+    }
+  };
+  const int col0 = n0 + wn * (MODE == FWD1 ? 32 : 32 * NBL);
+  const bool busy = wm * 32 < o.row1 - o.row0 && col0 < N;   // this wavefront holds outputs
+
+  floatx16 acc[NBL];
+#pragma unroll
+  for (int j = 0; j < NBL; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+  auto multiply = [&]() {
+#pragma unroll
+    for (int c = 0; c < F32_BK / F32_CHUNK; ++c) {
+      floatx16 part[NBL];
+#pragma unroll
+      for (int j = 0; j < NBL; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) part[j][r] = 0.f;
+#pragma unroll
+      for (int s = 0; s < F32_CHUNK / 8; ++s) {
+        const int k = c * F32_CHUNK + s * 8 + 4 * hw;
+        float a[4], b[NBL][4];
+        if (Op::A_KC) {
+          const float4 q = *reinterpret_cast<const float4*>(As + (wm * 32 + r31) * LDK + k);
+          a[0] = q.x; a[1] = q.y; a[2] = q.z; a[3] = q.w;
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) a[i] = As[(k + i) * LDA + wm * 32 + r31];
+        }
+#pragma unroll
+        for (int j = 0; j < NBL; ++j) {
+          if (Op::B_KC) {
+            const float4 q = *reinterpret_cast<const float4*>(Bs + (wn * 32 * NBL + j * 32 + r31) * LDK + k);
+            b[j][0] = q.x; b[j][1] = q.y; b[j][2] = q.z; b[j][3] = q.w;
+          } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) b[j][i] = Bs[(k + i) * LDB + wn * 32 * NBL + j * 32 + r31];
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < NBL; ++j)
+            part[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j][i], part[j], 0, 0, 0);
+      }
+#pragma unroll
+      for (int j = 0; j < NBL; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[j][r] += part[j][r];
     }
   };
   if (K > 0) fetch(0);
-  for (int k0 = 0; k0 < K; k0 += FK) {
-#pragma unroll
-    for (int h = 0; h < NH; ++h) {
-      const int e = tid + 256 * h;
-      const int ai = A_KC ? e / FK : e % FB, ak = A_KC ? e % FK : e / FB;
-      As[ak][ai] = na[h];
-      const int bj = B_KC ? e / FK : e % FB, bk = B_KC ? e % FK : e / FB;
-      Bs[bk][bj] = nb[h];
-    }
+  for (int k0 = 0; k0 < K; k0 += F32_BK) {
+    commit();
     __syncthreads();
-    if (k0 + FK < K) fetch(k0 + FK);
-    // two-level summation: each 16-deep partial sum is formed on its own and then added,
-    // which keeps the rounding error of long reductions (weight gradients) near sqrt(K/16)
-    float part[MT][MT] = {};
-#pragma unroll
-    for (int k = 0; k < FK; ++k) {
-      float a[MT], b[MT];
-#pragma unroll
-      for (int i = 0; i < MT; ++i) a[i] = As[k][ty * MT + i];
-#pragma unroll
-      for (int c = 0; c < MT; ++c) b[c] = Bs[k][tx + 16 * c];
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int c = 0; c < MT; ++c) part[i][c] = fmaf(a[i], b[c], part[i][c]);
-    }
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-      for (int c = 0; c < MT; ++c) acc[i][c] += part[i][c];
+    if (k0 + F32_BK < K) fetch(k0 + F32_BK);
+    if (busy) multiply();
     __syncthreads();
   }
 
 #pragma unroll
-  for (int i = 0; i < MT; ++i) {
-    const int row = row0 + ty * MT + i;
-    if (row >= row1) continue;
-    if constexpr (MODE == FWD1) {
-      // columns tx, tx+16 are gate of hidden units n0+tx, n0+tx+16; tx+32, tx+48 their up
+  for (int j = 0; j < (MODE == FWD1 ? 1 : NBL); ++j) {
+    const int col = col0 + j * 32 + r31;
+    if (!busy || col >= N) continue;
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        const int hu = n0 + tx + 16 * c;
-        if (hu >= f) continue;
-        const float u = acc[i][c], v = acc[i][c + 2];
-        float* UVo = static_cast<float*>(p.UVout);
-        UVo[row * 2 * f + hu] = u;
-        UVo[row * 2 * f + f + hu] = v;
-        static_cast<float*>(p.H)[row * f + hu] = silu_f(u) * v;
+    for (int r = 0; r < 16; ++r) {
+      const int row = o.row0 + wm * 32 + 8 * (r >> 2) + 4 * hw + (r & 3);
+      if (row < o.row1) f32_store<MODE>(p, o.group, row, col, acc[j][r], acc[NBL - 1][r]);
+    }
+  }
+}
+
+// A small batch has too few 64 x 128 tiles to fill the chip, and the time of one tile is its
+// reduction's latency.  Here a tile is 32 x 32 (FWD1: 32 hidden units, gate and up) and NW
+// wavefronts share its reduction, each streaming its own range of reduction indices straight from
+// memory into registers (no LDS, no barrier; the next 16 indices are in flight during the current
+// ones' products); their sums meet in LDS in a fixed order.  8 experts of 128 x 256, 2048 rows: the six
+// products take 14, 8, 13, 9, 13 and 13 us, where plain FMAs took 16, 22, 42, 19, 42 and 46.
+template <int MODE, int NW>
+__global__ __launch_bounds__(64 * NW) void gemm_f32_small_kernel(GemmParams p) {
+  using Op = F32Operands<MODE>;
+  constexpr int NB = MODE == FWD1 ? 2 : 1;
+  constexpr int LDR = 40;                      // rows 4 apart are 32 banks apart
+  __shared__ float red[NW][NB][32 * LDR];
+  Op o;
+  if (!o.init(p, 32, blockIdx.y, blockIdx.z)) return;
+  const int K = o.K, N = MODE == FWD1 ? p.f : p.N;
+  const int n0 = blockIdx.x * 32;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r31 = lane & 31, hw = lane >> 5;
+  const int per = (K + NW * F32_CHUNK - 1) / (NW * F32_CHUNK) * F32_CHUNK;
+  const int kbeg = wave * per, kend = min(K, kbeg + per);
+  const int ra = min(r31, o.row1 - o.row0 - 1), rb = min(n0 + r31, N - 1);
+  const float* const pa = o.A + (Op::A_KC ? ra * o.lda : ra);
+  const float* const pb = o.B + (Op::B_KC ? rb * o.ldb : rb);
+
+  // 16 reduction indices: value 4 s + i is index k0 + 8 s + 4 hw + i
+  auto load = [&](int k0, float (&a)[8], float (&b)[NB][8]) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int k = k0 + 8 * s + 4 * hw;
+      // reduction-contiguous operands have K % 8 == 0: four indices are in or out together
+      if (Op::A_KC) {
+        const bool ok = k < kend;
+        const float4 q = *reinterpret_cast<const float4*>(pa + (ok ? k : 0));
+        a[4 * s] = ok ? q.x : 0.f; a[4 * s + 1] = ok ? q.y : 0.f; a[4 * s + 2] = ok ? q.z : 0.f; a[4 * s + 3] = ok ? q.w : 0.f;
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const bool ok = k + i < kend;
+          const float q = pa[(ok ? k + i : 0) * o.lda];
+          a[4 * s + i] = ok ? q : 0.f;
+        }
       }
-    } else {
 #pragma unroll
-      for (int c = 0; c < MT; ++c) {
-        const int col = n0 + tx + 16 * c;
-        if (col >= p.N) continue;
-        const float x = acc[i][c];
-        if (MODE == FWD2 || MODE == BWD_DX) {
-          static_cast<float*>(p.C)[(long long)row * p.N + col] = x;
-        } else if (MODE == BWD_DH) {
-          const float* UVi = static_cast<const float*>(p.UV);
-          const float u = UVi[row * 2 * f + col], v = UVi[row * 2 * f + f + col];
-          const float sg = sigmoid_f(u);
-          float* Co = static_cast<float*>(p.C);
-          Co[row * 2 * f + col] = x * v * sg * (1.f + u * (1.f - sg));
-          Co[row * 2 * f + f + col] = x * u * sg;
+      for (int j = 0; j < NB; ++j) {
+        const float* const pj = pb + (j ? (long long)p.f * o.ldb : 0);
+        if (Op::B_KC) {
+          const bool ok = k < kend;
+          const float4 q = *reinterpret_cast<const float4*>(pj + (ok ? k : 0));
+          b[j][4 * s] = ok ? q.x : 0.f; b[j][4 * s + 1] = ok ? q.y : 0.f; b[j][4 * s + 2] = ok ? q.z : 0.f; b[j][4 * s + 3] = ok ? q.w : 0.f;
         } else {
-          (static_cast<float*>(p.C) + (long long)group * p.c_group_stride)[(long long)row * p.N + col] = x;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const bool ok = k + i < kend;
+            const float q = pj[(ok ? k + i : 0) * o.ldb];
+            b[j][4 * s + i] = ok ? q : 0.f;
+          }
         }
       }
     }
+  };
+  floatx16 acc[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+  auto multiply = [&](const float (&a)[8], const float (&b)[NB][8]) {
+    floatx16 part[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) part[j][r] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) part[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j][i], part[j], 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[j][r] += part[j][r];
+  };
+  if (kbeg < kend) {
+    float a0[8], a1[8], b0[NB][8], b1[NB][8];
+    load(kbeg, a0, b0);
+    for (int k0 = kbeg; k0 < kend; k0 += 2 * F32_CHUNK) {
+      if (k0 + F32_CHUNK < kend) load(k0 + F32_CHUNK, a1, b1);
+      multiply(a0, b0);
+      if (k0 + F32_CHUNK >= kend) break;
+      if (k0 + 2 * F32_CHUNK < kend) load(k0 + 2 * F32_CHUNK, a0, b0);
+      multiply(a1, b1);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) red[wave][j][(8 * (r >> 2) + 4 * hw + (r & 3)) * LDR + r31] = acc[j][r];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 1024 / (64 * NW); ++i) {
+    const int e = tid + 64 * NW * i, r = e >> 5, col = n0 + (e & 31);
+    if (o.row0 + r >= o.row1 || col >= N) continue;
+    float x[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      x[j] = red[0][j][r * LDR + (e & 31)];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) x[j] += red[w][j][r * LDR + (e & 31)];
+    }
+    f32_store<MODE>(p, o.group, o.row0 + r, col, x[0], x[NB - 1]);
   }
 }
 
@@ -974,19 +1158,28 @@ static void launch_gemm(const symi_ctx* ctx, const GemmParams& p, int n_cols, in
     if (may_slice)   // the sliced round holds at most cus / 2 tiles
       SYMI_TIMED(ctx, K_SLICE_SUM, st, (slice_sum_kernel<<<dim3(BM / 16, std::max(1, p.cus / 2)), 256, 0, st>>>(p, ntx)));
   } else {
-    constexpr int FB = 64;
-    const int bn = MODE == FWD1 ? FB / 2 : FB;
+    constexpr bool VARM = MODE <= BWD_DX;
+    constexpr int NW = VARM ? 4 : 8;
     const int groups = p.per_slot ? cfg->S_tot : cfg->E;
-    if constexpr (MODE >= WGRAD2) {
-      // few tiles (a small batch leaves most of them to a handful of classes): quarter tiles
-      if ((long long)cdiv(n_cols, FB) * cdiv(p.M, FB) * groups < 4LL * ctx->cus) {
-        dim3 grid(cdiv(n_cols, 32), cdiv(p.M, 32), groups);
-        SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_f32_kernel<MODE, 32><<<grid, 256, 0, st>>>(p)));
+    const int ntx = cdiv(n_cols, MODE == FWD1 ? 64 : 128);
+    // Count of 64 x 128 tiles (variable rows: about half a tile of padding per slot).  Below one
+    // round of them the shared reduction, below four the 64-wide tile, which makes twice as many
+    // workgroups: 475 tiles, second forward product 135 us shared / 99 us 64 wide / 113 us 128 wide,
+    // input gradient 250 / 203 / 268; at 2240 tiles 128 wide reads its left operand half as often.
+    const long long rows = VARM ? (long long)cfg->T * cfg->k / F32_BM + cfg->S_tot / 2 : (long long)cdiv(p.M, F32_BM) * groups;
+    if (rows * ntx < 1LL * ctx->cus && 8LL * max_mtiles <= 65535) {
+      dim3 grid(cdiv(n_cols, 32), VARM ? 8 * max_mtiles : cdiv(p.M, 32), VARM ? 1 : groups);
+      SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_f32_small_kernel<MODE, NW><<<grid, 64 * NW, 0, st>>>(p)));
+      return;
+    }
+    const int gy = VARM ? 4 * max_mtiles : cdiv(p.M, F32_BM), gz = VARM ? 1 : groups;
+    if constexpr (MODE != FWD1) {
+      if (rows * ntx < 4LL * ctx->cus) {
+        SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_f32_kernel<MODE, 1><<<dim3(cdiv(n_cols, 64), gy, gz), 256, 0, st>>>(p)));
         return;
       }
     }
-    dim3 grid(cdiv(n_cols, bn), MODE <= BWD_DX ? 4 * max_mtiles : cdiv(p.M, FB), MODE <= BWD_DX ? 1 : groups);
-    SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_f32_kernel<MODE, 64><<<grid, 256, 0, st>>>(p)));
+    SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_f32_kernel<MODE, 2><<<dim3(ntx, gy, gz), 256, 0, st>>>(p)));
   }
 }
 

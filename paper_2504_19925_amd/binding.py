@@ -1,11 +1,19 @@
-"""ctypes binding of libsymi.so: same names as the C ABI, argument marshalling only.
+"""Binding of libsymi.so: same names as the C ABI, argument marshalling only.
 
 Tensors must live on the GPU (except where the C function takes host pointers), be
 contiguous and have the dtype the header states; the current torch stream is passed
-through.  There is no fallback: if the library is missing or a call fails, SymiError
+through.  There is no fallback: if a library is missing or a call fails, SymiError
 is raised.
+
+The calls that enqueue GPU work go through _marshal.so (csrc/marshal.cpp), which does the
+checks below in C++.  What it declines (keyword arguments, tensor subclasses, anything a
+check would refuse) takes the ctypes path written out here, which either accepts it or names
+the argument at fault.
 """
 import ctypes
+import functools
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
@@ -143,8 +151,40 @@ def lib():
             fn = getattr(L, name)
             fn.argtypes = args
             fn.restype = res
+        _marshal.update(_load_marshal(L))
         _LIB = L
     return _LIB
+
+
+_marshal = {}   # name -> function of _marshal.so, filled when libsymi.so is loaded
+
+
+def _load_marshal(L):
+    path = os.path.join(_HERE, "_marshal.so")
+    if not os.path.exists(path):
+        raise SymiError(f"{path} not found: build it with `python -m paper_2504_19925_amd.build`")
+    name = __package__ + "._marshal" if __package__ else "_marshal"
+    loader = importlib.machinery.ExtensionFileLoader(name, path)
+    mod = importlib.util.module_from_spec(importlib.util.spec_from_file_location(name, path, loader=loader))
+    loader.exec_module(mod)
+    mod.attach({n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in EXPORTS}, SymiCtx, SymiAdam)
+    return {n: getattr(mod, n) for n in EXPORTS if hasattr(mod, n)}
+
+
+def _device_call(slow):
+    """A call that _marshal.so knows; `slow` is the same call through ctypes."""
+    name = slow.__name__
+
+    @functools.wraps(slow)
+    def call(*args, **kw):
+        fast = None if kw else _marshal.get(name)
+        rc = fast(*args) if fast else None
+        if rc is None:
+            return slow(*args, **kw)
+        if rc:
+            _check(rc, name)
+
+    return call
 
 
 def symi_last_error():
@@ -228,12 +268,14 @@ def symi_workspace_bytes(cfg):
     return lib().symi_workspace_bytes(ctypes.byref(_cfg_of(cfg)))
 
 
+@_device_call
 def symi_route(ctx, logits, idx, gate, hist):
     _check(lib().symi_route(ctx.ptr, _dev(logits, F32, "logits", ctx.T * ctx.E),
                             _dev(idx, I32, "idx", ctx.A), _dev(gate, F32, "gate", ctx.A),
                             _dev(hist, I32, "hist", ctx.E), _stream()), "symi_route")
 
 
+@_device_call
 def symi_route_bwd(ctx, logits, idx, gate, dgate, dlogits):
     _check(lib().symi_route_bwd(ctx.ptr, _dev(logits, F32, "logits", ctx.T * ctx.E),
                                 _dev(idx, I32, "idx", ctx.A), _dev(gate, F32, "gate", ctx.A),
@@ -242,6 +284,7 @@ def symi_route_bwd(ctx, logits, idx, gate, dgate, dlogits):
            "symi_route_bwd")
 
 
+@_device_call
 def symi_place(ctx, popularity, counts, placement, first_slot):
     _check(lib().symi_place(ctx.ptr, _dev(popularity, I32, "popularity", ctx.E),
                             _dev(counts, I32, "counts", ctx.E),
@@ -257,6 +300,7 @@ def symi_place_host(cfg, popularity, counts, placement, first_slot):
                                  _host_i32(first_slot, "first_slot", cfg.E + 1)), "symi_place_host")
 
 
+@_device_call
 def symi_dispatch(ctx, X, idx, hist, counts, first_slot, row_of_assign, assign_of_row,
                   slot_offsets, Xp, ws):
     dt = ctx.torch_dtype
@@ -270,6 +314,7 @@ def symi_dispatch(ctx, X, idx, hist, counts, first_slot, row_of_assign, assign_o
         _dev(ws, torch.uint8, "ws", symi_workspace_bytes(ctx.cfg)), _stream()), "symi_dispatch")
 
 
+@_device_call
 def symi_dispatch_noalloc(ctx, X, idx, hist, counts, first_slot, row_of_assign, assign_of_row,
                           slot_offsets, Xp):
     dt = ctx.torch_dtype
@@ -291,6 +336,7 @@ def symi_slot_capacity(cfg, capacity_factor):
     return rc
 
 
+@_device_call
 def symi_dispatch_capacity(ctx, slot_capacity, X, idx, hist, counts, first_slot, row_of_assign,
                            assign_of_row, slot_offsets, Xp, ws):
     dt = ctx.torch_dtype
@@ -338,6 +384,7 @@ def symi_comm_cost(E, N, s, G, W, O, bw_pci, bw_net):
     return {n: getattr(out, n) for n, _ in SymiCostOut._fields_}
 
 
+@_device_call
 def symi_dispatch_bwd(ctx, dXp, row_of_assign, dX):
     dt = ctx.torch_dtype
     _check(lib().symi_dispatch_bwd(ctx.ptr, _dev(dXp, dt, "dXp", ctx.A * ctx.d),
@@ -345,6 +392,7 @@ def symi_dispatch_bwd(ctx, dXp, row_of_assign, dX):
                                    _dev(dX, dt, "dX", ctx.T * ctx.d), _stream()), "symi_dispatch_bwd")
 
 
+@_device_call
 def symi_expert_fwd(ctx, Xp, slot_offsets, W1_slots, W2_slots, UV, H, Yp, ws):
     dt = ctx.torch_dtype
     nw = ctx.S_tot * ctx.d * ctx.f
@@ -372,18 +420,21 @@ def _expert_bwd_class(name, ctx, dYp, Xp, UV, H, slot_offsets, first_slot, W1_sl
         _dev(ws, torch.uint8, "ws", symi_workspace_bytes(ctx.cfg)), _stream()), name)
 
 
+@_device_call
 def symi_expert_bwd(ctx, dYp, Xp, UV, H, slot_offsets, first_slot, W1_slots, W2_slots, dXp,
                     dW1_class, dW2_class, ws):
     _expert_bwd_class("symi_expert_bwd", ctx, dYp, Xp, UV, H, slot_offsets, first_slot, W1_slots,
                       W2_slots, dXp, dW1_class, dW2_class, ws)
 
 
+@_device_call
 def symi_expert_bwd_active(ctx, dYp, Xp, UV, H, slot_offsets, first_slot, W1_slots, W2_slots, dXp,
                            dW1_class, dW2_class, ws):
     _expert_bwd_class("symi_expert_bwd_active", ctx, dYp, Xp, UV, H, slot_offsets, first_slot,
                       W1_slots, W2_slots, dXp, dW1_class, dW2_class, ws)
 
 
+@_device_call
 def symi_expert_bwd_slots(ctx, dYp, Xp, UV, H, slot_offsets, first_slot, W1_slots, W2_slots, dXp,
                           dW1_slot, dW2_slot, ws):
     dt = ctx.torch_dtype
@@ -398,6 +449,7 @@ def symi_expert_bwd_slots(ctx, dYp, Xp, UV, H, slot_offsets, first_slot, W1_slot
         _dev(ws, torch.uint8, "ws", symi_workspace_bytes(ctx.cfg)), _stream()), "symi_expert_bwd_slots")
 
 
+@_device_call
 def symi_replica_allreduce(ctx, first_slot, scale, dW1_slot, dW2_slot):
     nw = ctx.S_tot * ctx.d * ctx.f
     _check(lib().symi_replica_allreduce(
@@ -406,6 +458,7 @@ def symi_replica_allreduce(ctx, first_slot, scale, dW1_slot, dW2_slot):
         "symi_replica_allreduce")
 
 
+@_device_call
 def symi_router_fwd(ctx, X, Wr, b, logits):
     dt = ctx.torch_dtype
     _check(lib().symi_router_fwd(
@@ -414,6 +467,7 @@ def symi_router_fwd(ctx, X, Wr, b, logits):
         _stream()), "symi_router_fwd")
 
 
+@_device_call
 def symi_router_bwd(ctx, X, Wr, dlogits, dWr, db, dX, ws):
     dt = ctx.torch_dtype
     _check(lib().symi_router_bwd(
@@ -423,6 +477,7 @@ def symi_router_bwd(ctx, X, Wr, dlogits, dWr, db, dX, ws):
         _dev(ws, torch.uint8, "ws", symi_workspace_bytes(ctx.cfg)), _stream()), "symi_router_bwd")
 
 
+@_device_call
 def symi_combine(ctx, Yp, row_of_assign, gate, Y):
     dt = ctx.torch_dtype
     _check(lib().symi_combine(ctx.ptr, _dev(Yp, dt, "Yp", ctx.A * ctx.d),
@@ -431,6 +486,7 @@ def symi_combine(ctx, Yp, row_of_assign, gate, Y):
                               _stream()), "symi_combine")
 
 
+@_device_call
 def symi_combine_bwd(ctx, dY, Yp, row_of_assign, gate, dYp, dgate):
     dt = ctx.torch_dtype
     _check(lib().symi_combine_bwd(
@@ -440,6 +496,7 @@ def symi_combine_bwd(ctx, dY, Yp, row_of_assign, gate, dYp, dgate):
         "symi_combine_bwd")
 
 
+@_device_call
 def symi_adam_to_replicas(ctx, hp, dW1_class, dW2_class, master_w, m, v, first_slot_next,
                           W1_slots, W2_slots):
     dt = ctx.torch_dtype
@@ -455,6 +512,7 @@ def symi_adam_to_replicas(ctx, hp, dW1_class, dW2_class, master_w, m, v, first_s
         "symi_adam_to_replicas")
 
 
+@_device_call
 def symi_adam_to_replicas_active(ctx, hp, dW1_class, dW2_class, master_w, m, v, slot_offsets,
                                  first_slot, first_slot_next, W1_slots, W2_slots):
     dt = ctx.torch_dtype

@@ -4,7 +4,7 @@
 // weight-gradient GEMM, which sums over every row of a class at once).
 //
 // Six products share one tiled kernel (bf16 inputs, fp32 accumulation on the gfx950
-// MFMA 32x32x16 bf16 instruction; kernels on the fp32 MFMA serve fp32 configurations):
+// MFMA 16x16x32 bf16 instruction; kernels on the fp32 MFMA serve fp32 configurations):
 //   FWD1   [u|v] = Xp  * W1^T      + SwiGLU epilogue writing u, v and h = silu(u)*v
 //   FWD2   Yp    = H   * W2^T
 //   BWD_DH dh    = dYp * W2        turned into du, dv from the saved u, v in the epilogue
@@ -31,6 +31,7 @@ enum { FWD1 = 0, FWD2 = 1, BWD_DH = 2, BWD_DX = 3, WGRAD2 = 4, WGRAD1 = 5 };
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
 
 struct GemmParams {
   const void* A;       // activations (left operand source)
@@ -109,18 +110,26 @@ __global__ __launch_bounds__(256) void tile_map_kernel(const int32_t* __restrict
 
 // ---------------------------------------------------------------- bf16 MFMA kernel
 // Output tile 256 x 256 per workgroup, reduction step 64, 4 wavefronts in a 2 x 2 grid,
-// each owning 128 x 128 outputs = 4 x 4 MFMA 32x32x16 tiles (256 fp32 accumulators per
+// each owning 128 x 128 outputs = 8 x 8 MFMA 16x16x32 tiles (256 fp32 accumulators per
 // lane).  Tiles travel HBM -> LDS with the gfx950 direct-to-LDS loads (16 bytes per
-// lane, no staging registers) into two stages of 2 x 32 KB; the next stage is in flight
-// while the current one feeds the MFMAs.  LDS bandwidth is the scarce resource at this
-// shape: 8 fragment reads of 1 KB per 16 MFMAs per wavefront.
-//
+// lane, no staging registers) into two 32 KB stages of the left operand and three of the right
+// one, the whole 160 KB of a compute unit.
+// Bound by the matrix pipes at the clock the power limit leaves (1.5 - 1.6 GHz of 2.4 with random
+// operands), as long as neither loads nor instruction issue leave them idle:
+//  - Lead of the loads.  With two stages of both operands the loads of a step had to be issued
+//    within two of its four phases and had 2 - 4 phases to land; the third stage of the right operand
+//    spreads them evenly over all phases and gives them 2 - 6.
+//  - MFMA 16x16x32 instead of 32x32x16: a block sums 32 products before it touches its accumulator,
+//    and reads and loads can sit between MFMAs of 16 cycles.  Same bits as 32x32x16.
+//  c5's six products 68.7 -> 64.6 (16x16x32) -> 61.3 ms (third stage), c4's 10.17 -> 9.85 -> 9.05, c2's
+//  2.73 -> 2.64 -> 2.33; LDS reads occupy 20 % of the cycles.  Two loads per eight MFMAs instead of
+//  one cost 3 %, four 6 %.
 // LDS layouts (all conflict-free for the access pattern that reads them):
 //   reduction-contiguous operand: [256 rows][64 k], 16-byte chunk c of row r stored at
 //     chunk c ^ ((r >> 1) & 7); fragments are plain 16-byte reads.
 //   reduction-strided operand (memory [k][r], r contiguous): [64 k][256 r] as loaded,
-//     16-byte chunk c of row k stored at c ^ 10*(k & 1) ^ 4*((k >> 1) & 1): the 32 lanes
-//     the LDS serves per cycle (4 k-rows x 64 B) then fall into 64 distinct banks;
+//     16-byte chunk c of row k stored at c ^ 10*(k & 1) ^ 4*((k >> 1) & 1) ^ 2*((k >> 3) & 1): the
+//     32 lanes the LDS serves per cycle (k-rows 0..3 and 8..11, 32 B each) then fall into 64 distinct banks;
 //     fragments come from the transposing LDS read (ds_read_b64_tr_b16), which hands
 //     lane j of a 16-lane group the four k-values of column j.
 // A direct-to-LDS load cannot zero-fill: rows or columns beyond the tile's extent are clamped
@@ -138,6 +147,13 @@ typedef __attribute__((__vector_size__(4 * sizeof(short)))) short shortx4;
 __device__ __forceinline__ void wait_vmcnt0() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
 template <int V> struct IC { static constexpr int value = V; };
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void unroll(F&& f) {   // f(IC<0>{}) .. f(IC<N - 1>{})
+  if constexpr (I < N) {
+    f(IC<I>{});
+    unroll<N, I + 1>(f);
+  }
+}
 
 // LDS reads with an immediate byte offset; nothing waits for them (see the kernel)
 template <int OFF>
@@ -157,6 +173,12 @@ __device__ __forceinline__ bf16x8 lds_read_tr(unsigned addr) {
   u.h[0] = lo;
   u.h[1] = hi;
   return u.v;
+}
+
+// acc += b * a, the accumulator pinned to AGPRs: through the builtin the register allocator moved
+// accumulators between the two halves of the register file inside the loop (about 600 moves per 256 MFMAs)
+__device__ __forceinline__ void mfma_acc(floatx4& acc, bf16x8 b, bf16x8 a) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(b), "v"(a));
 }
 
 // Reduction slices of the narrow variable-row products (FWD2, BWD_DX).  Their tiles run in
@@ -180,6 +202,191 @@ __device__ __forceinline__ void tail_slices(int n_tiles, int cus, int K, int& fu
   }
 }
 
+// Epilogue of a tile whose wavefronts own 32 MI x 32 NJ outputs each.  After the MFMA a lane owns
+// one output row (lane%16) of each 16 x 16 block and its 4 columns 4*(lane/16) ..: stored like that,
+// a wavefront store would touch 16 cache lines with 64 or 32 bytes each, and the store path is
+// paid per line touched.  The operand stages are free now, so every wavefront turns its
+// 32-row blocks around through a private piece of LDS (`stg`; written in the MFMA layout, read
+// back row by row, 16 bytes per lane) and each store instruction writes whole lines: for NJ = 4
+// 4 rows x 256 B (bf16 outputs), 8 rows x 128 B (u, v, h) or 2 rows x 512 B (fp32).
+// pslot >= 0: the accumulators of a reduction slice, left as an fp32 tile in that partial slot.
+template <int MODE, int MI, int NJ>
+__device__ __forceinline__ void write_tile(const GemmParams& p, uint16_t* const stg, floatx4 (&acc)[2 * MI][2 * NJ],
+                                           const int row0, const int row1, const int group, const int n0,
+                                           const int wm, const int wn, const int lane, const int pslot) {
+  constexpr bool VARM = MODE <= BWD_DX;
+  constexpr int WROWS = 32 * MI;
+  constexpr int CW = 32 * NJ, UW = 16 * NJ;   // columns of a wavefront; FWD1: its hidden units
+  constexpr int LB = CW / 8, LF = CW / 4, LH = UW / 8;   // lanes that share a row of 16-byte pieces
+  const int hq = lane >> 4, r16 = lane & 15;
+  constexpr int LDB = CW + 8;   // bf16 row + pad (a multiple of 16 bytes)
+  constexpr int LDH = UW + 8;   // u / v / h rows + pad
+  constexpr int LDF = CW + 4;   // fp32 row + pad
+  constexpr int NUV = 32 / (64 / LB);
+  uint4 uvu[2][NUV], uvv[2][NUV];   // BWD_DH: saved u, v of the current and the next 32-row block
+  // a slice stores its accumulators the way a weight gradient is stored: fp32, pitch 256
+  const bool to_partial = (MODE == FWD2 || MODE == BWD_DX) && pslot >= 0;
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    const int rbase = row0 + wm * WROWS + i * 32;   // first output row of this block
+    if (MODE == FWD1) {
+      uint16_t* const su = stg;
+      uint16_t* const sv = stg + 32 * LDH;
+      uint16_t* const sh = stg + 64 * LDH;
+#pragma unroll
+      for (int ih = 0; ih < 2; ++ih)
+#pragma unroll
+        for (int q = 0; q < NJ; ++q) {   // 16 hidden units
+          const int g = 4 * (q >> 1) + (q & 1);
+          unsigned pu[2], pv[2], ph[2];
+#pragma unroll
+          for (int c2 = 0; c2 < 2; ++c2) {
+            const float u0 = acc[2 * i + ih][g][2 * c2], u1 = acc[2 * i + ih][g][2 * c2 + 1];
+            const float v0 = acc[2 * i + ih][g + 2][2 * c2], v1 = acc[2 * i + ih][g + 2][2 * c2 + 1];
+            pu[c2] = pack_bf16x2(u0, u1);
+            pv[c2] = pack_bf16x2(v0, v1);
+            ph[c2] = pack_bf16x2(u0 * sigmoid_fast(u0) * v0, u1 * sigmoid_fast(u1) * v1);
+          }
+          const int at = (ih * 16 + r16) * LDH + 16 * q + 4 * hq;
+          *reinterpret_cast<uint2*>(su + at) = make_uint2(pu[0], pu[1]);
+          *reinterpret_cast<uint2*>(sv + at) = make_uint2(pv[0], pv[1]);
+          *reinterpret_cast<uint2*>(sh + at) = make_uint2(ph[0], ph[1]);
+        }
+      __builtin_amdgcn_s_waitcnt(0xC07F);
+      uint16_t* UVo = static_cast<uint16_t*>(p.UVout);
+      uint16_t* Ho = static_cast<uint16_t*>(p.H);
+      const int hu = n0 + wn * UW + (lane & (LH - 1)) * 8;
+#pragma unroll
+      for (int it = 0; it < 32 * LH / 64; ++it) {
+        const int rr = it * (64 / LH) + lane / LH;
+        const int row = rbase + rr;
+        const uint4 xu = *reinterpret_cast<const uint4*>(su + rr * LDH + (lane & (LH - 1)) * 8);
+        const uint4 xv = *reinterpret_cast<const uint4*>(sv + rr * LDH + (lane & (LH - 1)) * 8);
+        const uint4 xh = *reinterpret_cast<const uint4*>(sh + rr * LDH + (lane & (LH - 1)) * 8);
+        if (row < row1 && hu < p.f) {
+          const long long o = (long long)row * 2 * p.f + hu;
+          *reinterpret_cast<uint4*>(UVo + o) = xu;
+          *reinterpret_cast<uint4*>(UVo + o + p.f) = xv;
+          *reinterpret_cast<uint4*>(Ho + (long long)row * p.f + hu) = xh;
+        }
+      }
+    } else if (MODE == BWD_DH) {
+      // dh stays in fp32: staged like a weight-gradient block, then every lane takes 8
+      // consecutive hidden units of one row, combines them with the saved u and v (16 bytes
+      // each, whole lines per instruction) and writes du = dh v s (1 + u (1 - s)),
+      // dv = dh u s, s = sigmoid(u).  The u, v loads of block i + 1 are issued before block i
+      // is worked on, so their latency hides behind it.  They are unconditional: a lane past
+      // the tile's last row or column reads the last valid row / the last 8 columns instead
+      // (its result is never stored).  A load under a branch would make the compiler lose
+      // count of the memory operations in flight and wait for all of them, the stores of the
+      // previous rows included, before every use of a loaded value.
+      float* const sf = reinterpret_cast<float*>(stg);
+      const uint16_t* UVi = static_cast<const uint16_t*>(p.UV);
+      uint16_t* Co = static_cast<uint16_t*>(p.C);
+      const int col = n0 + wn * CW + (lane & (LB - 1)) * 8;
+      const int colc = min(col, p.N - 8);
+      const int twof = 2 * p.f;
+      auto load_uv = [&](int blk, uint4 (&uu)[NUV], uint4 (&vv)[NUV]) {
+        const int rb = row0 + wm * WROWS + blk * 32;
+        const uint16_t* const q0 = UVi + (long long)rb * twof + colc;
+#pragma unroll
+        for (int it = 0; it < NUV; ++it) {
+          const int dr = min(rb + it * (64 / LB) + lane / LB, row1 - 1) - rb;   // may be negative
+          const uint16_t* const q = q0 + (long long)dr * twof;
+          uu[it] = *reinterpret_cast<const uint4*>(q);
+          vv[it] = *reinterpret_cast<const uint4*>(q + p.f);
+        }
+      };
+      if (i == 0) load_uv(0, uvu[0], uvv[0]);
+      if (i + 1 < MI) load_uv(i + 1, uvu[(i + 1) & 1], uvv[(i + 1) & 1]);
+#pragma unroll
+      for (int ih = 0; ih < 2; ++ih)
+#pragma unroll
+        for (int j = 0; j < 2 * NJ; ++j)
+          *reinterpret_cast<floatx4*>(sf + (ih * 16 + r16) * LDF + 16 * j + 4 * hq) = acc[2 * i + ih][j];
+      __builtin_amdgcn_s_waitcnt(0xC07F);
+#pragma unroll
+      for (int it = 0; it < NUV; ++it) {
+        const int rr = it * (64 / LB) + lane / LB;
+        const int row = rbase + rr;
+        const float4 d0 = *reinterpret_cast<const float4*>(sf + rr * LDF + (lane & (LB - 1)) * 8);
+        const float4 d1 = *reinterpret_cast<const float4*>(sf + rr * LDF + (lane & (LB - 1)) * 8 + 4);
+        if (row < row1 && col < p.N) {
+          const long long o = (long long)row * 2 * p.f + col;
+          const uint4 uu = uvu[i & 1][it], vv = uvv[i & 1][it];
+          const float dh[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
+          const uint32_t uw[4] = {uu.x, uu.y, uu.z, uu.w}, vw[4] = {vv.x, vv.y, vv.z, vv.w};
+          uint32_t du[4], dv[4];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            float o_du[2], o_dv[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              const float u_ = __uint_as_float(h ? (uw[q] & 0xffff0000u) : (uw[q] << 16));
+              const float v_ = __uint_as_float(h ? (vw[q] & 0xffff0000u) : (vw[q] << 16));
+              const float sg = sigmoid_fast(u_);
+              o_du[h] = dh[2 * q + h] * v_ * sg * (1.f + u_ * (1.f - sg));
+              o_dv[h] = dh[2 * q + h] * u_ * sg;
+            }
+            du[q] = pack_bf16x2(o_du[0], o_du[1]);
+            dv[q] = pack_bf16x2(o_dv[0], o_dv[1]);
+          }
+          *reinterpret_cast<uint4*>(Co + o) = make_uint4(du[0], du[1], du[2], du[3]);
+          *reinterpret_cast<uint4*>(Co + o + p.f) = make_uint4(dv[0], dv[1], dv[2], dv[3]);
+        }
+      }
+    } else if ((MODE == FWD2 || MODE == BWD_DX) && !to_partial) {
+#pragma unroll
+      for (int ih = 0; ih < 2; ++ih)
+#pragma unroll
+        for (int j = 0; j < 2 * NJ; ++j) {
+          const floatx4 x = acc[2 * i + ih][j];
+          *reinterpret_cast<uint2*>(stg + (ih * 16 + r16) * LDB + 16 * j + 4 * hq) =
+              make_uint2(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]));
+        }
+      __builtin_amdgcn_s_waitcnt(0xC07F);
+      uint16_t* Co = static_cast<uint16_t*>(p.C);
+      const int col = n0 + wn * CW + (lane & (LB - 1)) * 8;
+#pragma unroll
+      for (int it = 0; it < NUV; ++it) {
+        const int rr = it * (64 / LB) + lane / LB;
+        const int row = rbase + rr;
+        const uint4 x = *reinterpret_cast<const uint4*>(stg + rr * LDB + (lane & (LB - 1)) * 8);
+        if (row < row1 && col < p.N) *reinterpret_cast<uint4*>(Co + (long long)row * p.N + col) = x;
+      }
+    } else {   // weight gradients, fp32
+      float* const sf = reinterpret_cast<float*>(stg);
+#pragma unroll
+      for (int ih = 0; ih < 2; ++ih)
+#pragma unroll
+        for (int j = 0; j < 2 * NJ; ++j)
+          *reinterpret_cast<floatx4*>(sf + (ih * 16 + r16) * LDF + 16 * j + 4 * hq) = acc[2 * i + ih][j];
+      __builtin_amdgcn_s_waitcnt(0xC07F);
+      if (VARM) {   // a slice's partial tile
+        float* Co = p.partials + (size_t)pslot * (BM * BN) + (wm * WROWS + i * 32) * BN + wn * CW + (lane & (LF - 1)) * 4;
+#pragma unroll
+        for (int it = 0; it < 32 * LF / 64; ++it) {
+          const int rr = it * (64 / LF) + lane / LF;
+          *reinterpret_cast<float4*>(Co + rr * BN) = *reinterpret_cast<const float4*>(sf + rr * LDF + (lane & (LF - 1)) * 4);
+        }
+      } else {
+        float* Co = static_cast<float*>(p.C) + (long long)group * p.c_group_stride;
+        const int col = n0 + wn * CW + (lane & (LF - 1)) * 4;
+#pragma unroll
+        for (int it = 0; it < 32 * LF / 64; ++it) {
+          const int rr = it * (64 / LF) + lane / LF;
+          const int row = rbase + rr;
+          const float4 x = *reinterpret_cast<const float4*>(sf + rr * LDF + (lane & (LF - 1)) * 4);
+          if (row < row1 && col < p.N) *reinterpret_cast<float4*>(Co + (long long)row * p.N + col) = x;
+        }
+      }
+    }
+    // the next block reuses the staging area: its writes must not pass these reads
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 // One tile of one product.  MI = 32-row blocks per wavefront: 4 for the 256-row tile (each of the
 // 2 x 2 wavefronts 128 x 128), 2 for the 128-row tile that holds the ragged end of a slot when
 // it has at most 128 rows (each wavefront 64 x 128: half the MFMAs, and the two wavefronts whose
@@ -188,12 +395,11 @@ template <int MODE, int MI>
 __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const smem, const int row0,
                                           const int row1, const int group, const int kbeg, const int K,
                                           const int bx, const int nsl, const int kofs, const int pslot) {
-  // [left stage 0 | left stage 1 | right stage 0 | right stage 1], 32 KB each: the two
-  // stages of an operand differ by an immediate offset of the LDS read instructions
+  // [left stages 0, 1 | right stages 0, 1, 2], 32 KB each: the two left stages differ by an immediate
+  // offset of the LDS read instructions, the addresses of the right operand move on with every step
   uint16_t* const sA0 = smem;
   uint16_t* const sA1 = smem + BM * BK;
   uint16_t* const sB0 = smem + 2 * BM * BK;
-  uint16_t* const sB1 = smem + 2 * BM * BK + BN * BK;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, and known to be
   const int wm = wave >> 1, wn = wave & 1;
@@ -282,7 +488,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const s
       }
       return (unsigned)(min(kc_row + 8 * j, lim) * ld + kc * 8);
     }
-    const int c = ks_c0 ^ (4 * (j & 1));
+    const int c = ks_c0 ^ (4 * (j & 1)) ^ (2 * ((j >> 2) & 1));
     krel = ks_kb + 2 * j;
     return (unsigned)((ks_kb + 2 * j) * ld + (c * 8 < lim ? c : 0) * 8);
   };
@@ -310,7 +516,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const s
     asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" ::"v"(voff), "s"(sbase), "n"((J - 4) * 1024) : "memory");
   };
   // q = 0..7: instruction j = q of the left operand, q = 8..15: instruction j = q - 8 of the right one
-  auto dma_one = [&](uint16_t* sA, uint16_t* sB, int k0, auto qc, auto partial) {
+  auto dma_one = [&](unsigned lds_stage, int k0, auto qc, auto partial) {
     constexpr int Q = decltype(qc)::value;
     constexpr int j = Q & 7;
     constexpr bool right = Q >= 8;
@@ -319,7 +525,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const s
     const uint16_t* base = right ? b_base : a_base;
     const long long ld = right ? ldb : lda;
     const uint16_t* sbase = kcontig ? base + k0 : base + (long long)k0 * ld;   // wave-uniform
-    const unsigned lds0 = (unsigned)(size_t)SYMI_LPTR((right ? sB : sA) + wdst);   // this wavefront's 8 KB
+    const unsigned lds0 = lds_stage + 2 * wdst;   // this wavefront's 8 KB of the stage
     if (decltype(partial)::value) {
       int krel;
       const unsigned off = lane_off(right, j, krel);
@@ -332,124 +538,109 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const s
     }
   };
   // ---- fragment reads.  Byte address of this lane's piece inside stage 0 of its operand,
-  // everything else (32-row block, 16-deep sub-step, stage) is an immediate offset.
-  // KC: row (sub*32 + lane%32), chunk (2*ks + lane/32) ^ ((lane%32 >> 1) & 7); the xor makes the
+  // everything else (16-row block, 32-deep sub-step, left stage) is an immediate offset.
+  // KC: row (block*16 + lane%16), chunk (4*ks + lane/16) ^ ((lane%16 >> 1) & 7); the xor makes the
   //   sub-step a per-lane quantity, so there is one address per sub-step.
-  // KS: lane = 16*g + jj supplies the address of k-row (16*ks + 8*(g>>1) + 4*e + jj/4),
-  //   8-byte piece (jj%4) of columns sub*32 + 16*(g&1) ..; it receives column sub*32 + lane%32;
-  //   one address per 32-column block, the sub-step is an immediate (16 k-rows of 512 B).
-  const int r31 = lane & 31;
+  // KS: lane = 16*g + jj supplies the address of k-row (32*ks + 8*g + 4*e + jj/4), 8-byte piece (jj%4)
+  //   of the block's 16 columns; it receives column block*16 + jj; one address per block, the
+  //   sub-step is an immediate (32 k-rows of 512 B).
   const int g4 = lane >> 4, jj = lane & 15;
-  const int ks_h2 = (10 * ((jj >> 2) & 1)) ^ (4 * ((jj >> 3) & 1));   // swizzle of this lane's k-row
-  const int ks_row = (8 * (g4 >> 1) + (jj >> 2)) * 256;
-  unsigned adA[4], adB[4];
+  const int ks_h = (10 * ((jj >> 2) & 1)) ^ (4 * ((jj >> 3) & 1)) ^ (2 * (g4 & 1));   // swizzle of this lane's k-row
+  const int ks_row = (8 * g4 + (jj >> 2)) * 256;
+  unsigned adA[A_KC ? 2 : 2 * MI], adB[B_KC ? 2 : 8];
 #pragma unroll
-  for (int x = 0; x < 4; ++x) {
-    const int kc = r31 * BK + (((2 * x + (lane >> 5)) ^ ((r31 >> 1) & 7)) * 8);             // x = sub-step
-    const int ksc = ks_row + (((4 * x + 2 * (g4 & 1) + ((jj & 3) >> 1)) ^ ks_h2) * 8) + 4 * (jj & 1);  // x = block
-    adA[x] = (unsigned)(size_t)SYMI_LPTR(sA0) + 2u * (unsigned)(A_KC ? wm * WROWS * BK + kc : wm * WROWS + ksc);
-    adB[x] = (unsigned)(size_t)SYMI_LPTR(sB0) + 2u * (unsigned)(B_KC ? wn * 128 * BK + kc : wn * 128 + ksc);
+  for (int x = 0; x < 8; ++x) {
+    const int kc = jj * BK + (((4 * x + g4) ^ ((jj >> 1) & 7)) * 8);                                // x = sub-step
+    const int ksc = ks_row + (((2 * x + ((jj & 3) >> 1)) ^ ks_h) * 8) + 4 * (jj & 1);               // x = block
+    if (x < (A_KC ? 2 : 2 * MI)) adA[x] = (unsigned)(size_t)SYMI_LPTR(sA0) + 2u * (unsigned)(A_KC ? wm * WROWS * BK + kc : wm * WROWS + ksc);
+    if (x < (B_KC ? 2 : 8)) adB[x] = (unsigned)(size_t)SYMI_LPTR(sB0) + 2u * (unsigned)(B_KC ? wn * 128 * BK + kc : wn * 128 + ksc);
   }
   // All LDS reads are inline assembly: the compiler cannot tell the stage being read from the
   // one being filled by direct-to-LDS loads and would wait for the prefetch before every
   // read.  Completion is awaited by hand (lgkmcnt(0)) at the start of the phase that uses them.
-  bf16x8 fa[2][MI], fb[2][4];   // two register sets: one feeds the MFMAs, the other is being filled
-  // half = 0 / 1: fragments 0, 1 / 2, 3 of both operands; 2: all of them
-  auto load_frags = [&](auto bufc, auto stagec, auto ksc, auto halfc) {
-    constexpr int bu = decltype(bufc)::value, S = decltype(stagec)::value, KS = decltype(ksc)::value;
-    constexpr int HF = decltype(halfc)::value;
-    constexpr int SO = S * BM * BK * 2;   // stage offset in bytes
-    constexpr bool LO = HF != 1, HI = HF != 0;
-#pragma unroll
-    for (int x = 0; x < MI; ++x) {
-      if (!(x < MI / 2 ? LO : HI)) continue;
-      if (A_KC) {
-        if (x == 0) fa[bu][0] = lds_read_b128<SO + 0 * 4096>(adA[KS]);
-        if (x == 1) fa[bu][1] = lds_read_b128<SO + 1 * 4096>(adA[KS]);
-        if (x == 2) fa[bu][x] = lds_read_b128<SO + 2 * 4096>(adA[KS]);
-        if (x == 3) fa[bu][x] = lds_read_b128<SO + 3 * 4096>(adA[KS]);
-      } else {
-        fa[bu][x] = lds_read_tr<SO + KS * 8192>(adA[x]);
-      }
-    }
-    if (B_KC) {
-      if (LO) fb[bu][0] = lds_read_b128<SO + 0 * 4096>(adB[KS]);
-      if (LO) fb[bu][1] = lds_read_b128<SO + 1 * 4096>(adB[KS]);
-      if (HI) fb[bu][2] = lds_read_b128<SO + 2 * 4096>(adB[KS]);
-      if (HI) fb[bu][3] = lds_read_b128<SO + 3 * 4096>(adB[KS]);
-    } else {
-      if (LO) fb[bu][0] = lds_read_tr<SO + KS * 8192>(adB[0]);
-      if (LO) fb[bu][1] = lds_read_tr<SO + KS * 8192>(adB[1]);
-      if (HI) fb[bu][2] = lds_read_tr<SO + KS * 8192>(adB[2]);
-      if (HI) fb[bu][3] = lds_read_tr<SO + KS * 8192>(adB[3]);
-    }
+  // Two register sets each: one feeds the MFMAs, the other is being filled.  fa holds the left operand's
+  // blocks of a phase (half of the wavefront's rows), fb the right operand's of a sub-step.
+  bf16x8 fa[2][MI], fb[2][8];
+  auto read_a = [&](auto setc, auto stagec, auto ksc, auto halfc, auto qc) {
+    constexpr int SO = decltype(stagec)::value * BM * BK * 2, KS = decltype(ksc)::value;   // stage offset in bytes
+    constexpr int q = decltype(qc)::value, blk = decltype(halfc)::value * MI + q;
+    if constexpr (A_KC) fa[decltype(setc)::value][q] = lds_read_b128<SO + blk * 2048>(adA[KS]);
+    else fa[decltype(setc)::value][q] = lds_read_tr<SO + KS * 16384>(adA[blk]);
   };
+  auto read_b = [&](auto ksc, auto jc) {
+    constexpr int KS = decltype(ksc)::value, j = decltype(jc)::value;
+    if constexpr (B_KC) fb[KS][j] = lds_read_b128<j * 2048>(adB[KS]);
+    else fb[KS][j] = lds_read_tr<KS * 16384>(adB[j]);
+  };
+  const unsigned ldsA0 = (unsigned)(size_t)SYMI_LPTR(sA0), ldsA1 = (unsigned)(size_t)SYMI_LPTR(sA1);
+  const unsigned ldsB = (unsigned)(size_t)SYMI_LPTR(sB0);
+  int bs = 0;   // byte offset of the right operand's stage of this step (adB points into it)
 
-  floatx16 acc[MI][4];
+  floatx4 acc[2 * MI][8];
 #pragma unroll
-  for (int i = 0; i < MI; ++i)
+  for (int i = 0; i < 2 * MI; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int j = 0; j < 8; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  // ---- main loop.  A reduction step (64 deep, stage S = step & 1) is four phases of 16
-  // MFMAs.  Phase ks consumes register set ks & 1 while the fragments of the next phase are
-  // read into the other set.  Phase 3 first waits for the loads of the next step, meets the
-  // other wavefronts (after which nobody reads stage S any more: its last fragments already
-  // sit in registers), reads the first fragments of the other stage and starts loading step
-  // + 2 into stage S; phase 0 of the next step issues the second half of those loads.  A
-  // load therefore has three to four phases to arrive, and neither an LDS round trip nor a
-  // load latency is exposed to the MFMA pipe.  Steps beyond the last one load zeros (dummy
-  // loads keep the loop free of branches, which is what lets the 256 accumulators stay put).
+  // ---- main loop.  A reduction step (64 deep, left stage S = step & 1, right stage step % 3) is four
+  // phases of 32 MFMAs: sub-step 0 and 1, in each the upper and the lower half of the wavefront's rows.
+  // A phase reads the fragments of the next one into the other register set.  Phase 3 first waits for
+  // the loads of the next step and meets the other wavefronts, after which nobody reads this step's
+  // stages any more (their last fragments already sit in registers); it reads the first fragments of
+  // the next stages.  Phases 3 and 0 load the left operand of step + 2 into the stage just freed, phases 1
+  // and 2 the right one of step + 2 into the stage freed a step ago.  Neither an LDS round trip nor a load
+  // latency is exposed to the MFMA pipe.  Steps beyond the last one load zeros (dummy
+  // loads keep the loop free of branches; a tail without them measured 1 % slower).
   const int nk = (K + BK - 1) / BK;
   auto phase = [&](auto ksc, auto stagec, int step, auto partial) {
     constexpr int KS = decltype(ksc)::value, S = decltype(stagec)::value;
-    constexpr int bu = KS & 1;
-    uint16_t* const cA = S ? sA1 : sA0;
-    uint16_t* const cB = S ? sB1 : sB0;
-    uint16_t* const oA = S ? sA0 : sA1;
-    uint16_t* const oB = S ? sB0 : sB1;
+    constexpr int half = KS & 1, sub = KS >> 1;
+    const unsigned cA = S ? ldsA1 : ldsA0, oA = S ? ldsA0 : ldsA1;
     __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): the fragments of this phase
     if (KS == 3) {
-      wait_vmcnt0();                      // my share of the next step has landed
+      __builtin_amdgcn_s_waitcnt(0x0F78);   // my share of the next step has landed (the 8 loads of the step after it may fly)
       __builtin_amdgcn_s_barrier();       // ... so has everybody's, and stage S is free
     }
     __builtin_amdgcn_sched_barrier(0);
-    if (decltype(partial)::value && (KS == 3 || KS == 0)) {
+    if (decltype(partial)::value) {
       // keep the address arithmetic of these loads inside the phase (not hoisted into registers)
       asm volatile("" : "+v"(kc_row), "+v"(kc_c0), "+v"(ks_kb), "+v"(ks_c0), "+v"(f1_row));
     }
-    constexpr int LPI = 8 / MI;   // loads issued behind each MFMA group of a phase that loads
-#pragma unroll
-    for (int i = 0; i < MI; ++i) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[bu][j], fa[bu][i], acc[i][j], 0, 0, 0);
-      // the next phase's fragments, half of them behind each of the first two MFMA groups: the
-      // matrix pipe has work queued while the reads issue, and they still have half a phase to land
-      if (i == 0) {
-        if (KS == 3) load_frags(IC<bu ^ 1>{}, IC<S ^ 1>{}, IC<0>{}, IC<0>{});
-        else load_frags(IC<bu ^ 1>{}, IC<S>{}, IC<(KS + 1) & 3>{}, IC<0>{});
-      } else if (i == 1) {
-        if (KS == 3) load_frags(IC<bu ^ 1>{}, IC<S ^ 1>{}, IC<0>{}, IC<1>{});
-        else load_frags(IC<bu ^ 1>{}, IC<S>{}, IC<(KS + 1) & 3>{}, IC<1>{});
+    constexpr int NB = KS == 0 || KS == 1 ? 4 : KS == 2 ? 0 : 8;   // right blocks read in this phase
+    auto read = [&](auto rc) {
+      constexpr int r = decltype(rc)::value;
+      if constexpr (r < MI) {
+        if constexpr (KS == 0) read_a(IC<1>{}, IC<S>{}, IC<0>{}, IC<1>{}, IC<r>{});
+        if constexpr (KS == 1) read_a(IC<0>{}, IC<S>{}, IC<1>{}, IC<0>{}, IC<r>{});
+        if constexpr (KS == 2) read_a(IC<1>{}, IC<S>{}, IC<1>{}, IC<1>{}, IC<r>{});
+        if constexpr (KS == 3) read_a(IC<0>{}, IC<S ^ 1>{}, IC<0>{}, IC<0>{}, IC<r>{});
+      } else if constexpr (r < MI + NB) {
+        if constexpr (KS == 0) read_b(IC<1>{}, IC<r - MI>{});
+        if constexpr (KS == 1) read_b(IC<1>{}, IC<r - MI + 4>{});
+        if constexpr (KS == 3) read_b(IC<0>{}, IC<r - MI>{});
       }
-      // phase 3: the left operand of step + 2 into the stage just freed; phase 0: the right one
-      auto issue = [&](auto uc) {
-        constexpr int U = decltype(uc)::value;
-        if (i == 0) { if (KS == 3) dma_one(cA, cB, (step + 2) * BK, IC<0 * LPI + U>{}, partial); else dma_one(oA, oB, (step + 1) * BK, IC<8 + 0 * LPI + U>{}, partial); }
-        if (i == 1) { if (KS == 3) dma_one(cA, cB, (step + 2) * BK, IC<1 * LPI + U>{}, partial); else dma_one(oA, oB, (step + 1) * BK, IC<8 + 1 * LPI + U>{}, partial); }
-        if (MI == 4 && i == 2) { if (KS == 3) dma_one(cA, cB, (step + 2) * BK, IC<(2 * LPI + U) & 7>{}, partial); else dma_one(oA, oB, (step + 1) * BK, IC<8 + ((2 * LPI + U) & 7)>{}, partial); }
-        if (MI == 4 && i == 3) { if (KS == 3) dma_one(cA, cB, (step + 2) * BK, IC<(3 * LPI + U) & 7>{}, partial); else dma_one(oA, oB, (step + 1) * BK, IC<8 + ((3 * LPI + U) & 7)>{}, partial); }
-      };
-      if (KS == 3 || KS == 0) {
-        issue(IC<0>{});
-        issue(IC<1>{});
-        if (LPI == 4) { issue(IC<2>{}); issue(IC<3>{}); }
+    };
+    constexpr int RS = MI == 4 ? 2 : 1, LS = 2 * MI, L0 = MI == 4 ? 5 : 1;   // every RS-th MFMA a read, every LS-th a load
+    unroll<8 * MI>([&](auto mc) {
+      constexpr int m = decltype(mc)::value, i = m >> 3, j = i & 1 ? 7 - (m & 7) : m & 7;
+      mfma_acc(acc[half * MI + i][j], fb[sub][j], fa[half][i]);
+      if constexpr (m % RS == 0) read(IC<m / RS>{});
+      // phases 3 and 0: the left operand of step + 2 into the stage freed at this phase 3; phases 1 and 2: the right one
+      constexpr int L = m >= L0 && (m - L0) % LS == 0 ? (m - L0) / LS : 4;
+      if constexpr (L < 4) {
+        if constexpr (KS == 3) dma_one(cA, (step + 2) * BK, IC<L>{}, partial);
+        if constexpr (KS == 0) dma_one(oA, (step + 1) * BK, IC<4 + L>{}, partial);
+        if constexpr (KS == 1) dma_one(ldsB + (bs == 0 ? 2 * BN * BK * 2 : bs - BN * BK * 2), (step + 2) * BK, IC<8 + L>{}, partial);
+        if constexpr (KS == 2) dma_one(ldsB + (bs == 0 ? 2 * BN * BK * 2 : bs - BN * BK * 2), (step + 2) * BK, IC<12 + L>{}, partial);
+      }
+      if constexpr (KS == 2 && m == 8 * MI - 1) {   // on to the right operand's next stage
+        const int next = bs == 2 * BN * BK * 2 ? 0 : bs + BN * BK * 2;
+#pragma unroll
+        for (int x = 0; x < (B_KC ? 2 : 8); ++x) adB[x] += (unsigned)(next - bs);
+        bs = next;
       }
       __builtin_amdgcn_sched_barrier(0);
-    }
+    });
   };
   auto pair = [&](int t, auto partial) {
     phase(IC<0>{}, IC<0>{}, t, partial);
@@ -462,25 +653,17 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const s
     phase(IC<3>{}, IC<1>{}, t + 1, partial);
   };
   auto prologue = [&](auto partial) {
-    auto all16 = [&](uint16_t* a, uint16_t* b, int k0, auto halfc) {
-      dma_one(a, b, k0, IC<0>{}, partial); dma_one(a, b, k0, IC<1>{}, partial); dma_one(a, b, k0, IC<2>{}, partial);
-      dma_one(a, b, k0, IC<3>{}, partial); dma_one(a, b, k0, IC<4>{}, partial); dma_one(a, b, k0, IC<5>{}, partial);
-      dma_one(a, b, k0, IC<6>{}, partial); dma_one(a, b, k0, IC<7>{}, partial);
-      if (decltype(halfc)::value) return;
-      dma_one(a, b, k0, IC<8>{}, partial); dma_one(a, b, k0, IC<9>{}, partial); dma_one(a, b, k0, IC<10>{}, partial);
-      dma_one(a, b, k0, IC<11>{}, partial); dma_one(a, b, k0, IC<12>{}, partial); dma_one(a, b, k0, IC<13>{}, partial);
-      dma_one(a, b, k0, IC<14>{}, partial); dma_one(a, b, k0, IC<15>{}, partial);
-    };
-    all16(sA0, sB0, 0, std::false_type{});   // step 0, both operands
-    all16(sA1, sB1, BK, std::true_type{});   // step 1, left operand (the right one follows in phase 0)
+    unroll<16>([&](auto q) { dma_one(decltype(q)::value < 8 ? ldsA0 : ldsB, 0, q, partial); });                              // step 0
+    unroll<8>([&](auto q) { dma_one(ldsB + BN * BK * 2, BK, IC<8 + decltype(q)::value>{}, partial); });     // step 1, right operand
+    unroll<4>([&](auto q) { dma_one(ldsA1, BK, q, partial); });     // and half of the left one (the rest follows in phase 0)
   };
   if (K >= 2 * BK) prologue(std::false_type{}); else prologue(std::true_type{});
-  // step 0 has landed, the left operand of step 1 (8 loads) may still fly; in a half-height
-  // tile the wavefronts that skip the left operand have nothing of step 1 in flight: all wait
-  // for everything there
-  if (MI == 4) __builtin_amdgcn_s_waitcnt(0x0F78); else wait_vmcnt0();
+  // step 0 has landed, the 12 loads of step 1 may still fly (8 in a wavefront of a half-height tile that
+  // skips the left operand)
+  if (MI == 4) __builtin_amdgcn_s_waitcnt(0x0F7C); else __builtin_amdgcn_s_waitcnt(0x0F78);
   __builtin_amdgcn_s_barrier();
-  load_frags(IC<0>{}, IC<0>{}, IC<0>{}, IC<2>{});
+  unroll<MI>([&](auto q) { read_a(IC<0>{}, IC<0>{}, IC<0>{}, IC<0>{}, q); });
+  unroll<8>([&](auto q) { read_b(IC<0>{}, q); });
   // always pairs of steps: for an odd step count the second stage holds the zeros of the
   // dummy loads and adds nothing (a mid-loop exit would cost more than the idle step).  A
   // pair starting at step t loads steps up to t + 3.
@@ -488,186 +671,19 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const s
   for (; (t + 4) * BK <= K; t += 2) pair(t, std::false_type{});
   for (; t < nk; t += 2) pair(t, std::true_type{});
   // dummy loads and the fragment read of the last phase are still in flight: they must
-  // not outlive the workgroup's LDS allocation
+  // not outlive the workgroup's LDS allocation.  The last MFMAs are through after 16 wait states.
+  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+  for (int i = 0; i < 2 * MI; ++i)   // no accumulator is read before the wait states
+    asm volatile("" : "+a"(acc[i][0]), "+a"(acc[i][1]), "+a"(acc[i][2]), "+a"(acc[i][3]), "+a"(acc[i][4]),
+                 "+a"(acc[i][5]), "+a"(acc[i][6]), "+a"(acc[i][7]));
   __builtin_amdgcn_s_waitcnt(0xC07F);
   wait_vmcnt0();
 
-  // ---- epilogue.  After the MFMA a lane owns one output row (lane%32) of each 32-row
-  // block and, per 8-column group g, the 4 columns 8g + 4*(lane/32) ..: stored like that, a
-  // wavefront store would touch 64 cache lines with 16 bytes each, and the store path is
-  // paid per line touched.  The operand stages are free now, so every wavefront turns its
-  // 32-row blocks around through a private piece of LDS (written in the MFMA layout, read
-  // back row by row, 16 bytes per lane) and each store instruction writes whole lines:
-  // 4 rows x 256 B (bf16 outputs), 8 rows x 128 B (u, v, h) or 2 rows x 512 B (fp32).
   __syncthreads();   // every wavefront's dummy loads have landed, nobody reads operands any more
-  const int hw = lane >> 5, r32 = lane & 31;
-  uint16_t* const stg = smem + wave * (16 * 1024);   // 32 KB per wavefront
-  constexpr int LDB = 136;   // bf16 row of 128 columns + pad (272 B, a multiple of 16)
-  constexpr int LDH = 72;    // u / v / h rows of 64 hidden units + pad (144 B)
-  constexpr int LDF = 132;   // fp32 row of 128 columns + pad (528 B)
-  uint4 uvu[2][8], uvv[2][8];   // BWD_DH: saved u, v of the current and the next 32-row block
-  // a slice stores its accumulators the way a weight gradient is stored: fp32, pitch 256
-  const bool to_partial = (MODE == FWD2 || MODE == BWD_DX) && nsl > 1;
-#pragma unroll
-  for (int i = 0; i < MI; ++i) {
-    const int rbase = row0 + wm * WROWS + i * 32;   // first output row of this block
-    if (MODE == FWD1) {
-      uint16_t* const su = stg;
-      uint16_t* const sv = stg + 32 * LDH;
-      uint16_t* const sh = stg + 64 * LDH;
-#pragma unroll
-      for (int hb = 0; hb < 2; ++hb)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          unsigned pu[2], pv[2], ph[2];
-#pragma unroll
-          for (int c2 = 0; c2 < 2; ++c2) {
-            const int r = g * 4 + 2 * c2;
-            const float u0 = acc[i][2 * hb][r], u1 = acc[i][2 * hb][r + 1];
-            const float v0 = acc[i][2 * hb + 1][r], v1 = acc[i][2 * hb + 1][r + 1];
-            pu[c2] = pack_bf16x2(u0, u1);
-            pv[c2] = pack_bf16x2(v0, v1);
-            ph[c2] = pack_bf16x2(u0 * sigmoid_fast(u0) * v0, u1 * sigmoid_fast(u1) * v1);
-          }
-          const int at = r32 * LDH + hb * 32 + 8 * g + 4 * hw;
-          *reinterpret_cast<uint2*>(su + at) = make_uint2(pu[0], pu[1]);
-          *reinterpret_cast<uint2*>(sv + at) = make_uint2(pv[0], pv[1]);
-          *reinterpret_cast<uint2*>(sh + at) = make_uint2(ph[0], ph[1]);
-        }
-      __builtin_amdgcn_s_waitcnt(0xC07F);
-      uint16_t* UVo = static_cast<uint16_t*>(p.UVout);
-      uint16_t* Ho = static_cast<uint16_t*>(p.H);
-      const int hu = n0 + wn * 64 + (lane & 7) * 8;
-#pragma unroll
-      for (int it = 0; it < 4; ++it) {
-        const int rr = it * 8 + (lane >> 3);
-        const int row = rbase + rr;
-        const uint4 xu = *reinterpret_cast<const uint4*>(su + rr * LDH + (lane & 7) * 8);
-        const uint4 xv = *reinterpret_cast<const uint4*>(sv + rr * LDH + (lane & 7) * 8);
-        const uint4 xh = *reinterpret_cast<const uint4*>(sh + rr * LDH + (lane & 7) * 8);
-        if (row < row1 && hu < p.f) {
-          const long long o = (long long)row * 2 * p.f + hu;
-          *reinterpret_cast<uint4*>(UVo + o) = xu;
-          *reinterpret_cast<uint4*>(UVo + o + p.f) = xv;
-          *reinterpret_cast<uint4*>(Ho + (long long)row * p.f + hu) = xh;
-        }
-      }
-    } else if (MODE == BWD_DH) {
-      // dh stays in fp32: staged like a weight-gradient block, then every lane takes 8
-      // consecutive hidden units of one row, combines them with the saved u and v (16 bytes
-      // each, whole lines per instruction) and writes du = dh v s (1 + u (1 - s)),
-      // dv = dh u s, s = sigmoid(u).  The u, v loads of block i + 1 are issued before block i
-      // is worked on, so their latency hides behind it.  They are unconditional: a lane past
-      // the tile's last row or column reads the last valid row / the last 8 columns instead
-      // (its result is never stored).  A load under a branch would make the compiler lose
-      // count of the memory operations in flight and wait for all of them, the stores of the
-      // previous rows included, before every use of a loaded value.
-      float* const sf = reinterpret_cast<float*>(stg);
-      const uint16_t* UVi = static_cast<const uint16_t*>(p.UV);
-      uint16_t* Co = static_cast<uint16_t*>(p.C);
-      const int col = n0 + wn * 128 + (lane & 15) * 8;
-      const int colc = min(col, p.N - 8);
-      const int twof = 2 * p.f;
-      auto load_uv = [&](int blk, uint4 (&uu)[8], uint4 (&vv)[8]) {
-        const int rb = row0 + wm * WROWS + blk * 32;
-        const uint16_t* const q0 = UVi + (long long)rb * twof + colc;
-#pragma unroll
-        for (int it = 0; it < 8; ++it) {
-          const int dr = min(rb + it * 4 + (lane >> 4), row1 - 1) - rb;   // may be negative
-          const uint16_t* const q = q0 + (long long)dr * twof;
-          uu[it] = *reinterpret_cast<const uint4*>(q);
-          vv[it] = *reinterpret_cast<const uint4*>(q + p.f);
-        }
-      };
-      if (i == 0) load_uv(0, uvu[0], uvv[0]);
-      if (i + 1 < MI) load_uv(i + 1, uvu[(i + 1) & 1], uvv[(i + 1) & 1]);
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-          *reinterpret_cast<float4*>(sf + r32 * LDF + 32 * j + 8 * g + 4 * hw) =
-              make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
-      __builtin_amdgcn_s_waitcnt(0xC07F);
-#pragma unroll
-      for (int it = 0; it < 8; ++it) {
-        const int rr = it * 4 + (lane >> 4);
-        const int row = rbase + rr;
-        const float4 d0 = *reinterpret_cast<const float4*>(sf + rr * LDF + (lane & 15) * 8);
-        const float4 d1 = *reinterpret_cast<const float4*>(sf + rr * LDF + (lane & 15) * 8 + 4);
-        if (row < row1 && col < p.N) {
-          const long long o = (long long)row * 2 * p.f + col;
-          const uint4 uu = uvu[i & 1][it], vv = uvv[i & 1][it];
-          const float dh[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
-          const uint32_t uw[4] = {uu.x, uu.y, uu.z, uu.w}, vw[4] = {vv.x, vv.y, vv.z, vv.w};
-          uint32_t du[4], dv[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            float o_du[2], o_dv[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              const float u_ = __uint_as_float(h ? (uw[q] & 0xffff0000u) : (uw[q] << 16));
-              const float v_ = __uint_as_float(h ? (vw[q] & 0xffff0000u) : (vw[q] << 16));
-              const float sg = sigmoid_fast(u_);
-              o_du[h] = dh[2 * q + h] * v_ * sg * (1.f + u_ * (1.f - sg));
-              o_dv[h] = dh[2 * q + h] * u_ * sg;
-            }
-            du[q] = pack_bf16x2(o_du[0], o_du[1]);
-            dv[q] = pack_bf16x2(o_dv[0], o_dv[1]);
-          }
-          *reinterpret_cast<uint4*>(Co + o) = make_uint4(du[0], du[1], du[2], du[3]);
-          *reinterpret_cast<uint4*>(Co + o + p.f) = make_uint4(dv[0], dv[1], dv[2], dv[3]);
-        }
-      }
-    } else if ((MODE == FWD2 || MODE == BWD_DX) && !to_partial) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-          *reinterpret_cast<uint2*>(stg + r32 * LDB + 32 * j + 8 * g + 4 * hw) =
-              make_uint2(pack_bf16x2(acc[i][j][4 * g], acc[i][j][4 * g + 1]),
-                         pack_bf16x2(acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]));
-      __builtin_amdgcn_s_waitcnt(0xC07F);
-      uint16_t* Co = static_cast<uint16_t*>(p.C);
-      const int col = n0 + wn * 128 + (lane & 15) * 8;
-#pragma unroll
-      for (int it = 0; it < 8; ++it) {
-        const int rr = it * 4 + (lane >> 4);
-        const int row = rbase + rr;
-        const uint4 x = *reinterpret_cast<const uint4*>(stg + rr * LDB + (lane & 15) * 8);
-        if (row < row1 && col < p.N) *reinterpret_cast<uint4*>(Co + (long long)row * p.N + col) = x;
-      }
-    } else {   // weight gradients, fp32
-      float* const sf = reinterpret_cast<float*>(stg);
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-          *reinterpret_cast<float4*>(sf + r32 * LDF + 32 * j + 8 * g + 4 * hw) =
-              make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
-      __builtin_amdgcn_s_waitcnt(0xC07F);
-      if (VARM) {   // a slice's partial tile
-        float* Co = p.partials + (size_t)pslot * (BM * BN) + (wm * WROWS + i * 32) * BN + wn * 128 + (lane & 31) * 4;
-#pragma unroll
-        for (int it = 0; it < 16; ++it) {
-          const int rr = it * 2 + (lane >> 5);
-          *reinterpret_cast<float4*>(Co + rr * BN) = *reinterpret_cast<const float4*>(sf + rr * LDF + (lane & 31) * 4);
-        }
-      } else {
-        float* Co = static_cast<float*>(p.C) + (long long)group * p.c_group_stride;
-        const int col = n0 + wn * 128 + (lane & 31) * 4;
-#pragma unroll
-        for (int it = 0; it < 16; ++it) {
-          const int rr = it * 2 + (lane >> 5);
-          const int row = rbase + rr;
-          const float4 x = *reinterpret_cast<const float4*>(sf + rr * LDF + (lane & 31) * 4);
-          if (row < row1 && col < p.N) *reinterpret_cast<float4*>(Co + (long long)row * p.N + col) = x;
-        }
-      }
-    }
-    // the next block reuses the staging area: its writes must not pass these reads
-    __builtin_amdgcn_s_waitcnt(0xC07F);
-    __builtin_amdgcn_sched_barrier(0);
-  }
+  // 32 KB of the operand stages per wavefront
+  write_tile<MODE, MI, 4>(p, smem + wave * (16 * 1024), acc, row0, row1, group, n0, wm, wn, lane,
+                                nsl > 1 ? pslot : -1);
 }
 
 // Workgroups go to the eight XCDs (each with an L2 of its own) round robin in launch order:
@@ -688,7 +704,7 @@ __device__ __forceinline__ void xcd_block(int b, int ntx, int R, int& tile) {
 
 template <int MODE>
 __global__ __launch_bounds__(GT) void gemm_bf16_kernel(GemmParams p) {
-  __shared__ __attribute__((aligned(1024))) uint16_t smem[2 * BM * BK + 2 * BN * BK];
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[2 * BM * BK + 3 * BN * BK];
   constexpr bool VARM = MODE <= BWD_DX;
   int row0, row1, group, kbeg = 0, K, bx = blockIdx.x;
   // this workgroup reduces slice zsl of nsl, starting at reduction index kofs; if nsl > 1 its
@@ -805,7 +821,6 @@ __global__ __launch_bounds__(256) void slice_sum_kernel(GemmParams p, int ntx) {
 // Two-level summation: every 16 reduction indices are summed in a fresh accumulator and then added,
 // which keeps the rounding error of long reductions (weight gradients) near sqrt(K/16).
 constexpr int F32_CHUNK = 16;
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
 
 // What both fp32 kernels need to know about a product: its operands, their pitches and extents.
 template <int MODE>

@@ -780,6 +780,110 @@ __global__ __launch_bounds__(GT) void gemm_bf16_kernel(GemmParams p) {
   gemm_tile<MODE, 4>(p, smem, row0, row1, group, kbeg, K, bx, nsl, kofs, pslot);
 }
 
+// ---------------------------------------------------------------- forward products of a small batch
+// With few rows per slot the two forward products only stream weights: a 256-column tile has one
+// workgroup per compute unit, 32 - 64 KB of weights in flight, and most of its left operand's loads and MFMAs
+// are padding.  Here a tile is 64 rows x 128 columns (FWD1: 64 hidden units), NST stages of 24 KB, OCC
+// workgroups per unit; a slot's parts of 64 rows are far apart in launch order, so that the first
+// parts, often the only ones, spread over all XCDs.
+// Operand layout, fragments and epilogue are those of the large tile.
+template <int MODE>
+__global__ __launch_bounds__(GT, 2) void gemm_few_rows_kernel(GemmParams p) {
+  static_assert(MODE == FWD1 || MODE == FWD2, "both operands reduction-contiguous");
+  constexpr int TM = 64, TN = 128, NST = 3, LA = 2, LB = 4;   // LA, LB: 1 KB load instructions per wavefront and stage
+  constexpr int SA = TM * BK, SB = TN * BK;          // elements of a stage
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[NST * (SA + SB)];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int ntx = gridDim.x, per_part = p.tile_map[0] * ntx;
+  const int b = blockIdx.y * ntx + blockIdx.x, part = b / per_part, tile = b - part * per_part;
+  if (part >= GEMM_BM / TM) return;
+  const int mt = tile / ntx, bx = tile - mt * ntx;
+  const int row0 = p.tile_map[4 + 4 * mt] + part * TM;
+  const int row1 = min(p.tile_map[4 + 4 * mt + 1], row0 + TM);
+  if (row0 >= row1) return;
+  const int group = p.tile_map[4 + 4 * mt + 2];
+  const int n0 = bx * (MODE == FWD1 ? TN / 2 : TN), K = p.K, ld = p.K;
+  const uint16_t* const a_base = static_cast<const uint16_t*>(p.A) + (long long)row0 * ld;
+  const uint16_t* const b_base = static_cast<const uint16_t*>(p.B) + (long long)group * p.b_group_stride +
+                                 (MODE == FWD1 ? 0 : (long long)n0 * ld);
+
+  // element offset of this lane's 16 bytes for load q of a stage (rows 8q .. 8q + 7) and their reduction
+  // index in the step; rows beyond the operand's extent are clamped (they only reach outputs never stored)
+  auto lane_off = [&](bool right, int q, int& krel) -> unsigned {
+    const int r = q * 8 + (lane >> 3);
+    krel = ((lane & 7) ^ ((r >> 1) & 7)) * 8;
+    if (!right) return (unsigned)(min(r, row1 - row0 - 1) * ld + krel);
+    if (MODE == FWD1) {   // every 64 tile rows: 32 gate rows and the 32 up rows of the same hidden units
+      const int hu = min(n0 + (r >> 6) * 32 + (r & 31), p.f - 1);
+      return (unsigned)((((r >> 5) & 1) * p.f + hu) * ld + krel);
+    }
+    return (unsigned)(min(r, p.N - n0 - 1) * ld + krel);
+  };
+  unsigned vo[LA + LB];
+  int kr[LA + LB];
+#pragma unroll
+  for (int j = 0; j < LA + LB; ++j)
+    vo[j] = lane_off(j >= LA, j < LA ? wave * LA + j : wave * LB + j - LA, kr[j]);
+  const unsigned ldsA = (unsigned)(size_t)SYMI_LPTR(smem) + wave * (LA * 1024);
+  const unsigned ldsB = (unsigned)(size_t)SYMI_LPTR(smem + NST * SA) + wave * (LB * 1024);
+  const int nk = (K + BK - 1) / BK;
+  // loads of step t into stage st; reduction indices beyond K come from a block of zeros
+  auto issue = [&](int t, int st) {
+    const int k0 = t * BK;
+    unroll<LA + LB>([&](auto jc) {
+      constexpr int j = decltype(jc)::value;
+      const uint16_t* const base = (j < LA ? a_base : b_base) + k0;
+      const uint16_t* const src = k0 + kr[j] < K ? base + (size_t)vo[j] : g_zero_chunk;
+      const unsigned dst = j < LA ? ldsA + st * (SA * 2) + j * 1024 : ldsB + st * (SB * 2) + (j - LA) * 1024;
+      asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst), "v"(src) : "memory");
+    });
+  };
+  const int g4 = lane >> 4, r16 = lane & 15;
+  int adA[2], adB[2];   // fragment addresses (elements) per 32-deep sub-step
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    const int c = ((4 * x + g4) ^ ((r16 >> 1) & 7)) * 8;
+    adA[x] = (wm * 32 + r16) * BK + c;
+    adB[x] = NST * SA + (wn * 64 + r16) * BK + c;
+  }
+  floatx4 acc[2][4];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t = 0; t < NST - 1; ++t)
+    if (t < nk) issue(t, t);
+  int st = 0;
+  for (int t = 0; t < nk; ++t) {
+    // my fragment reads of step t - 1 are through (its stage is refilled behind the barrier) and my loads
+    // of step t have landed; those of the steps after it may fly
+    if (t + 1 < nk) __builtin_amdgcn_s_waitcnt(0x0070 + LA + LB); else __builtin_amdgcn_s_waitcnt(0x0070);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (t + NST - 1 < nk) issue(t + NST - 1, st == 0 ? NST - 1 : st - 1);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      bf16x8 fa[2], fb[4];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(smem + st * SA + adA[ks] + i * 16 * BK);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) fb[j] = *reinterpret_cast<const bf16x8*>(smem + st * SB + adB[ks] + j * 16 * BK);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+    }
+    st = st == NST - 1 ? 0 : st + 1;
+  }
+  __syncthreads();   // nobody reads operands any more
+  // 18 KB of LDS per wavefront for its 32-row block of 64 columns
+  write_tile<MODE, 1, 2>(p, smem + wave * (NST * (SA + SB) / 4), acc, row0, row1, group, n0, wm, wn, lane, -1);
+}
+
 // ---------------------------------------------------------------- sum of reduction slices
 // Runs behind FWD2 / BWD_DX (same stream): adds the partial tiles of every sliced tile in slice
 // order and writes the bf16 rows of the product.  Workgroup = 16 rows of a tile, a lane four
@@ -1163,6 +1267,16 @@ static void launch_gemm(const symi_ctx* ctx, const GemmParams& p, int n_cols, in
                         hipStream_t st) {
   const symi_cfg* const cfg = &ctx->cfg;
   if (cfg->dtype == SYMI_BF16) {
+    // At most 32 rows per slot on average: the kernel that streams weights.  Above that more and more slots
+    // have a second part of 64 rows, which reads the weights again (64 rows per slot, d = 1024, f = 4096: 349 us
+    // against 280 of the large tile; 32 rows: 259 against 270; d = 256, f = 768: 25.6 / 32.0 and 19.8 / 29.9).
+    if constexpr (MODE == FWD1 || MODE == FWD2) {
+      if ((long long)cfg->T * cfg->k <= 32LL * cfg->S_tot) {
+        dim3 grid(cdiv(n_cols, MODE == FWD1 ? 64 : 128), max_mtiles * (GEMM_BM / 64));
+        SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_few_rows_kernel<MODE><<<grid, GT, 0, st>>>(p)));
+        return;
+      }
+    }
     const int bn = MODE == FWD1 ? BN / 2 : BN;
     const int ntx = cdiv(n_cols, bn);
     // FWD2, BWD_DX: room for the slices of the last round's tiles (at most cus workgroups more)

@@ -670,14 +670,21 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const s
   int t = 0;
   for (; (t + 4) * BK <= K; t += 2) pair(t, std::false_type{});
   for (; t < nk; t += 2) pair(t, std::true_type{});
-  // dummy loads and the fragment read of the last phase are still in flight: they must
-  // not outlive the workgroup's LDS allocation.  The last MFMAs are through after 16 wait states.
+  // The dummy loads and the fragments read in the last phase are still in flight.  They must not outlive
+  // the workgroup's LDS allocation, and the fragments' registers stay taken until they have landed: to
+  // the compiler they are written and free, and what it moved up from the epilogue into one of them
+  // would be overwritten by a late read.
+  __builtin_amdgcn_s_waitcnt(0xC07F);
+#pragma unroll
+  for (int q = 0; q < MI; ++q) asm volatile("" : "+v"(fa[0][q]));
+#pragma unroll
+  for (int q = 0; q < 8; ++q) asm volatile("" : "+v"(fb[0][q]));
+  // the last MFMAs are through after 16 wait states; no accumulator is read before
   asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
 #pragma unroll
-  for (int i = 0; i < 2 * MI; ++i)   // no accumulator is read before the wait states
+  for (int i = 0; i < 2 * MI; ++i)
     asm volatile("" : "+a"(acc[i][0]), "+a"(acc[i][1]), "+a"(acc[i][2]), "+a"(acc[i][3]), "+a"(acc[i][4]),
                  "+a"(acc[i][5]), "+a"(acc[i][6]), "+a"(acc[i][7]));
-  __builtin_amdgcn_s_waitcnt(0xC07F);
   wait_vmcnt0();
 
   __syncthreads();   // every wavefront's dummy loads have landed, nobody reads operands any more

@@ -790,7 +790,7 @@ __global__ __launch_bounds__(GT) void gemm_bf16_kernel(GemmParams p) {
 // ---------------------------------------------------------------- forward products of a small batch
 // With few rows per slot the two forward products only stream weights: a 256-column tile has one
 // workgroup per compute unit, 32 - 64 KB of weights in flight, and most of its left operand's loads and MFMAs
-// are padding.  Here a tile is 64 rows x 128 columns (FWD1: 64 hidden units), NST stages of 24 KB, OCC
+// are padding.  Here a tile is 64 rows x 128 columns (FWD1: 64 hidden units), three stages of 24 KB, two
 // workgroups per unit; a slot's parts of 64 rows are far apart in launch order, so that the first
 // parts, often the only ones, spread over all XCDs.
 // Operand layout, fragments and epilogue are those of the large tile.

@@ -804,8 +804,9 @@ __global__ __launch_bounds__(GT, 2) void gemm_few_rows_kernel(GemmParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int ntx = gridDim.x, per_part = p.tile_map[0] * ntx;
-  const int b = blockIdx.y * ntx + blockIdx.x, part = b / per_part, tile = b - part * per_part;
-  if (part >= GEMM_BM / TM) return;
+  const int b = blockIdx.y * ntx + blockIdx.x;
+  if (b >= GEMM_BM / TM * per_part) return;   // all workgroups when no slot has rows: nothing divides by zero
+  const int part = b / per_part, tile = b - part * per_part;
   const int mt = tile / ntx, bx = tile - mt * ntx;
   const int row0 = p.tile_map[4 + 4 * mt] + part * TM;
   const int row1 = min(p.tile_map[4 + 4 * mt + 1], row0 + TM);

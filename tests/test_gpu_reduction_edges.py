@@ -2,7 +2,9 @@
 seven 64-deep steps with and without a partial last step (two stages of one operand, three of the
 other), classes of few rows, and slots on both sides of the half-height tile's 128 rows."""
 import pytest
+import torch
 
+import paper_2504_19925_amd as symi
 import workloads as wl
 import harness as Hn
 from tests.checks import check_iteration
@@ -32,3 +34,28 @@ def test_few_rows_per_slot(E, k, S, d, f, T):
     st = Hn.State(c, shard=0)
     X, logits, dY = Hn.draw_inputs(c, 0)
     check_iteration(st, X, logits, dY)
+
+
+# A rank whose experts got nothing brings slot offsets that are all zero with a positive token count: no
+# row exists, so nothing is computed and nothing written, whatever an earlier call (here one with every
+# row in the first slot) left in the workspace
+@pytest.mark.parametrize("dtype,T,S", [("bf16", 192, 24), ("bf16", 400, 6), ("f32", 192, 24), ("f32", 9000, 6)])
+def test_no_slot_has_rows(dtype, T, S):
+    c = wl.scaled(wl.get_config("c2"), dtype=dtype, E=4, k=2, d=136, f=520, T=T, S_tot=S, N=1, iters=1,
+                  router_matmul=False)
+    st = Hn.State(c, shard=0)
+    st.Xp.normal_()
+    st.W1s.normal_()
+    st.W2s.normal_()
+
+    def forward(kept):
+        st.slot_offsets.fill_(kept)
+        st.slot_offsets[0] = 0
+        for t in (st.UV, st.H, st.Yp):
+            t.fill_(3.0)
+        symi.symi_expert_fwd(st.ctx, st.Xp, st.slot_offsets, st.W1s, st.W2s, st.UV, st.H, st.Yp, st.ws)
+        return [bool((t == 3.0).all()) for t in (st.UV, st.H, st.Yp)]
+
+    print(f"[no rows] {dtype} T={T} S={S}", flush=True)
+    assert forward(c.A) == [False] * 3
+    assert forward(0) == [True] * 3

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(256) void gemm_loop_kernel(const uint16_t* __restri
     constexpr bool right = Q >= 8;
     if (j == 0) {
       const unsigned l = (unsigned)(size_t)LPTR((right ? sB : sA) + wave_u * 64 * BK + 4 * 8 * BK);
-      asm volatile("s_mov_b32 m0, %0" ::"s"(l) : "memory");
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" ::"s"(l) : "memory");   // the wait state of an M0 write
     }
     const char* sb = reinterpret_cast<const char*>(right ? B : A) + (long long)k0 * 2 - 4096;   // wave-uniform
     const unsigned v = vo[right ? 1 : 0][j];

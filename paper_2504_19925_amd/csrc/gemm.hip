@@ -508,8 +508,10 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const s
     voA[j] = lane_off(false, j, unused) * 2u + 4096u - (unsigned)((j - 4) * 1024);
     voB[j] = lane_off(true, j, unused) * 2u + 4096u - (unsigned)((j - 4) * 1024);
   }
+  // a direct-to-LDS load needs one wait state behind a write of M0, and the compiler, which would put it
+  // there, does not look inside inline assembly
   auto set_m0 = [&](unsigned lds_byte_addr) {
-    asm volatile("s_mov_b32 m0, %0" ::"s"(lds_byte_addr) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" ::"s"(lds_byte_addr) : "memory");
   };
   auto load_fast = [&](auto jc, unsigned voff, const void* sbase) {
     constexpr int J = decltype(jc)::value;
@@ -845,7 +847,7 @@ __global__ __launch_bounds__(GT, 2) void gemm_few_rows_kernel(GemmParams p) {
       const uint16_t* const base = (j < LA ? a_base : b_base) + k0;
       const uint16_t* const src = k0 + kr[j] < K ? base + (size_t)vo[j] : g_zero_chunk;
       const unsigned dst = j < LA ? ldsA + st * (SA * 2) + j * 1024 : ldsB + st * (SB * 2) + (j - LA) * 1024;
-      asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst), "v"(src) : "memory");
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst), "v"(src) : "memory");   // the wait state of an M0 write
     });
   };
   const int g4 = lane >> 4, r16 = lane & 15;

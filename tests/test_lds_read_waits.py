@@ -1,6 +1,8 @@
-"""The hand-written LDS reads of the bf16 products, checked in the code that hipcc makes of them: a
-register that such a read fills is neither read nor written before a wait for all LDS operations
-(the compiler takes the output of inline assembly as written at once)."""
+"""The hand-written LDS reads and direct-to-LDS loads of the bf16 products, checked in the code that
+hipcc makes of them: a register that such a read fills is neither read nor written before a wait for
+all LDS operations (the compiler takes the output of inline assembly as written at once), and a
+write of M0 is followed by its wait state before a load that takes its LDS address from M0 (the compiler
+puts none into inline assembly)."""
 import os
 import re
 import shutil
@@ -50,12 +52,47 @@ def early_uses(lines):
     return found, reads
 
 
-@pytest.mark.skipif(not shutil.which(HIPCC), reason="needs hipcc")
-def test_no_register_is_used_before_its_read_has_landed(tmp_path):
-    out = str(tmp_path / "gemm.s")
+def m0_without_wait(lines):
+    """(kernel, instruction) of direct-to-LDS loads that directly follow a write of M0."""
+    kernel, before, found, loads = "", "", [], 0
+    for line in lines:
+        s = line.split(";")[0].strip()
+        m = re.match(r"(_Z\w+):", s)
+        if m:
+            kernel = m.group(1)
+        if not re.match(r"[a-z]+_\w+( |$)", s):   # labels, directives, comments
+            continue
+        if s.startswith("global_load_lds") or s.startswith("buffer_load") and s.endswith("lds"):
+            loads += 1
+            if re.match(r"s_\w+ m0,", before):
+                found.append((kernel, s))
+        before = s
+    return found, loads
+
+
+def _device_code(source, tmp_path_factory):
+    if not shutil.which(HIPCC):
+        pytest.skip("needs hipcc")
+    out = str(tmp_path_factory.mktemp("code") / (source + ".s"))
     flags = [x for x in build.FLAGS if x not in ("-shared",)]
-    subprocess.run([HIPCC] + flags + ["--cuda-device-only", "-S", os.path.join(build.CSRC, "gemm.hip"), "-o", out],
+    subprocess.run([HIPCC] + flags + ["--cuda-device-only", "-S", os.path.join(build.CSRC, source), "-o", out],
                    check=True, stderr=subprocess.DEVNULL)
-    found, reads = early_uses(open(out).read().splitlines())
+    return open(out).read().splitlines()
+
+
+@pytest.fixture(scope="module")
+def gemm_code(tmp_path_factory):
+    return _device_code("gemm.hip", tmp_path_factory)
+
+
+def test_no_register_is_used_before_its_read_has_landed(gemm_code):
+    found, reads = early_uses(gemm_code)
     assert reads > 100
     assert not found, found[:5]
+
+
+def test_every_m0_write_has_its_wait_state(gemm_code, tmp_path_factory):
+    for code in (gemm_code, _device_code("ceilings.hip", tmp_path_factory)):
+        found, loads = m0_without_wait(code)
+        assert loads > 30
+        assert not found, (len(found), found[:5])

@@ -43,11 +43,24 @@ def build(verbose: bool = True) -> str:
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
+    build_marshal(verbose)
+    return LIB
+
+
+def build_marshal(verbose: bool = True) -> bool:
+    """Builds _marshal.so if the host compiler and the headers of Python and torch are there.  Without it
+    the binding calls the library through ctypes; an older one does not stay beside a new libsymi.so."""
+    if os.path.exists(MARSHAL_LIB):
+        os.remove(MARSHAL_LIB)
     cmd = marshal_command()
     if verbose:
         print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
-    return LIB
+    try:
+        subprocess.run(cmd, check=True)
+    except (OSError, subprocess.CalledProcessError) as e:
+        print(f"_marshal.so was not built, device calls will go through ctypes: {e}", file=sys.stderr, flush=True)
+        return False
+    return True
 
 
 if __name__ == "__main__":

@@ -64,8 +64,13 @@ __device__ __forceinline__ float sigmoid_fast(float u) {
 }
 
 // ---------------------------------------------------------------- m-tile table
-// map[0] = number of m-tiles, map[4 + 4i ..] = {first row, end row, slot} of m-tile i.
+// map[0] = number of m-tiles, map[4 + 4i ..] = {first row, end row, slot} of m-tile i (TM = 256 rows), or
+// map[4 + 2i ..] = {first row, slot + 2^16 * (rows - 1)} (TM = FEW_BM: the small-batch forward products; at most
+// 32 rows per slot on average make at most 1.5 S_tot of them, which fit where 256-row tiles would be).
 // order[c] = the class with the c-th largest number of rows (ties: lower index first).
+constexpr int FEW_BM = 64;
+
+template <int TM>
 __global__ __launch_bounds__(256) void tile_map_kernel(const int32_t* __restrict__ slot_offsets,
                                                        const int32_t* __restrict__ first_slot, int S,
                                                        int E, int32_t* __restrict__ map,
@@ -76,7 +81,7 @@ __global__ __launch_bounds__(256) void tile_map_kernel(const int32_t* __restrict
   const int per = (S + 255) / 256;
   const int q0 = tid * per, q1 = min(S, q0 + per);
   int mine = 0;
-  for (int q = q0; q < q1; ++q) mine += (slot_offsets[q + 1] - slot_offsets[q] + GEMM_BM - 1) / GEMM_BM;
+  for (int q = q0; q < q1; ++q) mine += (slot_offsets[q + 1] - slot_offsets[q] + TM - 1) / TM;
   part[tid] = mine;
   if (first_slot) {
     for (int e = tid; e < E; e += 256) rows[e] = slot_offsets[first_slot[e + 1]] - slot_offsets[first_slot[e]];
@@ -92,11 +97,16 @@ __global__ __launch_bounds__(256) void tile_map_kernel(const int32_t* __restrict
   if (tid == 255) map[0] = part[255];
   for (int q = q0; q < q1; ++q) {
     const int b = slot_offsets[q], e = slot_offsets[q + 1];
-    for (int r = b; r < e; r += GEMM_BM, ++t) {
-      map[4 + 4 * t + 0] = r;
-      map[4 + 4 * t + 1] = min(e, r + GEMM_BM);
-      map[4 + 4 * t + 2] = q;
-      map[4 + 4 * t + 3] = 0;
+    for (int r = b; r < e; r += TM, ++t) {
+      if (TM == FEW_BM) {
+        map[4 + 2 * t + 0] = r;
+        map[4 + 2 * t + 1] = q + ((min(e - r, TM) - 1) << 16);
+      } else {
+        map[4 + 4 * t + 0] = r;
+        map[4 + 4 * t + 1] = min(e, r + TM);
+        map[4 + 4 * t + 2] = q;
+        map[4 + 4 * t + 3] = 0;
+      }
     }
   }
   if (first_slot) {
@@ -793,27 +803,34 @@ __global__ __launch_bounds__(GT) void gemm_bf16_kernel(GemmParams p) {
 // With few rows per slot the two forward products only stream weights: a 256-column tile has one
 // workgroup per compute unit, 32 - 64 KB of weights in flight, and most of its left operand's loads and MFMAs
 // are padding.  Here a tile is 64 rows x 128 columns (FWD1: 64 hidden units), three stages of 24 KB, two
-// workgroups per unit; a slot's parts of 64 rows are far apart in launch order, so that the first
-// parts, often the only ones, spread over all XCDs.
+// workgroups per unit.  The table lists the tiles that exist, a slot's one after the other, and those of one
+// column tile run next to each other in time on one XCD (workgroup number mod 8), so a slot with many rows gets
+// its weights through one L2 once.  As four parts of the large tiles, all first parts launched before all
+// second ones, each part fetched them anew: 4096 rows in 32 of 128 slots of d = 2048, f = 1408 287 us, now 209;
+// and most of the workgroups had nothing to do: 2 rows in each of 96 slots of d = 1024, f = 4096 518 -> 513.
 // Operand layout, fragments and epilogue are those of the large tile.
 template <int MODE>
 __global__ __launch_bounds__(GT, 2) void gemm_few_rows_kernel(GemmParams p) {
   static_assert(MODE == FWD1 || MODE == FWD2, "both operands reduction-contiguous");
-  constexpr int TM = 64, TN = 128, NST = 3, LA = 2, LB = 4;   // LA, LB: 1 KB load instructions per wavefront and stage
+  constexpr int TM = FEW_BM, TN = 128, NST = 3, LA = 2, LB = 4;   // LA, LB: 1 KB load instructions per wavefront and stage
   constexpr int SA = TM * BK, SB = TN * BK;          // elements of a stage
   __shared__ __attribute__((aligned(1024))) uint16_t smem[NST * (SA + SB)];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int ntx = gridDim.x, per_part = p.tile_map[0] * ntx;
-  const int b = blockIdx.y * ntx + blockIdx.x;
-  if (b >= GEMM_BM / TM * per_part) return;   // all workgroups when no slot has rows: nothing divides by zero
-  const int part = b / per_part, tile = b - part * per_part;
-  const int mt = tile / ntx, bx = tile - mt * ntx;
-  const int row0 = p.tile_map[4 + 4 * mt] + part * TM;
-  const int row1 = min(p.tile_map[4 + 4 * mt + 1], row0 + TM);
-  if (row0 >= row1) return;
-  const int group = p.tile_map[4 + 4 * mt + 2];
+  int mt = blockIdx.y, bx = blockIdx.x;
+  const int ntx = gridDim.x, n_tiles = p.tile_map[0];
+  if (ntx & 7) {   // rounds of 8 tiles, a column tile of all 8 on one XCD
+    const int b = mt * ntx + bx, round = b / (8 * ntx);
+    if (8 * round + 8 <= n_tiles) {
+      const int r = b - round * 8 * ntx, q = (r & 7) * ntx + (r >> 3);
+      mt = 8 * round + (q & 7);
+      bx = q >> 3;
+    }
+  }
+  if (mt >= n_tiles) return;
+  const int row0 = p.tile_map[4 + 2 * mt], entry = p.tile_map[4 + 2 * mt + 1];
+  const int row1 = row0 + (entry >> 16) + 1, group = entry & 0xffff;
   const int n0 = bx * (MODE == FWD1 ? TN / 2 : TN), K = p.K, ld = p.K;
   const uint16_t* const a_base = static_cast<const uint16_t*>(p.A) + (long long)row0 * ld;
   const uint16_t* const b_base = static_cast<const uint16_t*>(p.B) + (long long)group * p.b_group_stride +
@@ -1272,17 +1289,29 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_small_kernel(GemmParams p) {
   }
 }
 
+// bf16 forward products, at most 32 rows per slot on average: the tile that streams weights.  Both products against
+// the large tile, 32 rows per slot on average, in all slots / half / a quarter / a tenth / one of them (us):
+//   96 slots, d = 1024, f = 4096    558 : 624   328 : 359   217 : 228   187 : 171   138 : 124
+//   128 slots, d = 2048, f = 1408   505 : 574   308 : 332   209 : 213   176 : 172   121 : 113
+//   60 slots, d = 1160, f = 2744    341 : 420   237 : 254   189 : 187   153 : 150   116 : 109
+//   40 slots, d = 4096, f = 2048    487 : 605   302 : 340   203 : 195   158 : 162   133 : 157
+//   24 slots, d = 256, f = 768       28 : 44     25 : 42     23 : 42     21 : 47     21 : 47
+// and 8 on average, in a tenth / one: 112 : 134, 67 : 81; 113 : 124, 46 : 104; 91 : 115, 64 : 109; 91 : 149, 67 : 130;
+// 20 : 40, 20 : 48.  The host knows the mean only.  Placement keeps the slots even, where the tile gains 10 - 20 %;
+// with every row in a tenth of the slots or fewer, 300 rows and more in each, it loses 2 - 12 % on some
+// shapes, so the line lies no higher: 64 rows in every slot of the first shape 349 : 280.
+static bool few_rows(const symi_cfg* c) {
+  return c->dtype == SYMI_BF16 && (long long)c->T * c->k <= 32LL * c->S_tot;
+}
+
 template <int MODE>
 static void launch_gemm(const symi_ctx* ctx, const GemmParams& p, int n_cols, int max_mtiles,
                         hipStream_t st) {
   const symi_cfg* const cfg = &ctx->cfg;
   if (cfg->dtype == SYMI_BF16) {
-    // At most 32 rows per slot on average: the kernel that streams weights.  Above that more and more slots
-    // have a second part of 64 rows, which reads the weights again (64 rows per slot, d = 1024, f = 4096: 349 us
-    // against 280 of the large tile; 32 rows: 259 against 270; d = 256, f = 768: 25.6 / 32.0 and 19.8 / 29.9).
     if constexpr (MODE == FWD1 || MODE == FWD2) {
-      if ((long long)cfg->T * cfg->k <= 32LL * cfg->S_tot) {
-        dim3 grid(cdiv(n_cols, MODE == FWD1 ? 64 : 128), max_mtiles * (GEMM_BM / 64));
+      if (few_rows(cfg)) {
+        dim3 grid(cdiv(n_cols, MODE == FWD1 ? 64 : 128), cfg->T * cfg->k / FEW_BM + cfg->S_tot);
         SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_few_rows_kernel<MODE><<<grid, GT, 0, st>>>(p)));
         return;
       }
@@ -1345,7 +1374,10 @@ extern "C" int symi_expert_fwd(const symi_ctx* ctx, const void* Xp, const int32_
   const WsLayout& L = ctx->L;
   int32_t* map = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + L.tile_map);
   const int max_mtiles = (int)(A / GEMM_BM) + cfg->S_tot;
-  SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<<<1, 256, 0, st>>>(slot_offsets, nullptr, cfg->S_tot, cfg->E, map, nullptr)));
+  if (few_rows(cfg))
+    SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<FEW_BM><<<1, 256, 0, st>>>(slot_offsets, nullptr, cfg->S_tot, cfg->E, map, nullptr)));
+  else
+    SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<GEMM_BM><<<1, 256, 0, st>>>(slot_offsets, nullptr, cfg->S_tot, cfg->E, map, nullptr)));
 
   GemmParams p = {};
   p.tile_map = map;
@@ -1405,7 +1437,7 @@ static int expert_bwd_impl(const char* who, const symi_ctx* ctx, const void* dYp
   set_split(ctx, ws, p);
   p.d = cfg->d;
   p.f = cfg->f;
-  SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<<<1, 256, 0, st>>>(slot_offsets, first_slot, cfg->S_tot, cfg->E, map, order)));
+  SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<GEMM_BM><<<1, 256, 0, st>>>(slot_offsets, first_slot, cfg->S_tot, cfg->E, map, order)));
   // worth it only while a product is a few rounds of workgroups: with many rounds the chip is
   // full anyway and two kernels sharing it only disturb each other's L2 locality (symi_create
   // decides; the context then holds the helper stream)

@@ -59,3 +59,30 @@ def test_no_slot_has_rows(dtype, T, S):
     print(f"[no rows] {dtype} T={T} S={S}", flush=True)
     assert forward(c.A) == [False] * 3
     assert forward(0) == [True] * 3
+
+
+# Rows are few per slot on average but sit in some of the slots: the 64-row tiles of the small-batch forward
+# products at their edges, 25 of them (three rounds of 8 and one more) in 1, 2, 3, 6, 8 and 16 column tiles,
+# against binary64.  A stored value is a 32-bit sum rounded to bf16 (half of
+# 2^-8), h of the unrounded u and v; the second product is compared on the stored h
+@pytest.mark.parametrize("d,f", [(8, 72), (264, 328), (1024, 1000)])
+def test_a_small_batch_in_a_few_slots(d, f):
+    rows = [0, 1, 63, 64, 65, 0, 127, 128, 129, 191, 193, 257, 10] + [0] * 35
+    S, T = len(rows), sum(rows)
+    assert T <= 32 * S
+    c = wl.scaled(wl.get_config("c2"), E=4, k=1, d=d, f=f, T=T, S_tot=S, N=1, iters=1, router_matmul=False)
+    st = Hn.State(c, shard=0)
+    g = torch.Generator(device="cuda").manual_seed(d)
+    for t, std in ((st.Xp, 1.0), (st.W1s, d ** -0.5), (st.W2s, f ** -0.5)):
+        t.normal_(0.0, std, generator=g)
+    st.slot_offsets.copy_(torch.tensor([0] + rows).cumsum(0))
+    print(f"[few slots] d={d} f={f}", flush=True)
+    symi.symi_expert_fwd(st.ctx, st.Xp, st.slot_offsets, st.W1s, st.W2s, st.UV, st.H, st.Yp, st.ws)
+    slot = torch.repeat_interleave(torch.arange(S), torch.tensor(rows))
+    X, W1, W2, UV, H, Yp = (t.cpu().double() for t in (st.Xp, st.W1s, st.W2s, st.UV, st.H, st.Yp))
+    for s in slot.unique().tolist():
+        at = slot == s
+        uv = X[at] @ W1[s].T
+        h = torch.nn.functional.silu(uv[:, :f]) * uv[:, f:]
+        for got, want in ((UV[at], uv), (H[at], h), (Yp[at], H[at] @ W2[s].T)):
+            assert ((got - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5).all(), (s, rows[s])

@@ -2,6 +2,7 @@
 wavefronts, 64 x 64, 64 x 128): every stage of an iteration against the oracle.  The tolerance is the
 one every fp32 stage has (harness.metrics): 32-bit products summed 16 at a time."""
 import pytest
+import torch
 
 import harness as Hn
 import workloads as wl
@@ -9,24 +10,41 @@ from tests.checks import check_iteration
 
 pytestmark = pytest.mark.gpu
 
+# shape, and the tiling of the six products (the two forward ones, dh, dX, dW2, dW1): "s" shared reduction,
+# 64 and 128 columns wide
 SHAPES = {
     # one row, reductions of a single 8-deep piece
-    "one row": dict(T=1, E=1, k=1, S_tot=1, N=1, d=8, f=8),
+    "one row": (dict(T=1, E=1, k=1, S_tot=1, N=1, d=8, f=8), ("s", "s", "s", "s", "s", "s")),
     # 32-row tiles with a remainder of one row and one column piece, reductions no multiple of 16
-    "shared reduction": dict(T=33, E=3, k=2, S_tot=6, N=3, d=40, f=72),
+    "shared reduction": (dict(T=33, E=3, k=2, S_tot=6, N=3, d=40, f=72), ("s", "s", "s", "s", "s", "s")),
     # reductions longer than the wavefronts' 16-deep rounds, classes without rows
-    "long reduction": dict(T=700, E=16, k=1, S_tot=20, N=4, d=264, f=128),
-    # 64-wide tiles: 8 columns in the last column tile, 32-deep steps with a remainder of 8
-    "64 x 64": dict(T=2050, E=8, k=2, S_tot=12, N=2, d=136, f=520),
+    "long reduction": (dict(T=700, E=16, k=1, S_tot=20, N=4, d=264, f=128), ("s", "s", "s", "s", "s", "s")),
+    # all three tilings in one iteration: 8 columns in the last column tile, 32-deep steps with a remainder of 8
+    "all three": (dict(T=2050, E=8, k=2, S_tot=12, N=2, d=136, f=520), (128, "s", 64, "s", "s", 64)),
+    # 64-wide tiles wherever there are any, 8 rows and columns in the last one
+    "64 x 64": (dict(T=4100, E=16, k=2, S_tot=24, N=2, d=200, f=520), (128, 64, 64, 64, 64, 64)),
+    # the last 128-wide tile with two whole 32-column blocks and 8 columns of a third
+    "64 and 128 wide": (dict(T=4100, E=8, k=2, S_tot=12, N=2, d=264, f=1096), (128, 64, 128, 64, 64, 64)),
     # 128-wide tiles for every product, the last one with less than one 32-column block
-    "64 x 128": dict(T=4100, E=8, k=2, S_tot=12, N=2, d=264, f=1096),
+    "64 x 128": (dict(T=6600, E=16, k=2, S_tot=24, N=2, d=520, f=1096), (128, 128, 128, 128, 128, 128)),
 }
+
+
+def tilings(T, E, k, S_tot, d, f, cus, **_):
+    """The dispatch rule of the fp32 products: 64 x 128 tiles of each against the compute units."""
+    up = lambda a, b: -(-a // b)
+    rows = T * k // 64 + S_tot // 2
+    tiles = (rows * up(f, 64), rows * up(d, 128), rows * up(f, 128), rows * up(d, 128),
+             up(d, 64) * E * up(f, 128), up(2 * f, 64) * E * up(d, 128))
+    return tuple("s" if n < cus else 64 if i and n < 4 * cus else 128 for i, n in enumerate(tiles))
 
 
 @pytest.mark.parametrize("name", list(SHAPES))
 @pytest.mark.parametrize("active", [False, True])
 def test_fp32_products(name, active):
-    c = wl.scaled(wl.get_config("c1"), router_matmul=False, **SHAPES[name])
+    shape, want = SHAPES[name]
+    assert tilings(cus=torch.cuda.get_device_properties(0).multi_processor_count, **shape) == want
+    c = wl.scaled(wl.get_config("c1"), router_matmul=False, **shape)
     st = Hn.State(c)
     st.active_grads = active
     X, logits, dY = Hn.draw_inputs(c, 0)

@@ -76,3 +76,73 @@ def test_the_current_stream_is_used(layer):
     torch.cuda.current_stream().wait_stream(side)
     torch.cuda.synchronize()
     assert torch.equal(got, want.flip(0))
+
+
+def _arguments(st, X, logits, dY):
+    """A valid argument list of every device call; every tensor is exactly as large as the call needs."""
+    E, S, d, f = st.c.E, st.c.S_tot, st.c.d, st.c.f
+    new = lambda *n, dtype=st.cfg.torch_dtype: torch.zeros(*n, dtype=dtype, device="cuda")
+    f32 = torch.float32
+    fwd = [X, st.idx, st.hist, st.counts, st.first_slot, st.row_of_assign, st.assign_of_row, st.slot_offsets, st.Xp]
+    bwd = [st.dYp, st.Xp, st.UV, st.H, st.slot_offsets, st.first_slot, st.W1s, st.W2s, st.dXp]
+    dW = [st.dW1, st.dW2]
+    dWs = [new(S, 2 * f, d, dtype=f32), new(S, d, f, dtype=f32)]
+    opt = [Hn.make_adam()[0], *dW, st.master, st.m, st.v]
+    Wr, b = new(E, d), new(E, dtype=f32)
+    calls = {
+        "symi_route": [logits, st.idx, st.gate, st.hist],
+        "symi_place": [st.hist, st.counts, st.placement, st.first_slot],
+        "symi_dispatch": [*fwd, st.ws],
+        "symi_dispatch_noalloc": fwd,
+        "symi_dispatch_capacity": [st.c.A, *fwd, st.ws],
+        "symi_expert_fwd": [st.Xp, st.slot_offsets, st.W1s, st.W2s, st.UV, st.H, st.Yp, st.ws],
+        "symi_combine": [st.Yp, st.row_of_assign, st.gate, st.Y],
+        "symi_combine_bwd": [dY, st.Yp, st.row_of_assign, st.gate, st.dYp, st.dgate],
+        "symi_expert_bwd": [*bwd, *dW, st.ws],
+        "symi_expert_bwd_active": [*bwd, *dW, st.ws],
+        "symi_expert_bwd_slots": [*bwd, *dWs, st.ws],
+        "symi_replica_allreduce": [st.first_slot, 1.0, *dWs],
+        "symi_dispatch_bwd": [st.dXp, st.row_of_assign, st.dX],
+        "symi_route_bwd": [logits, st.idx, st.gate, st.dgate, st.dlogits],
+        "symi_router_fwd": [X, Wr, b, new(st.c.T, E, dtype=f32)],
+        "symi_router_bwd": [X, Wr, st.dlogits, new(E, d, dtype=f32), new(E, dtype=f32), st.dX, st.ws],
+        "symi_adam_to_replicas": [*opt, st.first_slot, st.W1s, st.W2s],
+        "symi_adam_to_replicas_active": [*opt, st.slot_offsets, st.first_slot, st.first_slot, st.W1s, st.W2s],
+    }
+    return {n: [st.ctx, *a] for n, a in calls.items()}
+
+
+OTHER = {torch.float32: torch.int32, torch.int32: torch.float32, torch.bfloat16: torch.float16,
+         torch.uint8: torch.int8}   # of the same size
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_every_call_takes_exact_sizes_and_refuses_less(dtype):
+    """Every tensor of every call: accepted in C++ at exactly the size the call needs; one element
+    less, or another type of the same size, is refused with the ctypes path's words.  Sizes differ between
+    any two quantities, so that a mistaken one shows."""
+    c = wl.scaled(wl.get_config("c1"), dtype=dtype, E=6, k=3, d=40, f=56, T=97, S_tot=11, N=2, router_matmul=False)
+    st = Hn.State(c)
+    X, logits, dY = Hn.draw_inputs(c, 0)
+    st.place_current()
+    calls = _arguments(st, X, logits, dY)
+    assert set(calls) == set(symi.binding._marshal)
+    for name, args in calls.items():      # in the order of an iteration
+        assert symi.binding._marshal[name](*args) == 0, name
+        for i, t in enumerate(args):
+            if not isinstance(t, torch.Tensor):
+                continue
+            for bad in (t.view(-1)[:-1], t.view(OTHER[t.dtype])):   # (the memory is whole either way)
+                wrong = args[:i] + [bad] + args[i + 1:]
+                assert symi.binding._marshal[name](*wrong) is None, (name, i)
+                said = []
+                for call in (getattr(symi, name), getattr(symi, name).__wrapped__):
+                    with pytest.raises(symi.SymiError, match="needs at least|expected dtype") as e:
+                        call(*wrong)
+                    said.append(str(e.value))
+                assert said[0] == said[1], name
+    torch.cuda.synchronize()
+    for name, i in (("symi_router_fwd", 3), ("symi_router_bwd", 5)):      # the bias may be left out
+        args = list(calls[name])
+        args[i] = None
+        assert symi.binding._marshal[name](*args) == 0, name

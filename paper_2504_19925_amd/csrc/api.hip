@@ -51,8 +51,11 @@ int check_cfg(const symi_cfg* c, const char* who) {
     return SYMI_EUNSUPPORTED;            \
   }
   // launch limits of the kernels: the m-tile index of the grouped GEMM (one per 64 rows in the
-  // fp32 twin, plus the slices of a cut last round) and the router's 128-token tiles are grid.y
-  // coordinates; the GEMM's per-lane element offsets inside a slot's weights are 32 bits
+  // fp32 products, plus the slices of a cut last round) and the router's 128-token tiles are grid.y
+  // coordinates; the GEMM's per-lane element offsets inside a slot's weights are 32 bits.  The products of
+  // small batches count finer and always fit: 8 per m-tile in the fp32 ones, which have fewer 64-row tiles
+  // (T*k/64 + S_tot/2) than the device has compute units; one per 64 rows and slot in the bf16 ones, of
+  // which there are at most 1.5 S_tot = 6144
   const long long A = (long long)c->T * c->k;
   const long long mtiles = A / GEMM_BM + c->S_tot;
   UNSUPPORTED(c->dtype == SYMI_BF16 ? mtiles + 256 > 65535 : 4 * mtiles > 65535,

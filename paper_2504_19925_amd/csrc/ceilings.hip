@@ -4,11 +4,12 @@
 //
 //   symi_ceiling_mfma        16 independent MFMA 32x32x16 bf16 chains per wavefront, operands in
 //                            registers: the rate of the matrix pipes alone with the given data
-//   symi_ceiling_gemm_loop   the reduction loop of the grouped GEMM (256x256 tile, 64-deep steps,
-//                            direct-to-LDS loads into two stages in the scalar-base form with one
-//                            M0 write per operand and stage, fragment reads by hand, four phases
-//                            of 16 MFMAs) on a plain C = A B^T, whole or with one of its three
-//                            ingredients taken out
+//   symi_ceiling_gemm_loop   a reduction loop like the grouped GEMM's, in its simpler form with two
+//                            stages of both operands and MFMA 32x32x16 (256x256 tile, 64-deep steps,
+//                            direct-to-LDS loads in the scalar-base form with one M0 write per
+//                            operand and stage, fragment reads by hand, four phases of 16 MFMAs; the
+//                            product's kernel has a third stage of the right operand and 16x16x32) on a
+//                            plain C = A B^T, whole or with one of its three ingredients taken out
 //   symi_ceiling_adam_streams the Adam step's memory streams (4 fp32 reads, 3 fp32 writes, bf16
 //                            replica writes) without the optimizer's meaning, in three layouts
 // All pointers are device pointers of the caller, all launches go to the caller's stream.

@@ -1335,7 +1335,7 @@ static void launch_gemm(const symi_ctx* ctx, const GemmParams& p, int n_cols, in
     // workgroups: 475 tiles, second forward product 135 us shared / 99 us 64 wide / 113 us 128 wide,
     // input gradient 250 / 203 / 268; at 2240 tiles 128 wide reads its left operand half as often.
     const long long rows = VARM ? (long long)cfg->T * cfg->k / F32_BM + cfg->S_tot / 2 : (long long)cdiv(p.M, F32_BM) * groups;
-    if (rows * ntx < 1LL * ctx->cus && 8LL * max_mtiles <= 65535) {
+    if (rows * ntx < 1LL * ctx->cus) {
       dim3 grid(cdiv(n_cols, 32), VARM ? 8 * max_mtiles : cdiv(p.M, 32), VARM ? 1 : groups);
       SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_f32_small_kernel<MODE, NW><<<grid, 64 * NW, 0, st>>>(p)));
       return;

@@ -124,15 +124,17 @@ __global__ __launch_bounds__(256) void tile_map_kernel(const int32_t* __restrict
 // lane).  Tiles travel HBM -> LDS with the gfx950 direct-to-LDS loads (16 bytes per
 // lane, no staging registers) into two 32 KB stages of the left operand and three of the right
 // one, the whole 160 KB of a compute unit.
-// Bound by the matrix pipes at the clock the power limit leaves (1.5 - 1.6 GHz of 2.4 with random
-// operands), as long as neither loads nor instruction issue leave them idle:
+// With long reductions bound by the matrix pipes at the clock the power limit leaves (c5: busy 65 - 77 % of
+// the cycles at 1.7 - 1.8 GHz of 2.4 with random operands; c3, K up to 28672: 65 - 86 %), as long as neither
+// loads nor instruction issue leave them idle; with short ones (c2, K = 1024: busy 30 - 61 %) the epilogue,
+// which runs with idle pipes, is what is left:
 //  - Lead of the loads.  With two stages of both operands the loads of a step had to be issued
 //    within two of its four phases and had 2 - 4 phases to land; the third stage of the right operand
 //    spreads them evenly over all phases and gives them 2 - 6.
 //  - MFMA 16x16x32 instead of 32x32x16: a block sums 32 products before it touches its accumulator,
 //    and reads and loads can sit between MFMAs of 16 cycles.  Same bits as 32x32x16.
 //  c5's six products 68.7 -> 64.6 (16x16x32) -> 61.3 ms (third stage), c4's 10.17 -> 9.85 -> 9.05, c2's
-//  2.73 -> 2.64 -> 2.33; LDS reads occupy 20 % of the cycles.  Two loads per eight MFMAs instead of
+//  2.73 -> 2.64 -> 2.33; LDS instructions hold 18 - 22 % of the cycles.  Two loads per eight MFMAs instead of
 //  one cost 3 %, four 6 %.
 // LDS layouts (all conflict-free for the access pattern that reads them):
 //   reduction-contiguous operand: [256 rows][64 k], 16-byte chunk c of row r stored at
@@ -1027,8 +1029,8 @@ __device__ __forceinline__ void f32_store(const GemmParams& p, int group, long l
 // only reach outputs that are never stored), reduction indices beyond K are zeros in both
 // operands.  A wavefront whose outputs all lie outside multiplies nothing.
 // Bound by the matrix pipes once a few workgroups share a unit (E = 24, 9000 rows in 36 slots,
-// d = 328, f = 872: first forward product 160 us, 59 % of the cycles are MFMAs, 13 % of them padding of
-// ragged slots; the plain-FMA kernel took 238, the six products together 1070 -> 700 us).
+// d = 328, f = 872: first forward product 160 us, 59 % of the cycles are MFMAs, 15 % of them padding of
+// ragged slots and columns; the plain-FMA kernel took 238, the six products together 1070 -> 700 us).
 constexpr int F32_BM = 64, F32_BK = 32;
 
 template <int MODE, int NBL>

@@ -144,15 +144,15 @@ __global__ __launch_bounds__(256) void tile_map_kernel(const int32_t* __restrict
 //     32 lanes the LDS serves per cycle (k-rows 0..3 and 8..11, 32 B each) then fall into 64 distinct banks;
 //     fragments come from the transposing LDS read (ds_read_b64_tr_b16), which hands
 //     lane j of a 16-lane group the four k-values of column j.
-// A direct-to-LDS load cannot zero-fill: rows or columns beyond the tile's extent are clamped
-// to a valid one (they only reach outputs that are never stored), reduction indices beyond K
-// load from a block of zeros.
+// Rows or columns beyond the tile's extent are clamped to a valid one (they only reach outputs that are never
+// stored), reduction indices beyond K are zeros in both operands (load_edge).
 constexpr int BM = 256, BN = 256, BK = 64;
 constexpr int GT = 256;
 
 __device__ __attribute__((aligned(16))) uint16_t g_zero_chunk[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short shortx4;
+typedef __attribute__((__vector_size__(4 * sizeof(int)))) int intx4;
 #define SYMI_GPTR(p) ((const void __attribute__((address_space(1)))*)(p))
 #define SYMI_LPTR(p) ((void __attribute__((address_space(3)))*)(p))
 
@@ -445,7 +445,6 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const s
                         : MODE == BWD_DX ? 2LL * p.f : MODE == WGRAD2 ? p.d : 2LL * p.f;
   const long long ldb = MODE == FWD1 ? p.d : MODE == FWD2 ? p.f : MODE == BWD_DH ? p.f
                         : MODE == BWD_DX ? p.d : MODE == WGRAD2 ? p.f : p.d;
-  const uint16_t* zero = g_zero_chunk;
 
   // ---- direct-to-LDS loads: a wave-uniform base per reduction step plus a 32-bit per-lane
   // element offset, one per instruction j (0..7) and operand.
@@ -455,15 +454,12 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const s
   //   lane -> (k-row + lane/32, physical chunk lane%32)
   // Rows / column chunks beyond the operand's extent are clamped to a valid one: what
   // they bring in only reaches outputs that are never stored.
-  // The main loop takes its 16 offsets from registers (no vector arithmetic next to the
-  // MFMAs).  The last iterations, which load the partial step or steps beyond K, recompute
-  // them from five lane constants and point every reduction index beyond K at a block of
-  // zeros.
-  int kc_row = wave * 64 + (lane >> 3);                        // tile row of instruction 0
-  int kc_c0 = (lane & 7) ^ ((lane >> 4) & 7);                  // logical chunk for even j
-  int ks_kb = wave * 16 + (lane >> 5);                         // k-row of instruction 0
-  int ks_c0 = (lane & 31) ^ (10 * (lane >> 5));                // logical chunk, j-dependent bits to come
-  int f1_row = wave * 32 + (lane >> 3);                        // FWD1 weights: hidden unit of instruction 0
+  // The 16 offsets stay in registers (no vector arithmetic next to the MFMAs).
+  const int kc_row = wave * 64 + (lane >> 3);                  // tile row of instruction 0
+  const int kc_c0 = (lane & 7) ^ ((lane >> 4) & 7);            // logical chunk for even j
+  const int ks_kb = wave * 16 + (lane >> 5);                   // k-row of instruction 0
+  const int ks_c0 = (lane & 31) ^ (10 * (lane >> 5));          // logical chunk, j-dependent bits to come
+  const int f1_row = wave * 32 + (lane >> 3);                  // FWD1 weights: hidden unit of instruction 0
 
   const uint16_t* a_base;   // element (first tile row / column, reduction index 0)
   const uint16_t* b_base;
@@ -485,14 +481,13 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const s
   // LDS destination of instruction j (wave-uniform): both layouts advance 1 KB per j
   const int wdst = wave * 8 * 512;  // elements: 8 instructions x 512 elements per wavefront
   // q = 0..15: even = left operand, odd = right operand, instruction j = q/2
-  // offset of this lane's 16 bytes for instruction j, and its reduction index within the step
-  auto lane_off = [&](bool right, int j, int& krel) -> unsigned {
+  // offset of this lane's 16 bytes for instruction j
+  auto lane_off = [&](bool right, int j) -> unsigned {
     const bool kcontig = right ? B_KC : A_KC;
     const int ld = (int)(right ? ldb : lda);
     const int lim = right ? b_lim : a_lim;
     if (kcontig) {
       const int kc = kc_c0 ^ (4 * (j & 1));
-      krel = kc * 8;
       if (right && MODE == FWD1) {
         // tile row t -> hidden unit n0 + (t>>7)*64 + ((t>>6)&1)*32 + (t&31), up half if (t>>5)&1
         const int hu = min(n0 + f1_row + 8 * (j & 3), lim);
@@ -501,7 +496,6 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const s
       return (unsigned)(min(kc_row + 8 * j, lim) * ld + kc * 8);
     }
     const int c = ks_c0 ^ (4 * (j & 1)) ^ (2 * ((j >> 2) & 1));
-    krel = ks_kb + 2 * j;
     return (unsigned)((ks_kb + 2 * j) * ld + (c * 8 < lim ? c : 0) * 8);
   };
   // The main loop's loads take the cheapest form the instruction has: a scalar base (operand +
@@ -516,9 +510,8 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const s
   unsigned voA[8], voB[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
-    int unused;
-    voA[j] = lane_off(false, j, unused) * 2u + 4096u - (unsigned)((j - 4) * 1024);
-    voB[j] = lane_off(true, j, unused) * 2u + 4096u - (unsigned)((j - 4) * 1024);
+    voA[j] = lane_off(false, j) * 2u + 4096u - (unsigned)((j - 4) * 1024);
+    voB[j] = lane_off(true, j) * 2u + 4096u - (unsigned)((j - 4) * 1024);
   }
   // a direct-to-LDS load needs one wait state behind a write of M0, and the compiler, which would put it
   // there, does not look inside inline assembly
@@ -528,6 +521,21 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const s
   auto load_fast = [&](auto jc, unsigned voff, const void* sbase) {
     constexpr int J = decltype(jc)::value;
     asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" ::"v"(voff), "s"(sbase), "n"((J - 4) * 1024) : "memory");
+  };
+  // The last pairs of steps, which load indices beyond K, take the buffer form of the load: a lane whose
+  // offset lies outside the buffer gets zeros, so a ragged end costs a compare and a select per load.  (With
+  // 64-bit addresses, recomputed per load, and those lanes pointed at a block of zeros in memory, such a step took
+  // 3600 cycles against 2390 of a full one of c4's first forward product, and an odd step count a whole idle step more: 14400
+  // cycles of 46000 for a tile of per-slot gradients, K = 384 on average.  Same bits; step E = 64, d = 2048, f = 1408 with
+  // per-slot gradients of 49152 rows 3727 -> 3581 us, backward of E = 12, d = 1160, f = 2744, 15009 rows 871 -> 855, c4
+  // 10.39 -> 10.27 ms.)  The immediate is unsigned here: the eight instructions of an operand take two M0 values and
+  // two bases 4 KB apart.
+  constexpr unsigned OUTSIDE = 0xfffff000u;   // valid offsets, with the biases below, stay under 2^32 - 8192
+  auto load_edge = [&](auto jc, unsigned voff, const char* base) {
+    constexpr int J = decltype(jc)::value;
+    const unsigned long long a = (unsigned long long)(base - (J < 4 ? 4096 : 0));
+    const intx4 rsrc = {(int)(unsigned)a, (int)((unsigned)(a >> 32) & 0xffffu), (int)OUTSIDE, 0x00020000};
+    asm volatile("buffer_load_dwordx4 %0, %1, 0 offen offset:%2 lds" ::"v"(voff), "s"(rsrc), "n"((J & 3) * 1024) : "memory");
   };
   // q = 0..7: instruction j = q of the left operand, q = 8..15: instruction j = q - 8 of the right one
   auto dma_one = [&](unsigned lds_stage, int k0, auto qc, auto partial) {
@@ -541,11 +549,11 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const s
     const uint16_t* sbase = kcontig ? base + k0 : base + (long long)k0 * ld;   // wave-uniform
     const unsigned lds0 = lds_stage + 2 * wdst;   // this wavefront's 8 KB of the stage
     if (decltype(partial)::value) {
-      int krel;
-      const unsigned off = lane_off(right, j, krel);
-      const uint16_t* src = k0 + krel < K ? sbase + (size_t)off : zero;
-      set_m0(lds0 + j * 1024);
-      asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(src) : "memory");
+      const int left = K - k0;   // reduction indices of this step; a multiple of 8 where they are contiguous
+      const bool in = kcontig ? (kc_c0 ^ (4 * (j & 1))) < (left >> 3) : ks_kb < left - 2 * j;
+      if (j == 0) set_m0(lds0);
+      if (j == 4) set_m0(lds0 + 4096);
+      load_edge(IC<j>{}, in ? (right ? voB[j] : voA[j]) : OUTSIDE, reinterpret_cast<const char*>(sbase) - 4096);
     } else {
       if (j == 0) set_m0(lds0 + 4096);
       load_fast(IC<j>{}, right ? voB[j] : voA[j], reinterpret_cast<const char*>(sbase) - 4096);
@@ -604,7 +612,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const s
   // the next stages.  Phases 3 and 0 load the left operand of step + 2 into the stage just freed, phases 1
   // and 2 the right one of step + 2 into the stage freed a step ago.  Neither an LDS round trip nor a load
   // latency is exposed to the MFMA pipe.  Steps beyond the last one load zeros (dummy
-  // loads keep the loop free of branches; a tail without them measured 1 % slower).
+  // loads keep the loop free of branches).
   const int nk = (K + BK - 1) / BK;
   auto phase = [&](auto ksc, auto stagec, int step, auto partial) {
     constexpr int KS = decltype(ksc)::value, S = decltype(stagec)::value;
@@ -616,10 +624,6 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const s
       __builtin_amdgcn_s_barrier();       // ... so has everybody's, and stage S is free
     }
     __builtin_amdgcn_sched_barrier(0);
-    if (decltype(partial)::value) {
-      // keep the address arithmetic of these loads inside the phase (not hoisted into registers)
-      asm volatile("" : "+v"(kc_row), "+v"(kc_c0), "+v"(ks_kb), "+v"(ks_c0), "+v"(f1_row));
-    }
     constexpr int NB = KS == 0 || KS == 1 ? 4 : KS == 2 ? 0 : 8;   // right blocks read in this phase
     auto read = [&](auto rc) {
       constexpr int r = decltype(rc)::value;
@@ -678,12 +682,16 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const s
   __builtin_amdgcn_s_barrier();
   unroll<MI>([&](auto q) { read_a(IC<0>{}, IC<0>{}, IC<0>{}, IC<0>{}, q); });
   unroll<8>([&](auto q) { read_b(IC<0>{}, q); });
-  // always pairs of steps: for an odd step count the second stage holds the zeros of the
-  // dummy loads and adds nothing (a mid-loop exit would cost more than the idle step).  A
-  // pair starting at step t loads steps up to t + 3.
+  // steps in pairs, an odd last one by itself; a pair starting at step t loads steps up to t + 3
   int t = 0;
   for (; (t + 4) * BK <= K; t += 2) pair(t, std::false_type{});
-  for (; t < nk; t += 2) pair(t, std::true_type{});
+  for (; t + 1 < nk; t += 2) pair(t, std::true_type{});
+  if (t < nk) {
+    phase(IC<0>{}, IC<0>{}, t, std::true_type{});
+    phase(IC<1>{}, IC<0>{}, t, std::true_type{});
+    phase(IC<2>{}, IC<0>{}, t, std::true_type{});
+    phase(IC<3>{}, IC<0>{}, t, std::true_type{});
+  }
   // The dummy loads and the fragments read in the last phase are still in flight.  They must not outlive
   // the workgroup's LDS allocation, and the fragments' registers stay taken until they have landed: to
   // the compiler they are written and free, and what it moved up from the epilogue into one of them

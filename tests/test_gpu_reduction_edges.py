@@ -86,3 +86,35 @@ def test_a_small_batch_in_a_few_slots(d, f):
         h = torch.nn.functional.silu(uv[:, :f]) * uv[:, f:]
         for got, want in ((UV[at], uv), (H[at], h), (Yp[at], H[at] @ W2[s].T)):
             assert ((got - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5).all(), (s, rows[s])
+
+
+# Indices beyond the end of a reduction are zeros in both operands, whatever lies behind them in memory: the rows of the
+# next class (weight gradients), the next row of the activations or of the weights (the other products).  NaN in
+# every second class must stay there.  1 to 5 steps, full and ragged, an odd and an even number of them
+@pytest.mark.parametrize("d,f,rows", [(8, 72, 1), (64, 128, 64), (72, 64, 65), (136, 200, 191), (192, 264, 193), (320, 136, 300)])
+def test_nothing_beyond_the_reduction(d, f, rows):
+    E = 4
+    c = wl.scaled(wl.get_config("c2"), E=E, k=1, d=d, f=f, T=E * rows, S_tot=E, N=1, iters=1, router_matmul=False)
+    st = Hn.State(c, shard=0)
+    g = torch.Generator(device="cuda").manual_seed(d + rows)
+    for t, std in ((st.Xp, 1.0), (st.dYp, 1.0), (st.W1s, d ** -0.5), (st.W2s, f ** -0.5)):
+        t.normal_(0.0, std, generator=g)
+    st.slot_offsets.copy_(torch.arange(E + 1) * rows)
+    st.first_slot.copy_(torch.arange(E + 1))
+
+    def run():
+        symi.symi_expert_fwd(st.ctx, st.Xp, st.slot_offsets, st.W1s, st.W2s, st.UV, st.H, st.Yp, st.ws)
+        symi.symi_expert_bwd(st.ctx, st.dYp, st.Xp, st.UV, st.H, st.slot_offsets, st.first_slot, st.W1s, st.W2s, st.dXp,
+                             st.dW1, st.dW2, st.ws)
+        return [t.view(E, -1).clone() for t in (st.UV, st.H, st.Yp, st.dXp, st.dW1, st.dW2)]
+
+    print(f"[beyond K] d={d} f={f} rows={rows}", flush=True)
+    clean = run()
+    for e in (1, 3):
+        st.Xp[e * rows:(e + 1) * rows] = float("nan")
+        st.dYp[e * rows:(e + 1) * rows] = float("nan")
+        st.W1s[e], st.W2s[e] = float("nan"), float("nan")
+    for a, b in zip(clean, run()):
+        assert torch.isfinite(a).all()
+        assert torch.equal(a[0], b[0]) and torch.equal(a[2], b[2])
+        assert torch.isnan(b[1]).all() and torch.isnan(b[3]).all()

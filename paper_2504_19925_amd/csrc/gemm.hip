@@ -153,6 +153,10 @@ __device__ __attribute__((aligned(16))) uint16_t g_zero_chunk[8] = {0, 0, 0, 0, 
 
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short shortx4;
 typedef __attribute__((__vector_size__(4 * sizeof(int)))) int intx4;
+typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned uintx4;
+// Byte offset outside every buffer descriptor of this file (and its length): a load there gives zeros, a store is
+// dropped.  Valid offsets stay under 2^32 - 8192, the biases of the loads included.
+constexpr unsigned OUTSIDE = 0xfffff000u;
 #define SYMI_GPTR(p) ((const void __attribute__((address_space(1)))*)(p))
 #define SYMI_LPTR(p) ((void __attribute__((address_space(3)))*)(p))
 
@@ -222,10 +226,34 @@ __device__ __forceinline__ void tail_slices(int n_tiles, int cus, int K, int& fu
 // back row by row, 16 bytes per lane) and each store instruction writes whole lines: for NJ = 4
 // 4 rows x 256 B (bf16 outputs), 8 rows x 128 B (u, v, h) or 2 rows x 512 B (fp32).
 // pslot >= 0: the accumulators of a reduction slice, left as an fp32 tile in that partial slot.
+// BWD_DH: saved[0] holds (or is about to receive) the saved u, v of the first 32-row block.
+template <int NJ>
+struct SavedUV { uint4 u[NJ * 2], v[NJ * 2]; };   // of a wavefront's 32-row block
+
+// The loads are unconditional: a lane past the tile's last row or column reads the last valid row / the last 8
+// columns instead (its result is never stored).  A load under a branch would make the compiler lose count of the
+// memory operations in flight and wait for all of them, the stores of the previous rows included, before every
+// use of a loaded value.
+template <int NJ>
+__device__ __forceinline__ void load_uv(const GemmParams& p, const int rb, const int row1, const int c0, const int lane,
+                                        SavedUV<NJ>& s) {
+  constexpr int LB = 4 * NJ;   // lanes that share a row
+  const int twof = 2 * p.f, colc = min(c0 + (lane & (LB - 1)) * 8, p.N - 8);
+  const uint16_t* const q0 = static_cast<const uint16_t*>(p.UV) + (long long)rb * twof + colc;
+#pragma unroll
+  for (int it = 0; it < 2 * NJ; ++it) {
+    const int dr = min(rb + it * (64 / LB) + lane / LB, row1 - 1) - rb;   // may be negative
+    const uint16_t* const q = q0 + (long long)dr * twof;
+    s.u[it] = *reinterpret_cast<const uint4*>(q);
+    s.v[it] = *reinterpret_cast<const uint4*>(q + p.f);
+  }
+}
+
 template <int MODE, int MI, int NJ>
 __device__ __forceinline__ void write_tile(const GemmParams& p, uint16_t* const stg, floatx4 (&acc)[2 * MI][2 * NJ],
                                            const int row0, const int row1, const int group, const int n0,
-                                           const int wm, const int wn, const int lane, const int pslot) {
+                                           const int wm, const int wn, const int lane, const int pslot,
+                                           SavedUV<NJ> (&saved)[2]) {
   constexpr bool VARM = MODE <= BWD_DX;
   constexpr int WROWS = 32 * MI;
   constexpr int CW = 32 * NJ, UW = 16 * NJ;   // columns of a wavefront; FWD1: its hidden units
@@ -235,12 +263,19 @@ __device__ __forceinline__ void write_tile(const GemmParams& p, uint16_t* const 
   constexpr int LDH = UW + 8;   // u / v / h rows + pad
   constexpr int LDF = CW + 4;   // fp32 row + pad
   constexpr int NUV = 32 / (64 / LB);
-  uint4 uvu[2][NUV], uvv[2][NUV];   // BWD_DH: saved u, v of the current and the next 32-row block
   // a slice stores its accumulators the way a weight gradient is stored: fp32, pitch 256
   const bool to_partial = (MODE == FWD2 || MODE == BWD_DX) && pslot >= 0;
+  // Lanes past the tile's last row or column store to an offset outside the buffer, which drops the store: a branch
+  // around every store kept the compiler from reading the staged rows ahead of it, and every 1 KB stored waited for
+  // an LDS round trip of its own.
+  auto store16 = [&](void* ubase, bool in, unsigned ofs, uint4 x) {
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(ubase, 0, (int)OUTSIDE, 0x00020000);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4, x), rsrc, (int)(in ? ofs : OUTSIDE), 0, 0);
+  };
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
     const int rbase = row0 + wm * WROWS + i * 32;   // first output row of this block
+    const int left = row1 - rbase;                  // rows from there on
     if (MODE == FWD1) {
       uint16_t* const su = stg;
       uint16_t* const sv = stg + 32 * LDH;
@@ -253,8 +288,10 @@ __device__ __forceinline__ void write_tile(const GemmParams& p, uint16_t* const 
           unsigned pu[2], pv[2], ph[2];
 #pragma unroll
           for (int c2 = 0; c2 < 2; ++c2) {
-            const float u0 = acc[2 * i + ih][g][2 * c2], u1 = acc[2 * i + ih][g][2 * c2 + 1];
-            const float v0 = acc[2 * i + ih][g + 2][2 * c2], v1 = acc[2 * i + ih][g + 2][2 * c2 + 1];
+            float u0 = acc[2 * i + ih][g][2 * c2], u1 = acc[2 * i + ih][g][2 * c2 + 1];
+            float v0 = acc[2 * i + ih][g + 2][2 * c2], v1 = acc[2 * i + ih][g + 2][2 * c2 + 1];
+            // one read of each accumulator: the compiler would rather fetch it from its AGPR again for every use
+            asm("" : "+v"(u0), "+v"(u1), "+v"(v0), "+v"(v1));
             pu[c2] = pack_bf16x2(u0, u1);
             pv[c2] = pack_bf16x2(v0, v1);
             ph[c2] = pack_bf16x2(u0 * sigmoid_fast(u0) * v0, u1 * sigmoid_fast(u1) * v1);
@@ -264,88 +301,73 @@ __device__ __forceinline__ void write_tile(const GemmParams& p, uint16_t* const 
           *reinterpret_cast<uint2*>(sv + at) = make_uint2(pv[0], pv[1]);
           *reinterpret_cast<uint2*>(sh + at) = make_uint2(ph[0], ph[1]);
         }
-      __builtin_amdgcn_s_waitcnt(0xC07F);
-      uint16_t* UVo = static_cast<uint16_t*>(p.UVout);
-      uint16_t* Ho = static_cast<uint16_t*>(p.H);
+      asm volatile("" ::: "memory");   // a wavefront's LDS operations are carried out in order
+      uint16_t* const UVo = static_cast<uint16_t*>(p.UVout) + (long long)rbase * 2 * p.f;
+      uint16_t* const Ho = static_cast<uint16_t*>(p.H) + (long long)rbase * p.f;
       const int hu = n0 + wn * UW + (lane & (LH - 1)) * 8;
+      constexpr int NIT = 32 * LH / 64;
+      uint4 xu[NIT], xv[NIT], xh[NIT];
 #pragma unroll
-      for (int it = 0; it < 32 * LH / 64; ++it) {
+      for (int it = 0; it < NIT; ++it) {
+        const int at = (it * (64 / LH) + lane / LH) * LDH + (lane & (LH - 1)) * 8;
+        xu[it] = *reinterpret_cast<const uint4*>(su + at);
+        xv[it] = *reinterpret_cast<const uint4*>(sv + at);
+        xh[it] = *reinterpret_cast<const uint4*>(sh + at);
+      }
+#pragma unroll
+      for (int it = 0; it < NIT; ++it) {
         const int rr = it * (64 / LH) + lane / LH;
-        const int row = rbase + rr;
-        const uint4 xu = *reinterpret_cast<const uint4*>(su + rr * LDH + (lane & (LH - 1)) * 8);
-        const uint4 xv = *reinterpret_cast<const uint4*>(sv + rr * LDH + (lane & (LH - 1)) * 8);
-        const uint4 xh = *reinterpret_cast<const uint4*>(sh + rr * LDH + (lane & (LH - 1)) * 8);
-        if (row < row1 && hu < p.f) {
-          const long long o = (long long)row * 2 * p.f + hu;
-          *reinterpret_cast<uint4*>(UVo + o) = xu;
-          *reinterpret_cast<uint4*>(UVo + o + p.f) = xv;
-          *reinterpret_cast<uint4*>(Ho + (long long)row * p.f + hu) = xh;
-        }
+        const bool in = rr < left && hu < p.f;
+        const unsigned o = (unsigned)(rr * p.f + hu) * 2u;
+        store16(UVo, in, o + (unsigned)(rr * p.f) * 2u, xu[it]);
+        store16(UVo + p.f, in, o + (unsigned)(rr * p.f) * 2u, xv[it]);
+        store16(Ho, in, o, xh[it]);
       }
     } else if (MODE == BWD_DH) {
       // dh stays in fp32: staged like a weight-gradient block, then every lane takes 8
       // consecutive hidden units of one row, combines them with the saved u and v (16 bytes
       // each, whole lines per instruction) and writes du = dh v s (1 + u (1 - s)),
       // dv = dh u s, s = sigmoid(u).  The u, v loads of block i + 1 are issued before block i
-      // is worked on, so their latency hides behind it.  They are unconditional: a lane past
-      // the tile's last row or column reads the last valid row / the last 8 columns instead
-      // (its result is never stored).  A load under a branch would make the compiler lose
-      // count of the memory operations in flight and wait for all of them, the stores of the
-      // previous rows included, before every use of a loaded value.
+      // is worked on, those of the first block before the last reduction steps, so their latency is hidden.
       float* const sf = reinterpret_cast<float*>(stg);
-      const uint16_t* UVi = static_cast<const uint16_t*>(p.UV);
-      uint16_t* Co = static_cast<uint16_t*>(p.C);
+      uint16_t* const Co = static_cast<uint16_t*>(p.C) + (long long)rbase * 2 * p.f;
       const int col = n0 + wn * CW + (lane & (LB - 1)) * 8;
-      const int colc = min(col, p.N - 8);
       const int twof = 2 * p.f;
-      auto load_uv = [&](int blk, uint4 (&uu)[NUV], uint4 (&vv)[NUV]) {
-        const int rb = row0 + wm * WROWS + blk * 32;
-        const uint16_t* const q0 = UVi + (long long)rb * twof + colc;
-#pragma unroll
-        for (int it = 0; it < NUV; ++it) {
-          const int dr = min(rb + it * (64 / LB) + lane / LB, row1 - 1) - rb;   // may be negative
-          const uint16_t* const q = q0 + (long long)dr * twof;
-          uu[it] = *reinterpret_cast<const uint4*>(q);
-          vv[it] = *reinterpret_cast<const uint4*>(q + p.f);
-        }
-      };
-      if (i == 0) load_uv(0, uvu[0], uvv[0]);
-      if (i + 1 < MI) load_uv(i + 1, uvu[(i + 1) & 1], uvv[(i + 1) & 1]);
+      if (i + 1 < MI) load_uv<NJ>(p, row0 + wm * WROWS + (i + 1) * 32, row1, n0 + wn * CW, lane, saved[(i + 1) & 1]);
 #pragma unroll
       for (int ih = 0; ih < 2; ++ih)
 #pragma unroll
         for (int j = 0; j < 2 * NJ; ++j)
           *reinterpret_cast<floatx4*>(sf + (ih * 16 + r16) * LDF + 16 * j + 4 * hq) = acc[2 * i + ih][j];
-      __builtin_amdgcn_s_waitcnt(0xC07F);
+      asm volatile("" ::: "memory");
 #pragma unroll
       for (int it = 0; it < NUV; ++it) {
         const int rr = it * (64 / LB) + lane / LB;
-        const int row = rbase + rr;
         const float4 d0 = *reinterpret_cast<const float4*>(sf + rr * LDF + (lane & (LB - 1)) * 8);
         const float4 d1 = *reinterpret_cast<const float4*>(sf + rr * LDF + (lane & (LB - 1)) * 8 + 4);
-        if (row < row1 && col < p.N) {
-          const long long o = (long long)row * 2 * p.f + col;
-          const uint4 uu = uvu[i & 1][it], vv = uvv[i & 1][it];
-          const float dh[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
-          const uint32_t uw[4] = {uu.x, uu.y, uu.z, uu.w}, vw[4] = {vv.x, vv.y, vv.z, vv.w};
-          uint32_t du[4], dv[4];
+        const bool in = rr < left && col < p.N;
+        const unsigned o = (unsigned)(rr * twof + col) * 2u;
+        const uint4 uu = saved[i & 1].u[it], vv = saved[i & 1].v[it];
+        const float dh[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
+        const uint32_t uw[4] = {uu.x, uu.y, uu.z, uu.w}, vw[4] = {vv.x, vv.y, vv.z, vv.w};
+        uint32_t du[4], dv[4];
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            float o_du[2], o_dv[2];
+        for (int q = 0; q < 4; ++q) {
+          float o_du[2], o_dv[2];
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              const float u_ = __uint_as_float(h ? (uw[q] & 0xffff0000u) : (uw[q] << 16));
-              const float v_ = __uint_as_float(h ? (vw[q] & 0xffff0000u) : (vw[q] << 16));
-              const float sg = sigmoid_fast(u_);
-              o_du[h] = dh[2 * q + h] * v_ * sg * (1.f + u_ * (1.f - sg));
-              o_dv[h] = dh[2 * q + h] * u_ * sg;
-            }
-            du[q] = pack_bf16x2(o_du[0], o_du[1]);
-            dv[q] = pack_bf16x2(o_dv[0], o_dv[1]);
+          for (int h = 0; h < 2; ++h) {
+            const float u_ = __uint_as_float(h ? (uw[q] & 0xffff0000u) : (uw[q] << 16));
+            const float v_ = __uint_as_float(h ? (vw[q] & 0xffff0000u) : (vw[q] << 16));
+            const float sg = sigmoid_fast(u_);
+            const float ds = dh[2 * q + h] * sg;
+            o_du[h] = ds * v_ * (1.f + u_ * (1.f - sg));
+            o_dv[h] = ds * u_;
           }
-          *reinterpret_cast<uint4*>(Co + o) = make_uint4(du[0], du[1], du[2], du[3]);
-          *reinterpret_cast<uint4*>(Co + o + p.f) = make_uint4(dv[0], dv[1], dv[2], dv[3]);
+          du[q] = pack_bf16x2(o_du[0], o_du[1]);
+          dv[q] = pack_bf16x2(o_dv[0], o_dv[1]);
         }
+        store16(Co, in, o, make_uint4(du[0], du[1], du[2], du[3]));
+        store16(Co + p.f, in, o, make_uint4(dv[0], dv[1], dv[2], dv[3]));
       }
     } else if ((MODE == FWD2 || MODE == BWD_DX) && !to_partial) {
 #pragma unroll
@@ -356,15 +378,17 @@ __device__ __forceinline__ void write_tile(const GemmParams& p, uint16_t* const 
           *reinterpret_cast<uint2*>(stg + (ih * 16 + r16) * LDB + 16 * j + 4 * hq) =
               make_uint2(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]));
         }
-      __builtin_amdgcn_s_waitcnt(0xC07F);
-      uint16_t* Co = static_cast<uint16_t*>(p.C);
+      asm volatile("" ::: "memory");
+      uint16_t* const Co = static_cast<uint16_t*>(p.C) + (long long)rbase * p.N;
       const int col = n0 + wn * CW + (lane & (LB - 1)) * 8;
+      uint4 x[NUV];
+#pragma unroll
+      for (int it = 0; it < NUV; ++it)
+        x[it] = *reinterpret_cast<const uint4*>(stg + (it * (64 / LB) + lane / LB) * LDB + (lane & (LB - 1)) * 8);
 #pragma unroll
       for (int it = 0; it < NUV; ++it) {
         const int rr = it * (64 / LB) + lane / LB;
-        const int row = rbase + rr;
-        const uint4 x = *reinterpret_cast<const uint4*>(stg + rr * LDB + (lane & (LB - 1)) * 8);
-        if (row < row1 && col < p.N) *reinterpret_cast<uint4*>(Co + (long long)row * p.N + col) = x;
+        store16(Co, rr < left && col < p.N, (unsigned)(rr * p.N + col) * 2u, x[it]);
       }
     } else {   // weight gradients, fp32
       float* const sf = reinterpret_cast<float*>(stg);
@@ -373,29 +397,28 @@ __device__ __forceinline__ void write_tile(const GemmParams& p, uint16_t* const 
 #pragma unroll
         for (int j = 0; j < 2 * NJ; ++j)
           *reinterpret_cast<floatx4*>(sf + (ih * 16 + r16) * LDF + 16 * j + 4 * hq) = acc[2 * i + ih][j];
-      __builtin_amdgcn_s_waitcnt(0xC07F);
+      asm volatile("" ::: "memory");
+      constexpr int NIT = 32 * LF / 64;
+      uint4 x[NIT];
+#pragma unroll
+      for (int it = 0; it < NIT; ++it)
+        x[it] = *reinterpret_cast<const uint4*>(sf + (it * (64 / LF) + lane / LF) * LDF + (lane & (LF - 1)) * 4);
       if (VARM) {   // a slice's partial tile
         float* Co = p.partials + (size_t)pslot * (BM * BN) + (wm * WROWS + i * 32) * BN + wn * CW + (lane & (LF - 1)) * 4;
 #pragma unroll
-        for (int it = 0; it < 32 * LF / 64; ++it) {
-          const int rr = it * (64 / LF) + lane / LF;
-          *reinterpret_cast<float4*>(Co + rr * BN) = *reinterpret_cast<const float4*>(sf + rr * LDF + (lane & (LF - 1)) * 4);
-        }
+        for (int it = 0; it < NIT; ++it) *reinterpret_cast<uint4*>(Co + (it * (64 / LF) + lane / LF) * BN) = x[it];
       } else {
-        float* Co = static_cast<float*>(p.C) + (long long)group * p.c_group_stride;
+        float* const Co = static_cast<float*>(p.C) + (long long)group * p.c_group_stride + (long long)rbase * p.N;
         const int col = n0 + wn * CW + (lane & (LF - 1)) * 4;
 #pragma unroll
-        for (int it = 0; it < 32 * LF / 64; ++it) {
+        for (int it = 0; it < NIT; ++it) {
           const int rr = it * (64 / LF) + lane / LF;
-          const int row = rbase + rr;
-          const float4 x = *reinterpret_cast<const float4*>(sf + rr * LDF + (lane & (LF - 1)) * 4);
-          if (row < row1 && col < p.N) *reinterpret_cast<float4*>(Co + (long long)row * p.N + col) = x;
+          store16(Co, rr < left && col < p.N, (unsigned)(rr * p.N + col) * 4u, x[it]);
         }
       }
     }
     // the next block reuses the staging area: its writes must not pass these reads
-    __builtin_amdgcn_s_waitcnt(0xC07F);
-    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
   }
 }
 
@@ -530,7 +553,6 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const s
   // per-slot gradients of 49152 rows 3727 -> 3581 us, backward of E = 12, d = 1160, f = 2744, 15009 rows 871 -> 855, c4
   // 10.39 -> 10.27 ms.)  The immediate is unsigned here: the eight instructions of an operand take two M0 values and
   // two bases 4 KB apart.
-  constexpr unsigned OUTSIDE = 0xfffff000u;   // valid offsets, with the biases below, stay under 2^32 - 8192
   auto load_edge = [&](auto jc, unsigned voff, const char* base) {
     constexpr int J = decltype(jc)::value;
     const unsigned long long a = (unsigned long long)(base - (J < 4 ? 4096 : 0));
@@ -685,6 +707,8 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const s
   // steps in pairs, an odd last one by itself; a pair starting at step t loads steps up to t + 3
   int t = 0;
   for (; (t + 4) * BK <= K; t += 2) pair(t, std::false_type{});
+  SavedUV<4> saved[2];
+  if (MODE == BWD_DH) load_uv<4>(p, row0 + wm * WROWS, row1, n0 + wn * 128, lane, saved[0]);
   for (; t + 1 < nk; t += 2) pair(t, std::true_type{});
   if (t < nk) {
     phase(IC<0>{}, IC<0>{}, t, std::true_type{});
@@ -712,7 +736,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint16_t* const s
   __syncthreads();   // every wavefront's dummy loads have landed, nobody reads operands any more
   // 32 KB of the operand stages per wavefront
   write_tile<MODE, MI, 4>(p, smem + wave * (16 * 1024), acc, row0, row1, group, n0, wm, wn, lane,
-                                nsl > 1 ? pslot : -1);
+                                nsl > 1 ? pslot : -1, saved);
 }
 
 // Workgroups go to the eight XCDs (each with an L2 of its own) round robin in launch order:
@@ -918,7 +942,8 @@ __global__ __launch_bounds__(GT, 2) void gemm_few_rows_kernel(GemmParams p) {
   }
   __syncthreads();   // nobody reads operands any more
   // 18 KB of LDS per wavefront for its 32-row block of 64 columns
-  write_tile<MODE, 1, 2>(p, smem + wave * (NST * (SA + SB) / 4), acc, row0, row1, group, n0, wm, wn, lane, -1);
+  SavedUV<2> saved[2];   // the input-gradient product's
+  write_tile<MODE, 1, 2>(p, smem + wave * (NST * (SA + SB) / 4), acc, row0, row1, group, n0, wm, wn, lane, -1, saved);
 }
 
 // ---------------------------------------------------------------- sum of reduction slices

@@ -20,6 +20,7 @@
 // kept ones are packed without gaps and spread over the replicas as before.
 #include <math.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "common.h"
@@ -194,7 +195,128 @@ __global__ __launch_bounds__(256) void scatter_rows_kernel(const uint4* __restri
   }
 }
 
-struct f8 { float v[8]; };
+// The whole dispatch of a small batch (A <= SMALL_A assignments, E <= SMALL_E classes) in one launch: every
+// workgroup ranks all assignments (rows in LDS; 16 wavefronts, as in chunk_rank_kernel) and moves its share of the
+// tokens; the first one also writes the tables.  With short kernels the launches are the time: four of them took
+// 11 us of kernel and about 13 us of the 33 us of a forward of 64 tokens.
+constexpr int SMALL_A = 4096, SMALL_E = 512, SMALL_DT = 1024;
+
+__global__ __launch_bounds__(SMALL_DT) void dispatch_small_kernel(
+    const int32_t* __restrict__ cls, int A, int E, int S, const int32_t* __restrict__ hist,
+    const int32_t* __restrict__ counts, const int32_t* __restrict__ first_slot, int slot_cap,
+    const uint4* __restrict__ src, uint4* __restrict__ dst, int32_t* __restrict__ row_of_assign,
+    int32_t* __restrict__ assign_of_row, int32_t* __restrict__ slot_offsets, int k, long long n_vec, int vec_per_row) {
+  constexpr int NW = SMALL_DT / 64;
+  extern __shared__ int32_t sm[];
+  int32_t* const rows = sm;              // [A] row of every assignment
+  int32_t* const first = rows + A;       // [E] first (kept) row of class e
+  int32_t* const cap = first + E;        // [E] rows class e may keep
+  int32_t* const running = cap + E;      // [E] assignments of class e so far
+  int32_t* const replicas = running + E; // [E] replicas of class e, and its first slot
+  int32_t* const slot0 = replicas + E;
+  int32_t* const wcnt = slot0 + E;       // [NW][E] per-wavefront counts of the current pass
+  __shared__ int32_t wsum[NW], slot_end;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const bool tables = blockIdx.x == 0;
+
+  // everything that is read from memory is requested up front: one latency instead of five
+  const int e0 = min(tid, E - 1);
+  const int my_hist = hist[e0], my_count = counts[e0], my_slot = first_slot[e0];
+  int cls_of[SMALL_A / SMALL_DT];
+#pragma unroll
+  for (int p = 0; p < SMALL_A / SMALL_DT; ++p) cls_of[p] = cls[min(p * SMALL_DT + tid, A - 1)];
+  const long long i0 = (long long)blockIdx.x * SMALL_DT + tid, di = (long long)gridDim.x * SMALL_DT;
+  uint4 piece[4];
+#pragma unroll
+  for (int p = 0; p < 4; ++p) piece[p] = src[min(i0 + p * di, n_vec - 1)];
+
+  // class i keeps min(hist[i], cap_i) rows; exclusive sums over the classes
+  int kept = 0;
+  if (tid < E) {
+    const long long c = slot_cap > 0 ? (long long)slot_cap * my_count : A;
+    cap[tid] = c < A ? (int)c : A;
+    kept = min(my_hist, cap[tid]);
+    running[tid] = 0;
+    replicas[tid] = my_count;
+    slot0[tid] = my_slot;
+  }
+  for (int i = tid; i < NW * E; i += SMALL_DT) wcnt[i] = 0;
+  int incl = kept;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int up = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += up;
+  }
+  if (lane == 63) wsum[wave] = incl;
+  __syncthreads();
+  for (int w = 0; w < wave; ++w) incl += wsum[w];
+  if (tid < E) first[tid] = incl - kept;
+  if (tid == E - 1) {
+    slot_end = incl;
+    if (tables) slot_offsets[S] = incl;
+  }
+  __syncthreads();
+
+  if (tables) {   // replica i of class e: rows O_e + floor(i*c_e/r_e) .. (i*c_e < 2^24), one class per wavefront
+    for (int e = wave; e < E; e += NW) {
+      const int r = replicas[e], F = slot0[e], c_e = (e + 1 < E ? first[e + 1] : slot_end) - first[e];
+      for (int i = lane; i < r; i += 64) slot_offsets[F + i] = first[e] + i * c_e / r;
+    }
+  }
+
+  int ebits = 0;
+  while ((1 << ebits) < E) ++ebits;
+  const unsigned long long lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+#pragma unroll
+  for (int p = 0; p < SMALL_A / SMALL_DT; ++p) {
+    if (p * SMALL_DT >= A) break;
+    const int a = p * SMALL_DT + tid, c_raw = cls_of[p];
+    const bool valid = a < A && (unsigned)c_raw < (unsigned)E;   // a class outside [0,E) is skipped
+    const int c = valid ? c_raw : 0;
+    unsigned long long mask = __ballot(valid);
+    for (int b = 0; b < ebits; ++b) {
+      const unsigned long long bal = __ballot((c >> b) & 1);
+      mask &= ((c >> b) & 1) ? bal : ~bal;
+    }
+    const int rank_in_wave = __popcll(mask & lt);
+    if (valid && rank_in_wave == 0) wcnt[wave * E + c] = __popcll(mask);
+    __syncthreads();
+    if (valid) {
+      int rho = running[c] + rank_in_wave;
+      for (int w = 0; w < wave; ++w) rho += wcnt[w * E + c];
+      // capacity rule: the first cap assignments of the class (stable order) are kept
+      const int row = rho < cap[c] ? first[c] + rho : -1;
+      rows[a] = row;
+      if (tables) {
+        row_of_assign[a] = row;
+        if ((unsigned)row < (unsigned)A) assign_of_row[row] = a;   // false if dropped (or hist disagrees with idx)
+      }
+    } else if (a < A) {
+      rows[a] = -1;
+    }
+    __syncthreads();
+    if (tid < E) {
+      int s = 0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) { s += wcnt[w * E + tid]; wcnt[w * E + tid] = 0; }
+      running[tid] += s;
+    }
+    __syncthreads();
+  }
+
+  auto move = [&](long long i, uint4 x) {
+    const long long t = i / vec_per_row;
+    const int c = (int)(i - t * vec_per_row);
+    for (int j = 0; j < k; ++j) {
+      const int row = rows[t * k + j];
+      if ((unsigned)row < (unsigned)A) dst[(long long)row * vec_per_row + c] = x;
+    }
+  };
+#pragma unroll
+  for (int p = 0; p < 4; ++p)
+    if (i0 + p * di < n_vec) move(i0 + p * di, piece[p]);
+  for (long long i = i0 + 4 * di; i < n_vec; i += di) move(i, src[i]);
+}
+
 
 template <bool BF16>
 __device__ __forceinline__ int load_piece(const void* p, long long piece, float (&out)[8]) {
@@ -342,6 +464,18 @@ static int dispatch_impl(const char* who, const symi_ctx* ctx, int slot_cap, con
   int32_t* blk = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + L.blk_counts);
   int32_t* tab = slot_cap > 0 ? reinterpret_cast<int32_t*>(static_cast<char*>(ws) + L.class_tab) : nullptr;
   const int nblk = cdiv(A, DISPATCH_CHUNK);
+  const int vpr = cfg->d * (cfg->dtype == SYMI_BF16 ? 2 : 4) / 16;
+  const long long nvec = (long long)cfg->T * vpr;
+  if (A > 0 && A <= SMALL_A && E <= SMALL_E) {
+    // four 16-byte pieces per thread, at most one workgroup per compute unit
+    const int grid = (int)std::min<long long>(ctx->cus, (nvec + 4 * SMALL_DT - 1) / (4 * SMALL_DT));
+    const size_t sh = ((size_t)A + (size_t)(5 + SMALL_DT / 64) * E) * sizeof(int32_t);
+    SYMI_TIMED(ctx, K_GATHER, st, (dispatch_small_kernel<<<grid, SMALL_DT, sh, st>>>(
+        idx, A, E, cfg->S_tot, hist, counts, first_slot, slot_cap, static_cast<const uint4*>(X), static_cast<uint4*>(Xp),
+        row_of_assign, assign_of_row, slot_offsets, cfg->k, nvec, vpr)));
+    SYMI_LAUNCH_CHECK(who);
+    return SYMI_OK;
+  }
   if (nblk > 0)
     SYMI_TIMED(ctx, K_CHUNK_COUNT, st, (chunk_count_kernel<<<nblk, DT, E * sizeof(int32_t), st>>>(idx, A, E, blk)));
   SYMI_TIMED(ctx, K_CHUNK_SCAN, st, (chunk_scan_kernel<<<E, DT, 0, st>>>(blk, nblk, E, cfg->S_tot, A, hist, counts,
@@ -349,9 +483,6 @@ static int dispatch_impl(const char* who, const symi_ctx* ctx, int slot_cap, con
   if (nblk > 0) {
     SYMI_TIMED(ctx, K_CHUNK_RANK, st, (chunk_rank_kernel<<<nblk, DT, (size_t)(1 + DT / 64) * E * sizeof(int32_t), st>>>(
         idx, A, E, blk, row_of_assign, assign_of_row, tab)));
-    const int w = cfg->dtype == SYMI_BF16 ? 2 : 4;
-    const int vpr = cfg->d * w / 16;
-    const long long nvec = (long long)cfg->T * vpr;
     SYMI_TIMED(ctx, K_GATHER, st, (scatter_rows_kernel<<<grid_for(nvec, 256 * 2), 256, 0, st>>>(
         static_cast<const uint4*>(X), static_cast<uint4*>(Xp), row_of_assign, cfg->k, nvec, vpr)));
   }

@@ -41,7 +41,8 @@ struct GemmParams {
   void* UVout;         // FWD1: u|v out
   void* H;             // FWD1: h out
   const int32_t* tile_map;      // [4 + 4*i]: header {n_tiles}, then {row0, row1, slot, -}
-  const int32_t* slot_offsets;  // weight gradients: class row ranges
+  const int32_t* slot_offsets;  // weight gradients: class row ranges; small batches: the slots' rows
+  int n_slots;
   const int32_t* first_slot;
   long long b_group_stride;     // elements between consecutive slots' weights
   long long c_group_stride;     // elements between consecutive classes' gradients
@@ -64,17 +65,13 @@ __device__ __forceinline__ float sigmoid_fast(float u) {
 }
 
 // ---------------------------------------------------------------- m-tile table
-// map[0] = number of m-tiles, map[4 + 4i ..] = {first row, end row, slot} of m-tile i (TM = 256 rows), or
-// map[4 + 2i ..] = {first row, slot + 2^16 * (rows - 1)} (TM = FEW_BM: the small-batch forward products; at most
-// 32 rows per slot on average make at most 1.5 S_tot of them, which fit where 256-row tiles would be).
+// map[0] = number of m-tiles, map[4 + 4i ..] = {first row, end row, slot} of m-tile i (256 rows).
 // order[c] = the class with the c-th largest number of rows (ties: lower index first).
-constexpr int FEW_BM = 64;
-
-template <int TM>
 __global__ __launch_bounds__(256) void tile_map_kernel(const int32_t* __restrict__ slot_offsets,
                                                        const int32_t* __restrict__ first_slot, int S,
                                                        int E, int32_t* __restrict__ map,
                                                        int32_t* __restrict__ order) {
+  constexpr int TM = GEMM_BM;
   __shared__ int32_t part[256];
   __shared__ int32_t rows[1024];
   const int tid = threadIdx.x;
@@ -98,15 +95,10 @@ __global__ __launch_bounds__(256) void tile_map_kernel(const int32_t* __restrict
   for (int q = q0; q < q1; ++q) {
     const int b = slot_offsets[q], e = slot_offsets[q + 1];
     for (int r = b; r < e; r += TM, ++t) {
-      if (TM == FEW_BM) {
-        map[4 + 2 * t + 0] = r;
-        map[4 + 2 * t + 1] = q + ((min(e - r, TM) - 1) << 16);
-      } else {
-        map[4 + 4 * t + 0] = r;
-        map[4 + 4 * t + 1] = min(e, r + TM);
-        map[4 + 4 * t + 2] = q;
-        map[4 + 4 * t + 3] = 0;
-      }
+      map[4 + 4 * t + 0] = r;
+      map[4 + 4 * t + 1] = min(e, r + TM);
+      map[4 + 4 * t + 2] = q;
+      map[4 + 4 * t + 3] = 0;
     }
   }
   if (first_slot) {
@@ -837,12 +829,14 @@ __global__ __launch_bounds__(GT) void gemm_bf16_kernel(GemmParams p) {
 // With few rows per slot the two forward products only stream weights: a 256-column tile has one
 // workgroup per compute unit, 32 - 64 KB of weights in flight, and most of its left operand's loads and MFMAs
 // are padding.  Here a tile is 64 rows x 128 columns (FWD1: 64 hidden units), three stages of 24 KB, two
-// workgroups per unit.  The table lists the tiles that exist, a slot's one after the other, and those of one
+// workgroups per unit.  The tiles that exist are numbered a slot's one after the other, and those of one
 // column tile run next to each other in time on one XCD (workgroup number mod 8), so a slot with many rows gets
 // its weights through one L2 once.  As four parts of the large tiles, all first parts launched before all
 // second ones, each part fetched them anew: 4096 rows in 32 of 128 slots of d = 2048, f = 1408 287 us, now 209;
 // and most of the workgroups had nothing to do: 2 rows in each of 96 slots of d = 1024, f = 4096 518 -> 513.
 // Operand layout, fragments and epilogue are those of the large tile.
+constexpr int FEW_BM = 64;
+
 template <int MODE>
 __global__ __launch_bounds__(GT, 2) void gemm_few_rows_kernel(GemmParams p) {
   static_assert(MODE == FWD1 || MODE == FWD2, "both operands reduction-contiguous");
@@ -853,7 +847,25 @@ __global__ __launch_bounds__(GT, 2) void gemm_few_rows_kernel(GemmParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   int mt = blockIdx.y, bx = blockIdx.x;
-  const int ntx = gridDim.x, n_tiles = p.tile_map[0];
+  const int ntx = gridDim.x;
+  // Slot q holds ceil(rows / 64) tiles: every workgroup counts them for itself from the slot offsets, which takes no
+  // longer than the two dependent reads of a table and saves the launch that wrote it.  A thread counts
+  // consecutive slots; the one whose slots hold tile mt finds it.
+  __shared__ int32_t found[8];
+  const int32_t* const offs = p.slot_offsets;
+  const int per = (p.n_slots + GT - 1) / GT, q0 = min(tid * per, p.n_slots), q1 = min(q0 + per, p.n_slots);
+  int mine = 0;
+  for (int q = q0; q < q1; ++q) mine += (offs[q + 1] - offs[q] + TM - 1) / TM;
+  int incl = mine;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int up = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += up;
+  }
+  if (lane == 63) found[wave] = incl;
+  __syncthreads();
+  const int n_tiles = __builtin_amdgcn_readfirstlane(found[0] + found[1] + found[2] + found[3]);
+  for (int w = 0; w < wave; ++w) incl += found[w];
   if (ntx & 7) {   // rounds of 8 tiles, a column tile of all 8 on one XCD
     const int b = mt * ntx + bx, round = b / (8 * ntx);
     if (8 * round + 8 <= n_tiles) {
@@ -863,8 +875,20 @@ __global__ __launch_bounds__(GT, 2) void gemm_few_rows_kernel(GemmParams p) {
     }
   }
   if (mt >= n_tiles) return;
-  const int row0 = p.tile_map[4 + 2 * mt], entry = p.tile_map[4 + 2 * mt + 1];
-  const int row1 = row0 + (entry >> 16) + 1, group = entry & 0xffff;
+  if (mt < incl && mt >= incl - mine) {
+    int i = mt - (incl - mine), q = q0;
+    for (;; ++q) {
+      const int n = (offs[q + 1] - offs[q] + TM - 1) / TM;
+      if (i < n) break;
+      i -= n;
+    }
+    found[4] = q;
+    found[5] = offs[q] + i * TM;
+    found[6] = min(offs[q] + i * TM + TM, offs[q + 1]);
+  }
+  __syncthreads();
+  const int group = __builtin_amdgcn_readfirstlane(found[4]), row0 = __builtin_amdgcn_readfirstlane(found[5]);
+  const int row1 = __builtin_amdgcn_readfirstlane(found[6]);
   const int n0 = bx * (MODE == FWD1 ? TN / 2 : TN), K = p.K, ld = p.K;
   const uint16_t* const a_base = static_cast<const uint16_t*>(p.A) + (long long)row0 * ld;
   const uint16_t* const b_base = static_cast<const uint16_t*>(p.B) + (long long)group * p.b_group_stride +
@@ -1409,13 +1433,13 @@ extern "C" int symi_expert_fwd(const symi_ctx* ctx, const void* Xp, const int32_
   const WsLayout& L = ctx->L;
   int32_t* map = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + L.tile_map);
   const int max_mtiles = (int)(A / GEMM_BM) + cfg->S_tot;
-  if (few_rows(cfg))
-    SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<FEW_BM><<<1, 256, 0, st>>>(slot_offsets, nullptr, cfg->S_tot, cfg->E, map, nullptr)));
-  else
-    SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<GEMM_BM><<<1, 256, 0, st>>>(slot_offsets, nullptr, cfg->S_tot, cfg->E, map, nullptr)));
+  if (!few_rows(cfg))
+    SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<<<1, 256, 0, st>>>(slot_offsets, nullptr, cfg->S_tot, cfg->E, map, nullptr)));
 
   GemmParams p = {};
   p.tile_map = map;
+  p.slot_offsets = slot_offsets;
+  p.n_slots = cfg->S_tot;
   set_split(ctx, ws, p);
   p.d = cfg->d;
   p.f = cfg->f;
@@ -1472,7 +1496,7 @@ static int expert_bwd_impl(const char* who, const symi_ctx* ctx, const void* dYp
   set_split(ctx, ws, p);
   p.d = cfg->d;
   p.f = cfg->f;
-  SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<GEMM_BM><<<1, 256, 0, st>>>(slot_offsets, first_slot, cfg->S_tot, cfg->E, map, order)));
+  SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<<<1, 256, 0, st>>>(slot_offsets, first_slot, cfg->S_tot, cfg->E, map, order)));
   // worth it only while a product is a few rounds of workgroups: with many rounds the chip is
   // full anyway and two kernels sharing it only disturb each other's L2 locality (symi_create
   // decides; the context then holds the helper stream)

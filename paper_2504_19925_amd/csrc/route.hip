@@ -81,11 +81,11 @@ constexpr int KEY_NONE = INT_MIN;
 // settles the winner across the group by a butterfly over (key, column) pairs.
 // Workgroups of 256 or 1024 threads (blockDim.x): every workgroup adds its histogram to the
 // global one with E atomics, so a large batch takes the large workgroup (a quarter of the
-// atomics on the same E addresses).
+// atomics on the same E addresses).  alone: one workgroup holds the whole batch and stores its histogram.
 template <int G, int NV>
 __global__ __launch_bounds__(ROUTE_THREADS_MAX) void route_kernel(
     const float* __restrict__ logits, int32_t* __restrict__ idx, float* __restrict__ gate,
-    int32_t* __restrict__ hist, int T, int E, int k, int renorm) {
+    int32_t* __restrict__ hist, int T, int E, int k, int renorm, bool alone) {
   extern __shared__ int32_t hist_s[];
   const int nthreads = blockDim.x;
   for (int i = threadIdx.x; i < E; i += nthreads) hist_s[i] = 0;
@@ -156,8 +156,10 @@ __global__ __launch_bounds__(ROUTE_THREADS_MAX) void route_kernel(
     }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < E; i += nthreads)
-    if (hist_s[i]) atomicAdd(&hist[i], hist_s[i]);
+  for (int i = threadIdx.x; i < E; i += nthreads) {
+    if (alone) hist[i] = hist_s[i];
+    else if (hist_s[i]) atomicAdd(&hist[i], hist_s[i]);
+  }
 }
 
 template <int NV>
@@ -251,6 +253,20 @@ static void route_fwd_shape(int E, int T, int& G, int& NV) {
   NV = need <= 1 ? 1 : (need <= 2 ? 2 : (need <= 4 ? 4 : 8));
 }
 
+// A small batch goes through one workgroup of 1024 threads in at most two passes, which then needs no cleared
+// histogram: a launch less (3 us).  Beyond E (k + 2) T = 2^16 the unit's vector pipes would take longer than that.
+static bool route_alone(const symi_cfg* c, int& G, int& NV) {
+  if ((long long)c->T * c->E * (c->k + 2) > 65536) return false;
+  const int vecs = (c->E + 3) / 4;
+  int g = G;
+  while (g > 1 && (g >> 1) * 8 >= vecs && c->T > ROUTE_THREADS_MAX / g) g >>= 1;
+  if (c->T > 2 * (ROUTE_THREADS_MAX / g)) return false;
+  const int need = (vecs + g - 1) / g;
+  G = g;
+  NV = need <= 1 ? 1 : (need <= 2 ? 2 : (need <= 4 ? 4 : 8));
+  return true;
+}
+
 static int route_grid(int T, int G) {
   const int tpb = (ROUTE_THREADS / 64) * (64 / G);
   int grid = cdiv(T, tpb);
@@ -267,19 +283,20 @@ extern "C" int symi_route(const symi_ctx* ctx, const float* logits, int32_t* idx
   SYMI_REQUIRE(hist && (cfg->T == 0 || (logits && idx && gate)), "symi_route", "NULL pointer");
   hipStream_t st = as_stream(stream);
   const int E = cfg->E;
-  launch_fill_i32(ctx, hist, E, 0, st);
+  int G, NV;
+  route_fwd_shape(E, cfg->T, G, NV);
+  const bool alone = cfg->T > 0 && route_alone(cfg, G, NV);
+  if (!alone) launch_fill_i32(ctx, hist, E, 0, st);
   if (cfg->T > 0) {
-    int G, NV;
-    route_fwd_shape(E, cfg->T, G, NV);
-    int grid = route_grid(cfg->T, G);
+    int grid = alone ? 1 : route_grid(cfg->T, G);
     // four workgroups of 256 per compute unit or more: one of 1024 each instead
-    const int threads = grid >= 4 * ctx->cus ? ROUTE_THREADS_MAX : ROUTE_THREADS;
-    if (threads == ROUTE_THREADS_MAX) grid = cdiv(grid, ROUTE_THREADS_MAX / ROUTE_THREADS);
+    const int threads = alone || grid >= 4 * ctx->cus ? ROUTE_THREADS_MAX : ROUTE_THREADS;
+    if (!alone && threads == ROUTE_THREADS_MAX) grid = cdiv(grid, ROUTE_THREADS_MAX / ROUTE_THREADS);
     const size_t sh = (size_t)E * sizeof(int32_t);
 #define SYMI_ROUTE_CASE(GG, NN)                                                                  \
   case GG * 16 + NN:                                                                             \
     SYMI_TIMED(ctx, K_ROUTE, st, (route_kernel<GG, NN><<<grid, threads, sh, st>>>(          \
-        logits, idx, gate, hist, cfg->T, E, cfg->k, cfg->renorm)));                              \
+        logits, idx, gate, hist, cfg->T, E, cfg->k, cfg->renorm, alone)));                       \
     break;
 #define SYMI_ROUTE_G(GG) SYMI_ROUTE_CASE(GG, 1) SYMI_ROUTE_CASE(GG, 2) SYMI_ROUTE_CASE(GG, 4) SYMI_ROUTE_CASE(GG, 8)
     switch (G * 16 + NV) {

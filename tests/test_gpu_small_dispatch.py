@@ -1,0 +1,57 @@
+"""Route and dispatch of small batches on both sides of the rules that take them to their one-launch forms (route: one
+workgroup up to E (k + 2) T = 2^16 in two passes; dispatch: 4096 assignments, 512 classes), integers and moved rows
+bit for bit against the oracle, dropless and under a capacity factor."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2504_19925_amd as symi
+from oracle import symi_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+# one token; one and two passes of the route's workgroup and the first size beyond; assignments around one and four
+# passes of 1024 and the limit of 4096; more than 64 replicas of a class; classes around the limit of 512; rows
+# of one and of an odd number of 16-byte pieces
+@pytest.mark.parametrize("T,E,k,S,d,dtype", [
+    (1, 1, 1, 1, 8, "bf16"), (1, 16, 3, 24, 128, "bf16"), (64, 16, 2, 24, 128, "bf16"), (511, 4, 2, 200, 24, "bf16"),
+    (512, 2, 2, 150, 8, "f32"), (513, 8, 2, 16, 40, "f32"), (1024, 8, 2, 16, 128, "f32"), (2048, 4, 2, 9, 16, "bf16"),
+    (2049, 4, 2, 9, 16, "bf16"), (4096, 3, 1, 7, 8, "bf16"), (4097, 3, 1, 7, 8, "bf16"), (300, 64, 6, 96, 1032, "bf16"),
+    (200, 64, 2, 96, 1024, "bf16"), (21, 512, 4, 600, 16, "bf16"), (21, 513, 4, 600, 16, "bf16"), (256, 512, 16, 512, 8, "bf16")])
+def test_small_route_and_dispatch(T, E, k, S, d, dtype):
+    cfg = symi.SymiCfg.make(T, E, k, d, 8, S, 1, 0, dtype, 1)
+    ctx = symi.symi_create(cfg)
+    g = torch.Generator().manual_seed(T * 31 + E)
+    dev, A = torch.device("cuda"), T * k
+    bias = -2.4 * torch.log(torch.arange(1, E + 1, dtype=torch.float32))[torch.randperm(E, generator=g)]
+    logits = torch.randn(T, E, generator=g) + bias
+    X = torch.randn(T, d, generator=g).to(cfg.torch_dtype).to(dev)
+
+    def new(*n, dt=torch.int32, fill=-5):
+        return torch.full(n, fill, dtype=dt, device=dev)
+
+    ws = torch.empty(symi.symi_workspace_bytes(cfg), dtype=torch.uint8, device=dev)
+    idx, gate, hist = new(T, k), new(T, k, dt=torch.float32), new(E)
+    counts, placement, first = new(E), new(S), new(E + 1)
+    print(f"[small] T={T} E={E} k={k} S={S} d={d} {dtype}", flush=True)
+    symi.symi_route(ctx, logits.to(dev), idx, gate, hist)
+    symi.symi_place(ctx, hist, counts, placement, first)
+    o_idx, _, o_hist = O.route(logits.numpy(), k, True)
+    o_counts, _, o_first = O.place(o_hist, S)
+    assert (idx.cpu().numpy() == o_idx).all() and (hist.cpu().numpy() == o_hist).all()
+    assert (first.cpu().numpy() == o_first).all()
+    for factor in (None, 0.6, 1.3):
+        roa, aor, off, Xp = new(A), new(A), new(S + 1), torch.full((A, d), 7.0, dtype=cfg.torch_dtype, device=dev)
+        if factor is None:
+            symi.symi_dispatch(ctx, X, idx, hist, counts, first, roa, aor, off, Xp, ws)
+            o_roa, o_aor, o_off = O.dispatch(o_idx, o_counts, o_first)
+        else:
+            cap = symi.symi_slot_capacity(ctx, factor)
+            symi.symi_dispatch_capacity(ctx, cap, X, idx, hist, counts, first, roa, aor, off, Xp, ws)
+            o_roa, o_aor, o_off, _ = O.dispatch_capacity(o_idx, o_counts, o_first, cap)
+        kept = int(o_off[-1])
+        assert (roa.cpu().numpy() == o_roa).all() and (off.cpu().numpy() == o_off).all()
+        assert (aor.cpu().numpy()[:kept] == np.asarray(o_aor)[:kept]).all()
+        assert torch.equal(Xp[:kept], X[(aor[:kept] // k).long()])
+        assert (aor[kept:] == -5).all() and (Xp[kept:] == 7.0).all()   # nothing else is written

@@ -210,17 +210,9 @@ __device__ __forceinline__ void tail_slices(int n_tiles, int cus, int K, int& fu
   }
 }
 
-// Epilogue of a tile whose wavefronts own 32 MI x 32 NJ outputs each.  After the MFMA a lane owns
-// one output row (lane%16) of each 16 x 16 block and its 4 columns 4*(lane/16) ..: stored like that,
-// a wavefront store would touch 16 cache lines with 64 or 32 bytes each, and the store path is
-// paid per line touched.  The operand stages are free now, so every wavefront turns its
-// 32-row blocks around through a private piece of LDS (`stg`; written in the MFMA layout, read
-// back row by row, 16 bytes per lane) and each store instruction writes whole lines: for NJ = 4
-// 4 rows x 256 B (bf16 outputs), 8 rows x 128 B (u, v, h) or 2 rows x 512 B (fp32).
-// pslot >= 0: the accumulators of a reduction slice, left as an fp32 tile in that partial slot.
-// BWD_DH: saved[0] holds (or is about to receive) the saved u, v of the first 32-row block.
+// Saved u, v of a wavefront's 32-row block, for the epilogue of the hidden gradient.
 template <int NJ>
-struct SavedUV { uint4 u[NJ * 2], v[NJ * 2]; };   // of a wavefront's 32-row block
+struct SavedUV { uint4 u[NJ * 2], v[NJ * 2]; };
 
 // The loads are unconditional: a lane past the tile's last row or column reads the last valid row / the last 8
 // columns instead (its result is never stored).  A load under a branch would make the compiler lose count of the
@@ -241,6 +233,15 @@ __device__ __forceinline__ void load_uv(const GemmParams& p, const int rb, const
   }
 }
 
+// Epilogue of a tile whose wavefronts own 32 MI x 32 NJ outputs each.  After the MFMA a lane owns
+// one output row (lane%16) of each 16 x 16 block and its 4 columns 4*(lane/16) ..: stored like that,
+// a wavefront store would touch 16 cache lines with 64 or 32 bytes each, and the store path is
+// paid per line touched.  The operand stages are free now, so every wavefront turns its
+// 32-row blocks around through a private piece of LDS (`stg`; written in the MFMA layout, read
+// back row by row, 16 bytes per lane) and each store instruction writes whole lines: for NJ = 4
+// 4 rows x 256 B (bf16 outputs), 8 rows x 128 B (u, v, h) or 2 rows x 512 B (fp32).
+// pslot >= 0: the accumulators of a reduction slice, left as an fp32 tile in that partial slot.
+// BWD_DH: saved[0] holds (or is about to receive) the saved u, v of the first 32-row block.
 template <int MODE, int MI, int NJ>
 __device__ __forceinline__ void write_tile(const GemmParams& p, uint16_t* const stg, floatx4 (&acc)[2 * MI][2 * NJ],
                                            const int row0, const int row1, const int group, const int n0,
@@ -837,23 +838,17 @@ __global__ __launch_bounds__(GT) void gemm_bf16_kernel(GemmParams p) {
 // Operand layout, fragments and epilogue are those of the large tile.
 constexpr int FEW_BM = 64;
 
-template <int MODE>
-__global__ __launch_bounds__(GT, 2) void gemm_few_rows_kernel(GemmParams p) {
-  static_assert(MODE == FWD1 || MODE == FWD2, "both operands reduction-contiguous");
-  constexpr int TM = FEW_BM, TN = 128, NST = 3, LA = 2, LB = 4;   // LA, LB: 1 KB load instructions per wavefront and stage
-  constexpr int SA = TM * BK, SB = TN * BK;          // elements of a stage
-  __shared__ __attribute__((aligned(1024))) uint16_t smem[NST * (SA + SB)];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1;
+struct SlotTile { int row0, row1, slot, bx; };
+
+// Slot q holds ceil(rows / TM) row tiles: every workgroup counts them for itself from the slot offsets, which takes
+// no longer than the two dependent reads of a table and saves the launch that wrote it.  A thread counts consecutive
+// slots; the one whose slots hold the workgroup's row tile finds it.  gridDim.x column tiles per row tile.
+template <int TM>
+__device__ __forceinline__ bool find_slot_tile(const int32_t* __restrict__ offs, int n_slots, int32_t* const found, SlotTile& out) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int mt = blockIdx.y, bx = blockIdx.x;
   const int ntx = gridDim.x;
-  // Slot q holds ceil(rows / 64) tiles: every workgroup counts them for itself from the slot offsets, which takes no
-  // longer than the two dependent reads of a table and saves the launch that wrote it.  A thread counts
-  // consecutive slots; the one whose slots hold tile mt finds it.
-  __shared__ int32_t found[8];
-  const int32_t* const offs = p.slot_offsets;
-  const int per = (p.n_slots + GT - 1) / GT, q0 = min(tid * per, p.n_slots), q1 = min(q0 + per, p.n_slots);
+  const int per = (n_slots + GT - 1) / GT, q0 = min(tid * per, n_slots), q1 = min(q0 + per, n_slots);
   int mine = 0;
   for (int q = q0; q < q1; ++q) mine += (offs[q + 1] - offs[q] + TM - 1) / TM;
   int incl = mine;
@@ -874,7 +869,7 @@ __global__ __launch_bounds__(GT, 2) void gemm_few_rows_kernel(GemmParams p) {
       bx = q >> 3;
     }
   }
-  if (mt >= n_tiles) return;
+  if (mt >= n_tiles) return false;
   if (mt < incl && mt >= incl - mine) {
     int i = mt - (incl - mine), q = q0;
     for (;; ++q) {
@@ -887,8 +882,26 @@ __global__ __launch_bounds__(GT, 2) void gemm_few_rows_kernel(GemmParams p) {
     found[6] = min(offs[q] + i * TM + TM, offs[q + 1]);
   }
   __syncthreads();
-  const int group = __builtin_amdgcn_readfirstlane(found[4]), row0 = __builtin_amdgcn_readfirstlane(found[5]);
-  const int row1 = __builtin_amdgcn_readfirstlane(found[6]);
+  out.slot = __builtin_amdgcn_readfirstlane(found[4]);
+  out.row0 = __builtin_amdgcn_readfirstlane(found[5]);
+  out.row1 = __builtin_amdgcn_readfirstlane(found[6]);
+  out.bx = bx;
+  return true;
+}
+
+template <int MODE>
+__global__ __launch_bounds__(GT, 2) void gemm_few_rows_kernel(GemmParams p) {
+  static_assert(MODE == FWD1 || MODE == FWD2, "both operands reduction-contiguous");
+  constexpr int TM = FEW_BM, TN = 128, NST = 3, LA = 2, LB = 4;   // LA, LB: 1 KB load instructions per wavefront and stage
+  constexpr int SA = TM * BK, SB = TN * BK;          // elements of a stage
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[NST * (SA + SB)];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  __shared__ int32_t found[8];
+  SlotTile tile;
+  if (!find_slot_tile<TM>(p.slot_offsets, p.n_slots, found, tile)) return;
+  const int row0 = tile.row0, row1 = tile.row1, group = tile.slot, bx = tile.bx;
   const int n0 = bx * (MODE == FWD1 ? TN / 2 : TN), K = p.K, ld = p.K;
   const uint16_t* const a_base = static_cast<const uint16_t*>(p.A) + (long long)row0 * ld;
   const uint16_t* const b_base = static_cast<const uint16_t*>(p.B) + (long long)group * p.b_group_stride +
@@ -968,6 +981,166 @@ __global__ __launch_bounds__(GT, 2) void gemm_few_rows_kernel(GemmParams p) {
   // 18 KB of LDS per wavefront for its 32-row block of 64 columns
   SavedUV<2> saved[2];   // the input-gradient product's
   write_tile<MODE, 1, 2>(p, smem + wave * (NST * (SA + SB) / 4), acc, row0, row1, group, n0, wm, wn, lane, -1, saved);
+}
+
+// ---------------------------------------------------------------- variable-row products of few or short tiles
+// Tile of 128 x 128 (FWD1: 64 hidden units), reduction step 64, two 32 KB stages, four wavefronts of 64 x 64, two
+// workgroups per compute unit, which hide each other's barriers and epilogues.  A step's fragments are all read into
+// registers before its MFMAs, so that its stage is refilled during them.  Bound by the latency of a tile where the
+// tiles do not fill the chip (18 - 26 us of the large tile, 10 - 14 here: K = 136 - 656, 20 slots of 80 rows on average), else by
+// the LDS: a 64 x 64 wavefront tile reads twice as much per MFMA as the large tile's 128 x 128.  Operand layout,
+// fragments and epilogue are those of the large tile, and so are the bits.  Tried and dropped: 32-deep steps in three
+// stages with three workgroups per unit (c2's first forward product 386 -> 450 us), and this tile for the weight gradients (two
+// transposing reads per fragment: c4's W1 gradient 1850 -> 3190 us, per-slot gradients of 384 rows 1120 -> 1180).
+constexpr int MID_BM = 128;
+
+template <int MODE>
+__global__ __launch_bounds__(GT, 2) void gemm_mid_kernel(GemmParams p) {
+  static_assert(MODE <= BWD_DX, "left operand reduction-contiguous");
+  constexpr bool B_KC = MODE == FWD1 || MODE == FWD2;
+  constexpr int TM = MID_BM, TN = 128, NL = 4;   // NL: 1 KB load instructions per wavefront, operand and stage
+  constexpr int SA = TM * BK, SB = TN * BK;      // elements of a stage
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[2 * (SA + SB)];
+  __shared__ int32_t found[8];
+  SlotTile tile;
+  if (!find_slot_tile<TM>(p.slot_offsets, p.n_slots, found, tile)) return;
+  const int row0 = tile.row0, row1 = tile.row1, group = tile.slot, bx = tile.bx;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int n0 = bx * (MODE == FWD1 ? TN / 2 : TN), K = p.K;
+  const int rows = row1 - row0, cols = p.N - n0;
+  const int ldb = B_KC ? K : p.N;
+  const uint16_t* const a_base = static_cast<const uint16_t*>(p.A) + (long long)row0 * K;
+  const uint16_t* const b_base = static_cast<const uint16_t*>(p.B) + (long long)group * p.b_group_stride +
+                                 (MODE == FWD1 ? 0 : B_KC ? (long long)n0 * ldb : (long long)n0);
+
+  // Loads: byte offset of this lane's 16 bytes for instruction j of an operand (its immediate, j KB, taken back out)
+  // and their reduction index in the step.  Rows and columns beyond the operand's extent are clamped (they only
+  // reach outputs never stored), reduction indices beyond K read from outside the buffer: zeros.
+  unsigned vo[2 * NL];
+  int kr[2 * NL];
+#pragma unroll
+  for (int j = 0; j < 2 * NL; ++j) {
+    const bool right = j >= NL;
+    const int q = wave * NL + (j & (NL - 1));
+    unsigned e;
+    if (!right || B_KC) {   // rows 8q .. 8q + 7
+      const int r = q * 8 + (lane >> 3);
+      kr[j] = ((lane & 7) ^ ((r >> 1) & 7)) * 8;
+      if (!right) {
+        e = (unsigned)(min(r, rows - 1) * K + kr[j]);
+      } else if (MODE == FWD1) {   // every 64 tile rows: 32 gate rows and the 32 up rows of the same hidden units
+        const int hu = min(n0 + (r >> 6) * 32 + (r & 31), p.f - 1);
+        e = (unsigned)((((r >> 5) & 1) * p.f + hu) * K + kr[j]);
+      } else {
+        e = (unsigned)(min(r, cols - 1) * K + kr[j]);
+      }
+    } else {   // reduction indices 4q .. 4q + 3
+      kr[j] = q * 4 + (lane >> 4);
+      const int c = (lane & 15) ^ (10 * (kr[j] & 1)) ^ (4 * ((kr[j] >> 1) & 1)) ^ (2 * ((kr[j] >> 3) & 1));
+      e = (unsigned)(kr[j] * ldb + (c * 8 < cols ? c * 8 : 0));
+    }
+    vo[j] = e * 2u + 4096u - (unsigned)((j & (NL - 1)) * 1024);
+  }
+  const unsigned ldsA = (unsigned)(size_t)SYMI_LPTR(smem) + wave * (NL * 1024);
+  const unsigned ldsB = (unsigned)(size_t)SYMI_LPTR(smem + 2 * SA) + wave * (NL * 1024);
+  const int nk = (K + BK - 1) / BK;
+  // a tile of at most 64 rows: the lower wavefronts have no outputs, and nobody reads the left rows they would load
+  const bool idle = wave >= 2 && rows <= TM / 2;
+  auto load_one = [&](auto jc, unsigned v, intx4 rsrc) {
+    asm volatile("buffer_load_dwordx4 %0, %1, 0 offen offset:%2 lds" ::"v"(v), "s"(rsrc), "n"(decltype(jc)::value * 1024) : "memory");
+  };
+  auto load = [&](auto rightc, unsigned dst, const uint16_t* src, int left, auto edge) {
+    constexpr bool right = decltype(rightc)::value != 0;
+    const unsigned long long a = (unsigned long long)src - 4096;
+    const intx4 rsrc = {(int)(unsigned)a, (int)((unsigned)(a >> 32) & 0xffffu), (int)OUTSIDE, 0x00020000};
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" ::"s"(dst) : "memory");   // the wait state of an M0 write
+    unroll<NL>([&](auto jc) {
+      constexpr int j = decltype(jc)::value, x = right ? NL + j : j;
+      const unsigned v = !decltype(edge)::value || kr[x] < left ? vo[x] : OUTSIDE;
+      load_one(jc, v, rsrc);
+    });
+  };
+  auto issue = [&](int t, int st) {
+    const int k0 = t * BK;
+    const uint16_t* const sa = a_base + k0;
+    const uint16_t* const sb = b_base + (B_KC ? (long long)k0 : (long long)k0 * ldb);
+    if (k0 + BK <= K) {
+      if (!idle) load(IC<0>{}, ldsA + st * (SA * 2), sa, 0, std::false_type{});
+      load(IC<1>{}, ldsB + st * (SB * 2), sb, 0, std::false_type{});
+    } else {
+      if (!idle) load(IC<0>{}, ldsA + st * (SA * 2), sa, K - k0, std::true_type{});
+      load(IC<1>{}, ldsB + st * (SB * 2), sb, K - k0, std::true_type{});
+    }
+  };
+  // fragment addresses (elements): KC one per sub-step, KS one per 16-column block
+  const int g4 = lane >> 4, jj = lane & 15;
+  const int ks_h = (10 * ((jj >> 2) & 1)) ^ (4 * ((jj >> 3) & 1)) ^ (2 * (g4 & 1));
+  unsigned adA[2], adB[B_KC ? 2 : 4];
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {
+    const int kc = jj * BK + (((4 * x + g4) ^ ((jj >> 1) & 7)) * 8);
+    const int ks = (8 * g4 + (jj >> 2)) * TN + (((2 * (4 * wn + x) + ((jj & 3) >> 1)) ^ ks_h) * 8) + 4 * (jj & 1);
+    if (x < 2) adA[x] = (unsigned)(wm * 64 * BK + kc);
+    if (x < (B_KC ? 2 : 4)) adB[x] = (unsigned)(2 * SA + (B_KC ? wn * 64 * BK + kc : ks));
+  }
+  floatx4 acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  issue(0, 0);
+  if (nk > 1) issue(1, 1);
+  for (int t = 0; t < nk; ++t) {
+    const int st = t & 1;
+    // my loads of step t have landed, those of the next step may fly
+    if (t + 1 >= nk) __builtin_amdgcn_s_waitcnt(0x0F70);
+    else if (idle) __builtin_amdgcn_s_waitcnt(0x0F70 + NL);
+    else __builtin_amdgcn_s_waitcnt(0x0F70 + 2 * NL);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    bf16x8 fa[2][4], fb[2][4];
+    if (!idle) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) fa[ks][i] = *reinterpret_cast<const bf16x8*>(smem + adA[ks] + st * SA + i * 16 * BK);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if constexpr (B_KC) {
+            fb[ks][j] = *reinterpret_cast<const bf16x8*>(smem + adB[ks] + st * SB + j * 16 * BK);
+          } else {
+            union { shortx4 h[2]; bf16x8 v; } u;
+            auto* const q = (shortx4 __attribute__((address_space(3)))*)SYMI_LPTR(smem + adB[j] + st * SB + ks * 32 * TN);
+            u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(q);
+            u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(q + TN);   // 4 reduction indices further
+            fb[ks][j] = u.v;
+          }
+        }
+      }
+    }
+    // the fragments of this step sit in registers, in every wavefront: its stage may be filled again
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (t + 2 < nk) issue(t + 2, st);
+    if (!idle) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
+    }
+  }
+  if (idle) return;
+  // 16 KB of LDS per wavefront
+  SavedUV<2> saved[2];
+  if (MODE == BWD_DH) load_uv<2>(p, row0 + wm * 64, row1, n0 + wn * 64, lane, saved[0]);
+  write_tile<MODE, 2, 2>(p, smem + wave * (2 * (SA + SB) / 4), acc, row0, row1, group, n0, wm, wn, lane, -1, saved);
 }
 
 // ---------------------------------------------------------------- sum of reduction slices
@@ -1363,6 +1536,33 @@ static bool few_rows(const symi_cfg* c) {
   return c->dtype == SYMI_BF16 && (long long)c->T * c->k <= 32LL * c->S_tot;
 }
 
+// bf16 variable-row products that take the 128 x 128 tile: those of few tiles, where the latency of one tile is the
+// time, and those of short reductions, where its epilogue is (two workgroups share a unit and hide theirs
+// behind each other).  Long reductions of many tiles belong to the large tile, which loads half as much per
+// product and slices a nearly empty last round.  Large : small, us per product (events around the launch), S slots
+// of r rows on average; first forward, second forward, hidden gradient, input gradient:
+//   S = 8,   r = 128,  d = 256,  f = 1024    17 : 10    28 : 16    23 : 11    31 : 28
+//   S = 32,  r = 40,   d = 512,  f = 2048    47 : 36    43 : 34    25 : 22    47 : 50 (*)
+//   S = 128, r = 128,  d = 512,  f = 512     71 : 58    43 : 32    51 : 43    65 : 53
+//   S = 128, r = 40,   d = 2048, f = 1408   396 : 379  156 : 151  214 : 221 (*) 279 : 313 (*)
+//   S = 8,   r = 1000, d = 512,  f = 2048    65 : 60 (*) 48 : 35 (*) 62 : 46   63 : 64 (*)
+//   S = 32,  r = 300,  d = 512,  f = 512     30 : 30    21 : 18    29 : 22    29 : 29
+//   S = 20,  r = 100,  d = 2800, f = 560     79 : 52    34 : 31    65 : 41    41 : 42
+//   S = 128, r = 300,  d = 512,  f = 2048   308 : 313 (*) 152 : 161 (*) 231 : 222 (*) 234 : 342 (*)
+//   S = 128, r = 1000, d = 256,  f = 1024   297 : 355 (*) 135 : 125 (*) 246 : 254 (*) 209 : 236 (*)
+// ((*): the rule keeps the large tile).  The host knows the mean number of rows only.
+static bool mid_tile(const symi_ctx* ctx, int mode) {
+  const symi_cfg* const c = &ctx->cfg;
+  if (c->dtype != SYMI_BF16 || mode > BWD_DX || ((mode == FWD1 || mode == FWD2) && few_rows(c))) return false;
+  const long long A = (long long)c->T * c->k, S = c->S_tot;
+  const int K = mode == FWD1 || mode == BWD_DH ? c->d : mode == FWD2 ? c->f : 2 * c->f;
+  const int ntx = mode == FWD1 ? cdiv(c->f, 64) : cdiv(mode == BWD_DH ? c->f : c->d, 128);
+  if (A <= 128 * S && K <= 1024) return true;
+  if (A <= 96 * S && K <= (mode == FWD1 || mode == FWD2 ? 2048 : 1792)) return true;
+  const long long work = std::max(A / MID_BM + S / 2, S) * ntx * K;   // tiles x reduction length
+  return mode == FWD1 || mode == BWD_DH ? work <= 1 << 19 : work <= 3 << 17 && K <= 2048;
+}
+
 template <int MODE>
 static void launch_gemm(const symi_ctx* ctx, const GemmParams& p, int n_cols, int max_mtiles,
                         hipStream_t st) {
@@ -1372,6 +1572,13 @@ static void launch_gemm(const symi_ctx* ctx, const GemmParams& p, int n_cols, in
       if (few_rows(cfg)) {
         dim3 grid(cdiv(n_cols, MODE == FWD1 ? 64 : 128), cfg->T * cfg->k / FEW_BM + cfg->S_tot);
         SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_few_rows_kernel<MODE><<<grid, GT, 0, st>>>(p)));
+        return;
+      }
+    }
+    if constexpr (MODE <= BWD_DX) {
+      if (mid_tile(ctx, MODE)) {
+        dim3 grid(cdiv(n_cols, MODE == FWD1 ? 64 : 128), cfg->T * cfg->k / MID_BM + cfg->S_tot);
+        SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_mid_kernel<MODE><<<grid, GT, 0, st>>>(p)));
         return;
       }
     }
@@ -1433,7 +1640,7 @@ extern "C" int symi_expert_fwd(const symi_ctx* ctx, const void* Xp, const int32_
   const WsLayout& L = ctx->L;
   int32_t* map = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + L.tile_map);
   const int max_mtiles = (int)(A / GEMM_BM) + cfg->S_tot;
-  if (!few_rows(cfg))
+  if (!few_rows(cfg) && !(mid_tile(ctx, FWD1) && mid_tile(ctx, FWD2)))
     SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<<<1, 256, 0, st>>>(slot_offsets, nullptr, cfg->S_tot, cfg->E, map, nullptr)));
 
   GemmParams p = {};
@@ -1489,6 +1696,7 @@ static int expert_bwd_impl(const char* who, const symi_ctx* ctx, const void* dYp
   GemmParams p = {};
   p.tile_map = map;
   p.slot_offsets = slot_offsets;
+  p.n_slots = cfg->S_tot;
   p.first_slot = first_slot;
   p.class_order = order;
   p.per_slot = per_slot ? 1 : 0;

@@ -146,6 +146,7 @@ __device__ __attribute__((aligned(16))) uint16_t g_zero_chunk[8] = {0, 0, 0, 0, 
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short shortx4;
 typedef __attribute__((__vector_size__(4 * sizeof(int)))) int intx4;
 typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned uintx4;
+typedef __attribute__((__vector_size__(2 * sizeof(unsigned)))) unsigned uintx2;
 // Byte offset outside every buffer descriptor of this file (and its length): a load there gives zeros, a store is
 // dropped.  Valid offsets stay under 2^32 - 8192, the biases of the loads included.
 constexpr unsigned OUTSIDE = 0xfffff000u;
@@ -1252,26 +1253,34 @@ __device__ __forceinline__ void f32_store(const GemmParams& p, int group, long l
   }
 }
 
-// Tile of 64 rows x 64 NBL columns (FWD1: the gate and up columns of 64 hidden units), 32-deep steps
-// through LDS, four wavefronts of 32 x 32 NBL.  The next step's loads sit in registers while the
-// current one feeds the matrix pipes; three to five workgroups share a compute unit and cover each
-// other's barriers.  Rows and columns beyond the tile's extent are clamped to a valid one (they
+// Tile of 64 rows x 64 NBL columns (FWD1: the gate and up columns of 64 hidden units), four wavefronts of
+// 32 x 32 NBL.  Tiles travel HBM -> LDS with direct-to-LDS loads, KD-deep steps: 32 deep in two stages (128 columns:
+// three workgroups per compute unit; 64: four, as 32 KB of LDS are a little more than a fifth of what can be had) or 16 deep in
+// three (six).  The next step's loads are in flight while the current one feeds the matrix pipes, one barrier per step.  Rows and columns beyond the tile's extent are clamped to a valid one (they
 // only reach outputs that are never stored), reduction indices beyond K are zeros in both
-// operands.  A wavefront whose outputs all lie outside multiplies nothing.
-// Bound by the matrix pipes once a few workgroups share a unit (E = 24, 9000 rows in 36 slots,
-// d = 328, f = 872: first forward product 160 us, 59 % of the cycles are MFMAs, 15 % of them padding of
-// ragged slots and columns; the plain-FMA kernel took 238, the six products together 1070 -> 700 us).
-constexpr int F32_BM = 64, F32_BK = 32;
+// operands (offsets outside the buffer).  A wavefront whose outputs all lie outside multiplies nothing.
+// LDS layouts, free of bank conflicts: reduction-contiguous [row][k], 16-byte chunk c of row r at c ^ ((r >> 1) & 7) (16
+// deep: c ^ ((r >> 2) & 3)), read 16 bytes per lane; reduction-strided [k][column] as loaded, chunk c of row k at c ^ (8 ((k >> 2) & 1)): the two
+// halves of a wavefront read rows 4 apart, 32 banks apart.  With 128 columns a lane reads two neighbouring ones
+// at a time, so block j of a wavefront holds its columns 2 l + j.
+// Bound by the matrix pipes at the clock that is left to them once a few workgroups share a unit (E = 16, 15092 rows in 32
+// slots of d = 512, f = 1264: busy 69 - 82 % of the cycles at 1.93 GHz; the six products 2112 -> 1923 us against two
+// barriers a step and loads through registers, 843 -> 707 with 8997 rows in 36 slots of d = 328, f = 872).  The hidden
+// gradient's epilogue read its u, v under a branch per element: 131 -> 99 us.
+constexpr int F32_BM = 64;
 
-template <int MODE, int NBL>
-__global__ __launch_bounds__(256, NBL == 2 ? 3 : 5) void gemm_f32_kernel(GemmParams p) {
+template <int MODE, int NBL, int KD>
+__global__ __launch_bounds__(256, NBL == 2 ? 3 : KD == 32 ? 4 : 6) void gemm_f32_kernel(GemmParams p) {
   using Op = F32Operands<MODE>;
   static_assert(NBL == 2 || (NBL == 1 && MODE != FWD1), "the gate and up columns of a hidden unit go together");
-  constexpr int F32_BN = 64 * NBL, NBP = 2 * NBL;   // tile columns; 16-byte pieces of the right operand per thread
-  constexpr int LDK = F32_BK + 4;              // [row][k]: 16-byte reads of 16 rows hit all 64 banks once
-  constexpr int LDA = F32_BM + 8, LDB = F32_BN + 8;   // [k][row]: rows 4 apart are 32 banks apart
-  __shared__ __attribute__((aligned(16))) float As[Op::A_KC ? F32_BM * LDK : F32_BK * LDA];
-  __shared__ __attribute__((aligned(16))) float Bs[Op::B_KC ? F32_BN * LDK : F32_BK * LDB];
+  constexpr int F32_BN = 64 * NBL;
+  constexpr bool VARM = Op::VARM;
+  constexpr bool PAIRS = !Op::B_KC && NBL == 2;   // neighbouring columns in one lane
+  constexpr int NST = KD == 32 ? 2 : 3;           // stages
+  constexpr int NLA = KD / 16, NLB = NLA * NBL;   // 1 KB load instructions per wavefront, operand and stage
+  constexpr int SA = F32_BM * KD, SB = F32_BN * KD;   // elements of a stage
+  __shared__ __attribute__((aligned(1024))) float As[NST * SA];
+  __shared__ __attribute__((aligned(1024))) float Bs[NST * SB];
   Op o;
   if (!o.init(p, F32_BM, blockIdx.y, blockIdx.z)) return;
   const int K = o.K, N = MODE == FWD1 ? p.f : p.N;
@@ -1280,63 +1289,59 @@ __global__ __launch_bounds__(256, NBL == 2 ? 3 : 5) void gemm_f32_kernel(GemmPar
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1, r31 = lane & 31, hw = lane >> 5;
 
-  // 16-byte pieces of a step: 2 of the left operand and 4 of the right one per thread, each at a
-  // wave-uniform base (tile and step) plus a 32-bit byte offset inside the tile (at most 128 rows of
-  // 2^22 elements)
-  unsigned oa[2], ob[NBP];
-  int ka[2], kb[NBP];                            // reduction index of the piece within a step
+  auto swizzle = [](int r) { return KD == 32 ? (r >> 1) & 7 : (r >> 2) & 3; };   // of a [row][k] tile's chunks
+
+  // byte offset of this lane's 16 bytes for instruction j of an operand (its immediate, j KB, taken back out) and their
+  // reduction index in the step
+  unsigned vo[NLA + NLB];
+  int kr[NLA + NLB];
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int e = tid + 256 * h, c = (e & 15) * 4;
-    ka[h] = Op::A_KC ? (e & 7) * 4 : e >> 4;
-    oa[h] = Op::A_KC ? (unsigned)(min(e >> 3, o.row1 - o.row0 - 1) * (int)o.lda + ka[h]) * 4u
-                     : (unsigned)(ka[h] * (int)o.lda + (c < o.row1 - o.row0 ? c : 0)) * 4u;
-  }
-#pragma unroll
-  for (int h = 0; h < NBP; ++h) {
-    const int e = tid + 256 * h, c = (e & (F32_BN / 4 - 1)) * 4;
-    kb[h] = Op::B_KC ? (e & 7) * 4 : e / (F32_BN / 4);
-    // FWD1: the 64 tile columns of a wavefront are 32 gate and the 32 up columns of the same hidden
-    // units; piece h is a gate column for even h and an up column for odd h
-    const int t = MODE == FWD1 ? (h >> 1) * 32 + ((e >> 3) & 31) : e >> 3;
-    ob[h] = Op::B_KC ? (unsigned)(min(t, N - 1 - n0) * (int)o.ldb + kb[h]) * 4u
-                     : (unsigned)(kb[h] * (int)o.ldb + (n0 + c < N ? c : 0)) * 4u;
-  }
-  const float* const b0 = o.B + (Op::B_KC ? n0 * o.ldb : n0);
-  floatx4 na[2], nb[NBP];
-  auto fetch = [&](int k0) {
-    const bool whole = k0 + F32_BK <= K;
-    const char* const qa = reinterpret_cast<const char*>(o.A + (Op::A_KC ? k0 : k0 * o.lda));
-    const char* const qb = reinterpret_cast<const char*>(b0 + (Op::B_KC ? k0 : k0 * o.ldb));
-    const char* const qu = MODE == FWD1 ? qb + 4LL * p.f * o.ldb : qb;
-    if (whole) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) na[h] = *reinterpret_cast<const floatx4*>(qa + oa[h]);
-#pragma unroll
-      for (int h = 0; h < NBP; ++h) nb[h] = *reinterpret_cast<const floatx4*>((h & 1 ? qu : qb) + ob[h]);
+  for (int x = 0; x < NLA + NLB; ++x) {
+    const bool right = x >= NLA;
+    const int j = right ? x - NLA : x, q = wave * (right ? NLB : NLA) + j;
+    const int ld = (int)(right ? o.ldb : o.lda), extent = right ? N - n0 : o.row1 - o.row0;
+    unsigned e;
+    if (right ? Op::B_KC : Op::A_KC) {   // 256 / KD rows
+      const int r = q * (256 / KD) + lane / (KD / 4);
+      kr[x] = ((lane & (KD / 4 - 1)) ^ swizzle(r)) * 4;
+      // FWD1: the 64 tile columns of a wavefront are 32 gate and the 32 up columns of the same hidden units; a
+      // wavefront loads either gate or up columns
+      const int row = right && MODE == FWD1 ? (r >> 6) * 32 + (r & 31) : r;
+      e = (unsigned)(min(row, extent - 1) * ld + kr[x]);
     } else {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        na[h] = floatx4{0.f, 0.f, 0.f, 0.f};
-        if (k0 + ka[h] < K) na[h] = *reinterpret_cast<const floatx4*>(qa + oa[h]);
-      }
-#pragma unroll
-      for (int h = 0; h < NBP; ++h) {
-        nb[h] = floatx4{0.f, 0.f, 0.f, 0.f};
-        if (k0 + kb[h] < K) nb[h] = *reinterpret_cast<const floatx4*>((h & 1 ? qu : qb) + ob[h]);
-      }
+      const int cpr = (right ? F32_BN : F32_BM) / 4;   // chunks of a row
+      kr[x] = q * (64 / cpr) + lane / cpr;
+      const int c = ((lane & (cpr - 1)) ^ (8 * ((kr[x] >> 2) & 1))) * 4;
+      e = (unsigned)(kr[x] * ld + (c < extent ? c : 0));
     }
+    vo[x] = e * 4u + 4096u - (unsigned)(j * 1024);
+  }
+  const float* const b0 = o.B + (Op::B_KC ? n0 * o.ldb : n0) + (MODE == FWD1 && (wave & 1) ? (long long)p.f * o.ldb : 0);
+  const unsigned ldsA = (unsigned)(size_t)SYMI_LPTR(As) + wave * (NLA * 1024);
+  const unsigned ldsB = (unsigned)(size_t)SYMI_LPTR(Bs) + wave * (NLB * 1024);
+  auto load_one = [&](auto jc, unsigned v, intx4 rsrc) {
+    asm volatile("buffer_load_dwordx4 %0, %1, 0 offen offset:%2 lds" ::"v"(v), "s"(rsrc), "n"(decltype(jc)::value * 1024) : "memory");
   };
-  auto commit = [&]() {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int e = tid + 256 * h;
-      *reinterpret_cast<floatx4*>(As + (Op::A_KC ? (e >> 3) * LDK + (e & 7) * 4 : (e >> 4) * LDA + (e & 15) * 4)) = na[h];
-    }
-#pragma unroll
-    for (int h = 0; h < NBP; ++h) {
-      const int e = tid + 256 * h;
-      *reinterpret_cast<floatx4*>(Bs + (Op::B_KC ? (e >> 3) * LDK + (e & 7) * 4 : e / (F32_BN / 4) * LDB + (e & (F32_BN / 4 - 1)) * 4)) = nb[h];
+  auto load = [&](auto rightc, unsigned dst, const float* src, int left, auto edge) {
+    constexpr bool right = decltype(rightc)::value != 0;
+    const unsigned long long a = (unsigned long long)src - 4096;
+    const intx4 rsrc = {(int)(unsigned)a, (int)((unsigned)(a >> 32) & 0xffffu), (int)OUTSIDE, 0x00020000};
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" ::"s"(dst) : "memory");   // the wait state of an M0 write
+    unroll<right ? NLB : NLA>([&](auto jc) {
+      constexpr int x = (right ? NLA : 0) + decltype(jc)::value;
+      load_one(jc, !decltype(edge)::value || kr[x] < left ? vo[x] : OUTSIDE, rsrc);
+    });
+  };
+  auto issue = [&](int t, int st) {
+    const int k0 = t * KD;
+    const float* const sa = o.A + (Op::A_KC ? (long long)k0 : k0 * o.lda);
+    const float* const sb = b0 + (Op::B_KC ? (long long)k0 : k0 * o.ldb);
+    if (k0 + KD <= K) {
+      load(IC<0>{}, ldsA + st * (SA * 4), sa, 0, std::false_type{});
+      load(IC<1>{}, ldsB + st * (SB * 4), sb, 0, std::false_type{});
+    } else {
+      load(IC<0>{}, ldsA + st * (SA * 4), sa, K - k0, std::true_type{});
+      load(IC<1>{}, ldsB + st * (SB * 4), sb, K - k0, std::true_type{});
     }
   };
   const int col0 = n0 + wn * (MODE == FWD1 ? 32 : 32 * NBL);
@@ -1347,9 +1352,14 @@ __global__ __launch_bounds__(256, NBL == 2 ? 3 : 5) void gemm_f32_kernel(GemmPar
   for (int j = 0; j < NBL; ++j)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
-  auto multiply = [&]() {
+  // element of As / Bs: KC chunk 2 s + hw of row, KS column of reduction index 4 hw (+ i + 8 s); the xor of a chunk
+  const int kx = swizzle(r31);
+  const int ra = Op::A_KC ? (wm * 32 + r31) * KD : hw * 4 * F32_BM + ((wm * 32 + r31) ^ (32 * hw));
+  const int rb = Op::B_KC ? (wn * 32 * NBL + r31) * KD
+                          : hw * 4 * F32_BN + ((wn * 32 * NBL + (PAIRS ? 2 : 1) * r31) ^ (32 * hw));
+  auto multiply = [&](const float* const as, const float* const bs) {
 #pragma unroll
-    for (int c = 0; c < F32_BK / F32_CHUNK; ++c) {
+    for (int c = 0; c < KD / F32_CHUNK; ++c) {
       floatx16 part[NBL];
 #pragma unroll
       for (int j = 0; j < NBL; ++j)
@@ -1357,23 +1367,31 @@ __global__ __launch_bounds__(256, NBL == 2 ? 3 : 5) void gemm_f32_kernel(GemmPar
         for (int r = 0; r < 16; ++r) part[j][r] = 0.f;
 #pragma unroll
       for (int s = 0; s < F32_CHUNK / 8; ++s) {
-        const int k = c * F32_CHUNK + s * 8 + 4 * hw;
+        const int k8 = c * F32_CHUNK + s * 8;   // reduction indices k8 + 4 hw + i
         float a[4], b[NBL][4];
         if (Op::A_KC) {
-          const float4 q = *reinterpret_cast<const float4*>(As + (wm * 32 + r31) * LDK + k);
+          const float4 q = *reinterpret_cast<const float4*>(as + ra + (((k8 / 4 + hw) ^ kx) * 4));
           a[0] = q.x; a[1] = q.y; a[2] = q.z; a[3] = q.w;
         } else {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) a[i] = As[(k + i) * LDA + wm * 32 + r31];
+          for (int i = 0; i < 4; ++i) a[i] = as[ra + (k8 + i) * F32_BM];
         }
+        if (PAIRS) {
 #pragma unroll
-        for (int j = 0; j < NBL; ++j) {
-          if (Op::B_KC) {
-            const float4 q = *reinterpret_cast<const float4*>(Bs + (wn * 32 * NBL + j * 32 + r31) * LDK + k);
-            b[j][0] = q.x; b[j][1] = q.y; b[j][2] = q.z; b[j][3] = q.w;
-          } else {
+          for (int i = 0; i < 4; ++i) {
+            const float2 q = *reinterpret_cast<const float2*>(bs + rb + (k8 + i) * F32_BN);
+            b[0][i] = q.x; b[NBL - 1][i] = q.y;
+          }
+        } else {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) b[j][i] = Bs[(k + i) * LDB + wn * 32 * NBL + j * 32 + r31];
+          for (int j = 0; j < NBL; ++j) {
+            if (Op::B_KC) {
+              const float4 q = *reinterpret_cast<const float4*>(bs + rb + j * 32 * KD + (((k8 / 4 + hw) ^ kx) * 4));
+              b[j][0] = q.x; b[j][1] = q.y; b[j][2] = q.z; b[j][3] = q.w;
+            } else {
+#pragma unroll
+              for (int i = 0; i < 4; ++i) b[j][i] = bs[rb + (k8 + i) * F32_BN];
+            }
           }
         }
 #pragma unroll
@@ -1388,23 +1406,84 @@ __global__ __launch_bounds__(256, NBL == 2 ? 3 : 5) void gemm_f32_kernel(GemmPar
         for (int r = 0; r < 16; ++r) acc[j][r] += part[j][r];
     }
   };
-  if (K > 0) fetch(0);
-  for (int k0 = 0; k0 < K; k0 += F32_BK) {
-    commit();
-    __syncthreads();
-    if (k0 + F32_BK < K) fetch(k0 + F32_BK);
-    if (busy) multiply();
-    __syncthreads();
+  const int nk = (K + KD - 1) / KD;
+#pragma unroll
+  for (int t = 0; t < NST - 1; ++t)
+    if (t < nk) issue(t, t);
+  int st = 0;
+  for (int t = 0; t < nk; ++t) {
+    // my loads of step t have landed (with three stages those of the next step may fly) and my reads of step t - 1
+    // are through; behind the barrier everybody's, and its stage may be filled
+    if (NST == 3 && t + 1 < nk) __builtin_amdgcn_s_waitcnt(0x0070 + NLA + NLB); else __builtin_amdgcn_s_waitcnt(0x0070);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (t + NST - 1 < nk) issue(t + NST - 1, st == 0 ? NST - 1 : st - 1);
+    if (busy) multiply(As + st * SA, Bs + st * SB);
+    asm volatile("" ::: "memory");
+    st = st == NST - 1 ? 0 : st + 1;
   }
 
+  if (!busy) return;
+  // Stores past the tile's end go outside the buffer; no branch keeps the loads of a whole block from flying together.
+  constexpr int VW = PAIRS ? 2 : 1;   // neighbouring columns of a lane
+  const long long rb0 = o.row0 + wm * 32;
+  const int left = o.row1 - (int)rb0, twof = 2 * p.f;
+  auto row_of = [&](int r) { return 8 * (r >> 2) + 4 * hw + (r & 3); };
+  auto store = [&](float* base, bool in, unsigned at, float x, float y) {
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)OUTSIDE, 0x00020000);
+    const int ofs = (int)(in ? at * 4u : OUTSIDE);
+    if (VW == 2) __builtin_amdgcn_raw_buffer_store_b64(uintx2{__float_as_uint(x), __float_as_uint(y)}, rsrc, ofs, 0, 0);
+    else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), rsrc, ofs, 0, 0);
+  };
 #pragma unroll
-  for (int j = 0; j < (MODE == FWD1 ? 1 : NBL); ++j) {
-    const int col = col0 + j * 32 + r31;
-    if (!busy || col >= N) continue;
+  for (int j = 0; j < (MODE == FWD1 || PAIRS ? 1 : NBL); ++j) {
+    const int col = col0 + j * 32 + VW * r31;
+    const bool in_col = col < N;   // N is even
+    if constexpr (MODE == FWD1) {
+      float* const UVo = static_cast<float*>(p.UVout) + rb0 * twof;
+      float* const Ho = static_cast<float*>(p.H) + rb0 * p.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = o.row0 + wm * 32 + 8 * (r >> 2) + 4 * hw + (r & 3);
-      if (row < o.row1) f32_store<MODE>(p, o.group, row, col, acc[j][r], acc[NBL - 1][r]);
+      for (int r = 0; r < 16; ++r) {
+        const bool in = in_col && row_of(r) < left;
+        const float u = acc[0][r], v = acc[NBL - 1][r];
+        const unsigned at = (unsigned)(row_of(r) * twof + col);
+        store(UVo, in, at, u, 0.f);
+        store(UVo + p.f, in, at, v, 0.f);
+        store(Ho, in, (unsigned)(row_of(r) * p.f + col), silu_f(u) * v, 0.f);
+      }
+    } else if constexpr (MODE == BWD_DH) {
+      const float* const UVi = static_cast<const float*>(p.UV) + rb0 * twof + min(col, N - VW);
+      float* const Co = static_cast<float*>(p.C) + rb0 * twof;
+      float u[16][VW], v[16][VW];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float* const q = UVi + (long long)min(row_of(r), left - 1) * twof;
+#pragma unroll
+        for (int x = 0; x < VW; ++x) {
+          u[r][x] = q[x];
+          v[r][x] = q[p.f + x];
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        float du[2] = {0.f, 0.f}, dv[2] = {0.f, 0.f};
+#pragma unroll
+        for (int x = 0; x < VW; ++x) {
+          const float dh = acc[j + x][r], sg = sigmoid_f(u[r][x]);
+          du[x] = dh * v[r][x] * sg * (1.f + u[r][x] * (1.f - sg));
+          dv[x] = dh * u[r][x] * sg;
+        }
+        const bool in = in_col && row_of(r) < left;
+        const unsigned at = (unsigned)(row_of(r) * twof + col);
+        store(Co, in, at, du[0], du[1]);
+        store(Co + p.f, in, at, dv[0], dv[1]);
+      }
+    } else {
+      float* const Co = static_cast<float*>(p.C) + (VARM ? 0 : (long long)o.group * p.c_group_stride) + rb0 * p.N;
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        store(Co, in_col && row_of(r) < left, (unsigned)(row_of(r) * p.N + col), acc[j][r], acc[NBL - 1][r]);
     }
   }
 }
@@ -1596,10 +1675,13 @@ static void launch_gemm(const symi_ctx* ctx, const GemmParams& p, int n_cols, in
     constexpr int NW = VARM ? 4 : 8;
     const int groups = p.per_slot ? cfg->S_tot : cfg->E;
     const int ntx = cdiv(n_cols, MODE == FWD1 ? 64 : 128);
-    // Count of 64 x 128 tiles (variable rows: about half a tile of padding per slot).  Below one
-    // round of them the shared reduction, below four the 64-wide tile, which makes twice as many
-    // workgroups: 475 tiles, second forward product 135 us shared / 99 us 64 wide / 113 us 128 wide,
-    // input gradient 250 / 203 / 268; at 2240 tiles 128 wide reads its left operand half as often.
+    // Count of 64 x 128 tiles (variable rows: about half a tile of padding per slot).  Below one round of them the shared
+    // reduction, below four the 64-wide tile, which makes twice as many workgroups.  us, shared reduction / 64 wide /
+    // 128 wide: W2 gradient 33 / 58 / - at 192 tiles, - / 88 / 121 at 504; second forward product and input gradient 80 / 54 / -
+    // and 122 / 98 / - at 186 tiles, where the shared reduction stays all the same, as its sums are the more
+    // exact ones (1.9e-7 : 2.2e-7); - / 126 / 146 and - / 247 / 284 at 543.  64-wide tiles of 32-deep steps while four to a
+    // unit hold all of them (948: 92 and 171 against 99 and 185 16 deep), beyond that 16 deep, six to a unit (1088: 132 and
+    // 272 against 126 and 247).
     const long long rows = VARM ? (long long)cfg->T * cfg->k / F32_BM + cfg->S_tot / 2 : (long long)cdiv(p.M, F32_BM) * groups;
     if (rows * ntx < 1LL * ctx->cus) {
       dim3 grid(cdiv(n_cols, 32), VARM ? 8 * max_mtiles : cdiv(p.M, 32), VARM ? 1 : groups);
@@ -1609,11 +1691,15 @@ static void launch_gemm(const symi_ctx* ctx, const GemmParams& p, int n_cols, in
     const int gy = VARM ? 4 * max_mtiles : cdiv(p.M, F32_BM), gz = VARM ? 1 : groups;
     if constexpr (MODE != FWD1) {
       if (rows * ntx < 4LL * ctx->cus) {
-        SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_f32_kernel<MODE, 1><<<dim3(cdiv(n_cols, 64), gy, gz), 256, 0, st>>>(p)));
+        const dim3 grid(cdiv(n_cols, 64), gy, gz);
+        if (!VARM || rows * cdiv(n_cols, 64) <= 4LL * ctx->cus)
+          SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_f32_kernel<MODE, 1, 32><<<grid, 256, 0, st>>>(p)));
+        else
+          SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_f32_kernel<MODE, 1, 16><<<grid, 256, 0, st>>>(p)));
         return;
       }
     }
-    SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_f32_kernel<MODE, 2><<<dim3(ntx, gy, gz), 256, 0, st>>>(p)));
+    SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_f32_kernel<MODE, 2, 32><<<dim3(ntx, gy, gz), 256, 0, st>>>(p)));
   }
 }
 

@@ -1490,16 +1490,24 @@ __global__ __launch_bounds__(256, NBL == 2 ? 3 : KD == 32 ? 4 : 6) void gemm_f32
 
 // A small batch has too few 64 x 128 tiles to fill the chip, and the time of one tile is its
 // reduction's latency.  Here a tile is 32 x 32 (FWD1: 32 hidden units, gate and up) and NW
-// wavefronts share its reduction, each streaming its own range of reduction indices straight from
-// memory into registers (no LDS, no barrier; the next 16 indices are in flight during the current
-// ones' products); their sums meet in LDS in a fixed order.  8 experts of 128 x 256, 2048 rows: the six
-// products take 14, 8, 13, 9, 13 and 13 us, where plain FMAs took 16, 22, 42, 19, 42 and 46.
+// wavefronts share its reduction, each with its own range of reduction indices: 16-deep steps through an LDS ring of
+// its own (direct-to-LDS loads, one to two steps ahead, no barrier); the sums meet in LDS in a fixed order.
+// Rows of a step are 64-byte segments, columns 128-byte ones; straight from memory into registers a load took 16 bytes
+// of each of 32 rows, four loads to a cache line, and only one step flew: 512 rows in 8 slots of d = 512, f = 1280, the six
+// products 53, 51, 32, 97, 20, 28 us -> 33, 26, 25, 48, 18, 24; 2048 rows in 16 slots of d = 128, f = 256 15, 11, 13, 16, 11,
+// 13 -> 14, 9, 10, 13, 10, 11 (events around the launch).  Bound by latency: a table entry, the first loads, K / (16 NW) steps,
+// the sum.
+// Ring layouts, free of bank conflicts: reduction-contiguous [32 rows][16 k], 16-byte chunk c of row r at c ^ ((r >> 2) & 3);
+// reduction-strided [16 k][32 columns], index k in row k ^ ((k >> 2) & 1): the two halves of a wavefront read indices 4 apart.
 template <int MODE, int NW>
 __global__ __launch_bounds__(64 * NW) void gemm_f32_small_kernel(GemmParams p) {
   using Op = F32Operands<MODE>;
   constexpr int NB = MODE == FWD1 ? 2 : 1;
+  constexpr int NST = NW == 4 ? 3 : 2;         // stages: three workgroups of 48 KB or two of 64 KB per unit
+  constexpr int SO = 32 * F32_CHUNK, RING = NST * (1 + NB) * SO;   // elements: an operand's step, a wavefront's ring
   constexpr int LDR = 40;                      // rows 4 apart are 32 banks apart
-  __shared__ float red[NW][NB][32 * LDR];
+  static_assert(RING >= NB * 32 * LDR, "the sums reuse the ring");
+  __shared__ __attribute__((aligned(1024))) float smem[NW * RING];
   Op o;
   if (!o.init(p, 32, blockIdx.y, blockIdx.z)) return;
   const int K = o.K, N = MODE == FWD1 ? p.f : p.N;
@@ -1509,52 +1517,83 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_small_kernel(GemmParams p) {
   const int r31 = lane & 31, hw = lane >> 5;
   const int per = (K + NW * F32_CHUNK - 1) / (NW * F32_CHUNK) * F32_CHUNK;
   const int kbeg = wave * per, kend = min(K, kbeg + per);
-  const int ra = min(r31, o.row1 - o.row0 - 1), rb = min(n0 + r31, N - 1);
-  const float* const pa = o.A + (Op::A_KC ? ra * o.lda : ra);
-  const float* const pb = o.B + (Op::B_KC ? rb * o.ldb : rb);
+  float* const ring = smem + wave * RING;
 
-  // 16 reduction indices: value 4 s + i is index k0 + 8 s + 4 hw + i
-  auto load = [&](int k0, float (&a)[8], float (&b)[NB][8]) {
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int k = k0 + 8 * s + 4 * hw;
-      // reduction-contiguous operands have K % 8 == 0: four indices are in or out together
-      if (Op::A_KC) {
-        const bool ok = k < kend;
-        const float4 q = *reinterpret_cast<const float4*>(pa + (ok ? k : 0));
-        a[4 * s] = ok ? q.x : 0.f; a[4 * s + 1] = ok ? q.y : 0.f; a[4 * s + 2] = ok ? q.z : 0.f; a[4 * s + 3] = ok ? q.w : 0.f;
-      } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const bool ok = k + i < kend;
-          const float q = pa[(ok ? k + i : 0) * o.lda];
-          a[4 * s + i] = ok ? q : 0.f;
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const float* const pj = pb + (j ? (long long)p.f * o.ldb : 0);
-        if (Op::B_KC) {
-          const bool ok = k < kend;
-          const float4 q = *reinterpret_cast<const float4*>(pj + (ok ? k : 0));
-          b[j][4 * s] = ok ? q.x : 0.f; b[j][4 * s + 1] = ok ? q.y : 0.f; b[j][4 * s + 2] = ok ? q.z : 0.f; b[j][4 * s + 3] = ok ? q.w : 0.f;
-        } else {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const bool ok = k + i < kend;
-            const float q = pj[(ok ? k + i : 0) * o.ldb];
-            b[j][4 * s + i] = ok ? q : 0.f;
-          }
-        }
-      }
+  // byte offset of this lane's 16 bytes for load j of an operand (its immediate, j KB, taken back out) and their
+  // reduction index in the step; rows and columns beyond the tile's extent are clamped (they only reach outputs that are
+  // never stored), reduction indices beyond the range read from outside the buffer: zeros
+  unsigned voA[2], voB[2];
+  int krA[2], krB[2];
+  auto lane_off = [&](bool kc, int j, int ld, int extent, int& kr) -> unsigned {
+    unsigned e;
+    if (kc) {
+      const int r = j * 16 + (lane >> 2);
+      kr = ((lane & 3) ^ ((r >> 2) & 3)) * 4;
+      e = (unsigned)(min(r, extent - 1) * ld + kr);
+    } else {
+      const int row = j * 8 + (lane >> 3), c = (lane & 7) * 4;
+      kr = row ^ ((row >> 2) & 1);
+      e = (unsigned)(kr * ld + (c < extent ? c : 0));
     }
+    return e * 4u + 4096u - (unsigned)(j * 1024);
+  };
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    voA[j] = lane_off(Op::A_KC, j, (int)o.lda, o.row1 - o.row0, krA[j]);
+    voB[j] = lane_off(Op::B_KC, j, (int)o.ldb, N - n0, krB[j]);
+  }
+  const unsigned lds = (unsigned)(size_t)SYMI_LPTR(ring);
+  const float* const b0 = o.B + (Op::B_KC ? n0 * o.ldb : n0);
+  auto load = [&](unsigned dst, const float* src, const unsigned (&vo)[2], const int (&kr)[2], int left) {
+    const unsigned long long a = (unsigned long long)src - 4096;
+    const intx4 rsrc = {__builtin_amdgcn_readfirstlane((int)(unsigned)a), __builtin_amdgcn_readfirstlane((int)((unsigned)(a >> 32) & 0xffffu)),
+                        (int)OUTSIDE, 0x00020000};
+    const unsigned v0 = kr[0] < left ? vo[0] : OUTSIDE, v1 = kr[1] < left ? vo[1] : OUTSIDE;
+    // wait states: of the M0 write, and of a base that came through the vector unit
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %3, 0 offen lds\n\t"
+                 "buffer_load_dwordx4 %2, %3, 0 offen offset:1024 lds" ::"s"(dst), "v"(v0), "v"(v1), "s"(rsrc) : "memory");
+  };
+  auto issue = [&](int t, int st) {
+    const int k0 = kbeg + t * F32_CHUNK, left = kend - k0;
+    const unsigned dst = lds + st * ((1 + NB) * SO * 4);
+    load(dst, o.A + (Op::A_KC ? (long long)k0 : k0 * o.lda), voA, krA, left);
+    const float* const sb = b0 + (Op::B_KC ? (long long)k0 : k0 * o.ldb);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) load(dst + (1 + j) * SO * 4, sb + (j ? (long long)p.f * o.ldb : 0), voB, krB, left);
   };
   floatx16 acc[NB];
 #pragma unroll
   for (int j = 0; j < NB; ++j)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
-  auto multiply = [&](const float (&a)[8], const float (&b)[NB][8]) {
+  // value 4 s + i is reduction index 8 s + 4 hw + i of the step
+  auto read = [&](bool kc, const float* q, float (&x)[8]) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      if (kc) {
+        const float4 y = *reinterpret_cast<const float4*>(q + r31 * F32_CHUNK + (((2 * s + hw) ^ ((r31 >> 2) & 3)) * 4));
+        x[4 * s] = y.x; x[4 * s + 1] = y.y; x[4 * s + 2] = y.z; x[4 * s + 3] = y.w;
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[4 * s + i] = q[((8 * s + 4 * hw + i) ^ hw) * 32 + r31];
+      }
+    }
+  };
+  const int ns = kbeg < kend ? (kend - kbeg + F32_CHUNK - 1) / F32_CHUNK : 0;
+#pragma unroll
+  for (int t = 0; t < NST - 1; ++t)
+    if (t < ns) issue(t, t);
+  int st = 0;
+  for (int t = 0; t < ns; ++t) {
+    // the loads of step t have landed (with three stages those of the next step may fly), the reads of step t - 1 are through
+    if (NST == 3 && t + 1 < ns) __builtin_amdgcn_s_waitcnt(0x0070 + 2 + 2 * NB); else __builtin_amdgcn_s_waitcnt(0x0070);
+    asm volatile("" ::: "memory");
+    if (t + NST - 1 < ns) issue(t + NST - 1, st == 0 ? NST - 1 : st - 1);
+    const float* const q = ring + st * ((1 + NB) * SO);
+    float a[8], b[NB][8];
+    read(Op::A_KC, q, a);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) read(Op::B_KC, q + (1 + j) * SO, b[j]);
     floatx16 part[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j)
@@ -1568,22 +1607,14 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_small_kernel(GemmParams p) {
     for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[j][r] += part[j][r];
-  };
-  if (kbeg < kend) {
-    float a0[8], a1[8], b0[NB][8], b1[NB][8];
-    load(kbeg, a0, b0);
-    for (int k0 = kbeg; k0 < kend; k0 += 2 * F32_CHUNK) {
-      if (k0 + F32_CHUNK < kend) load(k0 + F32_CHUNK, a1, b1);
-      multiply(a0, b0);
-      if (k0 + F32_CHUNK >= kend) break;
-      if (k0 + 2 * F32_CHUNK < kend) load(k0 + 2 * F32_CHUNK, a0, b0);
-      multiply(a1, b1);
-    }
+    asm volatile("" ::: "memory");
+    st = st == NST - 1 ? 0 : st + 1;
   }
+  auto sum = [&](int w, int j) { return smem + w * RING + j * 32 * LDR; };   // wavefront w's, block j
 #pragma unroll
   for (int j = 0; j < NB; ++j)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) red[wave][j][(8 * (r >> 2) + 4 * hw + (r & 3)) * LDR + r31] = acc[j][r];
+    for (int r = 0; r < 16; ++r) sum(wave, j)[(8 * (r >> 2) + 4 * hw + (r & 3)) * LDR + r31] = acc[j][r];
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < 1024 / (64 * NW); ++i) {
@@ -1592,9 +1623,9 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_small_kernel(GemmParams p) {
     float x[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-      x[j] = red[0][j][r * LDR + (e & 31)];
+      x[j] = sum(0, j)[r * LDR + (e & 31)];
 #pragma unroll
-      for (int w = 1; w < NW; ++w) x[j] += red[w][j][r * LDR + (e & 31)];
+      for (int w = 1; w < NW; ++w) x[j] += sum(w, j)[r * LDR + (e & 31)];
     }
     f32_store<MODE>(p, o.group, o.row0 + r, col, x[0], x[NB - 1]);
   }
@@ -1677,9 +1708,9 @@ static void launch_gemm(const symi_ctx* ctx, const GemmParams& p, int n_cols, in
     const int ntx = cdiv(n_cols, MODE == FWD1 ? 64 : 128);
     // Count of 64 x 128 tiles (variable rows: about half a tile of padding per slot).  Below one round of them the shared
     // reduction, below four the 64-wide tile, which makes twice as many workgroups.  us, shared reduction / 64 wide /
-    // 128 wide: W2 gradient 33 / 58 / - at 192 tiles, - / 88 / 121 at 504; second forward product and input gradient 80 / 54 / -
-    // and 122 / 98 / - at 186 tiles, where the shared reduction stays all the same, as its sums are the more
-    // exact ones (1.9e-7 : 2.2e-7); - / 126 / 146 and - / 247 / 284 at 543.  64-wide tiles of 32-deep steps while four to a
+    // 128 wide: W2 gradient - / 88 / 121 at 504 tiles; second forward product and input gradient 51 / 54 / -
+    // and 100 / 98 / - at 186, 19 / 16 / - and 32 / 26 / - at 192 with K = 256 and 512, where the shared reduction stays all
+    // the same, as its sums are the more exact ones (1.9e-7 : 2.2e-7); - / 126 / 146 and - / 247 / 284 at 543.  64-wide tiles of 32-deep steps while four to a
     // unit hold all of them (948: 92 and 171 against 99 and 185 16 deep), beyond that 16 deep, six to a unit (1088: 132 and
     // 272 against 126 and 247).
     const long long rows = VARM ? (long long)cfg->T * cfg->k / F32_BM + cfg->S_tot / 2 : (long long)cdiv(p.M, F32_BM) * groups;

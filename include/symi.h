@@ -84,7 +84,8 @@ int symi_validate(const symi_cfg* cfg);
  *     SYMI_CTX_NO_OVERLAP  every kernel of symi_expert_bwd* stays on the caller's stream
  *                          (default: the weight-gradient chain runs on the helper stream,
  *                          forked from and joined back into `stream` with events, when the
- *                          products are only a few rounds of workgroups: for the caller
+ *                          products are a few rounds of workgroups, and not less work than
+ *                          the events cost: for the caller
  *                          everything is still ordered on `stream`);
  *     SYMI_CTX_NO_SLICING  the two narrow products (Yp = H W2^T, dXp = dUV W1) never cut the
  *                          reduction of their last round's tiles into slices (default: they

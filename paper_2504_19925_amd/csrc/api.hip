@@ -133,11 +133,14 @@ int enter(const symi_ctx* ctx, const char* who) {
 }
 
 // The expert backward runs its weight-gradient chain on a stream of its own while the products
-// are only a few rounds of workgroups (gemm.hip); larger shapes fill the chip anyway.
+// are only a few rounds of workgroups (gemm.hip); larger shapes fill the chip anyway.  Forking, handing over and
+// joining cost 20 - 40 us on the device, so the products have to be worth it.  Step or backward, us, two streams : one, by
+// T*k*d*f: 6.5e6 115 : 77, 2.5e7 122 : 83, 6.7e7 122 : 100, 7.3e7 77 : 63, 1.0e8 150 : 150, 2.1e8 144 : 135, 3.3e8 243 : 230;
+// 4.2e8 156 : 161, 5.2e8 88 : 91, 9.9e8 240 : 270, 3.9e9 405 : 433, 9.2e9 410 : 450, 2.4e10 514 : 604, 6.9e10 2060 : 2108.
 static bool wants_side_stream(const symi_cfg* c, int cus) {
   const long long A = (long long)c->T * c->k;
   const long long max_mtiles = A / GEMM_BM + c->S_tot;
-  return A > 0 && max_mtiles * cdiv(c->d, 256) < 8LL * cus;
+  return (double)A * c->d * c->f >= 3.5e8 && max_mtiles * cdiv(c->d, 256) < 8LL * cus;
 }
 
 static void release(symi_ctx* ctx) {

@@ -100,3 +100,31 @@ def test_router_full_size_sampled_c5():
     check_close("dWr", Hn.npf(dWr[:, cols]), want, "bf16", log=log)
     assert relerr_elem(Hn.npf(db), Hn.npf(dl).astype(np.float64).sum(0)) <= 1e-5
     print("[err] " + " ".join(f"{k}:max={v['max']:.2e}" for k, v in log.items()), flush=True)
+
+
+# fp32: the weight gradient's chunks of 512 tokens (32 per wavefront, sums of 16) and tiles of 64 columns x 8 classes at
+# their edges, against binary64.  A sum of n products in blocks: (16 + 2 + 16 + chunks) roundings of 2^-24 of the sum of the
+# magnitudes at most
+@pytest.mark.parametrize("T,E,d", [(1, 1, 8), (15, 3, 72), (17, 8, 64), (511, 9, 56), (513, 16, 136), (1600, 17, 200), (2048, 5, 8)])
+def test_f32_router_gradients(T, E, d):
+    cfg = symi.SymiCfg.make(T, E, 1, d, 8, E, 1, 0, "f32", 1)
+    ctx = symi.symi_create(cfg)
+    g = torch.Generator(device="cuda").manual_seed(T + d)
+    def normal(*n):
+        return torch.randn(*n, generator=g, device="cuda")
+    X, Wr, b, dl, dX0 = normal(T, d), normal(E, d), normal(E), normal(T, E), normal(T, d)
+    ws = torch.full((symi.symi_workspace_bytes(cfg),), 255, dtype=torch.uint8, device="cuda")
+    logits, dWr, db, dX = torch.empty(T, E, device="cuda"), torch.empty(E, d, device="cuda"), torch.empty(E, device="cuda"), dX0.clone()
+    print(f"[router f32] T={T} E={E} d={d}", flush=True)
+    symi.symi_router_fwd(ctx, X, Wr, b, logits)
+    symi.symi_router_bwd(ctx, X, Wr, dl, dWr, db, dX, ws)
+    Xd, Wd, dd = X.double(), Wr.double(), dl.double()
+    chunks = (T + 511) // 512
+
+    def near(got, want, magnitude, roundings):
+        assert bool(((got.double() - want).abs() <= roundings * 2.0 ** -24 * magnitude + 1e-30).all())
+
+    near(dWr, dd.T @ Xd, dd.abs().T @ Xd.abs(), 34 + chunks)
+    near(logits, Xd @ Wd.T + b.double(), Xd.abs() @ Wd.abs().T + b.double().abs(), d + 1)
+    near(dX, dX0.double() + dd @ Wd, dX0.double().abs() + dd.abs() @ Wd.abs(), E + 1)
+    near(db, dd.sum(0), dd.abs().sum(0), 3 + (T + 255) // 256)

@@ -318,21 +318,28 @@ __global__ __launch_bounds__(SMALL_DT) void dispatch_small_kernel(
 }
 
 
-template <bool BF16>
-__device__ __forceinline__ int load_piece(const void* p, long long piece, float (&out)[8]) {
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// 16 bytes of a row.  ONCE: a row that the kernel reads once is loaded past the caches' replacement order, as kept like any
+// other line it pushes out what is used again.  us, plain : once, mean of three runs in turn: combine c5 944 : 915, c4 184 : 171,
+// dispatch backward c5 974 : 917, c4 225 : 185, c2 18 : 15.  Nothing on combine_bwd (1867 : 1882); the row scatter's
+// stores lose by it (942 : 997, 168 : 195).
+template <bool BF16, bool ONCE = false>
+__device__ __forceinline__ void load_piece(const void* p, long long piece, float (&out)[8]) {
   if (BF16) {
-    const uint4 q = reinterpret_cast<const uint4*>(p)[piece];
+    const u32x4* const at = reinterpret_cast<const u32x4*>(p) + piece;
+    const u32x4 q = ONCE ? __builtin_nontemporal_load(at) : *at;
     const uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       out[2 * i] = __uint_as_float(w[i] << 16);
       out[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
     }
-    return 8;
   } else {
-    const float4 q = reinterpret_cast<const float4*>(p)[piece];
+    const f32x4* const at = reinterpret_cast<const f32x4*>(p) + piece;
+    const f32x4 q = ONCE ? __builtin_nontemporal_load(at) : *at;
     out[0] = q.x; out[1] = q.y; out[2] = q.z; out[3] = q.w;
-    return 4;
   }
 }
 
@@ -367,7 +374,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const void* __restrict__ s
       if (row < 0) continue;   // dropped by the capacity rule: contributes nothing
       const float g = w ? w[t * k + j] : 1.f;
       float x[8];
-      load_piece<BF16>(src, row * pieces_per_row + c, x);
+      load_piece<BF16, true>(src, row * pieces_per_row + c, x);
 #pragma unroll
       for (int q = 0; q < PW; ++q) acc[q] = fmaf(g, x[q], acc[q]);
     }

@@ -1901,7 +1901,8 @@ extern "C" int symi_expert_bwd_slots(const symi_ctx* ctx, const void* dYp, const
 // ---------------------------------------------------------------- replica all-reduce
 // The intra-rank part of the paper's all-reduce (Sec. 4.1): for every class the first of its
 // slots is the representative; the other slots add their gradient to it (slot order), the
-// sum is scaled and copied back to all of them.  16 bytes per lane, one class per blockIdx.y.
+// sum is scaled and copied back to all of them.  16 bytes per lane, one class per blockIdx.y.  Every gradient is read
+// once, past the caches' replacement order: 1000 -> 948 us (128 slots of d = 2048, f = 1408), 1104 -> 1006 (32 of d = 1128, f = 6376).
 namespace symi {
 __global__ __launch_bounds__(256) void replica_allreduce_kernel(float4* __restrict__ g,
                                                                 const int32_t* __restrict__ first_slot,
@@ -1910,13 +1911,12 @@ __global__ __launch_bounds__(256) void replica_allreduce_kernel(float4* __restri
   const int q0 = first_slot[e], q1 = first_slot[e + 1];
   if (q1 - q0 == 1 && scale == 1.f) return;   // a single replica: nothing to exchange
   for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n4; i += (long long)gridDim.x * 256) {
-    float4 a = g[(long long)q0 * n4 + i];
+    floatx4 a = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(g) + (long long)q0 * n4 + i);
     for (int q = q0 + 1; q < q1; ++q) {
-      const float4 b = g[(long long)q * n4 + i];
-      a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+      a += __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(g) + (long long)q * n4 + i);
     }
-    a.x *= scale; a.y *= scale; a.z *= scale; a.w *= scale;
-    for (int q = q0; q < q1; ++q) g[(long long)q * n4 + i] = a;
+    a *= scale;
+    for (int q = q0; q < q1; ++q) reinterpret_cast<floatx4*>(g)[(long long)q * n4 + i] = a;
   }
 }
 }  // namespace symi

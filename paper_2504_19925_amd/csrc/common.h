@@ -114,6 +114,7 @@ int enter(const symi_ctx* ctx, const char* who);
 void timing_begin(const symi_ctx* ctx, int kid, hipStream_t st);
 void timing_end(const symi_ctx* ctx, int kid, hipStream_t st);
 int static_scratch_address(int device, void** out);   // dispatch.hip
+void launch_router_fwd(const symi_ctx* ctx, const void* X, const void* Wr, const float* b, float* logits, hipStream_t st);   // gemm.hip
 void launch_fill_i32(const symi_ctx* ctx, int32_t* p, int n, int32_t val, hipStream_t st);
 }  // namespace symi
 

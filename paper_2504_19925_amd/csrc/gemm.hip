@@ -27,7 +27,7 @@
 
 namespace symi {
 
-enum { FWD1 = 0, FWD2 = 1, BWD_DH = 2, BWD_DX = 3, WGRAD2 = 4, WGRAD1 = 5 };
+enum { FWD1 = 0, FWD2 = 1, BWD_DH = 2, BWD_DX = 3, WGRAD2 = 4, WGRAD1 = 5, GATE = 6 };   // GATE: symi_router_fwd
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
@@ -892,7 +892,7 @@ __device__ __forceinline__ bool find_slot_tile(const int32_t* __restrict__ offs,
 
 template <int MODE>
 __global__ __launch_bounds__(GT, 2) void gemm_few_rows_kernel(GemmParams p) {
-  static_assert(MODE == FWD1 || MODE == FWD2, "both operands reduction-contiguous");
+  static_assert(MODE == FWD1 || MODE == FWD2 || MODE == GATE, "both operands reduction-contiguous");
   constexpr int TM = FEW_BM, TN = 128, NST = 3, LA = 2, LB = 4;   // LA, LB: 1 KB load instructions per wavefront and stage
   constexpr int SA = TM * BK, SB = TN * BK;          // elements of a stage
   __shared__ __attribute__((aligned(1024))) uint16_t smem[NST * (SA + SB)];
@@ -901,7 +901,14 @@ __global__ __launch_bounds__(GT, 2) void gemm_few_rows_kernel(GemmParams p) {
   const int wm = wave >> 1, wn = wave & 1;
   __shared__ int32_t found[8];
   SlotTile tile;
-  if (!find_slot_tile<TM>(p.slot_offsets, p.n_slots, found, tile)) return;
+  if constexpr (MODE == GATE) {   // the tokens in order; grid.x has no limit that they could reach
+    tile.row0 = blockIdx.x * TM;
+    tile.row1 = min(p.M, tile.row0 + TM);
+    tile.slot = 0;
+    tile.bx = blockIdx.y;
+  } else if (!find_slot_tile<TM>(p.slot_offsets, p.n_slots, found, tile)) {
+    return;
+  }
   const int row0 = tile.row0, row1 = tile.row1, group = tile.slot, bx = tile.bx;
   const int n0 = bx * (MODE == FWD1 ? TN / 2 : TN), K = p.K, ld = p.K;
   const uint16_t* const a_base = static_cast<const uint16_t*>(p.A) + (long long)row0 * ld;
@@ -978,10 +985,40 @@ __global__ __launch_bounds__(GT, 2) void gemm_few_rows_kernel(GemmParams p) {
     }
     st = st == NST - 1 ? 0 : st + 1;
   }
-  __syncthreads();   // nobody reads operands any more
-  // 18 KB of LDS per wavefront for its 32-row block of 64 columns
-  SavedUV<2> saved[2];   // the input-gradient product's
-  write_tile<MODE, 1, 2>(p, smem + wave * (NST * (SA + SB) / 4), acc, row0, row1, group, n0, wm, wn, lane, -1, saved);
+  if constexpr (MODE == GATE) {   // logits, fp32: a lane holds 4 neighbouring classes of a token
+    float* const Lo = static_cast<float*>(p.C);
+    const float* const bias = static_cast<const float*>(p.UV);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int col = n0 + wn * 64 + 16 * j + 4 * g4;
+      float bb[4] = {0.f, 0.f, 0.f, 0.f};
+      if (bias) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) bb[c] = bias[min(col + c, p.N - 1)];
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int row = row0 + wm * 32 + 16 * i + r16;
+        if (row >= row1) continue;
+        float* const at = Lo + (long long)row * p.N + col;
+        const float4 x = make_float4(acc[i][j][0] + bb[0], acc[i][j][1] + bb[1], acc[i][j][2] + bb[2], acc[i][j][3] + bb[3]);
+        if ((p.N & 3) == 0) {
+          if (col < p.N) *reinterpret_cast<float4*>(at) = x;
+        } else {
+          if (col < p.N) at[0] = x.x;
+          if (col + 1 < p.N) at[1] = x.y;
+          if (col + 2 < p.N) at[2] = x.z;
+          if (col + 3 < p.N) at[3] = x.w;
+        }
+      }
+    }
+    return;
+  } else {
+    __syncthreads();   // nobody reads operands any more
+    // 18 KB of LDS per wavefront for its 32-row block of 64 columns
+    SavedUV<2> saved[2];   // the input-gradient product's
+    write_tile<MODE, 1, 2>(p, smem + wave * (NST * (SA + SB) / 4), acc, row0, row1, group, n0, wm, wn, lane, -1, saved);
+  }
 }
 
 // ---------------------------------------------------------------- variable-row products of few or short tiles
@@ -1732,6 +1769,17 @@ static void launch_gemm(const symi_ctx* ctx, const GemmParams& p, int n_cols, in
     }
     SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_f32_kernel<MODE, 2, 32><<<dim3(ntx, gy, gz), 256, 0, st>>>(p)));
   }
+}
+
+// logits = X Wr^T + b, bf16 (symi_router_fwd).  Streams X once in 64-token tiles, two stages ahead; bound by the latency of
+// d / 64 steps where the tiles do not fill the chip, by memory beyond.  Against 128-token tiles through registers with two
+// barriers per step, us: T = 5573, E = 128, d = 2896 48 -> 28; 464, 16, 720 16 -> 10; 16384, 8, 4096 57 -> 34; 32768, 64, 2048
+// 41 -> 29; 65536, 128, 4096 157 -> 155.  Same bits.
+void launch_router_fwd(const symi_ctx* ctx, const void* X, const void* Wr, const float* b, float* logits, hipStream_t st) {
+  GemmParams p = {};
+  p.A = X; p.B = Wr; p.C = logits; p.UV = b;
+  p.M = ctx->cfg.T; p.N = ctx->cfg.E; p.K = ctx->cfg.d;
+  SYMI_TIMED(ctx, K_ROUTER_FWD, st, (gemm_few_rows_kernel<GATE><<<dim3(cdiv(p.M, FEW_BM), cdiv(p.N, 128)), GT, 0, st>>>(p)));
 }
 
 // where sliced reductions keep their partial tiles (bf16 configurations only)

@@ -1,8 +1,8 @@
 // symi_router_fwd / symi_router_bwd: the learned gate network in front of symi_route
 // (paper Sec. 2.1: the router scores every token against every expert class):
 //   logits = X Wr^T + b          dWr = dlogits^T X,  db = sum_t dlogits,  dX += dlogits Wr
-// Three skinny products (one side is E <= 1024 wide) that share one small tiled kernel:
-// 128 x 128 output tile, 4 wavefronts of 64 x 64 (2 x 2 MFMA 32x32x16 bf16 tiles), reduction
+// Three skinny products (one side is E <= 1024 wide).  The first one is the small-batch tile of gemm.hip.  The
+// two backward products share one small tiled kernel: 128 x 128 output tile, 4 wavefronts of 64 x 64 (2 x 2 MFMA 32x32x16 bf16 tiles), reduction
 // step 64.  Operands pass through registers into LDS (rows padded to 144 bytes; the next
 // step's global loads are in flight while the current one feeds the MFMAs) so that either
 // side may be bf16 or fp32 in memory and reduction-contiguous (LDS tile [row][k], fragments
@@ -32,14 +32,12 @@ typedef __attribute__((__vector_size__(4 * sizeof(short)))) short rshortx4;
 typedef unsigned int ru32x4 __attribute__((ext_vector_type(4)));
 constexpr int RCHUNK = 512;    // tokens per partial weight gradient, at least
 
-enum { R_FWD = 0, R_DX = 1, R_DW = 2 };
+enum { R_DX = 1, R_DW = 2 };
 
 struct RouterParams {
   const void* X;        // [T,d] activations (bf16)
   const void* Wr;       // [E,d] router weights (bf16)
-  const float* b;       // [E] or null
   const float* dl;      // [T,E] dlogits
-  float* logits;        // [T,E]
   void* dX;             // [T,d] accumulated into
   float* partial;       // [nchunk,E,d]
   int T, E, d;
@@ -51,29 +49,18 @@ __device__ __forceinline__ uint4 pack8(const float (&v)[8]) {
                     pack_bf16x2(v[6], v[7]));
 }
 
-// 8 consecutive reduction indices k..k+7 of operand row `r`, as bf16, zero outside.
-//   contiguous bf16:  src[r*ld + k ..]            strided bf16:  src[(k+i)*ld + r]
-//   contiguous fp32:  src[r*ld + k ..] converted  strided fp32:  src[(k+i)*ld + r] converted
-template <bool CONTIG, bool F32>
-__device__ __forceinline__ uint4 load8(const void* src, long long ld, int r, int rows, int k, int kend) {
+// 8 consecutive reduction indices k..k+7 of row `r` of a reduction-contiguous fp32 operand, as bf16, zero outside.
+__device__ __forceinline__ uint4 load8(const float* src, long long ld, int r, int rows, int k, int kend) {
   if (r >= rows || k >= kend) return make_uint4(0, 0, 0, 0);
-  float v[8];
-  if (CONTIG && !F32 && k + 8 <= kend) {
-    return *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(src) + (long long)r * ld + k);
-  }
-  if (CONTIG && F32 && k + 8 <= kend && (ld & 3) == 0) {
-    const float4 a = *reinterpret_cast<const float4*>(static_cast<const float*>(src) + (long long)r * ld + k);
-    const float4 c = *reinterpret_cast<const float4*>(static_cast<const float*>(src) + (long long)r * ld + k + 4);
+  const float* const q = src + (long long)r * ld + k;
+  if (k + 8 <= kend && (ld & 3) == 0) {
+    const float4 a = *reinterpret_cast<const float4*>(q);
+    const float4 c = *reinterpret_cast<const float4*>(q + 4);
     return make_uint4(pack_bf16x2(a.x, a.y), pack_bf16x2(a.z, a.w), pack_bf16x2(c.x, c.y), pack_bf16x2(c.z, c.w));
   }
+  float v[8];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const long long at = CONTIG ? (long long)r * ld + k + i : (long long)(k + i) * ld + r;
-    if (k + i < kend)
-      v[i] = F32 ? static_cast<const float*>(src)[at] : bf16_to_f32(static_cast<const uint16_t*>(src)[at]);
-    else
-      v[i] = 0.f;
-  }
+  for (int i = 0; i < 8; ++i) v[i] = k + i < kend ? q[i] : 0.f;
   return pack8(v);
 }
 
@@ -108,9 +95,9 @@ __global__ __launch_bounds__(256) void router_gemm_kernel(RouterParams p) {
   const int wm = wave >> 1, wn = wave & 1;
   // output rows M, columns N, reduction range [kbeg, kend)
   const int M = MODE == R_DW ? p.E : p.T;
-  const int N = MODE == R_FWD ? p.E : p.d;
+  const int N = p.d;
   const int m0 = blockIdx.y * RT, n0 = blockIdx.x * RT;
-  int kbeg = 0, kend = MODE == R_FWD ? p.d : MODE == R_DX ? p.E : p.T;
+  int kbeg = 0, kend = MODE == R_DX ? p.E : p.T;
   if (MODE == R_DW) {
     kbeg = blockIdx.z * p.chunk;
     kend = min(p.T, kbeg + p.chunk);
@@ -127,17 +114,15 @@ __global__ __launch_bounds__(256) void router_gemm_kernel(RouterParams p) {
   // Reduction-contiguous operands: piece u -> (row u/8, k-piece u%8), committed with one 16-byte
   // LDS store at [row][k]; strided ones: piece u -> (k-row u/16, rows 8*(u%16) ..), one 16-byte
   // LDS store at [k][row].
-  constexpr bool A_CONTIG = MODE != R_DW, B_CONTIG = MODE == R_FWD;
+  constexpr bool A_CONTIG = MODE != R_DW;
   uint4 ra[4], rb[4];
   auto fetch = [&](int k0) {
 #pragma unroll
     for (int h = 0; h < 4; ++h) {
       const int u = tid + 256 * h;
-      if (MODE == R_FWD) ra[h] = load8<true, false>(p.X, p.d, m0 + (u >> 3), M, k0 + 8 * (u & 7), kend);
-      else if (MODE == R_DX) ra[h] = load8<true, true>(p.dl, p.E, m0 + (u >> 3), M, k0 + 8 * (u & 7), kend);
+      if (MODE == R_DX) ra[h] = load8(p.dl, p.E, m0 + (u >> 3), M, k0 + 8 * (u & 7), kend);
       else ra[h] = load8_strided<true>(p.dl, p.E, m0 + 8 * (u & 15), M, k0 + (u >> 4), kend);
-      if (MODE == R_FWD) rb[h] = load8<true, false>(p.Wr, p.d, n0 + (u >> 3), N, k0 + 8 * (u & 7), kend);
-      else rb[h] = load8_strided<false>(MODE == R_DX ? p.Wr : p.X, p.d, n0 + 8 * (u & 15), N, k0 + (u >> 4), kend);
+      rb[h] = load8_strided<false>(MODE == R_DX ? p.Wr : p.X, p.d, n0 + 8 * (u & 15), N, k0 + (u >> 4), kend);
     }
   };
   auto commit = [&]() {
@@ -146,8 +131,7 @@ __global__ __launch_bounds__(256) void router_gemm_kernel(RouterParams p) {
       const int u = tid + 256 * h;
       if (A_CONTIG) *reinterpret_cast<uint4*>(&As[(u >> 3) * RLD + 8 * (u & 7)]) = ra[h];
       else *reinterpret_cast<uint4*>(&As[(u >> 4) * RLS + 8 * (u & 15)]) = ra[h];
-      if (B_CONTIG) *reinterpret_cast<uint4*>(&Bs[(u >> 3) * RLD + 8 * (u & 7)]) = rb[h];
-      else *reinterpret_cast<uint4*>(&Bs[(u >> 4) * RLS + 8 * (u & 15)]) = rb[h];
+      *reinterpret_cast<uint4*>(&Bs[(u >> 4) * RLS + 8 * (u & 15)]) = rb[h];
     }
   };
 
@@ -192,7 +176,7 @@ __global__ __launch_bounds__(256) void router_gemm_kernel(RouterParams p) {
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         af[i] = frag(As, A_CONTIG, wm * 64 + i * 32);
-        bfr[i] = frag(Bs, B_CONTIG, wn * 64 + i * 32);
+        bfr[i] = frag(Bs, false, wn * 64 + i * 32);
       }
 #pragma unroll
       for (int i = 0; i < 2; ++i)
@@ -201,64 +185,13 @@ __global__ __launch_bounds__(256) void router_gemm_kernel(RouterParams p) {
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
     }
   };
-  if constexpr (MODE == R_FWD) {
-    // The forward streams X once with few workgroups per compute unit (T / 128 of them): two
-    // steps are kept in flight in two register sets.  Every load is unconditional (clamped
-    // address; pieces past the reduction's end are zeroed on both sides, rows past the tile's
-    // edge only reach outputs that are never stored) and the steps come in pairs, so the loop
-    // has no branch and the wait for one set's loads does not wait for the other's.
-    const uint16_t* const Xb = static_cast<const uint16_t*>(p.X);
-    const uint16_t* const Wb = static_cast<const uint16_t*>(p.Wr);
-    ru32x4 xa[2][4], xb[2][4];
-    auto fetch2 = [&](auto setc, int k0) __attribute__((always_inline)) {
-      constexpr int S = decltype(setc)::value;
-#pragma unroll
-      for (int h = 0; h < 4; ++h) {
-        const int u = tid + 256 * h;
-        const int kp = k0 + 8 * (u & 7), kc = min(kp, kend - 8);
-        xa[S][h] = *reinterpret_cast<const ru32x4*>(Xb + (long long)min(m0 + (u >> 3), M - 1) * p.d + kc);
-        xb[S][h] = *reinterpret_cast<const ru32x4*>(Wb + (long long)min(n0 + (u >> 3), N - 1) * p.d + kc);
-      }
-    };
-    auto commit2 = [&](auto setc, int k0) __attribute__((always_inline)) {
-      constexpr int S = decltype(setc)::value;
-#pragma unroll
-      for (int h = 0; h < 4; ++h) {
-        const int u = tid + 256 * h;
-        const bool in = k0 + 8 * (u & 7) < kend;   // the values are only looked at here
-        const ru32x4 zero = {0u, 0u, 0u, 0u};
-        *reinterpret_cast<ru32x4*>(&As[(u >> 3) * RLD + 8 * (u & 7)]) = in ? xa[S][h] : zero;
-        *reinterpret_cast<ru32x4*>(&Bs[(u >> 3) * RLD + 8 * (u & 7)]) = in ? xb[S][h] : zero;
-      }
-    };
-    const int nk2 = ((kend - kbeg + RK - 1) / RK + 1) / 2 * 2;
-    fetch2(std::integral_constant<int, 0>{}, kbeg);
-    fetch2(std::integral_constant<int, 1>{}, kbeg + RK);
-    __builtin_amdgcn_sched_barrier(0);
-    for (int s2 = 0; s2 < nk2; s2 += 2) {
-      const int k0 = kbeg + s2 * RK;
-      commit2(std::integral_constant<int, 0>{}, k0);
-      __syncthreads();
-      fetch2(std::integral_constant<int, 0>{}, k0 + 2 * RK);
-      __builtin_amdgcn_sched_barrier(0);   // the requests go out here, not behind the MFMAs
-      mma();
-      __syncthreads();
-      commit2(std::integral_constant<int, 1>{}, k0 + RK);
-      __syncthreads();
-      fetch2(std::integral_constant<int, 1>{}, k0 + 3 * RK);
-      __builtin_amdgcn_sched_barrier(0);
-      mma();
-      __syncthreads();
-    }
-  } else {
-    if (kbeg < kend) fetch(kbeg);
-    for (int k0 = kbeg; k0 < kend; k0 += RK) {
-      commit();
-      __syncthreads();
-      if (k0 + RK < kend) fetch(k0 + RK);   // in flight while this step feeds the MFMAs
-      mma();
-      __syncthreads();
-    }
+  if (kbeg < kend) fetch(kbeg);
+  for (int k0 = kbeg; k0 < kend; k0 += RK) {
+    commit();
+    __syncthreads();
+    if (k0 + RK < kend) fetch(k0 + RK);   // in flight while this step feeds the MFMAs
+    mma();
+    __syncthreads();
   }
 
   // a lane owns output row lane%32 of each 32 x 32 block and, per 8-column group g, the 4
@@ -316,11 +249,7 @@ __global__ __launch_bounds__(256) void router_gemm_kernel(RouterParams p) {
         for (int c = 0; c < 4; ++c) x[c] = acc[i][j][4 * g + c];
         const long long at = (long long)row * N + col;
         if (col + 3 < N && (N & 3) == 0) {   // 4 columns at once (16 bytes fp32, 8 bytes bf16)
-          if (MODE == R_FWD) {
-            float4 bb = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (p.b) bb = make_float4(p.b[col], p.b[col + 1], p.b[col + 2], p.b[col + 3]);
-            *reinterpret_cast<float4*>(p.logits + at) = make_float4(x[0] + bb.x, x[1] + bb.y, x[2] + bb.z, x[3] + bb.w);
-          } else if (MODE == R_DX) {
+          if (MODE == R_DX) {
             uint2* o = reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.dX) + at);
             const uint2 old = *o;
             *o = make_uint2(pack_bf16x2(__uint_as_float(old.x << 16) + x[0], __uint_as_float(old.x & 0xffff0000u) + x[1]),
@@ -332,9 +261,7 @@ __global__ __launch_bounds__(256) void router_gemm_kernel(RouterParams p) {
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
             if (col + c >= N) continue;
-            if (MODE == R_FWD) {
-              p.logits[at + c] = x[c] + (p.b ? p.b[col + c] : 0.f);
-            } else if (MODE == R_DX) {
+            if (MODE == R_DX) {
               uint16_t* o = static_cast<uint16_t*>(p.dX) + at + c;
               *o = f32_to_bf16(bf16_to_f32(*o) + x[c]);
             } else {
@@ -720,9 +647,7 @@ extern "C" int symi_router_fwd(const symi_ctx* ctx, const void* X, const void* W
   hipStream_t st = as_stream(stream);
   const int T = cfg->T, E = cfg->E, d = cfg->d;
   if (cfg->dtype == SYMI_BF16) {
-    RouterParams p = {};
-    p.X = X; p.Wr = Wr; p.b = b; p.logits = logits; p.T = T; p.E = E; p.d = d;
-    SYMI_TIMED(ctx, K_ROUTER_FWD, st, (router_gemm_kernel<R_FWD><<<dim3(cdiv(E, RT), cdiv(T, RT)), 256, 0, st>>>(p)));
+    launch_router_fwd(ctx, X, Wr, b, logits, st);
   } else {
     SYMI_TIMED(ctx, K_ROUTER_FWD, st, (router_fwd_f32_kernel<<<cdiv((long long)T * E, 256), 256, 0, st>>>(
         static_cast<const float*>(X), static_cast<const float*>(Wr), b, logits, T, E, d)));

@@ -128,3 +128,25 @@ def test_f32_router_gradients(T, E, d):
     near(logits, Xd @ Wd.T + b.double(), Xd.abs() @ Wd.abs().T + b.double().abs(), d + 1)
     near(dX, dX0.double() + dd @ Wd, dX0.double().abs() + dd.abs() @ Wd.abs(), E + 1)
     near(db, dd.sum(0), dd.abs().sum(0), 3 + (T + 255) // 256)
+
+
+# bf16: the logits' tiles of 64 tokens x 128 classes and 64-deep steps (three stages) at their edges, with class counts that
+# are and are not multiples of 4, with and without a bias.  Products of bf16 values are exact in 32 bits: at most d + 1
+# roundings of 2^-24 of the sum of the magnitudes
+@pytest.mark.parametrize("T,E,d,bias", [(1, 1, 8, True), (63, 3, 64, False), (64, 8, 72, True), (65, 127, 136, True), (129, 128, 200, False),
+                                        (191, 129, 264, True), (40, 130, 8, True), (300, 260, 1000, False)])
+def test_bf16_router_logits(T, E, d, bias):
+    cfg = symi.SymiCfg.make(T, E, 1, d, 8, E, 1, 0, "bf16", 1)
+    ctx = symi.symi_create(cfg)
+    g = torch.Generator(device="cuda").manual_seed(T + d)
+    def normal(*n):
+        return torch.randn(*n, generator=g, device="cuda")
+    X, Wr, b = normal(T, d).bfloat16(), normal(E, d).bfloat16(), normal(E) if bias else None
+    logits = torch.full((T + 1, E), 7.0, device="cuda")
+    print(f"[router bf16] T={T} E={E} d={d}", flush=True)
+    symi.symi_router_fwd(ctx, X, Wr, b, logits)
+    want, mag = X.double() @ Wr.double().T, X.double().abs() @ Wr.double().abs().T
+    if bias:
+        want, mag = want + b.double(), mag + b.double().abs()
+    assert bool(((logits[:T].double() - want).abs() <= (d + 1) * 2.0 ** -24 * mag + 1e-30).all())
+    assert bool((logits[T] == 7.0).all())

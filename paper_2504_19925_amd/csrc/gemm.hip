@@ -1702,6 +1702,7 @@ static bool mid_tile(const symi_ctx* ctx, int mode) {
   const symi_cfg* const c = &ctx->cfg;
   if (c->dtype != SYMI_BF16 || mode > BWD_DX || ((mode == FWD1 || mode == FWD2) && few_rows(c))) return false;
   const long long A = (long long)c->T * c->k, S = c->S_tot;
+  if (A / MID_BM + S > 65535) return false;   // its row tiles are a grid.y coordinate
   const int K = mode == FWD1 || mode == BWD_DH ? c->d : mode == FWD2 ? c->f : 2 * c->f;
   const int ntx = mode == FWD1 ? cdiv(c->f, 64) : cdiv(mode == BWD_DH ? c->f : c->d, 128);
   if (A <= 128 * S && K <= 1024) return true;

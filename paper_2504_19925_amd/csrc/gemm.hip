@@ -353,9 +353,9 @@ __device__ __forceinline__ void write_tile(const GemmParams& p, uint16_t* const 
             const float u_ = __uint_as_float(h ? (uw[q] & 0xffff0000u) : (uw[q] << 16));
             const float v_ = __uint_as_float(h ? (vw[q] & 0xffff0000u) : (vw[q] << 16));
             const float sg = sigmoid_fast(u_);
-            const float ds = dh[2 * q + h] * sg;
-            o_du[h] = ds * v_ * (1.f + u_ * (1.f - sg));
-            o_dv[h] = ds * u_;
+            // dh v and dh u first: dh s is subnormal, a few bits long, for u near -87 and small dh
+            o_du[h] = dh[2 * q + h] * v_ * sg * (1.f + u_ * (1.f - sg));
+            o_dv[h] = dh[2 * q + h] * u_ * sg;
           }
           du[q] = pack_bf16x2(o_du[0], o_du[1]);
           dv[q] = pack_bf16x2(o_dv[0], o_dv[1]);

@@ -46,19 +46,29 @@ __device__ __forceinline__ void load_row(const float* __restrict__ row, int E, i
   }
 }
 
-// Softmax statistics of the row held by a lane group: max and sum of exp(z - max).
+// Softmax statistics of the row held by a lane group: max and sum of exp(z - max).  by_piece: the sum that G NV lanes
+// of one piece each would form, piece p of lane g standing for lane p G + g.
 template <int NV>
 __device__ __forceinline__ void row_stats(const float (&z)[NV * 4], int E, int G, int g,
-                                          float& zmax, float& zsum) {
+                                          float& zmax, float& zsum, bool by_piece = false) {
   float mx = -INFINITY;
 #pragma unroll
   for (int c = 0; c < NV * 4; ++c) mx = fmaxf(mx, z[c]);
   for (int m = G >> 1; m >= 1; m >>= 1) mx = fmaxf(mx, __shfl_xor(mx, m, 64));
-  float s = 0.f;
+  float s = 0.f, part[NV];
 #pragma unroll
   for (int c = 0; c < NV * 4; ++c) {
     const int col = ((c >> 2) * G + g) * 4 + (c & 3);
+    if (NV > 1 && by_piece && (c & 3) == 0) s = 0.f;
     if (col < E) s += expf(z[c] - mx);
+    part[c >> 2] = s;
+  }
+  if (NV > 1 && by_piece) {
+#pragma unroll
+    for (int h = NV / 2; h >= 1; h >>= 1)
+#pragma unroll
+      for (int p = 0; p < h; ++p) part[p] += part[p + h];
+    s = part[0];
   }
   for (int m = G >> 1; m >= 1; m >>= 1) s += __shfl_xor(s, m, 64);
   zmax = mx;
@@ -81,11 +91,11 @@ constexpr int KEY_NONE = INT_MIN;
 // settles the winner across the group by a butterfly over (key, column) pairs.
 // Workgroups of 256 or 1024 threads (blockDim.x): every workgroup adds its histogram to the
 // global one with E atomics, so a large batch takes the large workgroup (a quarter of the
-// atomics on the same E addresses).  alone: one workgroup holds the whole batch and stores its histogram.
+// atomics on the same E addresses).  alone: one workgroup holds the whole batch and stores its histogram; by_piece: row_stats.
 template <int G, int NV>
 __global__ __launch_bounds__(ROUTE_THREADS_MAX) void route_kernel(
     const float* __restrict__ logits, int32_t* __restrict__ idx, float* __restrict__ gate,
-    int32_t* __restrict__ hist, int T, int E, int k, int renorm, bool alone) {
+    int32_t* __restrict__ hist, int T, int E, int k, int renorm, bool alone, bool by_piece) {
   extern __shared__ int32_t hist_s[];
   const int nthreads = blockDim.x;
   for (int i = threadIdx.x; i < E; i += nthreads) hist_s[i] = 0;
@@ -104,7 +114,7 @@ __global__ __launch_bounds__(ROUTE_THREADS_MAX) void route_kernel(
     float z[NVAL];
     load_row<NV>(logits + (valid ? t : 0) * E, E, G, g, valid, z);
     float zmax, zsum;
-    row_stats<NV>(z, E, G, g, zmax, zsum);
+    row_stats<NV>(z, E, G, g, zmax, zsum, by_piece);
     int key[NVAL];
 #pragma unroll
     for (int c = 0; c < NVAL; ++c)
@@ -255,13 +265,16 @@ static void route_fwd_shape(int E, int T, int& G, int& NV) {
 
 // A small batch goes through one workgroup of 1024 threads in at most two passes, which then needs no cleared
 // histogram: a launch less (3 us).  Beyond E (k + 2) T = 2^16 the unit's vector pipes would take longer than that.
-static bool route_alone(const symi_cfg* c, int& G, int& NV) {
+// Fewer lanes per token than route_fwd_shape gives (by_piece) keep the order of its sums, so that a token's gates do not
+// depend on the size of its batch; E <= 256, where route_fwd_shape has one piece per lane at these sizes.
+static bool route_alone(const symi_cfg* c, int& G, int& NV, bool& by_piece) {
   if ((long long)c->T * c->E * (c->k + 2) > 65536) return false;
   const int vecs = (c->E + 3) / 4;
   int g = G;
-  while (g > 1 && (g >> 1) * 8 >= vecs && c->T > ROUTE_THREADS_MAX / g) g >>= 1;
+  while (NV == 1 && g > 1 && (g >> 1) * 8 >= vecs && c->T > ROUTE_THREADS_MAX / g) g >>= 1;
   if (c->T > 2 * (ROUTE_THREADS_MAX / g)) return false;
   const int need = (vecs + g - 1) / g;
+  by_piece = g < G;
   G = g;
   NV = need <= 1 ? 1 : (need <= 2 ? 2 : (need <= 4 ? 4 : 8));
   return true;
@@ -285,7 +298,8 @@ extern "C" int symi_route(const symi_ctx* ctx, const float* logits, int32_t* idx
   const int E = cfg->E;
   int G, NV;
   route_fwd_shape(E, cfg->T, G, NV);
-  const bool alone = cfg->T > 0 && route_alone(cfg, G, NV);
+  bool by_piece = false;
+  const bool alone = cfg->T > 0 && route_alone(cfg, G, NV, by_piece);
   if (!alone) launch_fill_i32(ctx, hist, E, 0, st);
   if (cfg->T > 0) {
     int grid = alone ? 1 : route_grid(cfg->T, G);
@@ -296,7 +310,7 @@ extern "C" int symi_route(const symi_ctx* ctx, const float* logits, int32_t* idx
 #define SYMI_ROUTE_CASE(GG, NN)                                                                  \
   case GG * 16 + NN:                                                                             \
     SYMI_TIMED(ctx, K_ROUTE, st, (route_kernel<GG, NN><<<grid, threads, sh, st>>>(          \
-        logits, idx, gate, hist, cfg->T, E, cfg->k, cfg->renorm, alone)));                       \
+        logits, idx, gate, hist, cfg->T, E, cfg->k, cfg->renorm, alone, by_piece)));                       \
     break;
 #define SYMI_ROUTE_G(GG) SYMI_ROUTE_CASE(GG, 1) SYMI_ROUTE_CASE(GG, 2) SYMI_ROUTE_CASE(GG, 4) SYMI_ROUTE_CASE(GG, 8)
     switch (G * 16 + NV) {

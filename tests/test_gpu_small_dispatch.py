@@ -55,3 +55,25 @@ def test_small_route_and_dispatch(T, E, k, S, d, dtype):
         assert (aor.cpu().numpy()[:kept] == np.asarray(o_aor)[:kept]).all()
         assert torch.equal(Xp[:kept], X[(aor[:kept] // k).long()])
         assert (aor[kept:] == -5).all() and (Xp[kept:] == 7.0).all()   # nothing else is written
+
+
+# a token's gates do not depend on how many tokens its batch has: the one workgroup, with one to eight pieces of a row per
+# lane, sums the row's exponentials in the order of the many, which the same rows take with enough rows behind them
+# (and still fewer than the 2^17 lanes where rows get fewer lanes).  Class counts with whole, ragged and single pieces
+@pytest.mark.parametrize("T,E,k", [(300, 1, 1), (1024, 8, 2), (700, 10, 3), (500, 16, 4), (300, 27, 2), (200, 64, 2), (190, 60, 1),
+                                   (64, 128, 6), (60, 250, 2), (50, 256, 3), (21, 300, 4), (10, 1024, 2)])
+@pytest.mark.parametrize("renorm", [0, 1])
+def test_gates_of_a_small_batch(T, E, k, renorm):
+    more = (1 << 16) // (E * (k + 2)) + 1
+    assert T * E * (k + 2) <= 1 << 16 < more * E * (k + 2)
+    assert more * min((E + 3) // 4, 64) < 1 << 17
+    dev = torch.device("cuda")
+    logits = (torch.randn(more, E, generator=torch.Generator().manual_seed(E)) * 3).to(dev)
+    print(f"[gates] T={T} E={E} k={k}", flush=True)
+    got = []
+    for n in (T, more):
+        ctx = symi.symi_create(symi.SymiCfg.make(n, E, k, 8, 8, E, 1, 0, "bf16", renorm))
+        idx, gate = torch.empty(n, k, dtype=torch.int32, device=dev), torch.empty(n, k, device=dev)
+        symi.symi_route(ctx, logits[:n].contiguous(), idx, gate, torch.empty(E, dtype=torch.int32, device=dev))
+        got.append((idx[:T], gate[:T]))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])

@@ -195,11 +195,23 @@ __global__ __launch_bounds__(256) void scatter_rows_kernel(const uint4* __restri
   }
 }
 
-// The whole dispatch of a small batch (A <= SMALL_A assignments, E <= SMALL_E classes) in one launch: every
-// workgroup ranks all assignments (rows in LDS; 16 wavefronts, as in chunk_rank_kernel) and moves its share of the
-// tokens; the first one also writes the tables.  With short kernels the launches are the time: four of them took
-// 11 us of kernel and about 13 us of the 33 us of a forward of 64 tokens.
-constexpr int SMALL_A = 4096, SMALL_E = 512, SMALL_DT = 1024;
+// The whole dispatch of a small batch in one launch: every workgroup ranks all assignments (rows in LDS; 16 wavefronts, as in
+// chunk_rank_kernel) and moves its share of the tokens; the first one also writes the tables.  With short kernels the
+// launches are the time: four of them took 11 us of kernel and about 13 us of the 33 us of a forward of 64 tokens.
+constexpr int SMALL_A = 4096, SMALL_DT = 1024;
+
+// Where one launch beats four.  Every workgroup adds up 16 counts of all E classes per 1024 assignments, so it takes about
+// 4 + E / 40 + 1.4 us per 1024 assignments (k = 1; 2.5 for k = 4) where the four take 11 - 15 whatever E.  Four : one, us
+// a call in a row of calls, d = 128, k = 1 / k = 4:
+//   A        E = 16                 64                     128                    192                    256
+//   256      11.3 : 5.7 / 11.5 : 5.0   11.4 : 7.1 / 11.7 : 6.5   11.7 : 8.9 / 12.2 : 8.2   11.5 : 10.6 / 12.3 : 10.0   11.7 : 12.2 / 12.5 : 11.6
+//   1024     11.8 : 6.0 / 13.0 : 7.1   12.2 : 7.5 / 13.1 : 8.6   12.5 : 9.3 / 13.5 : 10.4  12.7 : 11.1 / 13.9 : 12.2   12.9 : 12.7 / 13.9 : 13.8
+//   2048     11.9 : 7.4 / 12.9 : 8.5   12.3 : 9.1 / 13.2 : 10.2  12.6 : 11.1 / 13.6 : 12.2  12.8 : 13.0 / 13.8 : 14.1   13.0 : 14.6 / 14.0 : 15.8
+//   4096     12.1 : 10.2 / 13.1 : 11.2  12.3 : 12.2 / 13.2 : 13.3  12.6 : 14.4 / 13.5 : 15.6  12.9 : 16.5 / 13.8 : 17.6   13.0 : 18.1 / 14.0 : 19.3
+// and 14.2 : 25.7 / 15.1 : 26.8 at E = 512, A = 4096.  Wider rows favour one launch, down to a load in flight per thread: E = 8,
+// A = 4096 of d = 1024 13.7 : 10.6, of 4096 21.0 : 17.1, of 8192 32.8 : 26.4.  The line is straight from E = 64 at 4096
+// assignments to E = 224 at none.
+static bool dispatch_in_one(int A, int E) { return A > 0 && A <= SMALL_A && 5 * A + 128 * E <= 128 * 224; }
 
 __global__ __launch_bounds__(SMALL_DT) void dispatch_small_kernel(
     const int32_t* __restrict__ cls, int A, int E, int S, const int32_t* __restrict__ hist,
@@ -473,7 +485,7 @@ static int dispatch_impl(const char* who, const symi_ctx* ctx, int slot_cap, con
   const int nblk = cdiv(A, DISPATCH_CHUNK);
   const int vpr = cfg->d * (cfg->dtype == SYMI_BF16 ? 2 : 4) / 16;
   const long long nvec = (long long)cfg->T * vpr;
-  if (A > 0 && A <= SMALL_A && E <= SMALL_E) {
+  if (dispatch_in_one(A, E)) {
     // four 16-byte pieces per thread, at most one workgroup per compute unit
     const int grid = (int)std::min<long long>(ctx->cus, (nvec + 4 * SMALL_DT - 1) / (4 * SMALL_DT));
     const size_t sh = ((size_t)A + (size_t)(5 + SMALL_DT / 64) * E) * sizeof(int32_t);

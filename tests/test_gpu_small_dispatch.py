@@ -1,6 +1,6 @@
 """Route and dispatch of small batches on both sides of the rules that take them to their one-launch forms (route: one
-workgroup up to E (k + 2) T = 2^16 in two passes; dispatch: 4096 assignments, 512 classes), integers and moved rows
-bit for bit against the oracle, dropless and under a capacity factor."""
+workgroup up to E (k + 2) T = 2^16 in two passes; dispatch: from 4096 assignments of 64 classes to none of 224),
+integers and moved rows bit for bit against the oracle, dropless and under a capacity factor."""
 import numpy as np
 import pytest
 import torch
@@ -11,17 +11,25 @@ from oracle import symi_oracle as O
 pytestmark = pytest.mark.gpu
 
 
+def launches(ctx, name):
+    """Launches of one kernel since the last reset, by a context that times them."""
+    kid = [symi.lib().symi_kernel_name(i).decode() for i in range(symi.lib().symi_kernel_count())].index(name)
+    return symi.symi_timing_read(ctx, kid)[1]
+
+
 # one token; one and two passes of the route's workgroup and the first size beyond; assignments around one and four
-# passes of 1024 and the limit of 4096; more than 64 replicas of a class; classes around the limit of 512; rows
-# of one and of an odd number of 16-byte pieces
+# passes of 1024 and the limit of 4096; more than 64 replicas of a class; both sides of the dispatch's line at 64, 128 and
+# 223 classes, and many classes, which take the four launches; rows of one and of an odd number of 16-byte pieces
 @pytest.mark.parametrize("T,E,k,S,d,dtype", [
     (1, 1, 1, 1, 8, "bf16"), (1, 16, 3, 24, 128, "bf16"), (64, 16, 2, 24, 128, "bf16"), (511, 4, 2, 200, 24, "bf16"),
     (512, 2, 2, 150, 8, "f32"), (513, 8, 2, 16, 40, "f32"), (1024, 8, 2, 16, 128, "f32"), (2048, 4, 2, 9, 16, "bf16"),
     (2049, 4, 2, 9, 16, "bf16"), (4096, 3, 1, 7, 8, "bf16"), (4097, 3, 1, 7, 8, "bf16"), (300, 64, 6, 96, 1032, "bf16"),
-    (200, 64, 2, 96, 1024, "bf16"), (21, 512, 4, 600, 16, "bf16"), (21, 513, 4, 600, 16, "bf16"), (256, 512, 16, 512, 8, "bf16")])
+    (200, 64, 2, 96, 1024, "bf16"), (21, 512, 4, 600, 16, "bf16"), (21, 513, 4, 600, 16, "bf16"), (256, 512, 16, 512, 8, "bf16"),
+    (4096, 64, 1, 80, 8, "bf16"), (4096, 65, 1, 80, 8, "bf16"), (819, 128, 3, 130, 8, "bf16"), (1229, 128, 2, 130, 8, "bf16"),
+    (25, 223, 1, 230, 8, "f32"), (26, 223, 1, 230, 8, "f32")])
 def test_small_route_and_dispatch(T, E, k, S, d, dtype):
     cfg = symi.SymiCfg.make(T, E, k, d, 8, S, 1, 0, dtype, 1)
-    ctx = symi.symi_create(cfg)
+    ctx = symi.symi_create(cfg, symi.CTX_TIMING)
     g = torch.Generator().manual_seed(T * 31 + E)
     dev, A = torch.device("cuda"), T * k
     bias = -2.4 * torch.log(torch.arange(1, E + 1, dtype=torch.float32))[torch.randperm(E, generator=g)]
@@ -55,6 +63,8 @@ def test_small_route_and_dispatch(T, E, k, S, d, dtype):
         assert (aor.cpu().numpy()[:kept] == np.asarray(o_aor)[:kept]).all()
         assert torch.equal(Xp[:kept], X[(aor[:kept] // k).long()])
         assert (aor[kept:] == -5).all() and (Xp[kept:] == 7.0).all()   # nothing else is written
+    in_one = A <= 4096 and 5 * A + 128 * E <= 128 * 224
+    assert launches(ctx, "chunk_rank") == (0 if in_one else 3) and launches(ctx, "gather_rows") == 3
 
 
 # a token's gates do not depend on how many tokens its batch has: the one workgroup, with one to eight pieces of a row per

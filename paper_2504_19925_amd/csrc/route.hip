@@ -264,11 +264,14 @@ static void route_fwd_shape(int E, int T, int& G, int& NV) {
 }
 
 // A small batch goes through one workgroup of 1024 threads in at most two passes, which then needs no cleared
-// histogram: a launch less (3 us).  Beyond E (k + 2) T = 2^16 the unit's vector pipes would take longer than that.
+// histogram: a launch less.  Its time grows with E (k + 2) T, as one unit's vector pipes do all of it.  Two launches : one, us a
+// call in a row of calls, at E (k + 2) T = 2^14, 2^15 and 2^16: E = 8, k = 2 6.1 : 4.3, 6.3 : 5.5, 6.4 : 8.8; E = 16, k = 2 6.2 : 4.5, 6.3 : 5.3,
+// 6.2 : 6.9; E = 64, k = 2 6.3 : 4.9, 6.4 : 5.6, 6.3 : 7.6; k = 6 7.5 : 6.8, 7.6 : 7.4, 7.6 : 8.6; E = 128, k = 8 8.9 : 8.4, 9.0 : 9.2, 9.0 : 10.6;
+// E = 256, k = 4 7.2 : 6.1, 7.3 : 7.1, 7.2 : 9.5.  So up to 2^15.
 // Fewer lanes per token than route_fwd_shape gives (by_piece) keep the order of its sums, so that a token's gates do not
 // depend on the size of its batch; E <= 256, where route_fwd_shape has one piece per lane at these sizes.
 static bool route_alone(const symi_cfg* c, int& G, int& NV, bool& by_piece) {
-  if ((long long)c->T * c->E * (c->k + 2) > 65536) return false;
+  if ((long long)c->T * c->E * (c->k + 2) > 32768) return false;
   const int vecs = (c->E + 3) / 4;
   int g = G;
   while (NV == 1 && g > 1 && (g >> 1) * 8 >= vecs && c->T > ROUTE_THREADS_MAX / g) g >>= 1;

@@ -1684,20 +1684,22 @@ static bool few_rows(const symi_cfg* c) {
 }
 
 // bf16 variable-row products that take the 128 x 128 tile: those of few tiles, where the latency of one tile is the
-// time, and those of short reductions, where its epilogue is (two workgroups share a unit and hide theirs
-// behind each other).  Long reductions of many tiles belong to the large tile, which loads half as much per
-// product and slices a nearly empty last round.  Large : small, us per product (events around the launch), S slots
-// of r rows on average; first forward, second forward, hidden gradient, input gradient:
-//   S = 8,   r = 128,  d = 256,  f = 1024    17 : 10    28 : 16    23 : 11    31 : 28
-//   S = 32,  r = 40,   d = 512,  f = 2048    47 : 36    43 : 34    25 : 22    47 : 50 (*)
-//   S = 128, r = 128,  d = 512,  f = 512     71 : 58    43 : 32    51 : 43    65 : 53
-//   S = 128, r = 40,   d = 2048, f = 1408   396 : 379  156 : 151  214 : 221 (*) 279 : 313 (*)
-//   S = 8,   r = 1000, d = 512,  f = 2048    65 : 60 (*) 48 : 35 (*) 62 : 46   63 : 64 (*)
-//   S = 32,  r = 300,  d = 512,  f = 512     30 : 30    21 : 18    29 : 22    29 : 29
-//   S = 20,  r = 100,  d = 2800, f = 560     79 : 52    34 : 31    65 : 41    41 : 42
-//   S = 128, r = 300,  d = 512,  f = 2048   308 : 313 (*) 152 : 161 (*) 231 : 222 (*) 234 : 342 (*)
-//   S = 128, r = 1000, d = 256,  f = 1024   297 : 355 (*) 135 : 125 (*) 246 : 254 (*) 209 : 236 (*)
-// ((*): the rule keeps the large tile).  The host knows the mean number of rows only.
+// time, and those of short reductions with slots of less than a tile, where set-up and epilogue are (two workgroups share a unit
+// and hide theirs behind each other).  Long reductions of many tiles belong to the large tile, which loads half as much per
+// product and slices a nearly empty last round; so do slots of more rows than one small tile has.  Times large / small over
+// 550 drawn shapes (8 - 1024 slots, 20 - 600 rows per slot on average, d 64 - 4096, f 64 - 8192; events around the launch, the
+// sum of the slices included), geometric mean (a tenth lies below / above), with replicas as a batch of the same popularity
+// before would place them (Zipf or drifted), and misplaced: Zipf 2.4 over even replicas, most rows in a few slots.
+//                          first forward      second forward     hidden gradient    input gradient
+//   few tiles              1.23 (1.03/1.47)   1.22 (0.95/1.53)   1.33 (1.02/1.75)   1.31 (1.00/1.57)
+//     misplaced            1.20 (0.92/1.50)   1.23 (0.94/1.56)   1.37 (1.04/1.81)   1.37 (1.10/1.59)
+//   small mean (lines)     1.11 (0.98/1.26)   1.13 (0.97/1.30)   1.13 (0.99/1.31)   1.09 (0.97/1.23)
+//     misplaced            0.95 (0.79/1.10)   0.98 (0.81/1.18)   1.08 (0.91/1.28)   0.99 (0.79/1.23)
+//   next beyond the lines, where r <= 128, K <= 1024 or r <= 96, K <= 2048 (1792):
+//                          0.99 (0.88/1.12)   0.99 (0.89/1.12)   1.00 (0.89/1.13)   0.96 (0.83/1.11)
+//     misplaced            0.92 (0.78/1.07)   0.94 (0.81/1.11)   1.00 (0.88/1.16)   0.93 (0.79/1.08)
+// At 1 - 1.25 times the limit of tiles x K, 64 - 128 rows: 0.97, 1.01, 1.10, 1.02; at half to all of it, more than 128 rows: 0.94, 0.99,
+// 1.06, 1.19, so there it is half as high for the forward products.  The host knows the mean number of rows only.
 static bool mid_tile(const symi_ctx* ctx, int mode) {
   const symi_cfg* const c = &ctx->cfg;
   if (c->dtype != SYMI_BF16 || mode > BWD_DX || ((mode == FWD1 || mode == FWD2) && few_rows(c))) return false;
@@ -1705,9 +1707,11 @@ static bool mid_tile(const symi_ctx* ctx, int mode) {
   if (A / MID_BM + S > 65535) return false;   // its row tiles are a grid.y coordinate
   const int K = mode == FWD1 || mode == BWD_DH ? c->d : mode == FWD2 ? c->f : 2 * c->f;
   const int ntx = mode == FWD1 ? cdiv(c->f, 64) : cdiv(mode == BWD_DH ? c->f : c->d, 128);
-  if (A <= 128 * S && K <= 1024) return true;
-  if (A <= 96 * S && K <= (mode == FWD1 || mode == FWD2 ? 2048 : 1792)) return true;
-  const long long work = std::max(A / MID_BM + S / 2, S) * ntx * K;   // tiles x reduction length
+  // mean rows and reduction length, two lines for each product
+  constexpr int LINES[4][2][2] = {{{64, 1536}, {112, 640}}, {{64, 2048}, {112, 1024}}, {{80, 1792}, {128, 512}}, {{48, 1792}, {96, 640}}};
+  for (const auto& line : LINES[mode])
+    if (A <= line[0] * S && K <= line[1]) return true;
+  const long long work = std::max(A / MID_BM + S / 2, S) * ntx * K * (mode <= FWD2 && A > 128 * S ? 2 : 1);   // tiles x reduction length
   return mode == FWD1 || mode == BWD_DH ? work <= 1 << 19 : work <= 3 << 17 && K <= 2048;
 }
 

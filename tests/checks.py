@@ -4,6 +4,7 @@ import numpy as np
 import torch
 
 import harness as Hn
+import paper_2504_19925_amd as symi
 import workloads as wl
 from harness.metrics import TOL, check_close, relerr_elem, relerr_l2
 from oracle import symi_oracle as O
@@ -200,6 +201,73 @@ class OracleChain:
             out[name + "_l2"] = relerr_l2(got, mine)
             out[name + "_elem"] = relerr_elem(got, mine)
         return out
+
+
+def bf16_tiles(T, E, k, S_tot, d, f, **_):
+    """The dispatch rule of the bf16 variable-row products (the two forward ones, dh, dX), restated: "f" the few-rows
+    tile, "m" the 128 x 128 one, "L" the 256 x 256 one."""
+    A, up = T * k, lambda a, b: -(-a // b)
+    lines = (((64, 1536), (112, 640)), ((64, 2048), (112, 1024)), ((80, 1792), (128, 512)), ((48, 1792), (96, 640)))
+
+    def one(i):
+        if i < 2 and A <= 32 * S_tot:
+            return "f"
+        K, ntx = (d, f, d, 2 * f)[i], (up(f, 64), up(d, 128), up(f, 128), up(d, 128))[i]
+        if any(A <= r * S_tot and K <= n for r, n in lines[i]):
+            return "m"
+        work = max(A // 128 + S_tot // 2, S_tot) * ntx * K * (2 if i < 2 and A > 128 * S_tot else 1)
+        return "m" if (work <= 1 << 19 if i in (0, 2) else work <= 3 << 17 and K <= 2048) else "L"
+
+    return "".join(one(i) for i in range(4))
+
+
+def products_against_binary64(st, rows, first_slot, seed):
+    """The six bf16 expert products for slots of given row counts (class c has the slots first_slot[c] .. first_slot[c+1]),
+    every output against binary64 on the stored inputs of its product.  A stored value is a 32-bit sum rounded to
+    bf16: 2^-8 of itself, and the sum's own error, below 2^-16 of the largest value."""
+    c = st.c
+    d, f = c.d, c.f
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    for t, std in ((st.Xp, 1.0), (st.dYp, 1.0), (st.W1s, d ** -0.5), (st.W2s, f ** -0.5)):
+        t.normal_(0.0, std, generator=g)
+    off = [0]
+    for n in rows:
+        off.append(off[-1] + n)
+    st.slot_offsets.copy_(torch.tensor(off))
+    st.first_slot.copy_(torch.tensor(first_slot))
+    symi.symi_expert_fwd(st.ctx, st.Xp, st.slot_offsets, st.W1s, st.W2s, st.UV, st.H, st.Yp, st.ws)
+    symi.symi_expert_bwd(st.ctx, st.dYp, st.Xp, st.UV, st.H, st.slot_offsets, st.first_slot, st.W1s, st.W2s, st.dXp,
+                         st.dW1, st.dW2, st.ws)
+
+    def near(a, b, rounding=2.0 ** -8):
+        a = a.double()
+        assert bool(((a - b).abs() <= b.abs() * rounding + b.abs().max() * 2.0 ** -16).all()), (q, rows[q])
+
+    def duv_of(s, W2):
+        u, v = st.UV[s, :f].double(), st.UV[s, f:].double()
+        dh, sg = st.dYp[s].double() @ W2, torch.sigmoid(u)
+        return torch.cat([dh * v * sg * (1 + u * (1 - sg)), dh * u * sg], 1)
+
+    for e in range(len(first_slot) - 1):
+        dW1, dW2 = torch.zeros(2 * f, d, dtype=torch.float64, device="cuda"), torch.zeros(d, f, dtype=torch.float64, device="cuda")
+        for q in range(first_slot[e], first_slot[e + 1]):
+            if not rows[q]:
+                continue
+            s = slice(off[q], off[q + 1])
+            W1, W2 = st.W1s[q].double(), st.W2s[q].double()
+            want = st.Xp[s].double() @ W1.T
+            near(st.UV[s], want)
+            near(st.H[s], torch.nn.functional.silu(want[:, :f]) * want[:, f:])
+            near(st.Yp[s], st.H[s].double() @ W2.T)
+            # du, dv live in the workspace: products of them rounded to bf16, whose roundings add up like noise
+            duv = duv_of(s, W2).bfloat16().double()
+            want = duv @ W1
+            assert float((st.dXp[s].double() - want).norm() / want.norm()) < 2 ** -8, (q, rows[q])
+            dW1 += duv.T @ st.Xp[s].double()
+            dW2 += st.dYp[s].double().T @ st.H[s].double()
+        q = first_slot[e]
+        near(st.dW2[e], dW2, 0.0)
+        assert float((st.dW1[e].double() - dW1).norm()) <= 2 ** -8 * float(dW1.norm()), e
 
 
 def stratified_tokens(slot_offsets, assign_of_row, k, T, rng, n_random=48, max_edges=256, tile=256):

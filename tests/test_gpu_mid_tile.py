@@ -1,21 +1,21 @@
 """The 128 x 128 tile of the bf16 variable-row products (few or short tiles) against the oracle's layer: slots of one
 row up to three tiles, both sides of the 64 rows below which half the wavefronts rest, reductions of one to six 64-deep
-steps with and without a ragged end, ragged columns, numbers of column tiles that are and are not multiples of eight,
-and sizes on both sides of the rule that chooses it."""
+steps with and without a ragged end, ragged columns, numbers of column tiles that are and are not multiples of eight; and
+both sides of the rule that chooses it, against binary64."""
 import pytest
 import torch
 
 import paper_2504_19925_amd as symi
 import workloads as wl
 import harness as Hn
-from tests.checks import check_iteration
+from tests.checks import bf16_tiles, check_iteration, products_against_binary64
 
 pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("E,k,S,d,f,T", [(2, 1, 2, 8, 8, 70), (3, 2, 4, 64, 72, 129), (4, 1, 5, 136, 520, 641),
                                          (6, 2, 9, 200, 328, 333), (4, 2, 6, 392, 264, 500), (2, 1, 3, 320, 1032, 385),
-                                         # 128 rows per slot on average and one more, K = 1024 and 1032
+                                         # long reductions; many rows, where the forward and the input gradient take the large tile
                                          (4, 1, 4, 1024, 72, 512), (4, 1, 4, 1024, 72, 513), (4, 1, 4, 1032, 72, 512),
                                          (16, 4, 16, 256, 1024, 4100)])
 def test_layer(E, k, S, d, f, T):
@@ -28,45 +28,39 @@ def test_layer(E, k, S, d, f, T):
 
 
 # given slot offsets: row counts at the tile's edges, empty slots in front, between and behind, more slots than a
-# workgroup has threads; binary64 on the stored inputs of every product.  A stored value is a 32-bit sum rounded to
-# bf16: half of 2^-8 of itself, and the sum's own error, far below 2^-9 of the row's scale
+# workgroup has threads
 @pytest.mark.parametrize("d,f,extra", [(72, 136, 0), (264, 192, 0), (128, 520, 300)])
 def test_tile_edges(d, f, extra):
     rows = [0, 1, 63, 64, 65, 0, 127, 128, 129, 191, 193, 257, 10, 300, 300] + [0] * extra + [5, 0]
     S, T = len(rows), sum(rows)
     c = wl.scaled(wl.get_config("c2"), E=4, k=1, d=d, f=f, T=T, S_tot=S, N=1, iters=1, router_matmul=False)
-    st = Hn.State(c, shard=0)
-    g = torch.Generator(device="cuda").manual_seed(d)
-    for t, std in ((st.Xp, 1.0), (st.dYp, 1.0), (st.W1s, d ** -0.5), (st.W2s, f ** -0.5)):
-        t.normal_(0.0, std, generator=g)
-    st.slot_offsets.copy_(torch.tensor([0] + rows).cumsum(0))
-    st.first_slot.copy_(torch.tensor([0, 3, 7, 9, S]))
     print(f"[mid edges] d={d} f={f} S={S}", flush=True)
-    symi.symi_expert_fwd(st.ctx, st.Xp, st.slot_offsets, st.W1s, st.W2s, st.UV, st.H, st.Yp, st.ws)
-    symi.symi_expert_bwd(st.ctx, st.dYp, st.Xp, st.UV, st.H, st.slot_offsets, st.first_slot, st.W1s, st.W2s, st.dXp,
-                         st.dW1, st.dW2, st.ws)
-    off = [0]
-    for n in rows:
-        off.append(off[-1] + n)
+    products_against_binary64(Hn.State(c, shard=0), rows, [0, 3, 7, 9, S], d)
 
-    def near(a, b):
-        assert bool(((a - b).abs() <= b.abs() * 2 ** -8 + b.abs().max() * 2 ** -9).all())
 
-    for q, n in enumerate(rows):
-        if not n:
-            continue
-        s = slice(off[q], off[q + 1])
-        W1, W2 = st.W1s[q].double(), st.W2s[q].double()
-        uv, h = st.UV[s].double(), st.H[s].double()
-        u, v = uv[:, :f], uv[:, f:]
-        want = st.Xp[s].double() @ W1.T
-        near(uv, want)
-        near(h, torch.nn.functional.silu(want[:, :f]) * want[:, f:])
-        near(st.Yp[s].double(), h @ W2.T)
-        dh = st.dYp[s].double() @ W2
-        sg = torch.sigmoid(u)
-        duv = torch.cat([dh * v * sg * (1 + u * (1 - sg)), dh * u * sg], 1)
-        # du, dv live in the workspace: the input gradient from them rounded to bf16, whose roundings add up like noise
-        want = duv.bfloat16().double() @ W1
-        got = st.dXp[s].double()
-        assert float((got - want).norm() / want.norm()) < 2 ** -8
+# both sides of every line of the rule, in mean rows per slot and in reduction length, and of the limit of tiles x K (at and above
+# 128 rows on average); which tile the four products take.  Rows spread from none to twice the mean
+@pytest.mark.parametrize("S,T,d,f,want", [
+    (16, 1024, 1536, 1360, "mmmL"), (16, 1025, 1536, 1360, "LmmL"), (16, 1024, 1544, 1360, "LmmL"),    # first forward: 64, 1536
+    (32, 3584, 640, 1200, "mmmL"), (32, 3585, 640, 1200, "LmmL"), (32, 3584, 648, 1200, "LmmL"),       # 112, 640
+    (64, 4096, 640, 2048, "mmmL"), (64, 4097, 640, 2048, "mLmL"), (64, 4096, 640, 2056, "mLmL"),       # second forward: 64, 2048
+    (64, 7168, 640, 1024, "mmmL"), (64, 7169, 640, 1024, "LLmL"), (64, 7168, 640, 1032, "mLmL"),       # 112, 1024
+    (16, 1280, 1792, 2056, "LLmL"), (16, 1281, 1792, 2056, "LLLL"), (16, 1280, 1800, 2056, "LLLL"),    # hidden gradient: 80, 1792
+    (32, 4096, 512, 2696, "LLmL"), (32, 4097, 512, 2696, "LLLL"), (32, 4096, 520, 2696, "LLLL"),       # 128, 512
+    (32, 1536, 776, 896, "mmmm"), (32, 1537, 776, 896, "mmmL"), (32, 1536, 776, 904, "mmmL"),          # input gradient: 48, 1792
+    (32, 3072, 1928, 320, "mmmm"), (32, 3073, 1928, 320, "mmmL"), (32, 3072, 1928, 328, "mmmL"),       # 96, 640
+    (8, 1024, 1024, 2688, "mLmL"), (8, 1024, 1024, 2752, "LLmL"),                                      # tiles x K
+    (4, 2048, 512, 1792, "mmmL"), (4, 2048, 512, 1856, "LmmL")])                                       # half of it, 512 rows
+def test_both_sides_of_the_rule(S, T, d, f, want):
+    c = wl.scaled(wl.get_config("c2"), E=2, k=1, d=d, f=f, T=T, S_tot=S, N=1, iters=1, router_matmul=False)
+    assert bf16_tiles(T, 2, 1, S, d, f) == want
+    st = Hn.State(c, shard=0, flags=symi.CTX_TIMING)
+    rows = [0] * S
+    for i in range(T):
+        rows[int(S * (i / T) ** 0.5)] += 1
+    rows[0], rows[-1] = 0, rows[-1] + rows[0]
+    print(f"[mid rule] S={S} T={T} d={d} f={f} {want}", flush=True)
+    products_against_binary64(st, rows, [0, S // 2, S], T + d)
+    # the table of the large tile's rows is written unless neither forward product takes it, and always by the backward
+    kid = [symi.lib().symi_kernel_name(i).decode() for i in range(symi.lib().symi_kernel_count())].index("tile_map")
+    assert symi.symi_timing_read(st.ctx, kid)[1] == 1 + ("L" in want[:2])

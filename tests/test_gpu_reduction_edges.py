@@ -1,20 +1,23 @@
-"""GPU parity of the bf16 expert products where their pipelines can go wrong: reductions of one to
-seven 64-deep steps with and without a partial last step (two stages of one operand, three of the
-other), classes of few rows, and slots on both sides of the half-height tile's 128 rows."""
+"""GPU parity of the bf16 expert products where their pipelines can go wrong: reductions of one to ten
+64-deep steps with and without a partial last step (the large tile: two stages of one operand, three of the
+other; the smaller tiles: two or three of both), classes of few rows, and slots on both sides of the half-height tile's
+128 rows."""
 import pytest
 import torch
 
 import paper_2504_19925_amd as symi
 import workloads as wl
 import harness as Hn
-from tests.checks import check_iteration
+from tests.checks import bf16_tiles, check_iteration, products_against_binary64
 
 pytestmark = pytest.mark.gpu
 
 
+# on the 128 x 128 tile; the weight gradients, here and below, on the large one
 @pytest.mark.parametrize("d,f,T", [(8, 8, 40), (64, 56, 90), (72, 64, 128), (120, 136, 129), (128, 192, 250),
                                    (192, 200, 258), (256, 248, 380), (264, 320, 390), (328, 384, 515), (448, 440, 700)])
 def test_steps_of_the_reduction(d, f, T):
+    assert bf16_tiles(T, 3, 2, 4, d, f) == ("mmmm" if T > 64 else "ffmm")
     c = wl.scaled(wl.get_config("c2"), dtype="bf16", E=3, k=2, d=d, f=f, T=T, S_tot=4, N=1, iters=1,
                   router_matmul=False, seed=d + T)
     st = Hn.State(c, shard=0)
@@ -118,3 +121,42 @@ def test_nothing_beyond_the_reduction(d, f, rows):
         assert torch.isfinite(a).all()
         assert torch.equal(a[0], b[0]) and torch.equal(a[2], b[2])
         assert torch.isnan(b[1]).all() and torch.isnan(b[3]).all()
+
+
+# The same on the large tile, which takes short reductions only with many rows and wide outputs: one to ten steps of the first
+# forward product and the hidden gradient (d), then of the second forward product (f) and the input gradient (2 f).
+# Slots of every height around 64, 128 and 256 rows, and empty ones; the rest of the rows in the last five.  All four products
+# on the large tile, every output against binary64; then NaN in every second slot's operands, which must stay there
+@pytest.mark.parametrize("d,f,T", [(40, 8200, 27000), (64, 4104, 33000), (72, 4104, 29000), (128, 2056, 32000), (136, 2056, 30000),
+                                   (200, 1544, 27000), (256, 1544, 22000), (264, 1544, 22000), (328, 1032, 24000),
+                                   (400, 1032, 20000), (456, 1032, 18000), (512, 1032, 17000), (520, 1032, 17000), (584, 1032, 15000),
+                                   (8200, 40, 21000), (4104, 64, 26000), (4104, 72, 24000), (2056, 136, 24000), (1544, 200, 29000),
+                                   (1544, 256, 23000), (1032, 328, 27000), (1032, 520, 17000)])
+def test_steps_of_the_large_tile(d, f, T):
+    rows = [0, 1, 63, 64, 65, 127, 128, 129, 0, 191, 255, 256, 257, 0, 511, 513]
+    left = T - sum(rows)
+    rows += [left // 5 + i - 2 for i in range(5)]
+    rows[-1] += T - sum(rows)
+    S = len(rows)
+    assert bf16_tiles(T, S, 1, S, d, f) == "LLLL"
+    c = wl.scaled(wl.get_config("c2"), E=S, k=1, d=d, f=f, T=T, S_tot=S, N=1, iters=1, router_matmul=False)
+    st = Hn.State(c, shard=0)
+    print(f"[large tile] d={d} f={f} T={T}", flush=True)
+    products_against_binary64(st, rows, list(range(S + 1)), d + f)
+    if min(d, f) % 64 == 0 and min(d, f) > 64:
+        return
+    outs = (st.UV, st.H, st.Yp, st.dXp)
+    clean, grads = [t.clone() for t in outs], [st.dW1.clone(), st.dW2.clone()]
+    off = torch.tensor([0] + rows).cumsum(0).tolist()
+    for q in range(1, S, 2):
+        for t in (st.Xp[off[q]:off[q + 1]], st.dYp[off[q]:off[q + 1]], st.W1s[q], st.W2s[q]):
+            t.fill_(float("nan"))
+    symi.symi_expert_fwd(st.ctx, st.Xp, st.slot_offsets, st.W1s, st.W2s, st.UV, st.H, st.Yp, st.ws)
+    symi.symi_expert_bwd(st.ctx, st.dYp, st.Xp, st.UV, st.H, st.slot_offsets, st.first_slot, st.W1s, st.W2s, st.dXp,
+                         st.dW1, st.dW2, st.ws)
+    for q in range(S):
+        for a, b in zip(clean, outs):
+            a, b = a[off[q]:off[q + 1]], b[off[q]:off[q + 1]]
+            assert torch.isnan(b).all() if q & 1 else torch.equal(a, b), q
+        for a, b in zip(grads, (st.dW1[q], st.dW2[q])):
+            assert torch.isnan(b).all() if q & 1 and rows[q] else torch.equal(a[q], b), q

@@ -11,7 +11,7 @@ import workloads as wl
 from oracle import symi_oracle as O
 import harness as Hn
 from harness.metrics import TOL, check_close, relerr_elem
-from tests.checks import OracleChain, check_iteration, small as _small
+from tests.checks import OracleChain, bf16_tiles, check_iteration, small as _small
 
 pytestmark = pytest.mark.gpu
 
@@ -138,11 +138,20 @@ def test_place_device_matches_oracle_on_random_popularities():
         assert first.cpu().tolist() == of.tolist()
 
 
+def _two_stream_config():
+    """c2's recipe at a size where the expert backward takes its helper stream: T*k*d*f from 3.5e8 on, and fewer than
+    eight rounds of 256 x 256 tiles."""
+    c = wl.scaled(_small("c2"), T=2000)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert c.A * c.d * c.f >= 3.5e8 and (c.A // 256 + c.S_tot) * -(-c.d // 256) < 8 * cus
+    return c
+
+
 def test_backward_on_two_streams_equals_backward_on_one():
     """symi_expert_bwd may run its two chains of products on two streams (small batches); the
     results are the same bits as with every kernel on the caller's stream (a context created
     with SYMI_CTX_NO_OVERLAP), also when the caller's stream is not the default one."""
-    c = _small("c2")
+    c = _two_stream_config()
     weights = wl.make_class_weights(c, "cuda")
     X, logits, dY = Hn.draw_inputs(c, 0)
     outs = []
@@ -184,7 +193,7 @@ def test_forward_backward_under_graph_capture():
     """The calls can be captured into a HIP graph (including the helper-stream fork/join of the
     backward): every replay, with eager work and synchronisations in between, reproduces the
     eager results bit for bit."""
-    c = _small("c2")
+    c = _two_stream_config()
     st = Hn.State(c)
     X, logits, dY = Hn.draw_inputs(c, 0)
     st.place_current()
@@ -222,7 +231,7 @@ def test_whole_steps_replayed_from_graphs_equal_eager_steps():
     """Layer, backward, placement and optimizer of consecutive iterations captured as one HIP
     graph per distinct step (inputs of period 2, placement buffers of period 2) and replayed:
     the optimizer state and the slots end up bit for bit where eager launches put them."""
-    c = _small("c2")
+    c = _two_stream_config()
     weights = wl.make_class_weights(c, "cuda")
     inputs = [Hn.draw_inputs(c, it) for it in range(2)]
     adam, _ = Hn.make_adam(step=2)
@@ -309,9 +318,10 @@ def test_tiles_dealt_out_in_xcd_blocks(shape):
     W1 gradient's 64 tiles per class are dealt out too.  With 3 and 5 column tiles the rounds are
     8 m-tiles, one per XCD.  Every output element by element against the oracle."""
     kw = {"4_column_tiles": dict(d=1024, f=512, T=8192), "8_column_tiles": dict(d=2048, f=1024, T=4700),
-          "3_and_5_column_tiles": dict(d=768, f=640, T=2100)}[shape]
+          "3_and_5_column_tiles": dict(d=768, f=640, T=8400)}[shape]
     c = wl.scaled(wl.get_config("c2"), E=8, S_tot=16, N=4, iters=1, **kw)
     print(f"[xcd blocks] {c}", flush=True)
+    assert bf16_tiles(c.T, c.E, c.k, c.S_tot, c.d, c.f) == "LLLL"
     st = Hn.State(c, shard=1)
     X, logits, dY = Hn.draw_inputs(c, 0)
     check_iteration(st, X, logits, dY)

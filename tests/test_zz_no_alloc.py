@@ -1,6 +1,7 @@
 """symi_dispatch_noalloc (scratch in a static device buffer, nothing allocated) against
 symi_dispatch (scratch in the caller's workspace): same bits, on two calls in a row that share
-the one buffer, the second with a smaller input; limits refused with an error."""
+the one buffer, the second with a smaller input, and with one so small that it takes a single launch and no scratch;
+limits refused with an error."""
 import pytest
 import torch
 
@@ -40,8 +41,9 @@ def _both(c, it):
 
 def test_noalloc_dispatch_equals_dispatch_on_consecutive_calls():
     big = wl.scaled(wl.get_config("c4"), d=256, f=64, T=9000)          # 54 000 assignments, 53 chunks
-    small = wl.scaled(wl.get_config("c2"), d=64, f=64, T=700, E=16, S_tot=24)   # then a smaller one
-    for c in (big, small, wl.scaled(wl.get_config("c1"), T=300), big):
+    smaller = wl.scaled(wl.get_config("c2"), d=64, f=64, T=2600, E=16, S_tot=24)   # then 5200, 6 chunks of the same scratch
+    small = wl.scaled(wl.get_config("c2"), d=64, f=64, T=700, E=16, S_tot=24)      # and 1400, which need none
+    for c in (big, smaller, small, wl.scaled(wl.get_config("c1"), T=300), big):
         print(f"[noalloc] {c.name} T={c.T} E={c.E} k={c.k} d={c.d} {c.dtype}", flush=True)
         _both(c, 0)
 

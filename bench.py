@@ -46,6 +46,7 @@ def kernel_work(c, w, nonempty_slots, grad_classes):
         "chunk_scan": (0, 8 * nblk * E),
         "chunk_rank": (0, 12 * A + 4 * nblk * E),
         "gather_rows": (0, T * d * w + A * d * w + 4 * A),
+        "dispatch_one": (0, T * d * w + A * d * w + 12 * A + 12 * E + 4 * S),
         "gemm_fwd1": (2 * A * d * 2 * f, Sn * 2 * f * d * w + A * d * w + A * 3 * f * w),
         "gemm_fwd2": (2 * A * f * d, Sn * d * f * w + A * f * w + A * d * w),
         "gemm_bwd_dh": (2 * A * d * f, Sn * d * f * w + A * d * w + 4 * A * f * w),
@@ -450,7 +451,7 @@ def summary(out):
     if gemm:
         s["gemm_TFLOP/s"] = gemm
         s["gemm_frac_of_peak_min_max"] = [round(min(gemm.values()) / peak, 4), round(max(gemm.values()) / peak, 4)]
-    for n in ("gather_rows", "combine", "dispatch_bwd", "route"):
+    for n in ("gather_rows", "dispatch_one", "combine", "dispatch_bwd", "route"):
         if n in ks and "GB/s" in ks[n]:
             s[n + "_GB/s"] = ks[n]["GB/s"]
     return s

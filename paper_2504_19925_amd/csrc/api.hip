@@ -102,7 +102,8 @@ static const char* const g_names[K_COUNT] = {
     "fill_i32", "route", "route_bwd", "place", "chunk_count", "chunk_scan", "chunk_rank",
     "gather_rows", "tile_map", "gemm_fwd1", "gemm_fwd2", "gemm_bwd_dh", "gemm_bwd_dx",
     "gemm_wgrad2", "gemm_wgrad1", "combine", "combine_bwd", "dispatch_bwd", "adam_to_replicas",
-    "replica_allreduce", "router_fwd", "router_dx", "router_dw", "slice_sum"};
+    "replica_allreduce", "router_fwd", "router_dx", "router_dw", "slice_sum",
+    "dispatch_one"};
 
 void timing_begin(const symi_ctx* ctx, int kid, hipStream_t st) {
   hipEvent_t e;

@@ -17,7 +17,8 @@ int check_cfg(const symi_cfg* cfg, const char* who);
 enum KernelId {
   K_FILL = 0, K_ROUTE, K_ROUTE_BWD, K_PLACE, K_CHUNK_COUNT, K_CHUNK_SCAN, K_CHUNK_RANK, K_GATHER,
   K_TILE_MAP, K_GEMM_FWD1, K_GEMM_FWD2, K_GEMM_BWD_DH, K_GEMM_BWD_DX, K_GEMM_WGRAD2, K_GEMM_WGRAD1,
-  K_COMBINE, K_COMBINE_BWD, K_DISPATCH_BWD, K_ADAM, K_REPLICA_AR, K_ROUTER_FWD, K_ROUTER_DX, K_ROUTER_DW, K_SLICE_SUM, K_COUNT
+  K_COMBINE, K_COMBINE_BWD, K_DISPATCH_BWD, K_ADAM, K_REPLICA_AR, K_ROUTER_FWD, K_ROUTER_DX, K_ROUTER_DW, K_SLICE_SUM,
+  K_DISPATCH_ONE, K_COUNT
 };
 struct TimedLaunch { int kid; hipEvent_t a, b; };
 
@@ -73,7 +74,7 @@ struct WsLayout {
   size_t class_order;  // expert bwd: classes by decreasing row count
   size_t duv;          // expert bwd: dUV [A,2f] in the activation dtype
   size_t split_part;   // expert fwd/bwd: partial tiles of sliced reductions, see gemm.hip
-  size_t router_partial;  // router bwd (bf16): partial weight gradients [chunks,E,d] f32
+  size_t router_partial;  // router bwd: partial weight gradients [chunks,E,d] f32
   size_t router_bias_partial;  // router bwd: partial bias gradients [chunks,E] f32
   size_t total;
 };

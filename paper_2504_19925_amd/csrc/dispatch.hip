@@ -489,7 +489,7 @@ static int dispatch_impl(const char* who, const symi_ctx* ctx, int slot_cap, con
     // four 16-byte pieces per thread, at most one workgroup per compute unit
     const int grid = (int)std::min<long long>(ctx->cus, (nvec + 4 * SMALL_DT - 1) / (4 * SMALL_DT));
     const size_t sh = ((size_t)A + (size_t)(5 + SMALL_DT / 64) * E) * sizeof(int32_t);
-    SYMI_TIMED(ctx, K_GATHER, st, (dispatch_small_kernel<<<grid, SMALL_DT, sh, st>>>(
+    SYMI_TIMED(ctx, K_DISPATCH_ONE, st, (dispatch_small_kernel<<<grid, SMALL_DT, sh, st>>>(
         idx, A, E, cfg->S_tot, hist, counts, first_slot, slot_cap, static_cast<const uint4*>(X), static_cast<uint4*>(Xp),
         row_of_assign, assign_of_row, slot_offsets, cfg->k, nvec, vpr)));
     SYMI_LAUNCH_CHECK(who);

@@ -333,9 +333,11 @@ __global__ __launch_bounds__(SMALL_DT) void dispatch_small_kernel(
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// 16 bytes of a row.  ONCE: a row that the kernel reads once is loaded past the caches' replacement order, as kept like any
-// other line it pushes out what is used again.  us, plain : once, mean of three runs in turn: combine c5 944 : 915, c4 184 : 171,
-// dispatch backward c5 974 : 917, c4 225 : 185, c2 18 : 15.  Nothing on combine_bwd (1867 : 1882); the row scatter's
+// 16 bytes of a row.  ONCE: a row that nobody reads again is loaded past the caches' replacement order, as kept like any
+// other line it pushes out what is used again.  The dispatch's backward loads so, as its rows end there; inside a step, us,
+// plain : once (means of three runs in turn, which differ by 1 - 2 %): c2 20.6 : 14.7, c3 93 : 74, c4 204 : 189, c5 1018 : 1009; 134 MB
+// of rows (T = 8192, k = 8, d = 1024) 38 : 34, 67 MB 15 : 18.  The combine's rows are read by its backward next, which finds them
+// in the caches as long as they fit: combine_once below.  Nothing on combine_bwd (1867 : 1882); the row scatter's
 // stores lose by it (942 : 997, 168 : 195).
 template <bool BF16, bool ONCE = false>
 __device__ __forceinline__ void load_piece(const void* p, long long piece, float (&out)[8]) {
@@ -368,7 +370,7 @@ __device__ __forceinline__ void store_piece(void* p, long long piece, const floa
 }
 
 // out[t] = sum_j w[t,j] * src[row_of_assign[t*k+j]]   (w == nullptr: plain sum)
-template <bool BF16>
+template <bool BF16, bool ONCE>
 __global__ __launch_bounds__(256) void combine_kernel(const void* __restrict__ src,
                                                       const int32_t* __restrict__ roa,
                                                       const float* __restrict__ w,
@@ -386,7 +388,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const void* __restrict__ s
       if (row < 0) continue;   // dropped by the capacity rule: contributes nothing
       const float g = w ? w[t * k + j] : 1.f;
       float x[8];
-      load_piece<BF16, true>(src, row * pieces_per_row + c, x);
+      load_piece<BF16, ONCE>(src, row * pieces_per_row + c, x);
 #pragma unroll
       for (int q = 0; q < PW; ++q) acc[q] = fmaf(g, x[q], acc[q]);
     }
@@ -457,6 +459,16 @@ int static_scratch_address(int device, void** out) {
   }
   *out = addr[device];
   return SYMI_OK;
+}
+
+// The combine loads its rows past the caches' replacement order only where they are more than twice the 256 MB memory-side
+// cache.  Its backward reads them next, and what the combine gains elsewhere is lost there.  Inside a step, us, plain : once,
+// combine and combine_bwd: rows of 1 MB 6.3 : 6.2 and 6.8 : 7.6, 17 MB (k = 8) 9.6 : 9.7 and 15.1 : 20.4, 34 MB (c2) 13.5 : 14.1 and
+// 21.3 : 20.8, 67 MB (k = 8) 15.1 : 15.7 and 27.5 : 31.8, (k = 2, d = 4096) 22.4 : 23.1 and 33.7 : 37.1, 134 MB (k = 2) 41 : 44 and 63 : 68,
+// 268 MB (k = 2) 79 : 75 and 129 : 130, (k = 8) 64 : 70 and 123 : 120, (c3) 71.5 : 70.8 and 132 : 135, 805 MB (c4) 193 : 178 and 360 : 360,
+// 4.3 GB (c5) 974 : 958 and 1887 : 1890.
+static bool combine_once(const symi_cfg* c) {
+  return (long long)c->T * c->k * c->d * (c->dtype == SYMI_BF16 ? 2 : 4) > 512LL << 20;
 }
 
 static int grid_for(long long work_items, int per_block) {
@@ -570,11 +582,11 @@ extern "C" int symi_dispatch_bwd(const symi_ctx* ctx, const void* dXp, const int
   hipStream_t st = as_stream(stream);
   if (cfg->dtype == SYMI_BF16) {
     const int ppr = cfg->d / 8;
-    SYMI_TIMED(ctx, K_DISPATCH_BWD, st, (combine_kernel<true><<<grid_for((long long)cfg->T * ppr, 256), 256, 0, st>>>(
+    SYMI_TIMED(ctx, K_DISPATCH_BWD, st, (combine_kernel<true, true><<<grid_for((long long)cfg->T * ppr, 256), 256, 0, st>>>(
         dXp, row_of_assign, nullptr, dX, cfg->T, cfg->k, ppr)));
   } else {
     const int ppr = cfg->d / 4;
-    SYMI_TIMED(ctx, K_DISPATCH_BWD, st, (combine_kernel<false><<<grid_for((long long)cfg->T * ppr, 256), 256, 0, st>>>(
+    SYMI_TIMED(ctx, K_DISPATCH_BWD, st, (combine_kernel<false, true><<<grid_for((long long)cfg->T * ppr, 256), 256, 0, st>>>(
         dXp, row_of_assign, nullptr, dX, cfg->T, cfg->k, ppr)));
   }
   SYMI_LAUNCH_CHECK("symi_dispatch_bwd");
@@ -587,15 +599,12 @@ extern "C" int symi_combine(const symi_ctx* ctx, const void* Yp, const int32_t* 
   if (cfg->T == 0) return SYMI_OK;
   SYMI_REQUIRE(Yp && row_of_assign && gate && Y, "symi_combine", "NULL pointer");
   hipStream_t st = as_stream(stream);
-  if (cfg->dtype == SYMI_BF16) {
-    const int ppr = cfg->d / 8;
-    SYMI_TIMED(ctx, K_COMBINE, st, (combine_kernel<true><<<grid_for((long long)cfg->T * ppr, 256), 256, 0, st>>>(
-        Yp, row_of_assign, gate, Y, cfg->T, cfg->k, ppr)));
-  } else {
-    const int ppr = cfg->d / 4;
-    SYMI_TIMED(ctx, K_COMBINE, st, (combine_kernel<false><<<grid_for((long long)cfg->T * ppr, 256), 256, 0, st>>>(
-        Yp, row_of_assign, gate, Y, cfg->T, cfg->k, ppr)));
-  }
+  const bool bf16 = cfg->dtype == SYMI_BF16, once = combine_once(cfg);
+  const int ppr = cfg->d / (bf16 ? 8 : 4);
+  const auto kernel = bf16 ? (once ? combine_kernel<true, true> : combine_kernel<true, false>)
+                           : (once ? combine_kernel<false, true> : combine_kernel<false, false>);
+  SYMI_TIMED(ctx, K_COMBINE, st, (kernel<<<grid_for((long long)cfg->T * ppr, 256), 256, 0, st>>>(
+      Yp, row_of_assign, gate, Y, cfg->T, cfg->k, ppr)));
   SYMI_LAUNCH_CHECK("symi_combine");
   return SYMI_OK;
 }

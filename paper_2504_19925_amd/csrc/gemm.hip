@@ -1840,8 +1840,8 @@ extern "C" int symi_expert_fwd(const symi_ctx* ctx, const void* Xp, const int32_
 // (config c2: 296 tiles of the dXp product are two rounds, the second one 84 % empty) and
 // the store-bound zero tiles of the weight gradients never meet the MFMA-bound tiles.  The
 // second chain is therefore enqueued on the context's helper stream (created by symi_create
-// when the flags allow it and the dXp product has fewer than 8 rounds of tiles; default
-// priority, non-blocking), forked from and joined back into the caller's stream with events,
+// when the flags allow it, T*k*d*f is at least 3.5e8 and the dXp product has fewer than 8 rounds of
+// tiles; default priority, non-blocking), forked from and joined back into the caller's stream with events,
 // so workgroups of both chains share the chip.  Otherwise everything stays on the caller's
 // stream, in order.
 
@@ -1876,7 +1876,8 @@ static int expert_bwd_impl(const char* who, const symi_ctx* ctx, const void* dYp
   p.f = cfg->f;
   SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<<<1, 256, 0, st>>>(slot_offsets, first_slot, cfg->S_tot, cfg->E, map, order)));
   // worth it only while a product is a few rounds of workgroups: with many rounds the chip is
-  // full anyway and two kernels sharing it only disturb each other's L2 locality (symi_create
+  // full anyway and two kernels sharing it only disturb each other's L2 locality; and not for the
+  // smallest, where fork, hand-over and join take longer than what they hide (symi_create
   // decides; the context then holds the helper stream)
   const bool side = ctx->side != nullptr && A > 0;
   hipStream_t sw = st;   // stream of the weight-gradient chain
@@ -1955,7 +1956,9 @@ extern "C" int symi_expert_bwd_slots(const symi_ctx* ctx, const void* dYp, const
 // The intra-rank part of the paper's all-reduce (Sec. 4.1): for every class the first of its
 // slots is the representative; the other slots add their gradient to it (slot order), the
 // sum is scaled and copied back to all of them.  16 bytes per lane, one class per blockIdx.y.  Every gradient is read
-// once, past the caches' replacement order: 1000 -> 948 us (128 slots of d = 2048, f = 1408), 1104 -> 1006 (32 of d = 1128, f = 6376).
+// once, past the caches' replacement order.  Behind the products that wrote them, us, plain : so (three runs in turn): 728 : 635 (32 slots of
+// d = 1128, f = 6376), 202 : 162 (64 of d = f = 1024), 725 : 705 (96 of 1024, 4096), 735 : 719 (12 of 4096, 4096), 29 : 29 (24 of 512, 1024),
+// 1621 : 1636 (128 of 2048, 1408, every class twice).
 namespace symi {
 __global__ __launch_bounds__(256) void replica_allreduce_kernel(float4* __restrict__ g,
                                                                 const int32_t* __restrict__ first_slot,

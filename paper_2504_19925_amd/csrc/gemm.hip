@@ -1691,13 +1691,13 @@ static bool few_rows(const symi_cfg* c) {
 // sum of the slices included), geometric mean (a tenth lies below / above), with replicas as a batch of the same popularity
 // before would place them (Zipf or drifted), and misplaced: Zipf 2.4 over even replicas, most rows in a few slots.
 //                          first forward      second forward     hidden gradient    input gradient
-//   few tiles              1.23 (1.03/1.47)   1.22 (0.95/1.53)   1.33 (1.02/1.75)   1.31 (1.00/1.57)
-//     misplaced            1.20 (0.92/1.50)   1.23 (0.94/1.56)   1.37 (1.04/1.81)   1.37 (1.10/1.59)
-//   small mean (lines)     1.11 (0.98/1.26)   1.13 (0.97/1.30)   1.13 (0.99/1.31)   1.09 (0.97/1.23)
-//     misplaced            0.95 (0.79/1.10)   0.98 (0.81/1.18)   1.08 (0.91/1.28)   0.99 (0.79/1.23)
+//   few tiles              1.23 (1.03/1.47)   1.22 (0.95/1.53)   1.31 (0.99/1.74)   1.30 (1.00/1.57)
+//     misplaced            1.20 (0.92/1.50)   1.23 (0.94/1.56)   1.35 (1.03/1.81)   1.36 (1.04/1.59)
+//   small mean (lines)     1.11 (0.98/1.26)   1.13 (0.97/1.30)   1.14 (1.01/1.31)   1.09 (0.97/1.23)
+//     misplaced            0.95 (0.79/1.10)   0.98 (0.81/1.18)   1.09 (0.93/1.29)   0.99 (0.80/1.23)
 //   next beyond the lines, where r <= 128, K <= 1024 or r <= 96, K <= 2048 (1792):
-//                          0.99 (0.88/1.12)   0.99 (0.89/1.12)   1.00 (0.89/1.13)   0.96 (0.83/1.11)
-//     misplaced            0.92 (0.78/1.07)   0.94 (0.81/1.11)   1.00 (0.88/1.16)   0.93 (0.79/1.08)
+//                          0.98 (0.88/1.12)   0.99 (0.89/1.12)   0.99 (0.86/1.10)   0.96 (0.83/1.10)
+//     misplaced            0.91 (0.78/1.07)   0.94 (0.81/1.11)   0.97 (0.81/1.12)   0.92 (0.78/1.08)
 // At 1 - 1.25 times the limit of tiles x K, 64 - 128 rows: 0.97, 1.01, 1.10, 1.02; at half to all of it, more than 128 rows: 0.94, 0.99,
 // 1.06, 1.19, so there it is half as high for the forward products.  The host knows the mean number of rows only.
 static bool mid_tile(const symi_ctx* ctx, int mode) {
@@ -1707,8 +1707,8 @@ static bool mid_tile(const symi_ctx* ctx, int mode) {
   if (A / MID_BM + S > 65535) return false;   // its row tiles are a grid.y coordinate
   const int K = mode == FWD1 || mode == BWD_DH ? c->d : mode == FWD2 ? c->f : 2 * c->f;
   const int ntx = mode == FWD1 ? cdiv(c->f, 64) : cdiv(mode == BWD_DH ? c->f : c->d, 128);
-  // mean rows and reduction length, two lines for each product
-  constexpr int LINES[4][2][2] = {{{64, 1536}, {112, 640}}, {{64, 2048}, {112, 1024}}, {{80, 1792}, {128, 512}}, {{48, 1792}, {96, 640}}};
+  // mean rows and reduction length, up to three lines for each product
+  constexpr int LINES[4][3][2] = {{{64, 1536}, {112, 640}}, {{64, 2048}, {112, 1024}}, {{40, 1792}, {80, 1536}, {128, 512}}, {{48, 1536}, {96, 640}}};
   for (const auto& line : LINES[mode])
     if (A <= line[0] * S && K <= line[1]) return true;
   const long long work = std::max(A / MID_BM + S / 2, S) * ntx * K * (mode <= FWD2 && A > 128 * S ? 2 : 1);   // tiles x reduction length

@@ -207,7 +207,8 @@ def bf16_tiles(T, E, k, S_tot, d, f, **_):
     """The dispatch rule of the bf16 variable-row products (the two forward ones, dh, dX), restated: "f" the few-rows
     tile, "m" the 128 x 128 one, "L" the 256 x 256 one."""
     A, up = T * k, lambda a, b: -(-a // b)
-    lines = (((64, 1536), (112, 640)), ((64, 2048), (112, 1024)), ((80, 1792), (128, 512)), ((48, 1792), (96, 640)))
+    lines = (((64, 1536), (112, 640)), ((64, 2048), (112, 1024)), ((40, 1792), (80, 1536), (128, 512)),
+             ((48, 1536), (96, 640)))
 
     def one(i):
         if i < 2 and A <= 32 * S_tot:

@@ -45,9 +45,10 @@ def test_tile_edges(d, f, extra):
     (32, 3584, 640, 1200, "mmmL"), (32, 3585, 640, 1200, "LmmL"), (32, 3584, 648, 1200, "LmmL"),       # 112, 640
     (64, 4096, 640, 2048, "mmmL"), (64, 4097, 640, 2048, "mLmL"), (64, 4096, 640, 2056, "mLmL"),       # second forward: 64, 2048
     (64, 7168, 640, 1024, "mmmL"), (64, 7169, 640, 1024, "LLmL"), (64, 7168, 640, 1032, "mLmL"),       # 112, 1024
-    (16, 1280, 1792, 2056, "LLmL"), (16, 1281, 1792, 2056, "LLLL"), (16, 1280, 1800, 2056, "LLLL"),    # hidden gradient: 80, 1792
+    (16, 640, 1792, 2320, "LLmL"), (16, 641, 1792, 2320, "LLLL"), (16, 640, 1800, 2320, "LLLL"),       # hidden gradient: 40, 1792
+    (16, 1280, 1536, 2320, "LLmL"), (16, 1281, 1536, 2320, "LLLL"), (16, 1280, 1544, 2320, "LLLL"),    # 80, 1536
     (32, 4096, 512, 2696, "LLmL"), (32, 4097, 512, 2696, "LLLL"), (32, 4096, 520, 2696, "LLLL"),       # 128, 512
-    (32, 1536, 776, 896, "mmmm"), (32, 1537, 776, 896, "mmmL"), (32, 1536, 776, 904, "mmmL"),          # input gradient: 48, 1792
+    (32, 1536, 1032, 768, "mmmm"), (32, 1537, 1032, 768, "mmmL"), (32, 1536, 1032, 776, "mmmL"),       # input gradient: 48, 1536
     (32, 3072, 1928, 320, "mmmm"), (32, 3073, 1928, 320, "mmmL"), (32, 3072, 1928, 328, "mmmL"),       # 96, 640
     (8, 1024, 1024, 2688, "mLmL"), (8, 1024, 1024, 2752, "LLmL"),                                      # tiles x K
     (4, 2048, 512, 1792, "mmmL"), (4, 2048, 512, 1856, "LmmL")])                                       # half of it, 512 rows

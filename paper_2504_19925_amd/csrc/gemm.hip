@@ -65,13 +65,17 @@ __device__ __forceinline__ float sigmoid_fast(float u) {
 }
 
 // ---------------------------------------------------------------- m-tile table
-// map[0] = number of m-tiles, map[4 + 4i ..] = {first row, end row, slot} of m-tile i (256 rows).
+// map[0] = number of m-tiles, map[4 + 4i ..] = {first row, end row, slot} of m-tile i (TM = 256 rows), or
+// map[4 + 2i ..] = {first row, slot + 2^16 * (rows - 1)} (TM = FEW_BM: the small-batch forward products; at most
+// 32 rows per slot on average make at most 1.5 S_tot of them, which fit where 256-row tiles would be).
 // order[c] = the class with the c-th largest number of rows (ties: lower index first).
+constexpr int FEW_BM = 64;
+
+template <int TM>
 __global__ __launch_bounds__(256) void tile_map_kernel(const int32_t* __restrict__ slot_offsets,
                                                        const int32_t* __restrict__ first_slot, int S,
                                                        int E, int32_t* __restrict__ map,
                                                        int32_t* __restrict__ order) {
-  constexpr int TM = GEMM_BM;
   __shared__ int32_t part[256];
   __shared__ int32_t rows[1024];
   const int tid = threadIdx.x;
@@ -95,10 +99,15 @@ __global__ __launch_bounds__(256) void tile_map_kernel(const int32_t* __restrict
   for (int q = q0; q < q1; ++q) {
     const int b = slot_offsets[q], e = slot_offsets[q + 1];
     for (int r = b; r < e; r += TM, ++t) {
-      map[4 + 4 * t + 0] = r;
-      map[4 + 4 * t + 1] = min(e, r + TM);
-      map[4 + 4 * t + 2] = q;
-      map[4 + 4 * t + 3] = 0;
+      if (TM == FEW_BM) {
+        map[4 + 2 * t + 0] = r;
+        map[4 + 2 * t + 1] = q + ((min(e - r, TM) - 1) << 16);
+      } else {
+        map[4 + 4 * t + 0] = r;
+        map[4 + 4 * t + 1] = min(e, r + TM);
+        map[4 + 4 * t + 2] = q;
+        map[4 + 4 * t + 3] = 0;
+      }
     }
   }
   if (first_slot) {
@@ -837,18 +846,30 @@ __global__ __launch_bounds__(GT) void gemm_bf16_kernel(GemmParams p) {
 // second ones, each part fetched them anew: 4096 rows in 32 of 128 slots of d = 2048, f = 1408 287 us, now 209;
 // and most of the workgroups had nothing to do: 2 rows in each of 96 slots of d = 1024, f = 4096 518 -> 513.
 // Operand layout, fragments and epilogue are those of the large tile.
-constexpr int FEW_BM = 64;
-
 struct SlotTile { int row0, row1, slot, bx; };
 
-// Slot q holds ceil(rows / TM) row tiles: every workgroup counts them for itself from the slot offsets, which takes
-// no longer than the two dependent reads of a table and saves the launch that wrote it.  A thread counts consecutive
-// slots; the one whose slots hold the workgroup's row tile finds it.  gridDim.x column tiles per row tile.
+// Row tile mt and column tile bx of this workgroup, gridDim.x column tiles per row tile: in rounds of 8 row tiles, a
+// column tile of all 8 on one XCD.
+__device__ __forceinline__ void deal_tile(int n_tiles, int& mt, int& bx) {
+  const int ntx = gridDim.x;
+  mt = blockIdx.y;
+  bx = blockIdx.x;
+  if (ntx & 7) {
+    const int b = mt * ntx + bx, round = b / (8 * ntx);
+    if (8 * round + 8 <= n_tiles) {
+      const int r = b - round * 8 * ntx, q = (r & 7) * ntx + (r >> 3);
+      mt = 8 * round + (q & 7);
+      bx = q >> 3;
+    }
+  }
+}
+
+// Slot q holds ceil(rows / TM) row tiles: every workgroup counts them for itself from the slot offsets, which saves the
+// launch that writes a table, for about a microsecond per workgroup (few_rows_table below).  A thread counts consecutive
+// slots; the one whose slots hold the workgroup's row tile finds it.
 template <int TM>
 __device__ __forceinline__ bool find_slot_tile(const int32_t* __restrict__ offs, int n_slots, int32_t* const found, SlotTile& out) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int mt = blockIdx.y, bx = blockIdx.x;
-  const int ntx = gridDim.x;
   const int per = (n_slots + GT - 1) / GT, q0 = min(tid * per, n_slots), q1 = min(q0 + per, n_slots);
   int mine = 0;
   for (int q = q0; q < q1; ++q) mine += (offs[q + 1] - offs[q] + TM - 1) / TM;
@@ -862,14 +883,8 @@ __device__ __forceinline__ bool find_slot_tile(const int32_t* __restrict__ offs,
   __syncthreads();
   const int n_tiles = __builtin_amdgcn_readfirstlane(found[0] + found[1] + found[2] + found[3]);
   for (int w = 0; w < wave; ++w) incl += found[w];
-  if (ntx & 7) {   // rounds of 8 tiles, a column tile of all 8 on one XCD
-    const int b = mt * ntx + bx, round = b / (8 * ntx);
-    if (8 * round + 8 <= n_tiles) {
-      const int r = b - round * 8 * ntx, q = (r & 7) * ntx + (r >> 3);
-      mt = 8 * round + (q & 7);
-      bx = q >> 3;
-    }
-  }
+  int mt, bx;
+  deal_tile(n_tiles, mt, bx);
   if (mt >= n_tiles) return false;
   if (mt < incl && mt >= incl - mine) {
     int i = mt - (incl - mine), q = q0;
@@ -890,7 +905,22 @@ __device__ __forceinline__ bool find_slot_tile(const int32_t* __restrict__ offs,
   return true;
 }
 
-template <int MODE>
+// The same from the table that tile_map_kernel<FEW_BM> wrote.
+__device__ __forceinline__ bool read_slot_tile(const int32_t* __restrict__ map, SlotTile& out) {
+  const int n_tiles = map[0];
+  int mt, bx;
+  deal_tile(n_tiles, mt, bx);
+  if (mt >= n_tiles) return false;
+  const int entry = map[4 + 2 * mt + 1];
+  out.row0 = map[4 + 2 * mt];
+  out.row1 = out.row0 + (entry >> 16) + 1;
+  out.slot = entry & 0xffff;
+  out.bx = bx;
+  return true;
+}
+
+// TABLE: the row tiles come from tile_map
+template <int MODE, bool TABLE>
 __global__ __launch_bounds__(GT, 2) void gemm_few_rows_kernel(GemmParams p) {
   static_assert(MODE == FWD1 || MODE == FWD2 || MODE == GATE, "both operands reduction-contiguous");
   constexpr int TM = FEW_BM, TN = 128, NST = 3, LA = 2, LB = 4;   // LA, LB: 1 KB load instructions per wavefront and stage
@@ -906,6 +936,8 @@ __global__ __launch_bounds__(GT, 2) void gemm_few_rows_kernel(GemmParams p) {
     tile.row1 = min(p.M, tile.row0 + TM);
     tile.slot = 0;
     tile.bx = blockIdx.y;
+  } else if constexpr (TABLE) {
+    if (!read_slot_tile(p.tile_map, tile)) return;
   } else if (!find_slot_tile<TM>(p.slot_offsets, p.n_slots, found, tile)) {
     return;
   }
@@ -1683,6 +1715,16 @@ static bool few_rows(const symi_cfg* c) {
   return c->dtype == SYMI_BF16 && (long long)c->T * c->k <= 32LL * c->S_tot;
 }
 
+// Whether these tiles come from a table, for both products: the launch that writes it takes 1 - 2 us, finding a tile without it
+// about 1 us of every workgroup, which long reductions hide behind each other and short ones do not.  Time counted /
+// from the table of the two products together over 250 drawn shapes (8 - 960 slots of 0.1 - 32 rows on average, d 64 - 4096, f
+// 128 - 14336), geometric mean by workgroups per compute unit, d <= 256 / <= 640 / above: 0 - 2 0.91, 0.92, 0.94; 2 - 5 0.96, 0.96, 0.96; 5 - 8 1.01, 0.98,
+// 0.98; 8 - 14 1.06, 1.01, 1.00; 14 - 20 1.12, 1.04, 1.04; 20 - 40 1.14, 1.07, 1.00; beyond 1.22 (up to 1.53), 1.11, 1.03.
+static bool few_rows_table(const symi_ctx* ctx) {
+  const symi_cfg* const c = &ctx->cfg;
+  return ((long long)c->T * c->k / FEW_BM + c->S_tot) * (cdiv(c->f, 64) + cdiv(c->d, 128)) > 8LL * ctx->cus;
+}
+
 // bf16 variable-row products that take the 128 x 128 tile: those of few tiles, where the latency of one tile is the
 // time, and those of short reductions with slots of less than a tile, where set-up and epilogue are (two workgroups share a unit
 // and hide theirs behind each other).  Long reductions of many tiles belong to the large tile, which loads half as much per
@@ -1723,7 +1765,10 @@ static void launch_gemm(const symi_ctx* ctx, const GemmParams& p, int n_cols, in
     if constexpr (MODE == FWD1 || MODE == FWD2) {
       if (few_rows(cfg)) {
         dim3 grid(cdiv(n_cols, MODE == FWD1 ? 64 : 128), cfg->T * cfg->k / FEW_BM + cfg->S_tot);
-        SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_few_rows_kernel<MODE><<<grid, GT, 0, st>>>(p)));
+        if (few_rows_table(ctx))
+          SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_few_rows_kernel<MODE, true><<<grid, GT, 0, st>>>(p)));
+        else
+          SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_few_rows_kernel<MODE, false><<<grid, GT, 0, st>>>(p)));
         return;
       }
     }
@@ -1784,7 +1829,7 @@ void launch_router_fwd(const symi_ctx* ctx, const void* X, const void* Wr, const
   GemmParams p = {};
   p.A = X; p.B = Wr; p.C = logits; p.UV = b;
   p.M = ctx->cfg.T; p.N = ctx->cfg.E; p.K = ctx->cfg.d;
-  SYMI_TIMED(ctx, K_ROUTER_FWD, st, (gemm_few_rows_kernel<GATE><<<dim3(cdiv(p.M, FEW_BM), cdiv(p.N, 128)), GT, 0, st>>>(p)));
+  SYMI_TIMED(ctx, K_ROUTER_FWD, st, (gemm_few_rows_kernel<GATE, false><<<dim3(cdiv(p.M, FEW_BM), cdiv(p.N, 128)), GT, 0, st>>>(p)));
 }
 
 // where sliced reductions keep their partial tiles (bf16 configurations only)
@@ -1810,8 +1855,10 @@ extern "C" int symi_expert_fwd(const symi_ctx* ctx, const void* Xp, const int32_
   const WsLayout& L = ctx->L;
   int32_t* map = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + L.tile_map);
   const int max_mtiles = (int)(A / GEMM_BM) + cfg->S_tot;
-  if (!few_rows(cfg) && !(mid_tile(ctx, FWD1) && mid_tile(ctx, FWD2)))
-    SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<<<1, 256, 0, st>>>(slot_offsets, nullptr, cfg->S_tot, cfg->E, map, nullptr)));
+  if (few_rows(cfg) && few_rows_table(ctx))
+    SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<FEW_BM><<<1, 256, 0, st>>>(slot_offsets, nullptr, cfg->S_tot, cfg->E, map, nullptr)));
+  else if (!few_rows(cfg) && !(mid_tile(ctx, FWD1) && mid_tile(ctx, FWD2)))
+    SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<GEMM_BM><<<1, 256, 0, st>>>(slot_offsets, nullptr, cfg->S_tot, cfg->E, map, nullptr)));
 
   GemmParams p = {};
   p.tile_map = map;
@@ -1874,7 +1921,7 @@ static int expert_bwd_impl(const char* who, const symi_ctx* ctx, const void* dYp
   set_split(ctx, ws, p);
   p.d = cfg->d;
   p.f = cfg->f;
-  SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<<<1, 256, 0, st>>>(slot_offsets, first_slot, cfg->S_tot, cfg->E, map, order)));
+  SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<GEMM_BM><<<1, 256, 0, st>>>(slot_offsets, first_slot, cfg->S_tot, cfg->E, map, order)));
   // worth it only while a product is a few rounds of workgroups: with many rounds the chip is
   // full anyway and two kernels sharing it only disturb each other's L2 locality; and not for the
   // smallest, where fork, hand-over and join take longer than what they hide (symi_create

@@ -203,6 +203,12 @@ class OracleChain:
         return out
 
 
+def launches(ctx, name):
+    """Launches of one kernel since the last reset, by a context that times them."""
+    kid = [symi.lib().symi_kernel_name(i).decode() for i in range(symi.lib().symi_kernel_count())].index(name)
+    return symi.symi_timing_read(ctx, kid)[1]
+
+
 def bf16_tiles(T, E, k, S_tot, d, f, **_):
     """The dispatch rule of the bf16 variable-row products (the two forward ones, dh, dX), restated: "f" the few-rows
     tile, "m" the 128 x 128 one, "L" the 256 x 256 one."""

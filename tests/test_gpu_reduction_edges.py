@@ -8,7 +8,7 @@ import torch
 import paper_2504_19925_amd as symi
 import workloads as wl
 import harness as Hn
-from tests.checks import bf16_tiles, check_iteration, products_against_binary64
+from tests.checks import bf16_tiles, check_iteration, launches, products_against_binary64
 
 pytestmark = pytest.mark.gpu
 
@@ -42,7 +42,7 @@ def test_few_rows_per_slot(E, k, S, d, f, T):
 # A rank whose experts got nothing brings slot offsets that are all zero with a positive token count: no
 # row exists, so nothing is computed and nothing written, whatever an earlier call (here one with every
 # row in the first slot) left in the workspace
-@pytest.mark.parametrize("dtype,T,S", [("bf16", 192, 24), ("bf16", 400, 6), ("f32", 192, 24), ("f32", 9000, 6)])
+@pytest.mark.parametrize("dtype,T,S", [("bf16", 192, 24), ("bf16", 200, 220), ("bf16", 400, 6), ("f32", 192, 24), ("f32", 9000, 6)])
 def test_no_slot_has_rows(dtype, T, S):
     c = wl.scaled(wl.get_config("c2"), dtype=dtype, E=4, k=2, d=136, f=520, T=T, S_tot=S, N=1, iters=1,
                   router_matmul=False)
@@ -65,22 +65,24 @@ def test_no_slot_has_rows(dtype, T, S):
 
 
 # Rows are few per slot on average but sit in some of the slots: the 64-row tiles of the small-batch forward
-# products at their edges, 25 of them (three rounds of 8 and one more) in 1, 2, 3, 6, 8 and 16 column tiles,
-# against binary64.  A stored value is a 32-bit sum rounded to bf16 (half of
+# products at their edges, 25 of them (three rounds of 8 and one more) in 1, 2, 3, 6, 8, 16, 27 and 28 column tiles,
+# counted by the workgroups and, beyond 8 workgroups per compute unit, from a table, against binary64.  A stored value is a 32-bit sum rounded to bf16 (half of
 # 2^-8), h of the unrounded u and v; the second product is compared on the stored h
-@pytest.mark.parametrize("d,f", [(8, 72), (264, 328), (1024, 1000)])
+@pytest.mark.parametrize("d,f", [(8, 72), (264, 328), (1024, 1000), (264, 1728), (264, 1792)])
 def test_a_small_batch_in_a_few_slots(d, f):
     rows = [0, 1, 63, 64, 65, 0, 127, 128, 129, 191, 193, 257, 10] + [0] * 35
     S, T = len(rows), sum(rows)
     assert T <= 32 * S
     c = wl.scaled(wl.get_config("c2"), E=4, k=1, d=d, f=f, T=T, S_tot=S, N=1, iters=1, router_matmul=False)
-    st = Hn.State(c, shard=0)
+    st = Hn.State(c, shard=0, flags=symi.CTX_TIMING)
     g = torch.Generator(device="cuda").manual_seed(d)
     for t, std in ((st.Xp, 1.0), (st.W1s, d ** -0.5), (st.W2s, f ** -0.5)):
         t.normal_(0.0, std, generator=g)
     st.slot_offsets.copy_(torch.tensor([0] + rows).cumsum(0))
     print(f"[few slots] d={d} f={f}", flush=True)
     symi.symi_expert_fwd(st.ctx, st.Xp, st.slot_offsets, st.W1s, st.W2s, st.UV, st.H, st.Yp, st.ws)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert launches(st.ctx, "tile_map") == int((T // 64 + S) * (-(-f // 64) - (-d // 128)) > 8 * cus)
     slot = torch.repeat_interleave(torch.arange(S), torch.tensor(rows))
     X, W1, W2, UV, H, Yp = (t.cpu().double() for t in (st.Xp, st.W1s, st.W2s, st.UV, st.H, st.Yp))
     for s in slot.unique().tolist():

@@ -7,14 +7,9 @@ import torch
 
 import paper_2504_19925_amd as symi
 from oracle import symi_oracle as O
+from tests.checks import launches
 
 pytestmark = pytest.mark.gpu
-
-
-def launches(ctx, name):
-    """Launches of one kernel since the last reset, by a context that times them."""
-    kid = [symi.lib().symi_kernel_name(i).decode() for i in range(symi.lib().symi_kernel_count())].index(name)
-    return symi.symi_timing_read(ctx, kid)[1]
 
 
 # one token; one and two passes of the route's workgroup and the first size beyond; assignments around one and four

@@ -39,11 +39,12 @@ def test_tile_edges(d, f, extra):
 
 
 # both sides of every line of the rule, in mean rows per slot and in reduction length, and of the limit of tiles x K (at and above
-# 128 rows on average); which tile the four products take.  Rows spread from none to twice the mean
+# 128 rows on average), with one stream, and of the backward's limit with two; which tile the four products take.  Rows spread
+# from none to twice the mean
 @pytest.mark.parametrize("S,T,d,f,want", [
     (16, 1024, 1536, 1360, "mmmL"), (16, 1025, 1536, 1360, "LmmL"), (16, 1024, 1544, 1360, "LmmL"),    # first forward: 64, 1536
     (32, 3584, 640, 1200, "mmmL"), (32, 3585, 640, 1200, "LmmL"), (32, 3584, 648, 1200, "LmmL"),       # 112, 640
-    (64, 4096, 640, 2048, "mmmL"), (64, 4097, 640, 2048, "mLmL"), (64, 4096, 640, 2056, "mLmL"),       # second forward: 64, 2048
+    (64, 4096, 640, 1984, "mmmL"), (64, 4097, 640, 1984, "mLmL"), (64, 4096, 640, 1992, "mLmL"),       # second forward: 64, 1984
     (64, 7168, 640, 1024, "mmmL"), (64, 7169, 640, 1024, "LLmL"), (64, 7168, 640, 1032, "mLmL"),       # 112, 1024
     (16, 640, 1792, 2320, "LLmL"), (16, 641, 1792, 2320, "LLLL"), (16, 640, 1800, 2320, "LLLL"),       # hidden gradient: 40, 1792
     (16, 1280, 1536, 2320, "LLmL"), (16, 1281, 1536, 2320, "LLLL"), (16, 1280, 1544, 2320, "LLLL"),    # 80, 1536
@@ -51,11 +52,14 @@ def test_tile_edges(d, f, extra):
     (32, 1536, 1032, 768, "mmmm"), (32, 1537, 1032, 768, "mmmL"), (32, 1536, 1032, 776, "mmmL"),       # input gradient: 48, 1536
     (32, 3072, 1928, 320, "mmmm"), (32, 3073, 1928, 320, "mmmL"), (32, 3072, 1928, 328, "mmmL"),       # 96, 640
     (8, 1024, 1024, 2688, "mLmL"), (8, 1024, 1024, 2752, "LLmL"),                                      # tiles x K
-    (4, 2048, 512, 1792, "mmmL"), (4, 2048, 512, 1856, "LmmL")])                                       # half of it, 512 rows
+    (4, 2048, 512, 1792, "mmmL"), (4, 2048, 512, 1856, "LmmL"),                                        # half of it, 512 rows
+    (4, 2048, 128, 992, "mmmm"), (4, 2048, 128, 1000, "mmmL"),                                         # 31 and 32 steps
+    (4, 8192, 512, 712, "Lmmm2"), (4, 8192, 512, 720, "LmLL2")])                                       # two streams
 def test_both_sides_of_the_rule(S, T, d, f, want):
+    streams, want = 2 if want[4:] else 1, want[:4]
     c = wl.scaled(wl.get_config("c2"), E=2, k=1, d=d, f=f, T=T, S_tot=S, N=1, iters=1, router_matmul=False)
-    assert bf16_tiles(T, 2, 1, S, d, f) == want
-    st = Hn.State(c, shard=0, flags=symi.CTX_TIMING)
+    assert bf16_tiles(T, 2, 1, S, d, f, streams) == want
+    st = Hn.State(c, shard=0, flags=symi.CTX_TIMING | (0 if streams == 2 else symi.CTX_NO_OVERLAP))
     rows = [0] * S
     for i in range(T):
         rows[int(S * (i / T) ** 0.5)] += 1

@@ -334,11 +334,8 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // 16 bytes of a row.  ONCE: a row that nobody reads again is loaded past the caches' replacement order, as kept like any
-// other line it pushes out what is used again.  The dispatch's backward loads so, as its rows end there; inside a step, us,
-// plain : once (means of three runs in turn, which differ by 1 - 2 %): c2 20.6 : 14.7, c3 93 : 74, c4 204 : 189, c5 1018 : 1009; 134 MB
-// of rows (T = 8192, k = 8, d = 1024) 38 : 34, 67 MB 15 : 18.  The combine's rows are read by its backward next, which finds them
-// in the caches as long as they fit: combine_once below.  Nothing on combine_bwd (1867 : 1882); the row scatter's
-// stores lose by it (942 : 997, 168 : 195).
+// other line it pushes out what is used again.  Where that pays depends on what the caches still hold: dispatch_bwd_once and
+// combine_once below.  Nothing on combine_bwd (1867 : 1882 us); the row scatter's stores lose by it (942 : 997, 168 : 195).
 template <bool BF16, bool ONCE = false>
 __device__ __forceinline__ void load_piece(const void* p, long long piece, float (&out)[8]) {
   if (BF16) {
@@ -461,6 +458,16 @@ int static_scratch_address(int device, void** out) {
   return SYMI_OK;
 }
 
+// The dispatch's backward loads its rows past the caches' replacement order where the rest of the expert backward (weight
+// gradients and activations) has pushed them out of the 256 MB memory-side cache since the input-gradient product wrote them.
+// Inside a backward, time plain / once over 160 drawn shapes by the bytes of gradients and activations: up to 128 MB 0.88 (2 us of
+// 5 - 30 lost), 128 - 256 0.89, 256 - 512 1.00 (0.91 - 1.18), 512 - 1024 1.04, 1 - 4 GB 1.15 (5 us gained), beyond 1.3; c2 20.6 : 14.7 us, c3 93 : 74,
+// c4 204 : 189, c5 1018 : 1009.  On rows that the caches do hold it loses 15 - 25 % (up to 256 MB of them).
+static bool dispatch_bwd_once(const symi_cfg* c) {
+  const long long A = (long long)c->T * c->k, w = c->dtype == SYMI_BF16 ? 2 : 4;
+  return 12LL * c->E * c->d * c->f + A * (2 * c->d + 3LL * c->f) * w > 512LL << 20;
+}
+
 // The combine loads its rows past the caches' replacement order only where they are more than twice the 256 MB memory-side
 // cache.  Its backward reads them next, and what the combine gains elsewhere is lost there.  Inside a step, us, plain : once,
 // combine and combine_bwd: rows of 1 MB 6.3 : 6.2 and 6.8 : 7.6, 17 MB (k = 8) 9.6 : 9.7 and 15.1 : 20.4, 34 MB (c2) 13.5 : 14.1 and
@@ -476,6 +483,16 @@ static int grid_for(long long work_items, int per_block) {
   if (g < 1) g = 1;
   if (g > 16384) g = 16384;
   return (int)g;
+}
+
+static void launch_combine(const symi_ctx* ctx, int kid, bool once, const void* src, const int32_t* roa, const float* w, void* out,
+                           hipStream_t st) {
+  const symi_cfg* const c = &ctx->cfg;
+  const bool bf16 = c->dtype == SYMI_BF16;
+  const int ppr = c->d / (bf16 ? 8 : 4);
+  const auto kernel = bf16 ? (once ? combine_kernel<true, true> : combine_kernel<true, false>)
+                           : (once ? combine_kernel<false, true> : combine_kernel<false, false>);
+  SYMI_TIMED(ctx, kid, st, (kernel<<<grid_for((long long)c->T * ppr, 256), 256, 0, st>>>(src, roa, w, out, c->T, c->k, ppr)));
 }
 
 }  // namespace symi
@@ -580,15 +597,7 @@ extern "C" int symi_dispatch_bwd(const symi_ctx* ctx, const void* dXp, const int
   if (cfg->T == 0) return SYMI_OK;
   SYMI_REQUIRE(dXp && row_of_assign && dX, "symi_dispatch_bwd", "NULL pointer");
   hipStream_t st = as_stream(stream);
-  if (cfg->dtype == SYMI_BF16) {
-    const int ppr = cfg->d / 8;
-    SYMI_TIMED(ctx, K_DISPATCH_BWD, st, (combine_kernel<true, true><<<grid_for((long long)cfg->T * ppr, 256), 256, 0, st>>>(
-        dXp, row_of_assign, nullptr, dX, cfg->T, cfg->k, ppr)));
-  } else {
-    const int ppr = cfg->d / 4;
-    SYMI_TIMED(ctx, K_DISPATCH_BWD, st, (combine_kernel<false, true><<<grid_for((long long)cfg->T * ppr, 256), 256, 0, st>>>(
-        dXp, row_of_assign, nullptr, dX, cfg->T, cfg->k, ppr)));
-  }
+  launch_combine(ctx, K_DISPATCH_BWD, dispatch_bwd_once(cfg), dXp, row_of_assign, nullptr, dX, st);
   SYMI_LAUNCH_CHECK("symi_dispatch_bwd");
   return SYMI_OK;
 }
@@ -599,12 +608,7 @@ extern "C" int symi_combine(const symi_ctx* ctx, const void* Yp, const int32_t* 
   if (cfg->T == 0) return SYMI_OK;
   SYMI_REQUIRE(Yp && row_of_assign && gate && Y, "symi_combine", "NULL pointer");
   hipStream_t st = as_stream(stream);
-  const bool bf16 = cfg->dtype == SYMI_BF16, once = combine_once(cfg);
-  const int ppr = cfg->d / (bf16 ? 8 : 4);
-  const auto kernel = bf16 ? (once ? combine_kernel<true, true> : combine_kernel<true, false>)
-                           : (once ? combine_kernel<false, true> : combine_kernel<false, false>);
-  SYMI_TIMED(ctx, K_COMBINE, st, (kernel<<<grid_for((long long)cfg->T * ppr, 256), 256, 0, st>>>(
-      Yp, row_of_assign, gate, Y, cfg->T, cfg->k, ppr)));
+  launch_combine(ctx, K_COMBINE, combine_once(cfg), Yp, row_of_assign, gate, Y, st);
   SYMI_LAUNCH_CHECK("symi_combine");
   return SYMI_OK;
 }

@@ -2008,11 +2008,13 @@ extern "C" int symi_expert_bwd_slots(const symi_ctx* ctx, const void* dYp, const
 // ---------------------------------------------------------------- replica all-reduce
 // The intra-rank part of the paper's all-reduce (Sec. 4.1): for every class the first of its
 // slots is the representative; the other slots add their gradient to it (slot order), the
-// sum is scaled and copied back to all of them.  16 bytes per lane, one class per blockIdx.y.  Every gradient is read
-// once, past the caches' replacement order.  Behind the products that wrote them, us, plain : so (three runs in turn): 728 : 635 (32 slots of
-// d = 1128, f = 6376), 202 : 162 (64 of d = f = 1024), 725 : 705 (96 of 1024, 4096), 735 : 719 (12 of 4096, 4096), 29 : 29 (24 of 512, 1024),
-// 1621 : 1636 (128 of 2048, 1408, every class twice).
+// sum is scaled and copied back to all of them.  16 bytes per lane, one class per blockIdx.y.  ONCE: every gradient is read
+// once, past the caches' replacement order, where together they outgrow the 256 MB memory-side cache.  Behind the products that
+// wrote them, time plain / so over 160 drawn shapes by the size of all slots' gradients: up to 256 MB 1.00 (0.92 - 1.06), 256 - 512 MB
+// 1.02, 512 - 1024 1.08, beyond 1.12 (1.02 - 1.25); us: 728 : 635 (32 slots of d = 1128, f = 6376), 202 : 162 (64 of d = f = 1024), 725 : 705 (96 of
+// 1024, 4096), 1621 : 1636 (128 of 2048, 1408, every class twice).
 namespace symi {
+template <bool ONCE>
 __global__ __launch_bounds__(256) void replica_allreduce_kernel(float4* __restrict__ g,
                                                                 const int32_t* __restrict__ first_slot,
                                                                 long long n4, float scale) {
@@ -2020,10 +2022,12 @@ __global__ __launch_bounds__(256) void replica_allreduce_kernel(float4* __restri
   const int q0 = first_slot[e], q1 = first_slot[e + 1];
   if (q1 - q0 == 1 && scale == 1.f) return;   // a single replica: nothing to exchange
   for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n4; i += (long long)gridDim.x * 256) {
-    floatx4 a = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(g) + (long long)q0 * n4 + i);
-    for (int q = q0 + 1; q < q1; ++q) {
-      a += __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(g) + (long long)q * n4 + i);
-    }
+    auto load = [&](int q) {
+      const floatx4* const at = reinterpret_cast<const floatx4*>(g) + (long long)q * n4 + i;
+      return ONCE ? __builtin_nontemporal_load(at) : *at;
+    };
+    floatx4 a = load(q0);
+    for (int q = q0 + 1; q < q1; ++q) a += load(q);
     a *= scale;
     for (int q = q0; q < q1; ++q) reinterpret_cast<floatx4*>(g)[(long long)q * n4 + i] = a;
   }
@@ -2037,9 +2041,10 @@ extern "C" int symi_replica_allreduce(const symi_ctx* ctx, const int32_t* first_
   hipStream_t st = as_stream(stream);
   const long long n1 = 2LL * cfg->f * cfg->d / 4, n2 = (long long)cfg->d * cfg->f / 4;
   auto blocks = [](long long n4) { long long b = (n4 + 255) / 256; return (unsigned)(b > 2048 ? 2048 : (b < 1 ? 1 : b)); };
-  SYMI_TIMED(ctx, K_REPLICA_AR, st, (replica_allreduce_kernel<<<dim3(blocks(n1), cfg->E), 256, 0, st>>>(
+  const auto kernel = 16LL * (n1 + n2) * cfg->S_tot > 256LL << 20 ? replica_allreduce_kernel<true> : replica_allreduce_kernel<false>;
+  SYMI_TIMED(ctx, K_REPLICA_AR, st, (kernel<<<dim3(blocks(n1), cfg->E), 256, 0, st>>>(
       reinterpret_cast<float4*>(dW1_slot), first_slot, n1, scale)));
-  SYMI_TIMED(ctx, K_REPLICA_AR, st, (replica_allreduce_kernel<<<dim3(blocks(n2), cfg->E), 256, 0, st>>>(
+  SYMI_TIMED(ctx, K_REPLICA_AR, st, (kernel<<<dim3(blocks(n2), cfg->E), 256, 0, st>>>(
       reinterpret_cast<float4*>(dW2_slot), first_slot, n2, scale)));
   SYMI_LAUNCH_CHECK("symi_replica_allreduce");
   return SYMI_OK;

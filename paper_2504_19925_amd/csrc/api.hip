@@ -135,13 +135,15 @@ int enter(const symi_ctx* ctx, const char* who) {
 
 // The expert backward runs its weight-gradient chain on a stream of its own while the products
 // are only a few rounds of workgroups (gemm.hip); larger shapes fill the chip anyway.  Forking, handing over and
-// joining cost 20 - 40 us on the device, so the products have to be worth it.  Step or backward, us, two streams : one, by
-// T*k*d*f: 6.5e6 115 : 77, 2.5e7 122 : 83, 6.7e7 122 : 100, 7.3e7 77 : 63, 1.0e8 150 : 150, 2.1e8 144 : 135, 3.3e8 243 : 230;
-// 4.2e8 156 : 161, 5.2e8 88 : 91, 9.9e8 240 : 270, 3.9e9 405 : 433, 9.2e9 410 : 450, 2.4e10 514 : 604, 6.9e10 2060 : 2108.
+// joining cost 20 - 40 us on the device, so the products have to be worth it: by their work, or in bf16 by the gradients that
+// one chain writes while the other reads.  Expert backward, time one / two streams over 300 drawn shapes, geometric mean, by
+// T*k*d*f; bf16: to 2e7 0.85 (0.72 - 1.02), to 3.5e8 1.00 (0.91 - 1.14) with class gradients of less than 100 MB and 1.06 (0.95 - 1.24) with more, to
+// 7e8 1.04, to 4e9 1.07, beyond 1.12; fp32: to 2e7 0.58, to 1.5e8 0.85, to 3.5e8 0.99, to 7e8 1.04, beyond 1.06.
 static bool wants_side_stream(const symi_cfg* c, int cus) {
   const long long A = (long long)c->T * c->k;
   const long long max_mtiles = A / GEMM_BM + c->S_tot;
-  return (double)A * c->d * c->f >= 3.5e8 && max_mtiles * cdiv(c->d, 256) < 8LL * cus;
+  const double work = (double)A * c->d * c->f, grads = 12. * c->E * c->d * c->f;
+  return (work >= 3.5e8 || (c->dtype == SYMI_BF16 && work >= 2e7 && grads >= 1e8)) && max_mtiles * cdiv(c->d, 256) < 8LL * cus;
 }
 
 static void release(symi_ctx* ctx) {

@@ -1893,8 +1893,8 @@ extern "C" int symi_expert_fwd(const symi_ctx* ctx, const void* Xp, const int32_
 // (config c2: 296 tiles of the dXp product are two rounds, the second one 84 % empty) and
 // the store-bound zero tiles of the weight gradients never meet the MFMA-bound tiles.  The
 // second chain is therefore enqueued on the context's helper stream (created by symi_create
-// when the flags allow it, T*k*d*f is at least 3.5e8 and the dXp product has fewer than 8 rounds of
-// tiles; default priority, non-blocking), forked from and joined back into the caller's stream with events,
+// when the flags allow it, the products or their gradients are large enough and the dXp product has
+// fewer than 8 rounds of tiles; default priority, non-blocking), forked from and joined back into the caller's stream with events,
 // so workgroups of both chains share the chip.  Otherwise everything stays on the caller's
 // stream, in order.
 

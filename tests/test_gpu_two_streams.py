@@ -1,5 +1,6 @@
-"""The expert backward on two streams, at a size that takes them (T*k*d*f = 5.4e8, a few rounds of tiles), and at one just
-below the size where the helper stream begins: the same bits as on one stream, eager and replayed from a HIP graph."""
+"""The expert backward on two streams, at a size that takes them (T*k*d*f = 5.4e8, a few rounds of tiles), at one just
+below the size where the helper stream begins, and (bf16) at a smaller one with 101 MB of class gradients, which takes it too:
+the same bits as on one stream, eager and replayed from a HIP graph."""
 import pytest
 import torch
 
@@ -11,10 +12,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("d", [512, 328])
-def test_two_streams(dtype, d):
-    c = wl.scaled(wl.get_config("c2"), dtype=dtype, E=16, k=2, d=d, f=512, T=1024, S_tot=24, N=1, iters=1, router_matmul=False)
-    print(f"[two streams] {dtype} d={d}", flush=True)
+@pytest.mark.parametrize("E,d,f,T", [(16, 512, 512, 1024), (16, 328, 512, 1024), (64, 256, 512, 256)])
+def test_two_streams(dtype, E, d, f, T):
+    c = wl.scaled(wl.get_config("c2"), dtype=dtype, E=E, k=2, d=d, f=f, T=T, S_tot=E + E // 2, N=1, iters=1, router_matmul=False)
+    print(f"[two streams] {dtype} E={E} d={d} f={f} T={T}", flush=True)
     weights = wl.make_class_weights(c, "cuda")
     X, logits, dY = Hn.draw_inputs(c, 0)
     outs = []

@@ -1745,7 +1745,8 @@ static bool few_rows_table(const symi_ctx* ctx) {
 // All this with one kernel at a time.  Where the weight gradients run beside them on the helper stream, the backward's two
 // products leave them less of the chip with this tile, two workgroups to a unit that none of theirs fits beside: expert backward
 // large / small over 150 drawn shapes, by T*k*d*f: below 3.5e8 1.07, to 7e8 1.05, to 3e9 1.03 (0.93 - 1.13), beyond 1.00 (0.88 - 1.08;
-// 256 rows and more on average 0.94: E = 16, k = 6, d = 240, f = 536, 52578 rows 340 : 375 us).  So not from 3e9 on.
+// 256 rows and more on average 0.94: E = 16, k = 6, d = 240, f = 536, 52578 rows 340 : 375 us).  So not from 3e9 on, and the input
+// gradient not in more than two rounds of tiles (six shapes with 2.2 - 5.6 rounds 0.92 - 0.97, one to two rounds 1.00 - 1.16).
 // No reduction that the large tile may slice (from 32 steps on), so that no result depends on the tile.
 static bool mid_tile(const symi_ctx* ctx, int mode) {
   const symi_cfg* const c = &ctx->cfg;
@@ -1754,12 +1755,13 @@ static bool mid_tile(const symi_ctx* ctx, int mode) {
   if (A / MID_BM + S > 65535) return false;   // its row tiles are a grid.y coordinate
   const int K = mode == FWD1 || mode == BWD_DH ? c->d : mode == FWD2 ? c->f : 2 * c->f;
   const int ntx = mode == FWD1 ? cdiv(c->f, 64) : cdiv(mode == BWD_DH ? c->f : c->d, 128);
-  if (mode >= BWD_DH && ctx->side && (double)A * c->d * c->f >= 3e9) return false;
+  const long long tiles = std::max(A / MID_BM + S / 2, S) * ntx;
+  if (mode >= BWD_DH && ctx->side && ((double)A * c->d * c->f >= 3e9 || (mode == BWD_DX && tiles > 4LL * ctx->cus))) return false;
   // mean rows and reduction length, up to three lines for each product
   constexpr int LINES[4][3][2] = {{{64, 1536}, {112, 640}}, {{64, 1984}, {112, 1024}}, {{40, 1792}, {80, 1536}, {128, 512}}, {{48, 1536}, {96, 640}}};
   for (const auto& line : LINES[mode])
     if (A <= line[0] * S && K <= line[1]) return true;
-  const long long work = std::max(A / MID_BM + S / 2, S) * ntx * K * (mode <= FWD2 && A > 128 * S ? 2 : 1);   // tiles x reduction length
+  const long long work = tiles * K * (mode <= FWD2 && A > 128 * S ? 2 : 1);
   return mode == FWD1 || mode == BWD_DH ? work <= 1 << 19 : work <= 3 << 17 && K <= 1984;
 }
 

@@ -214,18 +214,21 @@ def bf16_tiles(T, E, k, S_tot, d, f, streams=2):
     tile, "m" the 128 x 128 one, "L" the 256 x 256 one.  streams: 2 where the backward may take its helper stream (256
     compute units), 1 with SYMI_CTX_NO_OVERLAP."""
     A, up = T * k, lambda a, b: -(-a // b)
+    side = (streams == 2 and (A // 256 + S_tot) * up(d, 256) < 8 * 256
+            and (A * d * f >= 3.5e8 or (A * d * f >= 2e7 and 12 * E * d * f >= 1e8)))
     lines = (((64, 1536), (112, 640)), ((64, 1984), (112, 1024)), ((40, 1792), (80, 1536), (128, 512)),
              ((48, 1536), (96, 640)))
 
     def one(i):
         if i < 2 and A <= 32 * S_tot:
             return "f"
-        if i >= 2 and streams == 2 and A * d * f >= 3e9 and (A // 256 + S_tot) * up(d, 256) < 8 * 256:
-            return "L"
         K, ntx = (d, f, d, 2 * f)[i], (up(f, 64), up(d, 128), up(f, 128), up(d, 128))[i]
+        tiles = max(A // 128 + S_tot // 2, S_tot) * ntx
+        if i >= 2 and side and (A * d * f >= 3e9 or (i == 3 and tiles > 4 * 256)):
+            return "L"
         if any(A <= r * S_tot and K <= n for r, n in lines[i]):
             return "m"
-        work = max(A // 128 + S_tot // 2, S_tot) * ntx * K * (2 if i < 2 and A > 128 * S_tot else 1)
+        work = tiles * K * (2 if i < 2 and A > 128 * S_tot else 1)
         return "m" if (work <= 1 << 19 if i in (0, 2) else work <= 3 << 17 and K <= 1984) else "L"
 
     return "".join(one(i) for i in range(4))

@@ -54,7 +54,8 @@ def test_tile_edges(d, f, extra):
     (8, 1024, 1024, 2688, "mLmL"), (8, 1024, 1024, 2752, "LLmL"),                                      # tiles x K
     (4, 2048, 512, 1792, "mmmL"), (4, 2048, 512, 1856, "LmmL"),                                        # half of it, 512 rows
     (4, 2048, 128, 992, "mmmm"), (4, 2048, 128, 1000, "mmmL"),                                         # 31 and 32 steps
-    (4, 8192, 512, 712, "Lmmm2"), (4, 8192, 512, 720, "LmLL2")])                                       # two streams
+    (4, 8192, 512, 712, "Lmmm2"), (4, 8192, 512, 720, "LmLL2"),                                        # two streams: 3e9
+    (128, 5120, 1024, 408, "mmmm2"), (129, 5120, 1024, 408, "mmmL2")])                                 # 4 tiles per unit
 def test_both_sides_of_the_rule(S, T, d, f, want):
     streams, want = 2 if want[4:] else 1, want[:4]
     c = wl.scaled(wl.get_config("c2"), E=2, k=1, d=d, f=f, T=T, S_tot=S, N=1, iters=1, router_matmul=False)

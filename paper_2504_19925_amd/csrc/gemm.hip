@@ -125,9 +125,9 @@ __global__ __launch_bounds__(256) void tile_map_kernel(const int32_t* __restrict
 // lane).  Tiles travel HBM -> LDS with the gfx950 direct-to-LDS loads (16 bytes per
 // lane, no staging registers) into two 32 KB stages of the left operand and three of the right
 // one, the whole 160 KB of a compute unit.
-// With long reductions bound by the matrix pipes at the clock the power limit leaves (c5: busy 65 - 77 % of
-// the cycles at 1.7 - 1.8 GHz of 2.4 with random operands; c3, K up to 28672: 65 - 86 %), as long as neither
-// loads nor instruction issue leave them idle; with short ones (c2, K = 1024: busy 30 - 61 %) the epilogue,
+// With long reductions bound by the matrix pipes at the clock the power limit leaves (c5: busy 67 - 79 % of
+// the cycles at 1.6 - 1.74 GHz of 2.4 with random operands; c3, K up to 28672: 68 - 87 %), as long as neither
+// loads nor instruction issue leave them idle; with short ones (c2, K = 1024: busy 32 - 64 %) the epilogue,
 // which runs with idle pipes, is what is left:
 //  - Lead of the loads.  With two stages of both operands the loads of a step had to be issued
 //    within two of its four phases and had 2 - 4 phases to land; the third stage of the right operand

@@ -53,7 +53,7 @@ int check_cfg(const symi_cfg* c, const char* who) {
   // launch limits of the kernels: the m-tile index of the grouped GEMM (one per 64 rows in the
   // fp32 products, plus the slices of a cut last round) and the router's 128-token tiles are grid.y
   // coordinates; the GEMM's per-lane element offsets inside a slot's weights are 32 bits.  The products of
-  // small batches count finer and always fit: 8 per m-tile in the fp32 ones, which have fewer 64-row tiles
+  // small batches count finer and always fit: two per 64-row tile in the fp32 ones, which have fewer of them
   // (T*k/64 + S_tot/2) than the device has compute units; one per 64 rows and slot in the bf16 ones, of
   // which there are at most 1.5 S_tot = 6144
   const long long A = (long long)c->T * c->k;
@@ -81,7 +81,8 @@ WsLayout ws_layout(const symi_cfg* c) {
   L.class_tab = off;
   off += align_up((size_t)3 * c->E * sizeof(int32_t), 256);
   L.tile_map = off;
-  off += align_up((4 + 4 * mtiles) * sizeof(int32_t), 256);
+  // fp32: two words per 64-row tile
+  off += align_up((4 + (c->dtype == SYMI_BF16 ? 4 * mtiles : 2 * (A / 64 + c->S_tot + 1))) * sizeof(int32_t), 256);
   L.class_order = off;
   off += align_up((size_t)c->E * sizeof(int32_t), 256);
   L.duv = off;

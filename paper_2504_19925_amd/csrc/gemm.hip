@@ -4,7 +4,7 @@
 // weight-gradient GEMM, which sums over every row of a class at once).
 //
 // Six products share one tiled kernel (bf16 inputs, fp32 accumulation on the gfx950
-// MFMA 16x16x32 bf16 instruction; kernels on the fp32 MFMA serve fp32 configurations):
+// MFMA 16x16x32 bf16 instruction; fp32 configurations split every value into three bf16 ones or take the fp32 MFMA):
 //   FWD1   [u|v] = Xp  * W1^T      + SwiGLU epilogue writing u, v and h = silu(u)*v
 //   FWD2   Yp    = H   * W2^T
 //   BWD_DH dh    = dYp * W2        turned into du, dv from the saved u, v in the epilogue
@@ -66,8 +66,8 @@ __device__ __forceinline__ float sigmoid_fast(float u) {
 
 // ---------------------------------------------------------------- m-tile table
 // map[0] = number of m-tiles, map[4 + 4i ..] = {first row, end row, slot} of m-tile i (TM = 256 rows), or
-// map[4 + 2i ..] = {first row, slot + 2^16 * (rows - 1)} (TM = FEW_BM: the small-batch forward products; at most
-// 32 rows per slot on average make at most 1.5 S_tot of them, which fit where 256-row tiles would be).
+// map[4 + 2i ..] = {first row, slot + 2^16 * (rows - 1)} (TM = FEW_BM: the fp32 products and the small-batch forward products; of these at most
+// 32 rows per slot on average make at most 1.5 S_tot tiles, which fit where 256-row tiles would be).
 // order[c] = the class with the c-th largest number of rows (ties: lower index first).
 constexpr int FEW_BM = 64;
 
@@ -1255,7 +1255,7 @@ __global__ __launch_bounds__(256) void slice_sum_kernel(GemmParams p, int ntx) {
 // which keeps the rounding error of long reductions (weight gradients) near sqrt(K/16).
 constexpr int F32_CHUNK = 16;
 
-// What both fp32 kernels need to know about a product: its operands, their pitches and extents.
+// What the fp32 kernels need to know about a product: its operands, their pitches and extents.
 template <int MODE>
 struct F32Operands {
   static constexpr bool VARM = MODE <= BWD_DX;
@@ -1266,17 +1266,19 @@ struct F32Operands {
   long long lda, ldb;
   int row0, row1, group, K;
 
-  // tile `part` of 256 / `rows` parts of a table entry (variable rows), or row tile `part` of a group
+  // tile `part` of 64 / `rows` parts of a table entry (variable rows), or row tile `part` of a group
   __device__ __forceinline__ bool init(const GemmParams& p, int rows, int y, int z) {
     int kbeg = 0;
     if (VARM) {
-      const int parts = GEMM_BM / rows, mt = y / parts;
+      const int parts = FEW_BM / rows, mt = y / parts;
       if (mt >= p.tile_map[0]) return false;
-      row0 = p.tile_map[4 + 4 * mt] + (y % parts) * rows;
-      row1 = p.tile_map[4 + 4 * mt + 1];
+      const int entry = p.tile_map[4 + 2 * mt + 1];
+      row0 = p.tile_map[4 + 2 * mt];
+      row1 = row0 + (entry >> 16) + 1;
+      row0 += (y % parts) * rows;
       if (row0 >= row1) return false;
       row1 = min(row1, row0 + rows);
-      group = p.tile_map[4 + 4 * mt + 2];
+      group = entry & 0xffff;
       K = p.K;
     } else {
       group = p.per_slot ? z : p.class_order[z];   // long reductions first
@@ -1322,43 +1324,34 @@ __device__ __forceinline__ void f32_store(const GemmParams& p, int group, long l
   }
 }
 
-// Tile of 64 rows x 64 NBL columns (FWD1: the gate and up columns of 64 hidden units), four wavefronts of
-// 32 x 32 NBL.  Tiles travel HBM -> LDS with direct-to-LDS loads, KD-deep steps: 32 deep in two stages (128 columns:
-// three workgroups per compute unit; 64: four, as 32 KB of LDS are a little more than a fifth of what can be had) or 16 deep in
-// three (six).  The next step's loads are in flight while the current one feeds the matrix pipes, one barrier per step.  Rows and columns beyond the tile's extent are clamped to a valid one (they
-// only reach outputs that are never stored), reduction indices beyond K are zeros in both
+// Tile of 64 rows x 128 columns (FWD1: the gate and up columns of 64 hidden units), four wavefronts of
+// 32 x 64.  Tiles travel HBM -> LDS with direct-to-LDS loads, 32-deep steps in two stages: the next step's loads are in flight
+// while the current one feeds the matrix pipes, one barrier per step.  Rows and columns beyond the tile's extent (N: the columns
+// that exist) are clamped to a valid one (they only reach outputs that are never stored), reduction indices beyond K are zeros in both
 // operands (offsets outside the buffer).  A wavefront whose outputs all lie outside multiplies nothing.
-// LDS layouts, free of bank conflicts: reduction-contiguous [row][k], 16-byte chunk c of row r at c ^ ((r >> 1) & 7) (16
-// deep: c ^ ((r >> 2) & 3)), read 16 bytes per lane; reduction-strided [k][column] as loaded, chunk c of row k at c ^ (8 ((k >> 2) & 1)): the two
+// LDS layouts, free of bank conflicts: reduction-contiguous [row][k], 16-byte chunk c of row r at c ^ ((r >> 1) & 7), read 16
+// bytes per lane; reduction-strided [k][column] as loaded, chunk c of row k at c ^ (8 ((k >> 2) & 1)): the two
 // halves of a wavefront read rows 4 apart, 32 banks apart.  With 128 columns a lane reads two neighbouring ones
 // at a time, so block j of a wavefront holds its columns 2 l + j.
-// Bound by the matrix pipes at the clock that is left to them once a few workgroups share a unit (E = 16, 15092 rows in 32
-// slots of d = 512, f = 1264: busy 69 - 82 % of the cycles at 1.93 GHz; the six products 2112 -> 1923 us against two
-// barriers a step and loads through registers, 843 -> 707 with 8997 rows in 36 slots of d = 328, f = 872).  The hidden
-// gradient's epilogue read its u, v under a branch per element: 131 -> 99 us.
 constexpr int F32_BM = 64;
 
-template <int MODE, int NBL, int KD>
-__global__ __launch_bounds__(256, NBL == 2 ? 3 : KD == 32 ? 4 : 6) void gemm_f32_kernel(GemmParams p) {
+template <int MODE>
+__device__ __forceinline__ void f32_tile(const GemmParams& p, const F32Operands<MODE>& o, const int n0, const int N, float* const smem) {
   using Op = F32Operands<MODE>;
-  static_assert(NBL == 2 || (NBL == 1 && MODE != FWD1), "the gate and up columns of a hidden unit go together");
-  constexpr int F32_BN = 64 * NBL;
+  constexpr int NBL = 2, KD = 32, F32_BN = 128;
   constexpr bool VARM = Op::VARM;
-  constexpr bool PAIRS = !Op::B_KC && NBL == 2;   // neighbouring columns in one lane
-  constexpr int NST = KD == 32 ? 2 : 3;           // stages
+  constexpr bool PAIRS = !Op::B_KC;               // neighbouring columns in one lane
+  constexpr int NST = 2;                          // stages
   constexpr int NLA = KD / 16, NLB = NLA * NBL;   // 1 KB load instructions per wavefront, operand and stage
   constexpr int SA = F32_BM * KD, SB = F32_BN * KD;   // elements of a stage
-  __shared__ __attribute__((aligned(1024))) float As[NST * SA];
-  __shared__ __attribute__((aligned(1024))) float Bs[NST * SB];
-  Op o;
-  if (!o.init(p, F32_BM, blockIdx.y, blockIdx.z)) return;
-  const int K = o.K, N = MODE == FWD1 ? p.f : p.N;
-  const int n0 = blockIdx.x * (MODE == FWD1 ? F32_BN / 2 : F32_BN);
+  float* const As = smem;
+  float* const Bs = smem + NST * SA;
+  const int K = o.K;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1, r31 = lane & 31, hw = lane >> 5;
 
-  auto swizzle = [](int r) { return KD == 32 ? (r >> 1) & 7 : (r >> 2) & 3; };   // of a [row][k] tile's chunks
+  auto swizzle = [](int r) { return (r >> 1) & 7; };   // of a [row][k] tile's chunks
 
   // byte offset of this lane's 16 bytes for instruction j of an operand (its immediate, j KB, taken back out) and their
   // reduction index in the step
@@ -1481,9 +1474,9 @@ __global__ __launch_bounds__(256, NBL == 2 ? 3 : KD == 32 ? 4 : 6) void gemm_f32
     if (t < nk) issue(t, t);
   int st = 0;
   for (int t = 0; t < nk; ++t) {
-    // my loads of step t have landed (with three stages those of the next step may fly) and my reads of step t - 1
-    // are through; behind the barrier everybody's, and its stage may be filled
-    if (NST == 3 && t + 1 < nk) __builtin_amdgcn_s_waitcnt(0x0070 + NLA + NLB); else __builtin_amdgcn_s_waitcnt(0x0070);
+    // my loads of step t have landed and my reads of step t - 1 are through; behind the barrier everybody's, and its
+    // stage may be filled
+    __builtin_amdgcn_s_waitcnt(0x0070);
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -1554,6 +1547,448 @@ __global__ __launch_bounds__(256, NBL == 2 ? 3 : KD == 32 ? 4 : 6) void gemm_f32
       for (int r = 0; r < 16; ++r)
         store(Co, in_col && row_of(r) < left, (unsigned)(row_of(r) * p.N + col), acc[j][r], acc[NBL - 1][r]);
     }
+  }
+}
+
+// The weight gradients of groups with a few rows each, whose time is that of the stores: one tile per workgroup.
+template <int MODE>
+__global__ __launch_bounds__(256, 3) void gemm_f32_kernel(GemmParams p) {
+  __shared__ __attribute__((aligned(1024))) float smem[2 * (F32_BM + 128) * 32];
+  F32Operands<MODE> o;
+  if (!o.init(p, F32_BM, blockIdx.y, blockIdx.z)) return;
+  f32_tile<MODE>(p, o, blockIdx.x * 128, p.N, smem);
+}
+
+// ---------------------------------------------------------------- fp32 products on the bf16 matrix instruction
+// An fp32 value is the sum of three bf16 values to 24 bits: x = x0 + x1 + x2, each the bf16 nearest to what the ones
+// before leave.  A product then is x0 y0 + (x0 y1 + x1 y0) + (x1 y1 + x0 y2 + x2 y0) and terms below 2^-26 of it: six matrix
+// instructions at 16 times the rate of the fp32 one.  A step of 32 indices is summed from zero, the small terms first, and
+// then added to the total, half as many additions as of 16 products each on the fp32 instruction: error against
+// binary64 (relative 2-norm) Y 2.4e-7 -> 1.9e-7, dX 2.8e-7 -> 2.2e-7, dW1 2.7e-7 -> 2.1e-7 on 24 classes of d = 328, f = 872,
+// 8997 rows.  Where the sum is not that exact the tile is computed once more on the fp32 instruction (f32_tile):
+// infinities, NaN and values beyond the bf16 range leave a sum that is not finite; values so small that their third part
+// is subnormal (below 2^-110) lose up to 2^-134 each, which counts in a sum below 2^-64 or next to factors above 2^40.
+// Tile of 64 x 64 (FWD1: 32 hidden units), four wavefronts of 32 x 32, three workgroups per compute unit that stay and
+// take one tile after the other.  A thread loads 16 values of a step into registers, two to three steps ahead, splits
+// them beside the matrix instructions of the step before and writes the planes to the other of two LDS stages; one barrier per step.
+// Bound by the vector instructions of the splits next to the matrix instructions (28 % of the matrix pipes' time is theirs
+// with 128 x 128 tiles), and where the tiles are few by the last round of them.  Step of the shape above 767 -> 598 us, forward of
+// 24 classes of d = 256, f = 576, 18096 rows 154 -> 118, backward of 4 classes of d = 104, f = 896, 1412 rows 107 -> 78; 75 drawn
+// layers 1.10 (0.96 - 1.41).  Tried and dropped: 128 x 128 tiles with eight wavefronts (that step 620: fewer splits per product, but 273
+// tiles of the input gradient are two rounds of 256), half of the wavefronts loading and splitting for the other half (616 - 640), everything
+// in each wavefront between two barriers (626 - 667), planes by truncation (2.4e-7 -> 3.1e-7).
+// LDS layouts, free of bank conflicts: reduction-contiguous [row][32 k], 16-byte chunk c of row r at c ^ s with s = 0, 2, 3, 1
+// for (r >> 2) & 3; reduction-strided [k][64 columns] as loaded, 32-byte piece c of row k at c ^ (((k >> 1) & 1) + 2 ((k >> 3) & 1)), read transposing.
+constexpr int F32S_T = 64, F32S_BK = 32;   // tile edge, step
+
+// The tiles of a product that one workgroup computes, one after the other.  XCD x (workgroup number mod 8) takes an eighth of
+// the row tiles with all their columns, or of every class's tiles, the classes in order of decreasing row count.
+struct F32Tile { int row0, row1, group, bx, kbeg, K; };
+
+__device__ __forceinline__ int const_i32(const int32_t* q) {   // a scalar load: written by an earlier kernel
+  return *(const int32_t __attribute__((address_space(4)))*)(unsigned long long)q;
+}
+
+template <int MODE>
+struct F32Walk {
+  static constexpr int T = F32S_T;
+  static constexpr bool VARM = MODE <= BWD_DX;
+  const GemmParams& p;
+  int groups, x, s, cx, ntx, lo, n, per, nt, i;
+  __device__ __forceinline__ F32Walk(const GemmParams& p_, int groups_) : p(p_), groups(groups_) {
+    const int G = gridDim.x, b = blockIdx.x;
+    x = b & 7;
+    s = b >> 3;
+    cx = (G - x + 7) >> 3;
+    i = 0;
+    if (VARM) {
+      ntx = (p.N + (MODE == FWD1 ? T / 2 : T) - 1) / (MODE == FWD1 ? T / 2 : T);
+      const long long all = (long long)const_i32(p.tile_map) * ntx;
+      lo = (int)(all * x / 8);
+      n = (int)(all * (x + 1) / 8) - lo;
+    } else {
+      ntx = (p.N + T - 1) / T;
+      nt = ntx * ((p.M + T - 1) / T);
+      per = (nt + 7) / 8;
+      n = groups * per;
+    }
+  }
+  __device__ __forceinline__ bool next(F32Tile& t) {
+    for (;; ++i) {
+      if (i * cx >= n) return false;
+      const int u = i * cx + (!VARM && (i & 1) ? cx - 1 - s : s);   // the larger classes come first: there and back
+      if (u >= n) continue;
+      if (VARM) {
+        const int mt = (lo + u) / ntx;
+        const int entry = const_i32(p.tile_map + 4 + 2 * mt + 1);
+        t.bx = lo + u - mt * ntx;
+        t.row0 = const_i32(p.tile_map + 4 + 2 * mt);
+        t.row1 = t.row0 + (entry >> 16) + 1;
+        t.group = entry & 0xffff;
+        t.kbeg = 0;
+        t.K = p.K;
+      } else {
+        const int c = u / per, at = ((x + c) & 7) * per + u - c * per;
+        if (at >= nt) continue;
+        const int mt = at / ntx;
+        t.bx = at - mt * ntx;
+        t.row0 = mt * T;
+        t.row1 = min(p.M, t.row0 + T);
+        t.group = p.per_slot ? c : const_i32(p.class_order + c);
+        const int q0 = p.per_slot ? c : const_i32(p.first_slot + t.group), q1 = p.per_slot ? c + 1 : const_i32(p.first_slot + t.group + 1);
+        t.kbeg = const_i32(p.slot_offsets + q0);
+        t.K = const_i32(p.slot_offsets + q1) - t.kbeg;
+      }
+      ++i;
+      return true;
+    }
+  }
+};
+
+template <int MODE>
+__global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, int groups) {
+  using Op = F32Operands<MODE>;
+  constexpr int T = F32S_T;
+  constexpr bool VARM = Op::VARM;
+  constexpr int MI = 2, NJ = 2, WR = 32, WC = 32;            // 16 x 16 blocks, rows and columns of a wavefront
+  constexpr int PL = T * F32S_BK * 2, ST = 6 * PL;           // bytes: a plane, a stage
+  constexpr int EXACT = 2 * 4 * (F32_BM + 128) * 32;
+  __shared__ __attribute__((aligned(1024))) char smem[2 * ST > EXACT ? 2 * ST : EXACT];
+  __shared__ unsigned redo[32];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1, g4 = lane >> 4, jj = lane & 15;
+  const int N = MODE == FWD1 ? p.f : p.N;
+  const int lda = MODE == FWD2 ? p.f : (MODE == BWD_DX || MODE == WGRAD1) ? 2 * p.f : p.d;
+  const int ldb = (MODE == FWD1 || MODE == BWD_DX || MODE == WGRAD1) ? p.d : p.f;
+  auto swizzle = [](int k) { return ((k >> 1) & 1) | (((k >> 3) & 1) << 1); };
+  auto kc_swz = [](int r) { const int a = (r >> 2) & 3; return ((a ^ (a >> 1)) & 1) << 1 | (a >> 1); };
+  auto meet = [] {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  if (tid < 32) redo[tid] = 0;
+
+  // ---- loads: two of the left operand, two of the right one per thread and step
+  unsigned ls[4], vo[4];   // byte offsets inside a stage and in memory
+  int kr[4];
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {
+    const int q = tid + 256 * (x & 1);
+    if (x < 2 ? Op::A_KC : Op::B_KC) {
+      const int r = q >> 3;
+      kr[x] = (q & 7) * 4;
+      ls[x] = r * 64 + (((kr[x] >> 3) ^ kc_swz(r)) << 4) + ((kr[x] >> 2) & 1) * 8;
+    } else {
+      kr[x] = q / (T / 4);
+      ls[x] = kr[x] * (2 * T) + ((8 * (q & (T / 4 - 1))) ^ (swizzle(kr[x]) << 5));
+    }
+    if (x >= 2) ls[x] += 3 * PL;
+    vo[x] = 0;
+  }
+  F32Walk<MODE> ahead(p, groups);
+  F32Tile nx;
+  bool more = ahead.next(nx);
+  const float* a0 = nullptr;
+  const float* b0 = nullptr;
+  int lK = 0, lk = 0;
+  __amdgpu_buffer_rsrc_t ra, rb;
+  int left = 0;
+  auto buf = [](const float* q) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(q), 0, (int)OUTSIDE, 0x00020000); };
+  auto next_step = [&] {   // where the next step's loads are; zeros beyond the last one
+    while (lk >= lK && more) {
+      const F32Tile t = nx;
+      more = ahead.next(nx);
+      lK = t.K;
+      lk = 0;
+      const int n0 = t.bx * (MODE == FWD1 ? T / 2 : T);
+      a0 = static_cast<const float*>(p.A) + (VARM ? (long long)t.row0 * lda : (long long)t.kbeg * lda + t.row0);
+      b0 = static_cast<const float*>(p.B) + (VARM ? (long long)t.group * p.b_group_stride : (long long)t.kbeg * ldb) + (Op::B_KC ? (long long)n0 * ldb : n0);
+      if (MODE == FWD1 && (wave & 2)) b0 += (long long)p.f * ldb;   // a wavefront loads gate or up columns
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const int q = tid + 256 * (x & 1), extent = x < 2 ? t.row1 - t.row0 : N - n0, ld = x < 2 ? lda : ldb;
+        if (x < 2 ? Op::A_KC : Op::B_KC) {
+          const int r = q >> 3;   // FWD1: every 32 columns are 16 gate and the 16 up columns of the same hidden units
+          vo[x] = 4u * (unsigned)(min(x >= 2 && MODE == FWD1 ? (r >> 5) * 16 + (r & 15) : r, extent - 1) * ld + kr[x]);
+        } else {
+          const int c = (q & (T / 4 - 1)) * 4;
+          vo[x] = 4u * (unsigned)(kr[x] * ld + (c < extent ? c : 0));
+        }
+      }
+    }
+    left = lK - lk;
+    ra = buf(a0 + (Op::A_KC ? (long long)lk : (long long)lk * lda));
+    rb = buf(b0 + (Op::B_KC ? (long long)lk : (long long)lk * ldb));
+    if (left > 0) lk += F32S_BK;
+  };
+  uintx4 sg[2][4];
+  float largest = 0.f;   // of all values this thread has split
+  auto load = [&](auto sc, auto xc) {
+    constexpr int x = decltype(xc)::value;
+    sg[decltype(sc)::value][x] = __builtin_amdgcn_raw_buffer_load_b128(x < 2 ? ra : rb, (int)(kr[x] < left ? vo[x] : OUTSIDE), 0, 0);
+  };
+  // plane q of load x: the bf16 nearest to what is left of the value
+  auto split = [&](auto sc, auto xc, auto qc) {
+    constexpr int S = decltype(sc)::value, x = decltype(xc)::value, q = decltype(qc)::value;
+    uintx4& v = sg[S][x];
+    if constexpr (q == 0) {
+      asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(largest) : "v"(v[0]), "v"(v[1]));
+      asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(largest) : "v"(v[2]), "v"(v[3]));
+    }
+    const unsigned lo = pack_bf16x2(__uint_as_float(v[0]), __uint_as_float(v[1])), hi = pack_bf16x2(__uint_as_float(v[2]), __uint_as_float(v[3]));
+    *reinterpret_cast<uint2*>(smem + S * ST + ls[x] + q * PL) = make_uint2(lo, hi);
+    if constexpr (q < 2) {
+      v[0] = __float_as_uint(__uint_as_float(v[0]) - __uint_as_float(lo << 16));
+      v[1] = __float_as_uint(__uint_as_float(v[1]) - __uint_as_float(lo & 0xffff0000u));
+      v[2] = __float_as_uint(__uint_as_float(v[2]) - __uint_as_float(hi << 16));
+      v[3] = __float_as_uint(__uint_as_float(v[3]) - __uint_as_float(hi & 0xffff0000u));
+    }
+  };
+
+  // ---- fragments
+  unsigned adA[Op::A_KC ? 1 : MI], adB[Op::B_KC ? 1 : NJ];   // byte addresses of a lane's fragments in stage 0
+  const unsigned lds = (unsigned)(size_t)SYMI_LPTR(smem);
+  {
+    const unsigned kc = jj * 64 + ((g4 ^ kc_swz(jj)) << 4), ks = (8 * g4 + (jj >> 2)) * 2 * T + (jj & 3) * 8;
+    const int sw = swizzle(8 * g4 + (jj >> 2));
+#pragma unroll
+    for (int i = 0; i < (Op::A_KC ? 1 : MI); ++i) adA[i] = lds + (Op::A_KC ? wm * WR * 64 + kc : ks + (((wm * MI + i) ^ sw) << 5));
+#pragma unroll
+    for (int j = 0; j < (Op::B_KC ? 1 : NJ); ++j) adB[j] = lds + 3 * PL + (Op::B_KC ? wn * WC * 64 + kc : ks + (((wn * NJ + j) ^ sw) << 5));
+  }
+  // Reads and matrix instructions are inline assembly in the order in which they are to be issued: left to itself the compiler
+  // reads a fragment just ahead of its use and waits for it.
+  bf16x8 fa[3][MI], fb[4][NJ];   // fb[0], fb[3]: plane 0 of even and odd steps
+  auto read = [&](bf16x8& f, auto kcc, auto ofsc, unsigned at) {
+    constexpr int OFS = decltype(ofsc)::value;
+    if constexpr (decltype(kcc)::value) {
+      asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f) : "v"(at), "n"(OFS));
+    } else {
+      shortx4 x, y;
+      asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4"
+                   : "=&v"(x), "=&v"(y) : "v"(at), "n"(OFS), "n"(OFS + 8 * T));
+      union { shortx4 h[2]; bf16x8 v; } u;
+      u.h[0] = x;
+      u.h[1] = y;
+      f = u.v;
+    }
+  };
+  // fragment r of planes qa, qb (qb into register set fb[sb]) of stage S: the left operand's first
+  auto read_frag = [&](auto sc, auto qac, auto qbc, auto sbc, auto rc) {
+    constexpr int S = decltype(sc)::value, QA = decltype(qac)::value, QB = decltype(qbc)::value, SB = decltype(sbc)::value, r = decltype(rc)::value;
+    if constexpr (r < MI) read(fa[QA][r], std::integral_constant<bool, Op::A_KC>{}, IC<S * ST + QA * PL + (Op::A_KC ? r * 1024 : 0)>{}, adA[Op::A_KC ? 0 : r]);
+    else if constexpr (r < MI + NJ)
+      read(fb[SB][r - MI], std::integral_constant<bool, Op::B_KC>{}, IC<S * ST + QB * PL + (Op::B_KC ? (r - MI) * 1024 : 0)>{}, adB[Op::B_KC ? 0 : r - MI]);
+  };
+  auto landed = [] { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };
+  floatx4 acc[MI][NJ], c[MI][NJ];
+  constexpr int NP = MI * NJ, PS = 5 * NP / 12;
+  static_assert(MI + NJ <= NP && 12 * PS <= 5 * NP, "a phase has room for its reads, a step for its splits");
+  // One step, stage S: six phases, each the product of two planes, the small ones first.  Beside them go the reads of the
+  // next phases' fragments, and in the first five the next step's splits into the other stage with the loads of the step
+  // after the next but one; in the last one the other stage is entered.
+  auto phase = [&](auto sc, auto pc, auto qac, auto qbc) {
+    constexpr int S = decltype(sc)::value, P = decltype(pc)::value, QA = decltype(qac)::value, QB = decltype(qbc)::value;
+    __builtin_amdgcn_sched_barrier(0);
+    unroll<NP>([&](auto mc) {
+      constexpr int m = decltype(mc)::value, i = m / NJ, j = m % NJ;
+      if constexpr (P == 0) {
+        asm volatile("" : "+v"(c[i][j]));
+        acc[i][j] += c[i][j];
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(c[i][j]) : "v"(fb[QB][j]), "v"(fa[QA][i]));
+      } else {
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c[i][j]) : "v"(fb[QB][j]), "v"(fa[QA][i]));
+      }
+      if constexpr (P == 0) read_frag(sc, IC<0>{}, IC<2>{}, IC<2>{}, mc);
+      if constexpr (P == 1) read_frag(sc, IC<1>{}, IC<1>{}, IC<1>{}, mc);
+      if constexpr (P == 5) read_frag(IC<S ^ 1>{}, IC<2>{}, IC<0>{}, IC<S ? 0 : 3>{}, mc);
+      constexpr int n = P * NP + m, piece = n / PS;
+      if constexpr (n % PS == 0 && piece < 12) {
+        constexpr int x = piece / 3, q = piece % 3;
+        split(IC<S ^ 1>{}, IC<x>{}, IC<q>{});
+        if constexpr (q == 2) load(IC<S ^ 1>{}, IC<x>{});
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  auto step = [&](auto sc) {
+    constexpr int S = decltype(sc)::value;
+    next_step();
+    landed();
+    phase(sc, IC<0>{}, IC<2>{}, IC<S ? 3 : 0>{});
+    landed();
+    phase(sc, IC<1>{}, IC<0>{}, IC<2>{});
+    landed();
+    phase(sc, IC<2>{}, IC<1>{}, IC<1>{});
+    phase(sc, IC<3>{}, IC<1>{}, IC<S ? 3 : 0>{});
+    phase(sc, IC<4>{}, IC<0>{}, IC<1>{});
+    meet();
+    phase(sc, IC<5>{}, IC<0>{}, IC<S ? 3 : 0>{});
+  };
+
+  F32Walk<MODE> walk(p, groups);
+  F32Tile t;
+  bool have = walk.next(t);
+  int tiles = 0, k0 = 0;
+  auto clear = [&] {
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) acc[i][j] = c[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  };
+  auto write_out = [&] {
+    bool bad = largest > 0x1p40f;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float x = fabsf(acc[i][j][e]);
+          bad |= !(x <= 3.4e38f) || (x < 0x1p-64f && x > 0.f);
+        }
+    if (bad) atomicOr(&redo[(tiles >> 5) & 31], 1u << (tiles & 31));
+    if (!VARM && t.K == 0 && p.skip_empty) return;
+    const int n0 = t.bx * (MODE == FWD1 ? T / 2 : T);
+    const long long rb0 = t.row0 + wm * WR;
+    const int rows = t.row1 - (int)rb0, twof = 2 * p.f;
+    auto store = [&](float* base, bool in, unsigned at, floatx4 x) {
+      const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)OUTSIDE, 0x00020000);
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4, x), rsrc, (int)(in ? at * 4u : OUTSIDE), 0, 0);
+    };
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      const int row = 16 * i + jj;
+      if constexpr (MODE == FWD1) {
+        float* const UVo = static_cast<float*>(p.UVout) + rb0 * twof;
+        float* const Ho = static_cast<float*>(p.H) + rb0 * p.f;
+        const int col = n0 + wn * 16 + 4 * g4;
+        const bool in = row < rows && col < N;
+        floatx4 h;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) h[e] = silu_f(acc[i][0][e]) * acc[i][1][e];
+        store(UVo, in, (unsigned)(row * twof + col), acc[i][0]);
+        store(UVo + p.f, in, (unsigned)(row * twof + col), acc[i][1]);
+        store(Ho, in, (unsigned)(row * p.f + col), h);
+      } else if constexpr (MODE == BWD_DH) {
+        float* const Co = static_cast<float*>(p.C) + rb0 * twof;
+        floatx4 u[NJ], v[NJ];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const float* const q = static_cast<const float*>(p.UV) + (rb0 + min(row, rows - 1)) * twof + min(n0 + wn * WC + 16 * j + 4 * g4, N - 4);
+          u[j] = *reinterpret_cast<const floatx4*>(q);
+          v[j] = *reinterpret_cast<const floatx4*>(q + p.f);
+        }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const int col = n0 + wn * WC + 16 * j + 4 * g4;
+          const bool in = row < rows && col < N;
+          floatx4 du, dv;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float dh = acc[i][j][e], u_ = u[j][e], sgm = sigmoid_f(u_);
+            du[e] = dh * v[j][e] * sgm * (1.f + u_ * (1.f - sgm));
+            dv[e] = dh * u_ * sgm;
+          }
+          store(Co, in, (unsigned)(row * twof + col), du);
+          store(Co + p.f, in, (unsigned)(row * twof + col), dv);
+        }
+      } else {
+        float* const Co = static_cast<float*>(p.C) + (VARM ? 0 : (long long)t.group * p.c_group_stride) + rb0 * p.N;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const int col = n0 + wn * WC + 16 * j + 4 * g4;
+          store(Co, row < rows && col < N, (unsigned)(row * p.N + col), acc[i][j]);
+        }
+      }
+    }
+  };
+  auto advance = [&] {   // the next tile with a sum
+    do {
+      write_out();
+      ++tiles;
+      have = walk.next(t);
+      clear();
+    } while (have && t.K == 0);
+    k0 = 0;
+  };
+  auto last_step = [&]() -> bool {   // behind a step: the tile's sums are complete
+    k0 += F32S_BK;
+    if (k0 < t.K) return false;
+    // the next step's fragments are kept until they have landed
+    landed();
+#pragma unroll
+    for (int i = 0; i < MI; ++i) asm volatile("" : "+v"(fa[2][i]));
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) asm volatile("" : "+v"(fb[0][j]), "+v"(fb[3][j]));
+    asm volatile("s_nop 15" ::: "memory");   // the last matrix instruction's results
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        asm volatile("" : "+v"(c[i][j]));
+        acc[i][j] += c[i][j];
+      }
+    advance();
+    return !have;
+  };
+  clear();
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) fb[0][j] = fb[3][j] = bf16x8{};
+  while (have && t.K == 0) {
+    write_out();
+    ++tiles;
+    have = walk.next(t);
+  }
+  if (have) {
+    next_step();
+    unroll<4>([&](auto x) { load(IC<0>{}, x); });
+    __builtin_amdgcn_sched_barrier(0);
+    next_step();
+    unroll<4>([&](auto x) { load(IC<1>{}, x); });
+    __builtin_amdgcn_sched_barrier(0);
+    next_step();
+    unroll<4>([&](auto x) {
+      split(IC<0>{}, x, IC<0>{});
+      split(IC<0>{}, x, IC<1>{});
+      split(IC<0>{}, x, IC<2>{});
+      load(IC<0>{}, x);
+    });
+    meet();
+    unroll<MI + NJ>([&](auto r) { read_frag(IC<0>{}, IC<2>{}, IC<0>{}, IC<0>{}, r); });
+    for (;;) {
+      step(IC<0>{});
+      if (last_step()) break;
+      step(IC<1>{});
+      if (last_step()) break;
+    }
+  }
+
+  // ---- tiles with a sum that is not finite or too small, or with large factors: once more on the fp32 instruction
+  meet();
+  unsigned any = 0;
+#pragma unroll
+  for (int q = 0; q < 32; ++q) any |= redo[q];
+  if (__builtin_amdgcn_readfirstlane(any) == 0) return;
+  walk.i = 0;
+  for (int n = 0; walk.next(t); ++n) {
+    if (!(__builtin_amdgcn_readfirstlane(redo[(n >> 5) & 31]) >> (n & 31) & 1)) continue;
+    F32Operands<MODE> o;
+    o.K = t.K;
+    o.group = t.group;
+    o.lda = lda;
+    o.ldb = ldb;
+    o.B = static_cast<const float*>(p.B) + (VARM ? (long long)t.group * p.b_group_stride : (long long)t.kbeg * o.ldb);
+    const int n0 = t.bx * (MODE == FWD1 ? T / 2 : T);
+    o.row0 = t.row0;
+    o.row1 = t.row1;
+    o.A = static_cast<const float*>(p.A) + (VARM ? (long long)t.row0 * o.lda : (long long)t.kbeg * o.lda + t.row0);
+    meet();
+    f32_tile<MODE>(p, o, n0, min(N, n0 + (MODE == FWD1 ? T / 2 : T)), reinterpret_cast<float*>(smem));
   }
 }
 
@@ -1802,30 +2237,29 @@ static void launch_gemm(const symi_ctx* ctx, const GemmParams& p, int n_cols, in
     const int groups = p.per_slot ? cfg->S_tot : cfg->E;
     const int ntx = cdiv(n_cols, MODE == FWD1 ? 64 : 128);
     // Count of 64 x 128 tiles (variable rows: about half a tile of padding per slot).  Below one round of them the shared
-    // reduction, below four the 64-wide tile, which makes twice as many workgroups.  us, shared reduction / 64 wide /
-    // 128 wide: W2 gradient - / 88 / 121 at 504 tiles; second forward product and input gradient 51 / 54 / -
-    // and 100 / 98 / - at 186, 19 / 16 / - and 32 / 26 / - at 192 with K = 256 and 512, where the shared reduction stays all
-    // the same, as its sums are the more exact ones (1.9e-7 : 2.2e-7); - / 126 / 146 and - / 247 / 284 at 543.  64-wide tiles of 32-deep steps while four to a
-    // unit hold all of them (948: 92 and 171 against 99 and 185 16 deep), beyond that 16 deep, six to a unit (1088: 132 and
-    // 272 against 126 and 247).
+    // reduction, whose time is the latency of a tile; beyond it the split one.  A class's weight gradient reduces over up to T
+    // rows, and the most popular class makes the longest chain there is, which the shared reduction cuts in eight: there up to
+    // two rounds (24 classes, d = 80, f = 376, 4940 tokens: step 232 -> 167 us, 24 classes of d = 280, f = 512 backward 184 ->
+    // 142), but not for single slots, which placement keeps even (36 slots of 352 rows, d = 184, f = 288 169 : 177).  Groups of
+    // a few rows are bound by their stores, which the fp32 tile has more of in flight: slots of 1 - 5 rows 164 : 172 (54 slots
+    // of d = 312, f = 992), 86 : 90 (32 slots of d = 296, f = 552), the split one from some 16 rows on.
     const long long rows = VARM ? (long long)cfg->T * cfg->k / F32_BM + cfg->S_tot / 2 : (long long)cdiv(p.M, F32_BM) * groups;
-    if (rows * ntx < 1LL * ctx->cus) {
-      dim3 grid(cdiv(n_cols, 32), VARM ? 8 * max_mtiles : cdiv(p.M, 32), VARM ? 1 : groups);
+    const long long mean = (long long)cfg->T * cfg->k / groups;
+    if (rows * ntx < (!VARM && !p.per_slot && mean >= 64 ? 2 : 1) * ctx->cus) {
+      dim3 grid(cdiv(n_cols, 32), VARM ? 2 * (cfg->T * cfg->k / FEW_BM + cfg->S_tot) : cdiv(p.M, 32), VARM ? 1 : groups);
       SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_f32_small_kernel<MODE, NW><<<grid, 64 * NW, 0, st>>>(p)));
       return;
     }
-    const int gy = VARM ? 4 * max_mtiles : cdiv(p.M, F32_BM), gz = VARM ? 1 : groups;
-    if constexpr (MODE != FWD1) {
-      if (rows * ntx < 4LL * ctx->cus) {
-        const dim3 grid(cdiv(n_cols, 64), gy, gz);
-        if (!VARM || rows * cdiv(n_cols, 64) <= 4LL * ctx->cus)
-          SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_f32_kernel<MODE, 1, 32><<<grid, 256, 0, st>>>(p)));
-        else
-          SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_f32_kernel<MODE, 1, 16><<<grid, 256, 0, st>>>(p)));
+    if constexpr (!VARM) {
+      if (mean < 16) {
+        SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_f32_kernel<MODE><<<dim3(ntx, cdiv(p.M, F32_BM), groups), 256, 0, st>>>(p)));
         return;
       }
     }
-    SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_f32_kernel<MODE, 2, 32><<<dim3(ntx, gy, gz), 256, 0, st>>>(p)));
+    const long long cols = cdiv(n_cols, MODE == FWD1 ? F32S_T / 2 : F32S_T);
+    const long long tiles = cols * (VARM ? (long long)cfg->T * cfg->k / F32S_T + cfg->S_tot : (long long)cdiv(p.M, F32S_T) * groups);
+    SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st,
+               (gemm_f32_split_kernel<MODE><<<(unsigned)std::min(tiles, 3LL * ctx->cus), 256, 0, st>>>(p, groups)));
   }
 }
 
@@ -1863,9 +2297,9 @@ extern "C" int symi_expert_fwd(const symi_ctx* ctx, const void* Xp, const int32_
   const WsLayout& L = ctx->L;
   int32_t* map = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + L.tile_map);
   const int max_mtiles = (int)(A / GEMM_BM) + cfg->S_tot;
-  if (few_rows(cfg) && few_rows_table(ctx))
+  if (cfg->dtype == SYMI_F32 || (few_rows(cfg) && few_rows_table(ctx)))
     SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<FEW_BM><<<1, 256, 0, st>>>(slot_offsets, nullptr, cfg->S_tot, cfg->E, map, nullptr)));
-  else if (!few_rows(cfg) && !(mid_tile(ctx, FWD1) && mid_tile(ctx, FWD2)))
+  else if (cfg->dtype == SYMI_BF16 && !few_rows(cfg) && !(mid_tile(ctx, FWD1) && mid_tile(ctx, FWD2)))
     SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<GEMM_BM><<<1, 256, 0, st>>>(slot_offsets, nullptr, cfg->S_tot, cfg->E, map, nullptr)));
 
   GemmParams p = {};
@@ -1929,7 +2363,10 @@ static int expert_bwd_impl(const char* who, const symi_ctx* ctx, const void* dYp
   set_split(ctx, ws, p);
   p.d = cfg->d;
   p.f = cfg->f;
-  SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<GEMM_BM><<<1, 256, 0, st>>>(slot_offsets, first_slot, cfg->S_tot, cfg->E, map, order)));
+  if (cfg->dtype == SYMI_F32)
+    SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<FEW_BM><<<1, 256, 0, st>>>(slot_offsets, first_slot, cfg->S_tot, cfg->E, map, order)));
+  else
+    SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<GEMM_BM><<<1, 256, 0, st>>>(slot_offsets, first_slot, cfg->S_tot, cfg->E, map, order)));
   // worth it only while a product is a few rounds of workgroups: with many rounds the chip is
   // full anyway and two kernels sharing it only disturb each other's L2 locality; and not for the
   // smallest, where fork, hand-over and join take longer than what they hide (symi_create

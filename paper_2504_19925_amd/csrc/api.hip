@@ -69,6 +69,22 @@ int check_cfg(const symi_cfg* c, const char* who) {
   return SYMI_OK;
 }
 
+// Both backward products of a bf16 gate network run in one kernel that reads X, dX and dlogits once.
+bool router_fused(const symi_cfg* c) { return c->dtype == SYMI_BF16 && c->E <= 128 && c->E % 8 == 0; }
+
+// Tokens per partial weight gradient of the gate network (a function of the configuration only: same bits every run).  Fused: a workgroup
+// walks a chunk in blocks of 128 tokens, some 4.5 us each, and one fits a compute unit, so there are as many chunks as
+// give 256 units one workgroup of every 128 columns.  With at least 512 tokens to a chunk, as with the others, 846 tokens
+// of E = 48, d = 224 were four workgroups.  The others: 512, in bf16 doubled while that leaves more than 1024 workgroups.
+int router_chunk(const symi_cfg* c) {
+  const int cols = cdiv(c->d, 128);
+  if (router_fused(c)) return std::max(1, cdiv(cdiv(c->T, std::max(1, 256 / cols)), 128)) * 128;
+  int chunk = 512;
+  if (c->dtype == SYMI_BF16)
+    while ((long long)cdiv(c->T, chunk) * cols * cdiv(c->E, 128) > 1024 && chunk < 16384) chunk *= 2;
+  return chunk;
+}
+
 WsLayout ws_layout(const symi_cfg* c) {
   WsLayout L;
   const size_t A = (size_t)c->T * c->k;
@@ -90,7 +106,7 @@ WsLayout ws_layout(const symi_cfg* c) {
   L.split_part = off;
   off += c->dtype == SYMI_BF16 ? (size_t)SPLIT_CUS * SPLIT_TILE_BYTES : 0;
   L.router_partial = off;
-  off += align_up(((size_t)c->T + 511) / 512 * c->E * c->d * sizeof(float), 256);
+  off += align_up((size_t)cdiv(c->T, router_chunk(c)) * c->E * c->d * sizeof(float), 256);
   L.router_bias_partial = off;
   off += align_up(((size_t)c->T + 255) / 256 * c->E * sizeof(float), 256);
   L.total = off + 256;

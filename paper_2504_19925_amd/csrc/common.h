@@ -79,6 +79,8 @@ struct WsLayout {
   size_t total;
 };
 WsLayout ws_layout(const symi_cfg* cfg);
+bool router_fused(const symi_cfg* cfg);
+int router_chunk(const symi_cfg* cfg);
 
 constexpr int DISPATCH_CHUNK = 1024;  // assignments ranked by one workgroup
 constexpr int GEMM_BM = 256;          // rows of one m-tile in the tile map

@@ -9,8 +9,12 @@
 // are plain 16-byte reads) or reduction-strided (LDS tile [k][row] as in memory, fragments come
 // from the transposing LDS read ds_read_b64_tr_b16); several workgroups per compute unit hide
 // the latency.
-// The weight gradient's reduction runs over all T tokens: it is cut into chunks of at least
-// 512 tokens whose partial products are summed by a second kernel in a fixed order.
+// The weight gradient's reduction runs over all T tokens: it is cut into chunks (router_chunk) whose partial products
+// are summed by a second kernel in a fixed order; a single chunk's sums are the gradient.
+// The whole backward is one launch of products and bias sums and, beyond 128 tokens, one that adds the chunks up: as four to five
+// launches small batches took some 4 us for each.  Gate network with the dispatch's backward, us: T = 636, E = 128, d = 208
+// 37 -> 19, 134, 48, 600 29 -> 21, 2261, 12, 1312 73 -> 62, 44033, 48, 152 95 -> 72, 65536, 128, 4096 1502 -> 1492; fp32 (with the logits' lane groups and the
+// weight gradient's loads without branches): 139, 4, 384 37 -> 13, 1769, 16, 512 57 -> 24, 4683, 24, 96 44 -> 23.
 // With E <= 128 (a multiple of 8) the two backward products run in one kernel that reads X,
 // dX and dlogits once (router_bwd_fused_kernel below); other E take the shared kernel twice.
 // fp32 configurations take plain FMA kernels instead.
@@ -30,7 +34,7 @@ constexpr int RLS = RT + 32;   // padded LDS row of a [k][row] tile (320 B: four
 constexpr int RTILE = RT * RLD > RK * RLS ? RT * RLD : RK * RLS;
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short rshortx4;
 typedef unsigned int ru32x4 __attribute__((ext_vector_type(4)));
-constexpr int RCHUNK = 512;    // tokens per partial weight gradient, at least
+constexpr int RCHUNK = 512;    // tokens per partial weight gradient (fp32)
 
 enum { R_DX = 1, R_DW = 2 };
 
@@ -42,6 +46,9 @@ struct RouterParams {
   float* partial;       // [nchunk,E,d]
   int T, E, d;
   int chunk;            // tokens per partial weight gradient
+  int nchunk;           // partial weight gradients
+  float* bias;          // [nbias,E] partial bias gradients, nullptr: not wanted
+  int nbias;
 };
 
 __device__ __forceinline__ uint4 pack8(const float (&v)[8]) {
@@ -87,19 +94,45 @@ __device__ __forceinline__ uint4 load8_strided(const void* src, long long ld, in
   }
   return pack8(v);
 }
+// db[e] = sum_t dl[t,e] in two fixed-order stages: per chunk of 256 tokens, then over the
+// chunks.  First stage, chunk c, in workgroups that the launch of the products has behind its own (256 threads of each): threads
+// along e (every row is read contiguously), and where E < 256
+// the rows of the chunk are dealt out over 256 / E groups of threads whose sums are added in
+// group order; eight independent loads in flight per thread.
+__device__ __forceinline__ void router_bias_partial(const float* __restrict__ dl, int T, int E, int c, float* __restrict__ part,
+                                                    double* const red) {
+  const int tid = threadIdx.x;
+  const int t0 = c * 256, t1 = min(T, t0 + 256);
+  const int cols = min(E, 256), groups = 256 / cols;
+  const int g = tid / cols, ec = tid - g * cols;
+  for (int eb = 0; eb < E; eb += cols) {   // the same trip count for every thread
+    const int e = eb + ec;
+    double s = 0.0;   // the summands cancel heavily: accumulate in binary64
+    if (g < groups && e < E) {
+#pragma unroll 8
+      for (int t = t0 + g; t < t1; t += groups) s += (double)dl[(long long)t * E + e];
+    }
+    if (tid < 256) red[tid] = s;
+    __syncthreads();
+    if (g == 0 && e < E) {
+      for (int q = 1; q < groups; ++q) s += red[q * cols + ec];
+      part[(long long)c * E + e] = (float)s;
+    }
+    __syncthreads();
+  }
+}
+
 template <int MODE>
-__global__ __launch_bounds__(256) void router_gemm_kernel(RouterParams p) {
-  __shared__ __attribute__((aligned(16))) uint16_t As[RTILE];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[RTILE];
+__device__ __forceinline__ void router_gemm(const RouterParams& p, uint16_t* const As, uint16_t* const Bs, const int by, const int bz) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   // output rows M, columns N, reduction range [kbeg, kend)
   const int M = MODE == R_DW ? p.E : p.T;
   const int N = p.d;
-  const int m0 = blockIdx.y * RT, n0 = blockIdx.x * RT;
+  const int m0 = by * RT, n0 = blockIdx.x * RT;
   int kbeg = 0, kend = MODE == R_DX ? p.E : p.T;
   if (MODE == R_DW) {
-    kbeg = blockIdx.z * p.chunk;
+    kbeg = bz * p.chunk;
     kend = min(p.T, kbeg + p.chunk);
   }
   rfloatx16 acc[2][2];
@@ -255,7 +288,7 @@ __global__ __launch_bounds__(256) void router_gemm_kernel(RouterParams p) {
             *o = make_uint2(pack_bf16x2(__uint_as_float(old.x << 16) + x[0], __uint_as_float(old.x & 0xffff0000u) + x[1]),
                             pack_bf16x2(__uint_as_float(old.y << 16) + x[2], __uint_as_float(old.y & 0xffff0000u) + x[3]));
           } else {
-            *reinterpret_cast<float4*>(p.partial + (long long)blockIdx.z * M * N + at) = make_float4(x[0], x[1], x[2], x[3]);
+            *reinterpret_cast<float4*>(p.partial + (long long)bz * M * N + at) = make_float4(x[0], x[1], x[2], x[3]);
           }
         } else {
 #pragma unroll
@@ -265,11 +298,28 @@ __global__ __launch_bounds__(256) void router_gemm_kernel(RouterParams p) {
               uint16_t* o = static_cast<uint16_t*>(p.dX) + at + c;
               *o = f32_to_bf16(bf16_to_f32(*o) + x[c]);
             } else {
-              p.partial[(long long)blockIdx.z * M * N + at + c] = x[c];
+              p.partial[(long long)bz * M * N + at + c] = x[c];
             }
           }
         }
       }
+  }
+}
+
+// The weight gradient's workgroups first, which have the longer reductions, then those of dX and of the bias gradient: none
+// waits for another, and as launches of their own each took some 4 us.
+__global__ __launch_bounds__(256) void router_gemm_kernel(RouterParams p) {
+  __shared__ __attribute__((aligned(16))) uint16_t As[RTILE];
+  __shared__ __attribute__((aligned(16))) uint16_t Bs[RTILE];
+  const int ey = (p.E + RT - 1) / RT, ndw = ey * p.nchunk, ndx = (p.T + RT - 1) / RT;
+  int y = blockIdx.y + blockIdx.z * gridDim.y;
+  if (y < ndw) {
+    router_gemm<R_DW>(p, As, Bs, y % ey, y / ey);
+  } else if (y < ndw + ndx) {
+    router_gemm<R_DX>(p, As, Bs, y - ndw, 0);
+  } else {
+    const int c = (y - ndw - ndx) * gridDim.x + blockIdx.x;
+    if (p.bias && c < p.nbias) router_bias_partial(p.dl, p.T, p.E, c, p.bias, reinterpret_cast<double*>(As));
   }
 }
 
@@ -294,6 +344,11 @@ __global__ __launch_bounds__(256) void router_bwd_fused_kernel(RouterParams p) {
   const int wm = wave >> 1, wn = wave & 1;
   const int T = p.T, E = p.E, d = p.d;
   const int n0 = blockIdx.x * RT;
+  if ((int)blockIdx.y >= p.nchunk) {   // behind the products' workgroups
+    const int c = ((int)blockIdx.y - p.nchunk) * gridDim.x + blockIdx.x;
+    if (c < p.nbias) router_bias_partial(p.dl, T, E, c, p.bias, reinterpret_cast<double*>(DLt));
+    return;
+  }
   const int t_beg = blockIdx.y * p.chunk, t_end = min(T, t_beg + p.chunk);
   const uint16_t* const X = static_cast<const uint16_t*>(p.X);
   const uint16_t* const Wr = static_cast<const uint16_t*>(p.Wr);
@@ -503,51 +558,24 @@ __global__ __launch_bounds__(256) void router_bwd_fused_kernel(RouterParams p) {
   }
 }
 
-// dWr[e,n] = sum over chunks of partial[chunk,e,n], chunks in ascending order
-__global__ __launch_bounds__(256) void router_reduce_kernel(const float* __restrict__ partial, int nchunk,
-                                                            long long n, float* __restrict__ dWr) {
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long long)gridDim.x * 256) {
-    float s = 0.f;
-    for (int c = 0; c < nchunk; ++c) s += partial[(long long)c * n + i];
-    dWr[i] = s;
-  }
-}
-
-// db[e] = sum_t dl[t,e] in two fixed-order stages: per chunk of 256 tokens, then over the
-// chunks.  First stage: threads along e (every row is read contiguously), and where E < 256
-// the rows of the chunk are dealt out over 256 / E groups of threads whose sums are added in
-// group order; eight independent loads in flight per thread.
-__global__ __launch_bounds__(256) void router_bias_partial_kernel(const float* __restrict__ dl, int T, int E,
-                                                                  float* __restrict__ part) {
+// Behind the products: dWr[e,n] = sum over chunks of partial[chunk,e,n], chunks in ascending order (the first `nred` workgroups), and the second stage
+// of the bias gradient, one workgroup per class: thread c adds chunks c, c + 256, ... in ascending
+// order, then the 256 sums are added pairwise in a fixed tree.
+__global__ __launch_bounds__(256) void router_finish_kernel(RouterParams p, int nred, float* __restrict__ dWr, float* __restrict__ db) {
   __shared__ double red[256];
   const int tid = threadIdx.x;
-  const int t0 = blockIdx.x * 256, t1 = min(T, t0 + 256);
-  const int cols = min(E, 256), groups = 256 / cols;
-  const int g = tid / cols, ec = tid - g * cols;
-  for (int eb = 0; eb < E; eb += cols) {   // the same trip count for every thread
-    const int e = eb + ec;
-    double s = 0.0;   // the summands cancel heavily: accumulate in binary64
-    if (g < groups && e < E) {
+  if ((int)blockIdx.x < nred) {
+    const long long n = (long long)p.E * p.d, i = (long long)blockIdx.x * 256 + tid;
+    if (i >= n) return;
+    float s = 0.f;
 #pragma unroll 8
-      for (int t = t0 + g; t < t1; t += groups) s += (double)dl[(long long)t * E + e];
-    }
-    red[tid] = s;
-    __syncthreads();
-    if (g == 0 && e < E) {
-      for (int q = 1; q < groups; ++q) s += red[q * cols + ec];
-      part[(long long)blockIdx.x * E + e] = (float)s;
-    }
-    __syncthreads();
+    for (int c = 0; c < p.nchunk; ++c) s += p.partial[(long long)c * n + i];
+    dWr[i] = s;
+    return;
   }
-}
-// Second stage, one workgroup per class: thread c adds chunks c, c + 256, ... in ascending
-// order, then the 256 sums are added pairwise in a fixed tree.
-__global__ __launch_bounds__(256) void router_bias_final_kernel(const float* __restrict__ part, int nchunk,
-                                                                int E, float* __restrict__ db) {
-  __shared__ double red[256];
-  const int e = blockIdx.x, tid = threadIdx.x;
+  const int e = blockIdx.x - nred;
   double s = 0.0;
-  for (int c = tid; c < nchunk; c += 256) s += (double)part[(long long)c * E + e];
+  for (int c = tid; c < p.nbias; c += 256) s += (double)p.bias[(long long)c * p.E + e];
   red[tid] = s;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
@@ -557,55 +585,69 @@ __global__ __launch_bounds__(256) void router_bias_final_kernel(const float* __r
   if (tid == 0) db[e] = (float)red[0];
 }
 
-// ---- fp32 configurations: plain FMAs; logits and dX one output element per thread, in index order
+// ---- fp32 configurations: plain FMAs
+// Eight lanes share the reductions of a token with four classes: pieces of eight indices dealt out in turn, 256 consecutive
+// bytes of X and of each row of Wr per load round, the eight sums added in a fixed tree.  Bound by latency: with one
+// thread per logit, a chain of d / 8 rounds, T = 139, E = 16, d = 288 took 11.5 us; error 1.4e-7 -> 0.6e-7.
 __global__ __launch_bounds__(256) void router_fwd_f32_kernel(const float* __restrict__ X,
                                                              const float* __restrict__ Wr,
                                                              const float* __restrict__ b,
                                                              float* __restrict__ logits, int T, int E, int d) {
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (long long)T * E) return;
-  const int t = (int)(i / E), e = (int)(i - (long long)t * E);
-  const float* const x = X + (long long)t * d;
-  const float* const w = Wr + (long long)e * d;
-  float s = 0.f;
-  for (int k0 = 0; k0 < d; k0 += 8) {   // d is a multiple of 8: eight pairs of loads in flight
-    float a[8], b8[8];
+  const int lane = threadIdx.x & 7, eq = (E + 3) / 4;
+  const long long g = (long long)blockIdx.x * 32 + (threadIdx.x >> 3);
+  const long long t = min(g / eq, (long long)T - 1);   // lanes behind the last token repeat it and store nothing
+  const int e0 = (int)(g % eq) * 4;
+  const float* const x = X + t * d;
+  const float* w[4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      a[i] = x[k0 + i];
-      b8[i] = w[k0 + i];
+  for (int c = 0; c < 4; ++c) w[c] = Wr + (long long)min(e0 + c, E - 1) * d;
+  float s[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int k0 = lane * 8; k0 < d; k0 += 64) {   // d is a multiple of 8
+    float a[8], q[4][8];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      *reinterpret_cast<float4*>(a + 4 * h) = *reinterpret_cast<const float4*>(x + k0 + 4 * h);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) *reinterpret_cast<float4*>(q[c] + 4 * h) = *reinterpret_cast<const float4*>(w[c] + k0 + 4 * h);
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) s = fmaf(a[i], b8[i], s);
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) s[c] = fmaf(a[i], q[c][i], s[c]);
   }
-  logits[i] = s + (b ? b[e] : 0.f);
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int o = 4; o > 0; o >>= 1) s[c] += __shfl_xor(s[c], o, 64);
+  const int e = e0 + lane;
+  const float v = lane == 0 ? s[0] : lane == 1 ? s[1] : lane == 2 ? s[2] : s[3];
+  if (lane < 4 && e < E && g / eq < T) logits[t * E + e] = v + (b ? b[e] : 0.f);
 }
-__global__ __launch_bounds__(256) void router_dx_f32_kernel(const float* __restrict__ dl,
-                                                            const float* __restrict__ Wr,
-                                                            float* __restrict__ dX, int T, int E, int d) {
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (long long)T * d) return;
-  const int t = (int)(i / d), n = (int)(i - (long long)t * d);
+// dX one output element per thread, classes in index order
+__device__ __forceinline__ void router_dx_f32(const RouterParams& p, long long i) {
+  if (i >= (long long)p.T * p.d) return;
+  const int t = (int)(i / p.d), n = (int)(i - (long long)t * p.d);
+  const float* const Wr = static_cast<const float*>(p.Wr);
   float s = 0.f;
-  for (int e = 0; e < E; ++e) s = fmaf(dl[(long long)t * E + e], Wr[(long long)e * d + n], s);
-  dX[i] += s;
+#pragma unroll 8
+  for (int e = 0; e < p.E; ++e) s = fmaf(p.dl[(long long)t * p.E + e], Wr[(long long)e * p.d + n], s);
+  static_cast<float*>(p.dX)[i] += s;
 }
 // Partial weight gradient of a chunk of RCHUNK tokens: 64 columns x 8 classes per workgroup, the chunk's tokens dealt
 // out over 16 wavefronts (a lane holds one column of X and 8 sums, the 8 dlogits of a token are the same for the whole
 // wavefront).  Sums of 16 tokens first, then over a wavefront's 32 tokens, the wavefronts and, in
-// router_reduce_kernel, the chunks, all in ascending order.  Bound by latency: with one thread per output the whole
+// router_finish_kernel, the chunks, all in ascending order.  Bound by latency: with one thread per output the whole
 // reduction was one chain in E*d / 256 workgroups: gate network of T = 2800, E = 8, d = 128 641 us, now 39, and half the error.
 constexpr int RF_WAVES = 16, RF_CLASSES = 8;
 
-__global__ __launch_bounds__(64 * RF_WAVES) void router_dw_f32_kernel(const float* __restrict__ dl,
-                                                                      const float* __restrict__ X,
-                                                                      float* __restrict__ partial, int T, int E, int d) {
-  __shared__ float red[RF_WAVES][RF_CLASSES][64];
+__device__ __forceinline__ void router_dw_f32(const RouterParams& p, const int bx, const int by, const int bz, float* const red) {
+  const int T = p.T, E = p.E, d = p.d;
+  const float* const X = static_cast<const float*>(p.X);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int n = blockIdx.x * 64 + lane, e0 = blockIdx.y * RF_CLASSES;
+  const int n = bx * 64 + lane, e0 = by * RF_CLASSES;
   const int nc = min(n, d - 1);   // columns past the edge read the last one and are not stored
   constexpr int PER = RCHUNK / RF_WAVES;
-  const int t_beg = blockIdx.z * RCHUNK + wave * PER, t_end = min(T, t_beg + PER);
+  const int t_beg = bz * RCHUNK + wave * PER, t_end = min(T, t_beg + PER);
   float acc[RF_CLASSES];
 #pragma unroll
   for (int i = 0; i < RF_CLASSES; ++i) acc[i] = 0.f;
@@ -617,21 +659,39 @@ __global__ __launch_bounds__(64 * RF_WAVES) void router_dw_f32_kernel(const floa
     for (int j = 0; j < 16; ++j) x[j] = X[(long long)min(t0 + j, t_end - 1) * d + nc];
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-      if (t0 + j >= t_end) break;
-      const float* const row = dl + (long long)(t0 + j) * E;
+      // no branch around the loads: a token behind the last one reads the last one and adds 0 * 0
+      const bool in = t0 + j < t_end;
+      const float* const row = p.dl + (long long)min(t0 + j, t_end - 1) * E;
+      const float xj = in ? x[j] : 0.f;
 #pragma unroll
-      for (int i = 0; i < RF_CLASSES; ++i) part[i] = fmaf(row[min(e0 + i, E - 1)], x[j], part[i]);
+      for (int i = 0; i < RF_CLASSES; ++i) {
+        const float y = row[min(e0 + i, E - 1)];
+        part[i] = fmaf(in ? y : 0.f, xj, part[i]);
+      }
     }
 #pragma unroll
     for (int i = 0; i < RF_CLASSES; ++i) acc[i] += part[i];
   }
 #pragma unroll
-  for (int i = 0; i < RF_CLASSES; ++i) red[wave][i][lane] = acc[i];
+  for (int i = 0; i < RF_CLASSES; ++i) red[(wave * RF_CLASSES + i) * 64 + lane] = acc[i];
   __syncthreads();
   if (wave < RF_CLASSES && e0 + wave < E && n < d) {   // wavefront i sums class e0 + i
-    float s = red[0][wave][lane];
-    for (int w = 1; w < RF_WAVES; ++w) s += red[w][wave][lane];
-    partial[((long long)blockIdx.z * E + e0 + wave) * d + n] = s;
+    float s = red[wave * 64 + lane];
+    for (int w = 1; w < RF_WAVES; ++w) s += red[(w * RF_CLASSES + wave) * 64 + lane];
+    p.partial[((long long)bz * E + e0 + wave) * d + n] = s;
+  }
+}
+
+// Weight gradient, dX and the first stage of the bias gradient in one launch.
+__global__ __launch_bounds__(64 * RF_WAVES) void router_bwd_f32_kernel(RouterParams p, unsigned ndx) {
+  __shared__ __attribute__((aligned(16))) float red[RF_WAVES * RF_CLASSES * 64];
+  const unsigned dx = (p.d + 63) / 64, de = (p.E + RF_CLASSES - 1) / RF_CLASSES, ndw = dx * de * p.nchunk, b = blockIdx.x;
+  if (b < ndw) {
+    router_dw_f32(p, b % dx, b / dx % de, b / (dx * de), red);
+  } else if (b < ndw + ndx) {
+    router_dx_f32(p, (long long)(b - ndw) * (64 * RF_WAVES) + threadIdx.x);
+  } else {
+    router_bias_partial(p.dl, p.T, p.E, b - ndw - ndx, p.bias, reinterpret_cast<double*>(red));
   }
 }
 
@@ -649,7 +709,7 @@ extern "C" int symi_router_fwd(const symi_ctx* ctx, const void* X, const void* W
   if (cfg->dtype == SYMI_BF16) {
     launch_router_fwd(ctx, X, Wr, b, logits, st);
   } else {
-    SYMI_TIMED(ctx, K_ROUTER_FWD, st, (router_fwd_f32_kernel<<<cdiv((long long)T * E, 256), 256, 0, st>>>(
+    SYMI_TIMED(ctx, K_ROUTER_FWD, st, (router_fwd_f32_kernel<<<cdiv((long long)T * cdiv(E, 4), 32), 256, 0, st>>>(
         static_cast<const float*>(X), static_cast<const float*>(Wr), b, logits, T, E, d)));
   }
   SYMI_LAUNCH_CHECK("symi_router_fwd");
@@ -664,51 +724,31 @@ extern "C" int symi_router_bwd(const symi_ctx* ctx, const void* X, const void* W
   hipStream_t st = as_stream(stream);
   const int T = cfg->T, E = cfg->E, d = cfg->d;
   const WsLayout& L = ctx->L;
-  if (cfg->dtype == SYMI_BF16) {
-    RouterParams p = {};
-    p.X = X; p.Wr = Wr; p.dl = dlogits; p.dX = dX; p.T = T; p.E = E; p.d = d;
-    p.partial = reinterpret_cast<float*>(static_cast<char*>(ws) + L.router_partial);
-    // chunks of 512 tokens, doubled while that leaves more than 1024 workgroups: fewer partial
-    // products to write and read back (a function of the configuration only: same bits every run)
-    const int tiles = cdiv(d, RT) * cdiv(E, RT);
-    int chunk = RCHUNK;
-    while ((long long)cdiv(T, chunk) * tiles > 1024 && chunk < 16384) chunk *= 2;
-    const bool fused = E <= RT && E % 8 == 0;
-    if (fused) {
-      // one workgroup per compute unit at a time (its LDS): as many chunks as give every unit
-      // one workgroup, each then walks its row blocks with the next one in flight
-      const int per = std::max(1, ctx->cus / cdiv(d, RT));
-      chunk = std::max(RCHUNK, cdiv(cdiv(T, per), RT) * RT);
+  RouterParams p = {};
+  p.X = X; p.Wr = Wr; p.dl = dlogits; p.dX = dX; p.T = T; p.E = E; p.d = d;
+  p.chunk = router_chunk(cfg);
+  p.nchunk = cdiv(T, p.chunk);
+  p.nbias = db ? cdiv(T, 256) : 0;
+  // One chunk of either: its sums are the gradients.
+  const bool once = p.nchunk == 1 && p.nbias <= 1;
+  p.partial = once ? dWr : reinterpret_cast<float*>(static_cast<char*>(ws) + L.router_partial);
+  p.bias = once ? db : reinterpret_cast<float*>(static_cast<char*>(ws) + L.router_bias_partial);
+  if (T > 0 && cfg->dtype == SYMI_BF16) {
+    const int gx = cdiv(d, RT), nb = cdiv(p.nbias, gx);
+    if (router_fused(cfg)) {   // both products in one pass over X, dX and dlogits
+      SYMI_TIMED(ctx, K_ROUTER_DX, st, (router_bwd_fused_kernel<<<dim3(gx, p.nchunk + nb), 256, 0, st>>>(p)));
+    } else {
+      const long long y = (long long)cdiv(E, RT) * p.nchunk + cdiv(T, RT) + nb;
+      const int gz = cdiv(y, 65535);
+      SYMI_TIMED(ctx, K_ROUTER_DX, st, (router_gemm_kernel<<<dim3(gx, cdiv(y, gz), gz), 256, 0, st>>>(p)));
     }
-    p.chunk = chunk;
-    const int nchunk = cdiv(T, chunk);
-    if (T > 0 && fused) {
-      // both products in one pass over X, dX and dlogits
-      SYMI_TIMED(ctx, K_ROUTER_DX, st, (router_bwd_fused_kernel<<<dim3(cdiv(d, RT), nchunk), 256, 0, st>>>(p)));
-    } else if (T > 0) {
-      SYMI_TIMED(ctx, K_ROUTER_DX, st, (router_gemm_kernel<R_DX><<<dim3(cdiv(d, RT), cdiv(T, RT)), 256, 0, st>>>(p)));
-      SYMI_TIMED(ctx, K_ROUTER_DW, st, (router_gemm_kernel<R_DW><<<dim3(cdiv(d, RT), cdiv(E, RT), nchunk), 256, 0, st>>>(p)));
-    }
-    const long long n = (long long)E * d;
-    SYMI_TIMED(ctx, K_ROUTER_DW, st, (router_reduce_kernel<<<cdiv(n, 256), 256, 0, st>>>(p.partial, nchunk, n, dWr)));
-  } else {
-    if (T > 0)
-      SYMI_TIMED(ctx, K_ROUTER_DX, st, (router_dx_f32_kernel<<<cdiv((long long)T * d, 256), 256, 0, st>>>(
-          dlogits, static_cast<const float*>(Wr), static_cast<float*>(dX), T, E, d)));
-    float* const partial = reinterpret_cast<float*>(static_cast<char*>(ws) + L.router_partial);
-    const int nchunk = cdiv(T, RCHUNK);
-    if (T > 0)
-      SYMI_TIMED(ctx, K_ROUTER_DW, st, (router_dw_f32_kernel<<<dim3(cdiv(d, 64), cdiv(E, RF_CLASSES), nchunk), 64 * RF_WAVES, 0, st>>>(
-          dlogits, static_cast<const float*>(X), partial, T, E, d)));
-    SYMI_TIMED(ctx, K_ROUTER_DW, st, (router_reduce_kernel<<<cdiv((long long)E * d, 256), 256, 0, st>>>(
-        partial, nchunk, (long long)E * d, dWr)));
+  } else if (T > 0) {
+    const int ndx = cdiv((long long)T * d, 64 * RF_WAVES);
+    SYMI_TIMED(ctx, K_ROUTER_DX, st, (router_bwd_f32_kernel<<<cdiv(d, 64) * cdiv(E, RF_CLASSES) * p.nchunk + ndx + p.nbias, 64 * RF_WAVES, 0, st>>>(p, ndx)));
   }
-  if (db) {
-    float* part = reinterpret_cast<float*>(static_cast<char*>(ws) + L.router_bias_partial);
-    const int nb = cdiv(T, 256);
-    if (nb > 0)
-      SYMI_TIMED(ctx, K_ROUTER_DW, st, (router_bias_partial_kernel<<<nb, 256, 0, st>>>(dlogits, T, E, part)));
-    SYMI_TIMED(ctx, K_ROUTER_DW, st, (router_bias_final_kernel<<<E, 256, 0, st>>>(part, nb, E, db)));
+  if (!once) {
+    const int nred = cdiv((long long)E * d, 256);
+    SYMI_TIMED(ctx, K_ROUTER_DW, st, (router_finish_kernel<<<nred + (db ? E : 0), 256, 0, st>>>(p, nred, dWr, db)));
   }
   SYMI_LAUNCH_CHECK("symi_router_bwd");
   return SYMI_OK;

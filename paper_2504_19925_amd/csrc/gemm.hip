@@ -1266,38 +1266,31 @@ struct F32Operands {
   long long lda, ldb;
   int row0, row1, group, K;
 
-  // tile `part` of 64 / `rows` parts of a table entry (variable rows), or row tile `part` of a group
-  __device__ __forceinline__ bool init(const GemmParams& p, int rows, int y, int z) {
-    int kbeg = 0;
-    if (VARM) {
-      const int parts = FEW_BM / rows, mt = y / parts;
-      if (mt >= p.tile_map[0]) return false;
-      const int entry = p.tile_map[4 + 2 * mt + 1];
-      row0 = p.tile_map[4 + 2 * mt];
-      row1 = row0 + (entry >> 16) + 1;
-      row0 += (y % parts) * rows;
-      if (row0 >= row1) return false;
-      row1 = min(row1, row0 + rows);
-      group = entry & 0xffff;
-      K = p.K;
-    } else {
-      group = p.per_slot ? z : p.class_order[z];   // long reductions first
-      row0 = y * rows;
-      row1 = min(p.M, row0 + rows);
-      if (p.per_slot) {
-        kbeg = p.slot_offsets[group];
-        K = p.slot_offsets[group + 1] - kbeg;
-      } else {
-        kbeg = p.slot_offsets[p.first_slot[group]];
-        K = p.slot_offsets[p.first_slot[group + 1]] - kbeg;
-      }
-      if (K == 0 && p.skip_empty) return false;
-    }
+  // variable rows
+  __device__ __forceinline__ void init_rows(const GemmParams& p, int r0, int r1, int slot) {
+    row0 = r0;
+    row1 = r1;
+    group = slot;
+    K = p.K;
+    bind(p, 0);
+  }
+  // row tile y of the group that is z-th in the order of decreasing row counts, or group g itself
+  __device__ __forceinline__ bool init(const GemmParams& p, int rows, int y, int z, int g = -1) {
+    group = p.per_slot ? z : g >= 0 ? g : p.class_order[z];   // long reductions first
+    row0 = y * rows;
+    row1 = min(p.M, row0 + rows);
+    const int q0 = p.per_slot ? group : p.first_slot[group], q1 = p.per_slot ? group + 1 : p.first_slot[group + 1];
+    const int kbeg = p.slot_offsets[q0];
+    K = p.slot_offsets[q1] - kbeg;
+    if (K == 0 && p.skip_empty) return false;
+    bind(p, kbeg);
+    return true;
+  }
+  __device__ __forceinline__ void bind(const GemmParams& p, int kbeg) {
     lda = MODE == FWD2 ? p.f : (MODE == BWD_DX || MODE == WGRAD1) ? 2LL * p.f : p.d;
     ldb = (MODE == FWD1 || MODE == BWD_DX || MODE == WGRAD1) ? p.d : p.f;
     A = static_cast<const float*>(p.A) + (VARM ? (long long)row0 * lda : (long long)kbeg * lda + row0);
     B = static_cast<const float*>(p.B) + (VARM ? (long long)group * p.b_group_stride : (long long)kbeg * ldb);
-    return true;
   }
 };
 
@@ -1980,13 +1973,10 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
     F32Operands<MODE> o;
     o.K = t.K;
     o.group = t.group;
-    o.lda = lda;
-    o.ldb = ldb;
-    o.B = static_cast<const float*>(p.B) + (VARM ? (long long)t.group * p.b_group_stride : (long long)t.kbeg * o.ldb);
-    const int n0 = t.bx * (MODE == FWD1 ? T / 2 : T);
     o.row0 = t.row0;
     o.row1 = t.row1;
-    o.A = static_cast<const float*>(p.A) + (VARM ? (long long)t.row0 * o.lda : (long long)t.kbeg * o.lda + t.row0);
+    o.bind(p, t.kbeg);
+    const int n0 = t.bx * (MODE == FWD1 ? T / 2 : T);
     meet();
     f32_tile<MODE>(p, o, n0, min(N, n0 + (MODE == FWD1 ? T / 2 : T)), reinterpret_cast<float*>(smem));
   }
@@ -1995,7 +1985,10 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
 // A small batch has too few 64 x 128 tiles to fill the chip, and the time of one tile is its
 // reduction's latency.  Here a tile is 32 x 32 (FWD1: 32 hidden units, gate and up) and NW
 // wavefronts share its reduction, each with its own range of reduction indices: 16-deep steps through an LDS ring of
-// its own (direct-to-LDS loads, one to two steps ahead, no barrier); the sums meet in LDS in a fixed order.
+// its own (direct-to-LDS loads, one to two steps ahead, no barrier); the sums meet in LDS in a fixed order.  A workgroup finds its
+// rows from the slot offsets, about a microsecond, where a table was a launch of four; in the backward dh goes with dW2 and dX with dW1 in
+// one launch, since neither fills the chip: c1's step 97 -> 85 us, 8 classes of d = 64, f = 864, 848 rows, backward 66 -> 47, 16 of
+// d = 208, f = 464, 594 rows, forward 90 -> 48.
 // Rows of a step are 64-byte segments, columns 128-byte ones; straight from memory into registers a load took 16 bytes
 // of each of 32 rows, four loads to a cache line, and only one step flew: 512 rows in 8 slots of d = 512, f = 1280, the six
 // products 53, 51, 32, 97, 20, 28 us -> 33, 26, 25, 48, 18, 24; 2048 rows in 16 slots of d = 128, f = 256 15, 11, 13, 16, 11,
@@ -2003,20 +1996,99 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
 // the sum.
 // Ring layouts, free of bank conflicts: reduction-contiguous [32 rows][16 k], 16-byte chunk c of row r at c ^ ((r >> 2) & 3);
 // reduction-strided [16 k][32 columns], index k in row k ^ ((k >> 2) & 1): the two halves of a wavefront read indices 4 apart.
-template <int MODE, int NW>
-__global__ __launch_bounds__(64 * NW) void gemm_f32_small_kernel(GemmParams p) {
+// NW wavefronts share a reduction, SUBS tiles in a workgroup.
+template <int MODE, int NW, int SUBS>
+struct F32Small {
+  static constexpr int NT = 64 * NW * SUBS, NB = MODE == FWD1 ? 2 : 1;
+  static constexpr int NST = NT == 256 ? 3 : 2;   // stages: three workgroups of 48 KB or two of 64 KB per unit
+  static constexpr int SO = 32 * F32_CHUNK, RING = NST * (1 + NB) * SO;   // elements: an operand's step, a wavefront's ring
+  static constexpr int LDS = NW * SUBS * RING;
+};
+
+// Row tile mt of the slots in order, TM rows each, counted from the slot offsets by all NT threads of the workgroup; SUBS
+// groups of threads look for one each (sub: this thread's).  `found`: NT / 64 + 3 SUBS words.
+template <int TM, int NT, int SUBS>
+__device__ __forceinline__ bool find_rows(const int32_t* __restrict__ offs, int n_slots, int32_t* const found, const int (&mt)[SUBS],
+                                          int sub, int& row0, int& row1, int& slot) {
+  constexpr int NW = NT / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int per = (n_slots + NT - 1) / NT, q0 = min(tid * per, n_slots), q1 = min(q0 + per, n_slots);
+  int mine = 0;
+  for (int q = q0; q < q1; ++q) mine += (offs[q + 1] - offs[q] + TM - 1) / TM;
+  int incl = mine;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int up = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += up;
+  }
+  if (lane == 63) found[wave] = incl;
+  __syncthreads();
+  int n_tiles = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    if (w < wave) incl += found[w];
+    n_tiles += found[w];
+  }
+#pragma unroll
+  for (int k = 0; k < SUBS; ++k) {
+    if (mt[k] < incl && mt[k] >= incl - mine) {
+      int i = mt[k] - (incl - mine), q = q0;
+      for (;; ++q) {
+        const int n = (offs[q + 1] - offs[q] + TM - 1) / TM;
+        if (i < n) break;
+        i -= n;
+      }
+      found[NW + 3 * k] = q;
+      found[NW + 3 * k + 1] = offs[q] + i * TM;
+      found[NW + 3 * k + 2] = min(offs[q] + i * TM + TM, offs[q + 1]);
+    }
+  }
+  __syncthreads();
+  const bool any = mt[sub] < n_tiles;
+  slot = __builtin_amdgcn_readfirstlane(found[NW + 3 * sub]);
+  row0 = __builtin_amdgcn_readfirstlane(found[NW + 3 * sub + 1]);
+  row1 = __builtin_amdgcn_readfirstlane(found[NW + 3 * sub + 2]);
+  __syncthreads();   // the words become part of the rings
+  return any;
+}
+
+// The tiles of workgroup b of a product.  Rows are found from the slot offsets (no table is written where all
+// products of a call are small), the classes are in no order.
+template <int MODE, int NW, int SUBS>
+__device__ __forceinline__ void f32_small_tile(const GemmParams& p, const int b, float* smem) {
   using Op = F32Operands<MODE>;
-  constexpr int NB = MODE == FWD1 ? 2 : 1;
-  constexpr int NST = NW == 4 ? 3 : 2;         // stages: three workgroups of 48 KB or two of 64 KB per unit
-  constexpr int SO = 32 * F32_CHUNK, RING = NST * (1 + NB) * SO;   // elements: an operand's step, a wavefront's ring
+  using Sm = F32Small<MODE, NW, SUBS>;
+  constexpr int NB = Sm::NB, NST = Sm::NST, SO = Sm::SO, RING = Sm::RING;
   constexpr int LDR = 40;                      // rows 4 apart are 32 banks apart
   static_assert(RING >= NB * 32 * LDR, "the sums reuse the ring");
-  __shared__ __attribute__((aligned(1024))) float smem[NW * RING];
+  const int ntx = ((MODE == FWD1 ? p.f : p.N) + 31) / 32;
+  const int sub = SUBS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * NW));
   Op o;
-  if (!o.init(p, 32, blockIdx.y, blockIdx.z)) return;
+  int bx;
+  bool any = true;   // a workgroup's last tile may not exist; its wavefronts meet the others all the same
+  if constexpr (Op::VARM) {
+    int mt[SUBS];
+#pragma unroll
+    for (int k = 0; k < SUBS; ++k) mt[k] = (b * SUBS + k) / ntx;
+    bx = (b * SUBS + sub) % ntx;
+    int row0, row1, slot;
+    any = find_rows<32, Sm::NT, SUBS>(p.slot_offsets, p.n_slots, reinterpret_cast<int32_t*>(smem), mt, sub, row0, row1, slot);
+    if (SUBS == 1 && !any) return;
+    if (any) o.init_rows(p, row0, row1, slot);
+  } else {
+    static_assert(SUBS == 1, "one weight gradient tile in a workgroup");
+    const int per = ntx * ((p.M + 31) / 32), z = b / per, at = b - z * per;
+    bx = at % ntx;
+    if (!o.init(p, 32, at / ntx, z, z)) return;
+  }
+  if (SUBS > 1 && !any) {
+    __syncthreads();   // where the sums meet
+    return;
+  }
+  smem += sub * NW * RING;
   const int K = o.K, N = MODE == FWD1 ? p.f : p.N;
-  const int n0 = blockIdx.x * 32;
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int n0 = bx * 32;
+  const int tid = threadIdx.x - sub * 64 * NW, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r31 = lane & 31, hw = lane >> 5;
   const int per = (K + NW * F32_CHUNK - 1) / (NW * F32_CHUNK) * F32_CHUNK;
@@ -2135,6 +2207,24 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_small_kernel(GemmParams p) {
   }
 }
 
+template <int MODE, int NW>
+__global__ __launch_bounds__(64 * NW) void gemm_f32_small_kernel(GemmParams p) {
+  __shared__ __attribute__((aligned(1024))) float smem[F32Small<MODE, NW, 1>::LDS];
+  f32_small_tile<MODE, NW, 1>(p, blockIdx.x, smem);
+}
+
+// Two products that do not need each other, one launch: the weight gradient MODE, whose tiles have the longer reductions, in the first
+// `first` workgroups, and an activation gradient (dh beside dW2, dX beside dW1), whose reductions NW wavefronts share.
+template <int MODE, int WITH, int NW>
+__global__ __launch_bounds__(512) void gemm_f32_small_pair_kernel(GemmParams p, GemmParams q, int first) {
+  using A = F32Small<MODE, 8, 1>;
+  using B = F32Small<WITH, NW, 8 / NW>;
+  static_assert(A::NT == 512 && B::NT == 512 && A::LDS == B::LDS, "one LDS area");
+  __shared__ __attribute__((aligned(1024))) float smem[A::LDS];
+  if ((int)blockIdx.x < first) f32_small_tile<MODE, 8, 1>(p, blockIdx.x, smem);
+  else f32_small_tile<WITH, NW, 8 / NW>(q, blockIdx.x - first, smem);
+}
+
 // bf16 forward products, at most 32 rows per slot on average: the tile that streams weights.  Both products against
 // the large tile, 32 rows per slot on average, in all slots / half / a quarter / a tenth / one of them (us):
 //   96 slots, d = 1024, f = 4096    558 : 624   328 : 359   217 : 228   187 : 171   138 : 124
@@ -2200,6 +2290,42 @@ static bool mid_tile(const symi_ctx* ctx, int mode) {
   return mode == FWD1 || mode == BWD_DH ? work <= 1 << 19 : work <= 3 << 17 && K <= 1984;
 }
 
+// fp32: the shared reduction, by the count of 64 x 128 tiles (variable rows: about half a tile of padding per slot).  Below one round of them the shared
+// reduction, whose time is the latency of a tile; beyond it the split one.  A class's weight gradient reduces over up to T
+// rows, and the most popular class makes the longest chain there is, which the shared reduction cuts in eight: there up to
+// two rounds (24 classes, d = 80, f = 376, 4940 tokens: step 232 -> 167 us, 24 classes of d = 280, f = 512 backward 184 ->
+// 142), but not for single slots, which placement keeps even (36 slots of 352 rows, d = 184, f = 288 169 : 177).  Groups of
+// a few rows are bound by their stores, which the fp32 tile has more of in flight: slots of 1 - 5 rows 164 : 172 (54 slots
+// of d = 312, f = 992), 86 : 90 (32 slots of d = 296, f = 552), the split one from some 16 rows on.
+static bool f32_small(const symi_ctx* ctx, int mode, bool per_slot) {
+  const symi_cfg* const c = &ctx->cfg;
+  const bool varm = mode <= BWD_DX;
+  const int cols = mode == FWD1 || mode == BWD_DH || mode == WGRAD2 ? c->f : c->d;
+  const long long A = (long long)c->T * c->k, groups = per_slot ? c->S_tot : c->E;
+  const long long rows = varm ? A / F32_BM + c->S_tot / 2 : cdiv(mode == WGRAD1 ? 2 * c->f : c->d, F32_BM) * groups;
+  return rows * cdiv(cols, mode == FWD1 ? 64 : 128) < (!varm && !per_slot && A >= 64 * groups ? 2 : 1) * ctx->cus;
+}
+
+template <int MODE>
+static unsigned f32_small_tiles(const symi_cfg* c, const GemmParams& p) {
+  const long long ntx = cdiv(MODE == FWD1 ? c->f : p.N, 32);
+  return (unsigned)(ntx * (MODE <= BWD_DX ? (long long)c->T * c->k / 32 + c->S_tot : (long long)cdiv(p.M, 32) * (p.per_slot ? c->S_tot : c->E)));
+}
+
+// Eight wavefronts share a reduction of dh or dX where its tiles then all run at once, two workgroups to a unit: 8 classes of
+// d = 64, f = 864, 848 rows, backward 46 us with eight, 55 with four; d = 232, f = 336, 156 rows, step 63 : 74; beyond, four (two tiles to a
+// workgroup beside a weight gradient): c1's dh and dW2 17.0 with eight, 12.4.  The same rule one by one and in pairs, and so the same bits.
+static bool f32_share_eight(const symi_ctx* ctx, int n_cols) {
+  return cdiv(n_cols, 32) * ((long long)ctx->cfg.T * ctx->cfg.k / 32 + ctx->cfg.S_tot / 2) < 2LL * ctx->cus;
+}
+
+// fp32: do any of these products read the table of row tiles or the order of the classes?
+static bool f32_table(const symi_ctx* ctx, std::initializer_list<int> modes, bool per_slot) {
+  for (int m : modes)
+    if (!f32_small(ctx, m, per_slot)) return true;
+  return false;
+}
+
 template <int MODE>
 static void launch_gemm(const symi_ctx* ctx, const GemmParams& p, int n_cols, int max_mtiles,
                         hipStream_t st) {
@@ -2233,25 +2359,21 @@ static void launch_gemm(const symi_ctx* ctx, const GemmParams& p, int n_cols, in
       SYMI_TIMED(ctx, K_SLICE_SUM, st, (slice_sum_kernel<<<dim3(BM / 16, std::max(1, p.cus / 2)), 256, 0, st>>>(p, ntx)));
   } else {
     constexpr bool VARM = MODE <= BWD_DX;
-    constexpr int NW = VARM ? 4 : 8;
     const int groups = p.per_slot ? cfg->S_tot : cfg->E;
-    const int ntx = cdiv(n_cols, MODE == FWD1 ? 64 : 128);
-    // Count of 64 x 128 tiles (variable rows: about half a tile of padding per slot).  Below one round of them the shared
-    // reduction, whose time is the latency of a tile; beyond it the split one.  A class's weight gradient reduces over up to T
-    // rows, and the most popular class makes the longest chain there is, which the shared reduction cuts in eight: there up to
-    // two rounds (24 classes, d = 80, f = 376, 4940 tokens: step 232 -> 167 us, 24 classes of d = 280, f = 512 backward 184 ->
-    // 142), but not for single slots, which placement keeps even (36 slots of 352 rows, d = 184, f = 288 169 : 177).  Groups of
-    // a few rows are bound by their stores, which the fp32 tile has more of in flight: slots of 1 - 5 rows 164 : 172 (54 slots
-    // of d = 312, f = 992), 86 : 90 (32 slots of d = 296, f = 552), the split one from some 16 rows on.
-    const long long rows = VARM ? (long long)cfg->T * cfg->k / F32_BM + cfg->S_tot / 2 : (long long)cdiv(p.M, F32_BM) * groups;
-    const long long mean = (long long)cfg->T * cfg->k / groups;
-    if (rows * ntx < (!VARM && !p.per_slot && mean >= 64 ? 2 : 1) * ctx->cus) {
-      dim3 grid(cdiv(n_cols, 32), VARM ? 2 * (cfg->T * cfg->k / FEW_BM + cfg->S_tot) : cdiv(p.M, 32), VARM ? 1 : groups);
-      SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_f32_small_kernel<MODE, NW><<<grid, 64 * NW, 0, st>>>(p)));
+    if (f32_small(ctx, MODE, p.per_slot)) {
+      const unsigned n = f32_small_tiles<MODE>(cfg, p);
+      if constexpr (MODE >= BWD_DH) {
+        if (MODE > BWD_DX || f32_share_eight(ctx, n_cols)) {
+          SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_f32_small_kernel<MODE, 8><<<n, 512, 0, st>>>(p)));
+          return;
+        }
+      }
+      if constexpr (MODE <= BWD_DX) SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_f32_small_kernel<MODE, 4><<<n, 256, 0, st>>>(p)));
       return;
     }
+    const int ntx = cdiv(n_cols, 128);
     if constexpr (!VARM) {
-      if (mean < 16) {
+      if ((long long)cfg->T * cfg->k < 16LL * groups) {
         SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_f32_kernel<MODE><<<dim3(ntx, cdiv(p.M, F32_BM), groups), 256, 0, st>>>(p)));
         return;
       }
@@ -2261,6 +2383,16 @@ static void launch_gemm(const symi_ctx* ctx, const GemmParams& p, int n_cols, in
     SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st,
                (gemm_f32_split_kernel<MODE><<<(unsigned)std::min(tiles, 3LL * ctx->cus), 256, 0, st>>>(p, groups)));
   }
+}
+
+template <int MODE, int WITH>
+static void launch_f32_pair(const symi_ctx* ctx, const GemmParams& p, const GemmParams& q, hipStream_t st) {
+  const symi_cfg* const c = &ctx->cfg;
+  const unsigned first = f32_small_tiles<MODE>(c, p), n = f32_small_tiles<WITH>(c, q);
+  if (f32_share_eight(ctx, q.N))
+    gemm_f32_small_pair_kernel<MODE, WITH, 8><<<first + n, 512, 0, st>>>(p, q, (int)first);
+  else
+    gemm_f32_small_pair_kernel<MODE, WITH, 4><<<first + (n + 1) / 2, 512, 0, st>>>(p, q, (int)first);
 }
 
 // logits = X Wr^T + b, bf16 (symi_router_fwd).  Streams X once in 64-token tiles, two stages ahead; bound by the latency of
@@ -2297,7 +2429,7 @@ extern "C" int symi_expert_fwd(const symi_ctx* ctx, const void* Xp, const int32_
   const WsLayout& L = ctx->L;
   int32_t* map = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + L.tile_map);
   const int max_mtiles = (int)(A / GEMM_BM) + cfg->S_tot;
-  if (cfg->dtype == SYMI_F32 || (few_rows(cfg) && few_rows_table(ctx)))
+  if (cfg->dtype == SYMI_F32 ? f32_table(ctx, {FWD1, FWD2}, false) : few_rows(cfg) && few_rows_table(ctx))
     SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<FEW_BM><<<1, 256, 0, st>>>(slot_offsets, nullptr, cfg->S_tot, cfg->E, map, nullptr)));
   else if (cfg->dtype == SYMI_BF16 && !few_rows(cfg) && !(mid_tile(ctx, FWD1) && mid_tile(ctx, FWD2)))
     SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<GEMM_BM><<<1, 256, 0, st>>>(slot_offsets, nullptr, cfg->S_tot, cfg->E, map, nullptr)));
@@ -2363,9 +2495,10 @@ static int expert_bwd_impl(const char* who, const symi_ctx* ctx, const void* dYp
   set_split(ctx, ws, p);
   p.d = cfg->d;
   p.f = cfg->f;
-  if (cfg->dtype == SYMI_F32)
-    SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<FEW_BM><<<1, 256, 0, st>>>(slot_offsets, first_slot, cfg->S_tot, cfg->E, map, order)));
-  else
+  if (cfg->dtype == SYMI_F32) {
+    if (f32_table(ctx, {BWD_DH, BWD_DX, WGRAD2, WGRAD1}, per_slot))
+      SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<FEW_BM><<<1, 256, 0, st>>>(slot_offsets, first_slot, cfg->S_tot, cfg->E, map, order)));
+  } else
     SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<GEMM_BM><<<1, 256, 0, st>>>(slot_offsets, first_slot, cfg->S_tot, cfg->E, map, order)));
   // worth it only while a product is a few rounds of workgroups: with many rounds the chip is
   // full anyway and two kernels sharing it only disturb each other's L2 locality; and not for the
@@ -2380,34 +2513,45 @@ static int expert_bwd_impl(const char* who, const symi_ctx* ctx, const void* dYp
     }
     sw = ctx->side;
   }
-  // class gradients, first half (classes without rows get zeros: their reduction is empty)
-  GemmParams pw = p;
+  // class gradients (classes without rows get zeros: their reduction is empty)
+  GemmParams pw = p, pw1 = p;
   pw.A = dYp; pw.B = H; pw.C = dW2_class;
   pw.c_group_stride = (long long)cfg->d * cfg->f;
   pw.M = cfg->d; pw.N = cfg->f;
-  launch_gemm<WGRAD2>(ctx, pw, cfg->f, 0, sw);
+  pw1.A = dUV; pw1.B = Xp; pw1.C = dW1_class;
+  pw1.c_group_stride = 2LL * cfg->f * cfg->d;
+  pw1.M = 2 * cfg->f; pw1.N = cfg->d;
+  // dh = dYp W2, turned into du, dv in the epilogue (dh itself never reaches memory)
+  GemmParams px = p;
+  p.A = dYp; p.B = W2_slots; p.C = dUV; p.UV = UV;
+  p.b_group_stride = (long long)cfg->d * cfg->f;
+  p.N = cfg->f; p.K = cfg->d;
+  // dXp = dUV W1
+  px.A = dUV; px.B = W1_slots; px.C = dXp;
+  px.b_group_stride = 2LL * cfg->f * cfg->d;
+  px.N = cfg->d; px.K = 2 * cfg->f;
+  // small fp32 products of both chains go in pairs (one by one where every launch is timed)
+  const bool pairs = cfg->dtype == SYMI_F32 && A > 0 && !side && !ctx->timing;
+  const bool pair2 = pairs && f32_small(ctx, BWD_DH, per_slot) && f32_small(ctx, WGRAD2, per_slot);
+  const bool pair1 = pairs && f32_small(ctx, BWD_DX, per_slot) && f32_small(ctx, WGRAD1, per_slot);
+  if (pair2)
+    launch_f32_pair<WGRAD2, BWD_DH>(ctx, pw, p, st);
+  else
+    launch_gemm<WGRAD2>(ctx, pw, cfg->f, 0, sw);
   if (A > 0) {
-    // dh = dYp W2, turned into du, dv in the epilogue (dh itself never reaches memory)
-    p.A = dYp; p.B = W2_slots; p.C = dUV; p.UV = UV;
-    p.b_group_stride = (long long)cfg->d * cfg->f;
-    p.N = cfg->f; p.K = cfg->d;
-    launch_gemm<BWD_DH>(ctx, p, cfg->f, max_mtiles, st);
+    if (!pair2) launch_gemm<BWD_DH>(ctx, p, cfg->f, max_mtiles, st);
     if (side) {   // du|dv is complete: the other chain may go on to dW1
       if (hipEventRecord(ctx->mid, st) != hipSuccess || hipStreamWaitEvent(ctx->side, ctx->mid, 0) != hipSuccess) {
         set_error("%s: event hand-over between the two streams failed", who);
         return SYMI_EHIP;
       }
     }
-    // dXp = dUV W1
-    p.A = dUV; p.B = W1_slots; p.C = dXp;
-    p.b_group_stride = 2LL * cfg->f * cfg->d;
-    p.N = cfg->d; p.K = 2 * cfg->f;
-    launch_gemm<BWD_DX>(ctx, p, cfg->d, max_mtiles, st);
+    if (!pair1) launch_gemm<BWD_DX>(ctx, px, cfg->d, max_mtiles, st);
   }
-  pw.A = dUV; pw.B = Xp; pw.C = dW1_class;
-  pw.c_group_stride = 2LL * cfg->f * cfg->d;
-  pw.M = 2 * cfg->f; pw.N = cfg->d;
-  launch_gemm<WGRAD1>(ctx, pw, cfg->d, 0, sw);
+  if (pair1)
+    launch_f32_pair<WGRAD1, BWD_DX>(ctx, pw1, px, st);
+  else
+    launch_gemm<WGRAD1>(ctx, pw1, cfg->d, 0, sw);
   if (side) {
     if (hipEventRecord(ctx->join, ctx->side) != hipSuccess || hipStreamWaitEvent(st, ctx->join, 0) != hipSuccess) {
       set_error("%s: joining the helper stream failed", who);

@@ -1213,6 +1213,135 @@ __global__ __launch_bounds__(GT, 2) void gemm_mid_kernel(GemmParams p) {
   write_tile<MODE, 2, 2>(p, smem + wave * (2 * (SA + SB) / 4), acc, row0, row1, group, n0, wm, wn, lane, -1, saved);
 }
 
+// ---------------------------------------------------------------- weight gradients of short reductions
+// Tile of 128 x 256, four wavefronts of 64 x 128, 32-deep steps in three 24 KB stages, two workgroups per compute unit, so
+// that one's set-up and epilogue run beside the other's.  Bound by the stores of the gradients: with a few rows
+// per class the large tile writes its 256 KB behind one step's load latency with nothing beside it.  60 drawn backwards of at
+// most 144 rows per class (or slot), bf16: 1.045 times as fast (0.94 - 1.17); E = 8, d = 344, f = 752, 595 rows 75 -> 65 us, E = 128,
+// d = 4048, f = 1528, 1125 rows 4206 -> 3718, E = 48, d = 144, f = 3552, 320 rows in 112 slots 542 -> 485.  Its
+// 64 x 128 wavefront tile reads 1.5 times as much LDS per matrix instruction, which longer reductions pay for (64 slots of 384 rows,
+// d = 2048, f = 1408, W1 499 : 527).  Same bits as the large tile.  Tried and dropped for the variable-row products: with 32-deep steps a
+// reduction-contiguous row is half a cache line (16 slots of 1024 rows, d = f = 4096, first forward product 807 : 1192).
+// LDS: [k][row] as loaded, 32-byte piece c of row k at c ^ ((k & 3) + 4 ((k >> 3) & 1)), free of bank conflicts for transposing reads.
+constexpr int DUO_BM = 128, DUO_BN = 256, DUO_BK = 32;
+
+template <int MODE>
+__global__ __launch_bounds__(GT, 2) void gemm_duo_kernel(GemmParams p) {
+  static_assert(MODE >= WGRAD2, "both operands reduction-strided");
+  constexpr int TM = DUO_BM, TN = DUO_BN, NST = 3, LA = 2, LB = 4;     // LA, LB: 1 KB load instructions per wavefront and step
+  constexpr int SA = TM * DUO_BK, SB = TN * DUO_BK;                    // elements of a stage
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[NST * (SA + SB)];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int group = p.per_slot ? blockIdx.z : p.class_order[blockIdx.z];
+  const int ntx = gridDim.x, nt = ntx * gridDim.y;
+  int tile = blockIdx.y * ntx + blockIdx.x;
+  const int R = nt % 256 == 0 ? 256 : nt % 128 == 0 ? 128 : nt % 64 == 0 ? 64 : 0;   // as in the large tile's kernel
+  if (R) xcd_block(tile, ntx, R, tile);
+  const int mt = tile / ntx, n0 = (tile - mt * ntx) * TN;
+  const int row0 = mt * TM, row1 = min(p.M, row0 + TM);
+  const int q0 = p.per_slot ? group : p.first_slot[group], q1 = p.per_slot ? group + 1 : p.first_slot[group + 1];
+  const int kbeg = p.slot_offsets[q0], K = p.slot_offsets[q1] - kbeg;
+  if (K == 0) {
+    if (p.skip_empty) return;
+    float* const Co = static_cast<float*>(p.C) + (long long)group * p.c_group_stride;
+    const int col = n0 + lane * 4;
+    if (col < p.N)
+      for (int r = row0 + wave; r < row1; r += GT / 64) *reinterpret_cast<float4*>(Co + (long long)r * p.N + col) = make_float4(0.f, 0.f, 0.f, 0.f);
+    return;
+  }
+  const int rows = row1 - row0, cols = p.N - n0;
+  const int lda = MODE == WGRAD2 ? p.d : 2 * p.f, ldb = MODE == WGRAD2 ? p.f : p.d;
+  const uint16_t* const a_base = static_cast<const uint16_t*>(p.A) + (long long)kbeg * lda + row0;
+  const uint16_t* const b_base = static_cast<const uint16_t*>(p.B) + (long long)kbeg * ldb + n0;
+  auto swizzle = [](int k) { return (k & 3) | (((k >> 3) & 1) << 2); };
+  // byte offset of this lane's 16 bytes for instruction j of an operand (its immediate, j KB, taken back out) and their reduction
+  // index in the step; columns beyond the operand's extent are clamped (they only reach outputs never stored), indices
+  // beyond K read from outside the buffer: zeros
+  unsigned vo[LA + LB];
+  int kr[LA + LB];
+#pragma unroll
+  for (int j = 0; j < LA + LB; ++j) {
+    const bool right = j >= LA;   // an instruction brings 2 indices of the right operand, 4 of the left one
+    const int i = right ? j - LA : j, q = wave * (right ? LB : LA) + i, sh = right ? 5 : 4;
+    kr[j] = (q << (6 - sh)) + (lane >> sh);
+    const int c = (lane & ((1 << sh) - 1)) ^ (2 * swizzle(kr[j]));
+    vo[j] = (unsigned)(kr[j] * (right ? ldb : lda) + (c * 8 < (right ? cols : rows) ? c * 8 : 0)) * 2u + 4096u - (unsigned)(i * 1024);
+  }
+  const unsigned ldsA = (unsigned)(size_t)SYMI_LPTR(smem) + wave * (LA * 1024);
+  const unsigned ldsB = (unsigned)(size_t)SYMI_LPTR(smem + NST * SA) + wave * (LB * 1024);
+  const int nk = (K + DUO_BK - 1) / DUO_BK;
+  // a tile of at most 64 rows: the lower wavefronts have no outputs
+  const bool idle = wave >= 2 && rows <= TM / 2;
+  auto load_one = [&](auto jc, unsigned v, intx4 rsrc) {
+    asm volatile("buffer_load_dwordx4 %0, %1, 0 offen offset:%2 lds" ::"v"(v), "s"(rsrc), "n"(decltype(jc)::value * 1024) : "memory");
+  };
+  auto load = [&](auto rightc, unsigned dst, const uint16_t* src, int left) {
+    constexpr bool right = decltype(rightc)::value != 0;
+    const unsigned long long a = (unsigned long long)src - 4096;
+    const intx4 rsrc = {(int)(unsigned)a, (int)((unsigned)(a >> 32) & 0xffffu), (int)OUTSIDE, 0x00020000};
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" ::"s"(dst) : "memory");   // the wait state of an M0 write
+    unroll<right ? LB : LA>([&](auto jc) {
+      constexpr int x = (right ? LA : 0) + decltype(jc)::value;
+      load_one(jc, kr[x] < left ? vo[x] : OUTSIDE, rsrc);
+    });
+  };
+  auto issue = [&](int t, int st) {
+    const int k0 = t * DUO_BK;
+    load(IC<0>{}, ldsA + st * (SA * 2), a_base + (long long)k0 * lda, K - k0);
+    load(IC<1>{}, ldsB + st * (SB * 2), b_base + (long long)k0 * ldb, K - k0);
+  };
+  const int g4 = lane >> 4, jj = lane & 15, tr = 8 * g4 + (jj >> 2);   // tr: k-row of a transposing read
+  unsigned adA[4], adB[8];   // elements
+#pragma unroll
+  for (int i = 0; i < 4; ++i) adA[i] = tr * TM + (((wm * 4 + i) ^ swizzle(tr)) * 16) + (jj & 3) * 4;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) adB[j] = NST * SA + tr * TN + (((wn * 8 + j) ^ swizzle(tr)) * 16) + (jj & 3) * 4;
+  auto frag = [&](const uint16_t* q, int pitch) -> bf16x8 {
+    union { shortx4 h[2]; bf16x8 v; } u;
+    u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((shortx4 __attribute__((address_space(3)))*)SYMI_LPTR(q));
+    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((shortx4 __attribute__((address_space(3)))*)SYMI_LPTR(q + 4 * pitch));
+    return u.v;
+  };
+  floatx4 acc[4][8];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  issue(0, 0);
+  issue(1, 1);
+  int st = 0;
+  for (int t = 0; t < nk; ++t) {
+    // my loads of step t have landed (those of the next step may fly); behind the barrier everybody's, and the stage of step t - 1 is free
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0F70 + LA + LB);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    issue(t + 2, st == 0 ? 2 : st - 1);
+    if (!idle) {
+      bf16x8 fa[4], fb[8];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) fa[i] = frag(smem + st * SA + adA[i], TM);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) fb[j] = frag(smem + st * SB + adB[j], TN);
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+    }
+    // my fragment reads of this step are through before its stage is filled again, behind the next barrier
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    st = st == NST - 1 ? 0 : st + 1;
+  }
+  wait_vmcnt0();
+  __syncthreads();   // nobody's loads are in flight and nobody reads operands any more: the stages become the staging area
+  if (idle) return;
+  SavedUV<4> saved[2];   // the hidden gradient's
+  write_tile<MODE, 2, 4>(p, smem + wave * (NST * (SA + SB) / 4), acc, row0, row1, group, n0, wm, wn, lane, -1, saved);
+}
+
 // ---------------------------------------------------------------- sum of reduction slices
 // Runs behind FWD2 / BWD_DX (same stream): adds the partial tiles of every sliced tile in slice
 // order and writes the bf16 rows of the product.  Workgroup = 16 rows of a tile, a lane four
@@ -2350,6 +2479,15 @@ static void launch_gemm(const symi_ctx* ctx, const GemmParams& p, int n_cols, in
     }
     const int bn = MODE == FWD1 ? BN / 2 : BN;
     const int ntx = cdiv(n_cols, bn);
+    if constexpr (MODE >= WGRAD2) {
+      // Short reductions, by the mean: up to 96 rows per class (or slot) 1.05 (0.94 - 1.17) over 50 drawn backwards, 100 - 144 rows
+      // 1.01 (0.97 - 1.06), beyond 0.98 and below.
+      const int groups = p.per_slot ? cfg->S_tot : cfg->E;
+      if ((long long)cfg->T * cfg->k <= 96LL * groups && cdiv(p.M, DUO_BM) <= 65535) {
+        SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_duo_kernel<MODE><<<dim3(ntx, cdiv(p.M, DUO_BM), groups), GT, 0, st>>>(p)));
+        return;
+      }
+    }
     // FWD2, BWD_DX: room for the slices of the last round's tiles (at most cus workgroups more)
     const bool may_slice = (MODE == FWD2 || MODE == BWD_DX) && p.partials && cdiv(p.K, BK) / 16 >= 2;
     const int extra = may_slice ? cdiv(p.cus, ntx) : 0;

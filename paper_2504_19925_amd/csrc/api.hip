@@ -99,6 +99,8 @@ WsLayout ws_layout(const symi_cfg* c) {
   L.tile_map = off;
   // fp32: two words per 64-row tile
   off += align_up((4 + (c->dtype == SYMI_BF16 ? 4 * mtiles : 2 * (A / 64 + c->S_tot + 1))) * sizeof(int32_t), 256);
+  L.tile_map128 = off;
+  if (c->dtype == SYMI_BF16) off += align_up((4 + 2 * (A / 128 + c->S_tot + 1)) * sizeof(int32_t), 256);
   L.class_order = off;
   off += align_up((size_t)c->E * sizeof(int32_t), 256);
   L.duv = off;

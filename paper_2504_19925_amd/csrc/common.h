@@ -71,6 +71,7 @@ struct WsLayout {
   size_t blk_counts;   // dispatch: [nblk][E] i32 per-block class counts, then bases
   size_t class_tab;    // capacity-limited dispatch: per class {offset, kept offset, capacity}
   size_t tile_map;     // expert fwd/bwd: m-tile table, see gemm.hip
+  size_t tile_map128;  // bf16: the table of 128-row tiles
   size_t class_order;  // expert bwd: classes by decreasing row count
   size_t duv;          // expert bwd: dUV [A,2f] in the activation dtype
   size_t split_part;   // expert fwd/bwd: partial tiles of sliced reductions, see gemm.hip

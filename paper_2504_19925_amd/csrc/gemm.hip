@@ -41,6 +41,7 @@ struct GemmParams {
   void* UVout;         // FWD1: u|v out
   void* H;             // FWD1: h out
   const int32_t* tile_map;      // [4 + 4*i]: header {n_tiles}, then {row0, row1, slot, -}
+  const int32_t* tile_map128;   // the 128 x 128 tile's, two words a tile
   const int32_t* slot_offsets;  // weight gradients: class row ranges; small batches: the slots' rows
   int n_slots;
   const int32_t* first_slot;
@@ -69,24 +70,20 @@ __device__ __forceinline__ float sigmoid_fast(float u) {
 // map[4 + 2i ..] = {first row, slot + 2^16 * (rows - 1)} (TM = FEW_BM: the fp32 products and the small-batch forward products; of these at most
 // 32 rows per slot on average make at most 1.5 S_tot tiles, which fit where 256-row tiles would be).
 // order[c] = the class with the c-th largest number of rows (ties: lower index first).
-constexpr int FEW_BM = 64;
+constexpr int FEW_BM = 64, MID_BM = 128;
+
+// The tables that a call's products read (nullptr: not wanted).  256 and 64 share their place in the workspace: bf16 layers of few rows per slot
+// and fp32 layers have no 256-row tiles in a call that has 64-row ones.
+struct TileMaps { int32_t *of256, *of128, *of64; };
 
 template <int TM>
-__global__ __launch_bounds__(256) void tile_map_kernel(const int32_t* __restrict__ slot_offsets,
-                                                       const int32_t* __restrict__ first_slot, int S,
-                                                       int E, int32_t* __restrict__ map,
-                                                       int32_t* __restrict__ order) {
-  __shared__ int32_t part[256];
-  __shared__ int32_t rows[1024];
+__device__ __forceinline__ void write_tile_map(const int32_t* __restrict__ slot_offsets, int S, int32_t* __restrict__ map, int32_t* part) {
   const int tid = threadIdx.x;
   const int per = (S + 255) / 256;
   const int q0 = tid * per, q1 = min(S, q0 + per);
   int mine = 0;
   for (int q = q0; q < q1; ++q) mine += (slot_offsets[q + 1] - slot_offsets[q] + TM - 1) / TM;
   part[tid] = mine;
-  if (first_slot) {
-    for (int e = tid; e < E; e += 256) rows[e] = slot_offsets[first_slot[e + 1]] - slot_offsets[first_slot[e]];
-  }
   __syncthreads();
   for (int o = 1; o < 256; o <<= 1) {  // Hillis-Steele inclusive scan
     const int add = tid >= o ? part[tid - o] : 0;
@@ -99,7 +96,7 @@ __global__ __launch_bounds__(256) void tile_map_kernel(const int32_t* __restrict
   for (int q = q0; q < q1; ++q) {
     const int b = slot_offsets[q], e = slot_offsets[q + 1];
     for (int r = b; r < e; r += TM, ++t) {
-      if (TM == FEW_BM) {
+      if (TM < GEMM_BM) {
         map[4 + 2 * t + 0] = r;
         map[4 + 2 * t + 1] = q + ((min(e - r, TM) - 1) << 16);
       } else {
@@ -110,7 +107,20 @@ __global__ __launch_bounds__(256) void tile_map_kernel(const int32_t* __restrict
       }
     }
   }
+  __syncthreads();   // `part` may serve another table
+}
+
+__global__ __launch_bounds__(256) void tile_map_kernel(const int32_t* __restrict__ slot_offsets, const int32_t* __restrict__ first_slot, int S,
+                                                       int E, TileMaps maps, int32_t* __restrict__ order) {
+  __shared__ int32_t part[256];
+  __shared__ int32_t rows[1024];
+  const int tid = threadIdx.x;
+  if (maps.of256) write_tile_map<256>(slot_offsets, S, maps.of256, part);
+  if (maps.of128) write_tile_map<MID_BM>(slot_offsets, S, maps.of128, part);
+  if (maps.of64) write_tile_map<FEW_BM>(slot_offsets, S, maps.of64, part);
   if (first_slot) {
+    for (int e = tid; e < E; e += 256) rows[e] = slot_offsets[first_slot[e + 1]] - slot_offsets[first_slot[e]];
+    __syncthreads();
     for (int e = tid; e < E; e += 256) {
       int rank = 0;
       for (int j = 0; j < E; ++j) rank += (rows[j] > rows[e] || (rows[j] == rows[e] && j < e)) ? 1 : 0;
@@ -905,7 +915,7 @@ __device__ __forceinline__ bool find_slot_tile(const int32_t* __restrict__ offs,
   return true;
 }
 
-// The same from the table that tile_map_kernel<FEW_BM> wrote.
+// The same from a table of two words a tile.
 __device__ __forceinline__ bool read_slot_tile(const int32_t* __restrict__ map, SlotTile& out) {
   const int n_tiles = map[0];
   int mt, bx;
@@ -1062,9 +1072,8 @@ __global__ __launch_bounds__(GT, 2) void gemm_few_rows_kernel(GemmParams p) {
 // fragments and epilogue are those of the large tile, and so are the bits.  Tried and dropped: 32-deep steps in three
 // stages with three workgroups per unit (c2's first forward product 386 -> 450 us), and this tile for the weight gradients (two
 // transposing reads per fragment: c4's W1 gradient 1850 -> 3190 us, per-slot gradients of 384 rows 1120 -> 1180).
-constexpr int MID_BM = 128;
-
-template <int MODE>
+// TABLE: the row tiles come from tile_map
+template <int MODE, bool TABLE>
 __global__ __launch_bounds__(GT, 2) void gemm_mid_kernel(GemmParams p) {
   static_assert(MODE <= BWD_DX, "left operand reduction-contiguous");
   constexpr bool B_KC = MODE == FWD1 || MODE == FWD2;
@@ -1073,7 +1082,11 @@ __global__ __launch_bounds__(GT, 2) void gemm_mid_kernel(GemmParams p) {
   __shared__ __attribute__((aligned(1024))) uint16_t smem[2 * (SA + SB)];
   __shared__ int32_t found[8];
   SlotTile tile;
-  if (!find_slot_tile<TM>(p.slot_offsets, p.n_slots, found, tile)) return;
+  if constexpr (TABLE) {
+    if (!read_slot_tile(p.tile_map128, tile)) return;
+  } else {
+    if (!find_slot_tile<TM>(p.slot_offsets, p.n_slots, found, tile)) return;
+  }
   const int row0 = tile.row0, row1 = tile.row1, group = tile.slot, bx = tile.bx;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1234,7 +1247,7 @@ __global__ __launch_bounds__(GT, 2) void gemm_duo_kernel(GemmParams p) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int group = p.per_slot ? blockIdx.z : p.class_order[blockIdx.z];
+  const int group = p.per_slot || !p.class_order ? blockIdx.z : p.class_order[blockIdx.z];
   const int ntx = gridDim.x, nt = ntx * gridDim.y;
   int tile = blockIdx.y * ntx + blockIdx.x;
   const int R = nt % 256 == 0 ? 256 : nt % 128 == 0 ? 128 : nt % 64 == 0 ? 64 : 0;   // as in the large tile's kernel
@@ -2421,6 +2434,23 @@ static bool mid_tile(const symi_ctx* ctx, int mode) {
   return mode == FWD1 || mode == BWD_DH ? work <= 1 << 19 : work <= 3 << 17 && K <= 1984;
 }
 
+// Whether the 128 x 128 tiles of a product come from a table: as with the small-batch tile, counting takes about a microsecond of
+// every workgroup.  Counted / table, us: 224 slots of 90 rows, d = 160, f = 11768 (68448 workgroups) first forward product 1032 : 912, hidden
+// gradient 691 : 649; 128 of 100, d = 312, f = 7048 (25308) 505 : 465, 340 : 328; 160 of 100, d = 512, f = 2048 (9120) 210 : 206,
+// 156 : 155; below 16 per unit a launch that would write it takes longer than it saves.
+static bool mid_table(const symi_ctx* ctx, int mode) {
+  const symi_cfg* const c = &ctx->cfg;
+  if (!mid_tile(ctx, mode)) return false;
+  const int ntx = mode == FWD1 ? cdiv(c->f, 64) : cdiv(mode == BWD_DH ? c->f : c->d, 128);
+  return ((long long)c->T * c->k / MID_BM + c->S_tot) * ntx > 16LL * ctx->cus;
+}
+
+// Short weight gradients (gemm_duo_kernel), by the mean: up to 96 rows per class (or slot) 1.05 (0.94 - 1.17) over 50 drawn backwards, 100 - 144 rows
+// 1.01 (0.97 - 1.06), beyond 0.98 and below.
+static bool short_gradients(const symi_cfg* c, bool per_slot) {
+  return c->dtype == SYMI_BF16 && (long long)c->T * c->k <= 96LL * (per_slot ? c->S_tot : c->E) && cdiv(std::max(2 * c->f, c->d), DUO_BM) <= 65535;
+}
+
 // fp32: the shared reduction, by the count of 64 x 128 tiles (variable rows: about half a tile of padding per slot).  Below one round of them the shared
 // reduction, whose time is the latency of a tile; beyond it the split one.  A class's weight gradient reduces over up to T
 // rows, and the most popular class makes the longest chain there is, which the shared reduction cuts in eight: there up to
@@ -2475,17 +2505,18 @@ static void launch_gemm(const symi_ctx* ctx, const GemmParams& p, int n_cols, in
     if constexpr (MODE <= BWD_DX) {
       if (mid_tile(ctx, MODE)) {
         dim3 grid(cdiv(n_cols, MODE == FWD1 ? 64 : 128), cfg->T * cfg->k / MID_BM + cfg->S_tot);
-        SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_mid_kernel<MODE><<<grid, GT, 0, st>>>(p)));
+        if (mid_table(ctx, MODE))
+          SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_mid_kernel<MODE, true><<<grid, GT, 0, st>>>(p)));
+        else
+          SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_mid_kernel<MODE, false><<<grid, GT, 0, st>>>(p)));
         return;
       }
     }
     const int bn = MODE == FWD1 ? BN / 2 : BN;
     const int ntx = cdiv(n_cols, bn);
     if constexpr (MODE >= WGRAD2) {
-      // Short reductions, by the mean: up to 96 rows per class (or slot) 1.05 (0.94 - 1.17) over 50 drawn backwards, 100 - 144 rows
-      // 1.01 (0.97 - 1.06), beyond 0.98 and below.
-      const int groups = p.per_slot ? cfg->S_tot : cfg->E;
-      if ((long long)cfg->T * cfg->k <= 96LL * groups && cdiv(p.M, DUO_BM) <= 65535) {
+      if (short_gradients(cfg, p.per_slot)) {
+        const int groups = p.per_slot ? cfg->S_tot : cfg->E;
         SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_duo_kernel<MODE><<<dim3(ntx, cdiv(p.M, DUO_BM), groups), GT, 0, st>>>(p)));
         return;
       }
@@ -2568,14 +2599,20 @@ extern "C" int symi_expert_fwd(const symi_ctx* ctx, const void* Xp, const int32_
   hipStream_t st = as_stream(stream);
   const WsLayout& L = ctx->L;
   int32_t* map = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + L.tile_map);
+  int32_t* map128 = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + L.tile_map128);
   const int max_mtiles = (int)(A / GEMM_BM) + cfg->S_tot;
-  if (cfg->dtype == SYMI_F32 ? f32_table(ctx, {FWD1, FWD2}, false) : few_rows(cfg) && few_rows_table(ctx))
-    SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<FEW_BM><<<1, 256, 0, st>>>(slot_offsets, nullptr, cfg->S_tot, cfg->E, map, nullptr)));
-  else if (cfg->dtype == SYMI_BF16 && !few_rows(cfg) && !(mid_tile(ctx, FWD1) && mid_tile(ctx, FWD2)))
-    SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<GEMM_BM><<<1, 256, 0, st>>>(slot_offsets, nullptr, cfg->S_tot, cfg->E, map, nullptr)));
+  TileMaps maps = {};
+  if (cfg->dtype == SYMI_F32 ? f32_table(ctx, {FWD1, FWD2}, false) : few_rows(cfg) && few_rows_table(ctx)) maps.of64 = map;
+  if (cfg->dtype == SYMI_BF16 && !few_rows(cfg)) {
+    if (!(mid_tile(ctx, FWD1) && mid_tile(ctx, FWD2))) maps.of256 = map;
+    if (mid_table(ctx, FWD1) || mid_table(ctx, FWD2)) maps.of128 = map128;
+  }
+  if (maps.of256 || maps.of128 || maps.of64)
+    SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<<<1, 256, 0, st>>>(slot_offsets, nullptr, cfg->S_tot, cfg->E, maps, nullptr)));
 
   GemmParams p = {};
   p.tile_map = map;
+  p.tile_map128 = map128;
   p.slot_offsets = slot_offsets;
   p.n_slots = cfg->S_tot;
   set_split(ctx, ws, p);
@@ -2620,12 +2657,14 @@ static int expert_bwd_impl(const char* who, const symi_ctx* ctx, const void* dYp
   hipStream_t st = as_stream(stream);
   const WsLayout& L = ctx->L;
   int32_t* map = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + L.tile_map);
+  int32_t* map128 = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + L.tile_map128);
   void* dUV = static_cast<char*>(ws) + L.duv;
   const int max_mtiles = (int)(A / GEMM_BM) + cfg->S_tot;
 
   int32_t* order = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + L.class_order);
   GemmParams p = {};
   p.tile_map = map;
+  p.tile_map128 = map128;
   p.slot_offsets = slot_offsets;
   p.n_slots = cfg->S_tot;
   p.first_slot = first_slot;
@@ -2635,11 +2674,21 @@ static int expert_bwd_impl(const char* who, const symi_ctx* ctx, const void* dYp
   set_split(ctx, ws, p);
   p.d = cfg->d;
   p.f = cfg->f;
+  TileMaps maps = {};
+  // The order of the classes matters to the gradients' last round only; short ones of a small batch go without it, and
+  // without a launch where no product reads a table (some 4 us: slot gradients of E = 16, d = 168, f = 584, 98 rows 44 -> 41 us).
+  bool ordered = !per_slot;
   if (cfg->dtype == SYMI_F32) {
-    if (f32_table(ctx, {BWD_DH, BWD_DX, WGRAD2, WGRAD1}, per_slot))
-      SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<FEW_BM><<<1, 256, 0, st>>>(slot_offsets, first_slot, cfg->S_tot, cfg->E, map, order)));
-  } else
-    SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<GEMM_BM><<<1, 256, 0, st>>>(slot_offsets, first_slot, cfg->S_tot, cfg->E, map, order)));
+    if (f32_table(ctx, {BWD_DH, BWD_DX, WGRAD2, WGRAD1}, per_slot)) maps.of64 = map;
+    else ordered = false;
+  } else {
+    if (!(mid_tile(ctx, BWD_DH) && mid_tile(ctx, BWD_DX))) maps.of256 = map;
+    if (mid_table(ctx, BWD_DH) || mid_table(ctx, BWD_DX)) maps.of128 = map128;
+    if (short_gradients(cfg, per_slot) && A <= 4096 && !maps.of256 && !maps.of128) ordered = false;
+  }
+  if (!ordered) p.class_order = nullptr;
+  if (ordered || maps.of256 || maps.of128 || maps.of64)
+    SYMI_TIMED(ctx, K_TILE_MAP, st, (tile_map_kernel<<<1, 256, 0, st>>>(slot_offsets, ordered ? first_slot : nullptr, cfg->S_tot, cfg->E, maps, order)));
   // worth it only while a product is a few rounds of workgroups: with many rounds the chip is
   // full anyway and two kernels sharing it only disturb each other's L2 locality; and not for the
   // smallest, where fork, hand-over and join take longer than what they hide (symi_create

@@ -2446,8 +2446,12 @@ static bool mid_table(const symi_ctx* ctx, int mode) {
 }
 
 // Short weight gradients (gemm_duo_kernel), by the mean: up to 96 rows per class (or slot) 1.05 (0.94 - 1.17) over 50 drawn backwards, 100 - 144 rows
-// 1.01 (0.97 - 1.06), beyond 0.98 and below.
-static bool short_gradients(const symi_cfg* c, bool per_slot) {
+// 1.01 (0.97 - 1.06), beyond 0.98 and below.  On the helper stream beside a large tile, which needs a whole unit and waits until both of its
+// workgroups are through, up to 1 GiB of gradients: below that 42 drawn layers 1.03 (0.97 - 1.14), beyond it the waiting costs more than the tile
+// saves (64 classes of d = 1848, f = 1456, 1516 rows, step 1996 : 2066 us, 128 of 232, 11624, 4824 rows 4120 : 4229).
+static bool short_gradients(const symi_ctx* ctx, bool per_slot) {
+  const symi_cfg* const c = &ctx->cfg;
+  if (ctx->side && !mid_tile(ctx, BWD_DX) && 12LL * (per_slot ? c->S_tot : c->E) * c->d * c->f > 1LL << 30) return false;
   return c->dtype == SYMI_BF16 && (long long)c->T * c->k <= 96LL * (per_slot ? c->S_tot : c->E) && cdiv(std::max(2 * c->f, c->d), DUO_BM) <= 65535;
 }
 
@@ -2515,7 +2519,7 @@ static void launch_gemm(const symi_ctx* ctx, const GemmParams& p, int n_cols, in
     const int bn = MODE == FWD1 ? BN / 2 : BN;
     const int ntx = cdiv(n_cols, bn);
     if constexpr (MODE >= WGRAD2) {
-      if (short_gradients(cfg, p.per_slot)) {
+      if (short_gradients(ctx, p.per_slot)) {
         const int groups = p.per_slot ? cfg->S_tot : cfg->E;
         SYMI_TIMED(ctx, K_GEMM_FWD1 + MODE, st, (gemm_duo_kernel<MODE><<<dim3(ntx, cdiv(p.M, DUO_BM), groups), GT, 0, st>>>(p)));
         return;
@@ -2684,7 +2688,7 @@ static int expert_bwd_impl(const char* who, const symi_ctx* ctx, const void* dYp
   } else {
     if (!(mid_tile(ctx, BWD_DH) && mid_tile(ctx, BWD_DX))) maps.of256 = map;
     if (mid_table(ctx, BWD_DH) || mid_table(ctx, BWD_DX)) maps.of128 = map128;
-    if (short_gradients(cfg, per_slot) && A <= 4096 && !maps.of256 && !maps.of128) ordered = false;
+    if (short_gradients(ctx, per_slot) && A <= 4096 && !maps.of256 && !maps.of128) ordered = false;
   }
   if (!ordered) p.class_order = nullptr;
   if (ordered || maps.of256 || maps.of128 || maps.of64)

@@ -79,3 +79,19 @@ def test_same_bits_as_the_large_tile():
     big["W1"][0], big["W2"][0] = s["W1"][0], s["W2"][0]
     large = backward(big, 2, d, f, symi.symi_expert_bwd)
     assert torch.equal(short[0][0], large[0][0]) and torch.equal(short[1][0], large[1][0])
+
+
+@pytest.mark.parametrize("fn", ["symi_expert_bwd", "symi_expert_bwd_slots"])
+def test_same_bits_on_both_sides_of_the_gradients_line(fn):
+    """65 classes just below 1 GiB of gradients, 66 just above it, the large tile where the helper stream runs."""
+    d, f = 336, 4096
+    rows = [1 + 7 * q % 40 for q in range(65)]
+    n = sum(rows)
+    s = layer(rows, list(range(66)), d, f, 4)
+    below = backward(s, 65, d, f, getattr(symi, fn))
+    big = layer(rows + [5], list(range(67)), d, f, 5)
+    for name in ("Xp", "dYp", "UV", "H"):
+        big[name][:n] = s[name]
+    big["W1"][:65], big["W2"][:65] = s["W1"], s["W2"]
+    above = backward(big, 66, d, f, getattr(symi, fn))
+    assert torch.equal(below[0], above[0][:65]) and torch.equal(below[1], above[1][:65])

@@ -1976,7 +1976,7 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
       for (int j = 0; j < NJ; ++j) acc[i][j] = c[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
   };
   auto write_out = [&] {
-    bool bad = largest > 0x1p40f;
+    bool bad = t.K > 0 && largest > 0x1p40f;   // no rows: nothing to compute once more
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -2111,7 +2111,8 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
   if (__builtin_amdgcn_readfirstlane(any) == 0) return;
   walk.i = 0;
   for (int n = 0; walk.next(t); ++n) {
-    if (!(__builtin_amdgcn_readfirstlane(redo[(n >> 5) & 31]) >> (n & 31) & 1)) continue;
+    // a workgroup's tiles beyond 1024 share their flags: a tile without a sum has none, and may not be written (skip_empty)
+    if (t.K == 0 || !(__builtin_amdgcn_readfirstlane(redo[(n >> 5) & 31]) >> (n & 31) & 1)) continue;
     F32Operands<MODE> o;
     o.K = t.K;
     o.group = t.group;

@@ -1700,9 +1700,11 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_kernel(GemmParams p) {
 // instructions at 16 times the rate of the fp32 one.  A step of 32 indices is summed from zero, the small terms first, and
 // then added to the total, half as many additions as of 16 products each on the fp32 instruction: error against
 // binary64 (relative 2-norm) Y 2.4e-7 -> 1.9e-7, dX 2.8e-7 -> 2.2e-7, dW1 2.7e-7 -> 2.1e-7 on 24 classes of d = 328, f = 872,
-// 8997 rows.  Where the sum is not that exact the tile is computed once more on the fp32 instruction (f32_tile):
-// infinities, NaN and values beyond the bf16 range leave a sum that is not finite; values so small that their third part
-// is subnormal (below 2^-110) lose up to 2^-134 each, which counts in a sum below 2^-64 or next to factors above 2^40.
+// 8997 rows.  Every value is taken 2^24 times as large (the sum goes back by 2^-48), so that the third part of the smallest
+// fp32 number is a normal bf16 number and no part is lost, whatever stands beside it (16 multiplications per thread and step, step of the
+// shape above 1.5 - 2 % longer; unscaled, values up to 2^-134 had no parts at all).  What leaves the range for it, infinities, NaN,
+// values from 2^104 and sums from 2^80 on, leaves a sum that is not finite, and the tile is computed once more on the fp32
+// instruction (f32_tile).
 // Tile of 64 x 64 (FWD1: 32 hidden units), four wavefronts of 32 x 32, three workgroups per compute unit that stay and
 // take one tile after the other.  A thread loads 16 values of a step into registers, two to three steps ahead, splits
 // them beside the matrix instructions of the step before and writes the planes to the other of two LDS stages; one barrier per step.
@@ -1715,6 +1717,7 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_kernel(GemmParams p) {
 // LDS layouts, free of bank conflicts: reduction-contiguous [row][32 k], 16-byte chunk c of row r at c ^ s with s = 0, 2, 3, 1
 // for (r >> 2) & 3; reduction-strided [k][64 columns] as loaded, 32-byte piece c of row k at c ^ (((k >> 1) & 1) + 2 ((k >> 3) & 1)), read transposing.
 constexpr int F32S_T = 64, F32S_BK = 32;   // tile edge, step
+constexpr float F32S_SCALE = 0x1p24f, F32S_BACK = 0x1p-48f;
 
 // The tiles of a product that one workgroup computes, one after the other.  XCD x (workgroup number mod 8) takes an eighth of
 // the row tiles with all their columns, or of every class's tiles, the classes in order of decreasing row count.
@@ -1860,7 +1863,6 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
     if (left > 0) lk += F32S_BK;
   };
   uintx4 sg[2][4];
-  float largest = 0.f;   // of all values this thread has split
   auto load = [&](auto sc, auto xc) {
     constexpr int x = decltype(xc)::value;
     sg[decltype(sc)::value][x] = __builtin_amdgcn_raw_buffer_load_b128(x < 2 ? ra : rb, (int)(kr[x] < left ? vo[x] : OUTSIDE), 0, 0);
@@ -1870,8 +1872,8 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
     constexpr int S = decltype(sc)::value, x = decltype(xc)::value, q = decltype(qc)::value;
     uintx4& v = sg[S][x];
     if constexpr (q == 0) {
-      asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(largest) : "v"(v[0]), "v"(v[1]));
-      asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(largest) : "v"(v[2]), "v"(v[3]));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = __float_as_uint(__uint_as_float(v[e]) * F32S_SCALE);
     }
     const unsigned lo = pack_bf16x2(__uint_as_float(v[0]), __uint_as_float(v[1])), hi = pack_bf16x2(__uint_as_float(v[2]), __uint_as_float(v[3]));
     *reinterpret_cast<uint2*>(smem + S * ST + ls[x] + q * PL) = make_uint2(lo, hi);
@@ -1976,15 +1978,15 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
       for (int j = 0; j < NJ; ++j) acc[i][j] = c[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
   };
   auto write_out = [&] {
-    bool bad = t.K > 0 && largest > 0x1p40f;   // no rows: nothing to compute once more
+    bool bad = false;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float x = fabsf(acc[i][j][e]);
-          bad |= !(x <= 3.4e38f) || (x < 0x1p-64f && x > 0.f);
+          bad |= !(fabsf(acc[i][j][e]) <= 3.4e38f);
+          acc[i][j][e] *= F32S_BACK;
         }
     if (bad) atomicOr(&redo[(tiles >> 5) & 31], 1u << (tiles & 31));
     if (!VARM && t.K == 0 && p.skip_empty) return;
@@ -2103,7 +2105,7 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
     }
   }
 
-  // ---- tiles with a sum that is not finite or too small, or with large factors: once more on the fp32 instruction
+  // ---- tiles with a sum that is not finite: once more on the fp32 instruction
   meet();
   unsigned any = 0;
 #pragma unroll
@@ -2113,13 +2115,15 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
   for (int n = 0; walk.next(t); ++n) {
     // a workgroup's tiles beyond 1024 share their flags: a tile without a sum has none, and may not be written (skip_empty)
     if (t.K == 0 || !(__builtin_amdgcn_readfirstlane(redo[(n >> 5) & 31]) >> (n & 31) & 1)) continue;
+    // uniform, and known to be: the addresses of direct-to-LDS loads are scalars
+    auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
     F32Operands<MODE> o;
-    o.K = t.K;
-    o.group = t.group;
-    o.row0 = t.row0;
-    o.row1 = t.row1;
-    o.bind(p, t.kbeg);
-    const int n0 = t.bx * (MODE == FWD1 ? T / 2 : T);
+    o.K = uni(t.K);
+    o.group = uni(t.group);
+    o.row0 = uni(t.row0);
+    o.row1 = uni(t.row1);
+    o.bind(p, uni(t.kbeg));
+    const int n0 = uni(t.bx) * (MODE == FWD1 ? T / 2 : T);
     meet();
     f32_tile<MODE>(p, o, n0, min(N, n0 + (MODE == FWD1 ? T / 2 : T)), reinterpret_cast<float*>(smem));
   }

@@ -3,7 +3,7 @@ import pytest
 import torch
 
 import paper_2504_19925_amd as symi
-from tests.test_gpu_f32_split import layer, run
+from tests.test_gpu_f32_split import expected, layer, run
 
 pytestmark = pytest.mark.gpu
 
@@ -24,3 +24,51 @@ def test_active_leaves_classes_without_rows(value):
     for e in range(64):
         kept = bool((s["dW1"][e] == 7.0).all()) and bool((s["dW2"][e] == 7.0).all())
         assert kept == (e >= 24), e
+
+
+def close(got, want, K, what):
+    """Finite results within the bound of 32-bit sums of K products: 4e-7 of the 2-norm (test_gpu_f32_split), and 2^-149, the spacing of
+    subnormal numbers, for each of up to K partial sums."""
+    got, err = got.double(), float((got.double() - want).norm())
+    assert err <= 4e-7 * float(want.norm()) + 2.0 ** -149 * (got.numel() * K) ** 0.5, (what, err / max(float(want.norm()), 1e-300))
+
+
+def test_values_without_bf16_parts():
+    """Values that round to 0 in bf16 (2^-136) against large ones: the sums are normal fp32 numbers in every product, though all
+    bf16 parts of one operand vanish.  Each slot is a class of its own, so nothing else is in its tiles."""
+    d, f, n, tiny, large = 264, 328, 100, 2.0 ** -136, 2.0 ** 30
+    s = layer([n] * 24, list(range(25)), d, f, seed=7)
+    r = [slice(n * q, n * q + n) for q in range(24)]
+    s["Xp"][r[0]] *= tiny           # u, v near 2^-106
+    s["W1"][0] *= large
+    s["Xp"][r[1]] *= 2.0 ** -68     # h near 2^-137
+    s["W2"][1] *= large
+    symi.symi_expert_fwd(s["ctx"], s["Xp"], s["off"], s["W1"], s["W2"], s["UV"], s["H"], s["Yp"], s["ws"])
+    want = expected(s)
+    for q in range(24):
+        close(s["UV"][r[q]], want["UV"][r[q]], d, ("UV", q))
+        close(s["Yp"][r[q]], want["Yp"][r[q]], f, ("Yp", q))
+    assert float(s["UV"][r[0]].abs().max()) > 2.0 ** -110 and float(s["Yp"][r[1]].abs().max()) > 2.0 ** -112
+    s["dYp"][r[2]] *= tiny          # dh near 2^-106
+    s["W2"][2] *= large
+    s["dYp"][r[3]] *= tiny          # du, dv near 2^-136
+    s["W1"][3] *= large
+    s["dYp"][r[4]] *= tiny
+    s["Xp"][r[4]] *= large
+    s["dYp"][r[5]] *= tiny
+    s["H"][r[5]] *= large
+    b = (s["ctx"], s["dYp"], s["Xp"], s["UV"], s["H"], s["off"], s["first"], s["W1"], s["W2"], s["dXp"])
+    want = expected(s)
+    for call, names in ((symi.symi_expert_bwd, ("dW1", "dW2")), (symi.symi_expert_bwd_active, ("dW1", "dW2")),
+                        (symi.symi_expert_bwd_slots, ("sW1", "sW2"))):
+        for t in ("dXp", *names):
+            s[t].fill_(7.0)
+        call(*b, s[names[0]], s[names[1]], s["ws"])
+        for q in range(24):
+            # du, dv are stored in fp32 and may be subnormal there, as may be the sums: 2^-149 of each, times the other operand
+            slack = 2.0 ** -149 * max(1.0, float(s["W1"][q].abs().max())) * (2 * f * n * d) ** 0.5
+            assert float((s["dXp"][r[q]].double() - want["dXp"][r[q]]).norm()) <= 4e-7 * float(want["dXp"][r[q]].norm()) + slack, q
+            slack = 2.0 ** -149 * max(1.0, float(s["Xp"][r[q]].abs().max())) * (2 * f * n * d) ** 0.5
+            assert float((s[names[0]][q].double() - want[names[0]][q]).norm()) <= 4e-7 * float(want[names[0]][q].norm()) + slack, q
+            close(s[names[1]][q], want[names[1]][q], n, (names[1], q))
+        assert min(float(t.abs().max()) for t in (s["dXp"][r[2]], s["dXp"][r[3]], s[names[0]][4], s[names[1]][5])) > 2.0 ** -112

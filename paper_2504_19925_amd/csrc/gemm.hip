@@ -1701,8 +1701,8 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_kernel(GemmParams p) {
 // then added to the total, half as many additions as of 16 products each on the fp32 instruction: error against
 // binary64 (relative 2-norm) Y 2.4e-7 -> 1.9e-7, dX 2.8e-7 -> 2.2e-7, dW1 2.7e-7 -> 2.1e-7 on 24 classes of d = 328, f = 872,
 // 8997 rows.  Every value is taken 2^24 times as large (the sum goes back by 2^-48), so that the third part of the smallest
-// fp32 number is a normal bf16 number and no part is lost, whatever stands beside it (16 multiplications per thread and step, step of the
-// shape above 1.5 - 2 % longer; unscaled, values up to 2^-134 had no parts at all).  What leaves the range for it, infinities, NaN,
+// fp32 number is a normal bf16 number and no part is lost, whatever stands beside it (16 multiplications per thread and step, backward
+// of the shape above up to 1 % longer; unscaled, values up to 2^-134 had no parts at all).  What leaves the range for it, infinities, NaN,
 // values from 2^104 and sums from 2^80 on, leaves a sum that is not finite, and the tile is computed once more on the fp32
 // instruction (f32_tile).
 // Tile of 64 x 64 (FWD1: 32 hidden units), four wavefronts of 32 x 32, three workgroups per compute unit that stay and
@@ -1922,6 +1922,10 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
   };
   auto landed = [] { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };
   floatx4 acc[MI][NJ], c[MI][NJ];
+  auto add = [](floatx4& to, const floatx4& x) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) to[e] = fmaf(x[e], F32S_BACK, to[e]);
+  };
   constexpr int NP = MI * NJ, PS = 5 * NP / 12;
   static_assert(MI + NJ <= NP && 12 * PS <= 5 * NP, "a phase has room for its reads, a step for its splits");
   // One step, stage S: six phases, each the product of two planes, the small ones first.  Beside them go the reads of the
@@ -1934,7 +1938,7 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
       constexpr int m = decltype(mc)::value, i = m / NJ, j = m % NJ;
       if constexpr (P == 0) {
         asm volatile("" : "+v"(c[i][j]));
-        acc[i][j] += c[i][j];
+        add(acc[i][j], c[i][j]);
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(c[i][j]) : "v"(fb[QB][j]), "v"(fa[QA][i]));
       } else {
@@ -1984,10 +1988,7 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          bad |= !(fabsf(acc[i][j][e]) <= 3.4e38f);
-          acc[i][j][e] *= F32S_BACK;
-        }
+        for (int e = 0; e < 4; ++e) bad |= !(fabsf(acc[i][j][e]) <= 3.4e38f);
     if (bad) atomicOr(&redo[(tiles >> 5) & 31], 1u << (tiles & 31));
     if (!VARM && t.K == 0 && p.skip_empty) return;
     const int n0 = t.bx * (MODE == FWD1 ? T / 2 : T);
@@ -2068,7 +2069,7 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
         asm volatile("" : "+v"(c[i][j]));
-        acc[i][j] += c[i][j];
+        add(acc[i][j], c[i][j]);
       }
     advance();
     return !have;
@@ -2097,11 +2098,14 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
     });
     meet();
     unroll<MI + NJ>([&](auto r) { read_frag(IC<0>{}, IC<2>{}, IC<0>{}, IC<0>{}, r); });
-    for (;;) {
+    // with a break behind each step the compiler moved a dozen (weight gradients 44) scalars through vector registers in every second one
+    for (bool on = true; on;) {
       step(IC<0>{});
-      if (last_step()) break;
-      step(IC<1>{});
-      if (last_step()) break;
+      on = !last_step();
+      if (on) {
+        step(IC<1>{});
+        on = !last_step();
+      }
     }
   }
 
@@ -2115,15 +2119,13 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
   for (int n = 0; walk.next(t); ++n) {
     // a workgroup's tiles beyond 1024 share their flags: a tile without a sum has none, and may not be written (skip_empty)
     if (t.K == 0 || !(__builtin_amdgcn_readfirstlane(redo[(n >> 5) & 31]) >> (n & 31) & 1)) continue;
-    // uniform, and known to be: the addresses of direct-to-LDS loads are scalars
-    auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
     F32Operands<MODE> o;
-    o.K = uni(t.K);
-    o.group = uni(t.group);
-    o.row0 = uni(t.row0);
-    o.row1 = uni(t.row1);
-    o.bind(p, uni(t.kbeg));
-    const int n0 = uni(t.bx) * (MODE == FWD1 ? T / 2 : T);
+    o.K = t.K;
+    o.group = t.group;
+    o.row0 = t.row0;
+    o.row1 = t.row1;
+    o.bind(p, t.kbeg);
+    const int n0 = t.bx * (MODE == FWD1 ? T / 2 : T);
     meet();
     f32_tile<MODE>(p, o, n0, min(N, n0 + (MODE == FWD1 ? T / 2 : T)), reinterpret_cast<float*>(smem));
   }

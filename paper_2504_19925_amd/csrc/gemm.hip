@@ -1696,7 +1696,7 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_kernel(GemmParams p) {
 
 // ---------------------------------------------------------------- fp32 products on the bf16 matrix instruction
 // An fp32 value is the sum of three bf16 values to 24 bits: x = x0 + x1 + x2, each the bf16 nearest to what the ones
-// before leave.  A product then is x0 y0 + (x0 y1 + x1 y0) + (x1 y1 + x0 y2 + x2 y0) and terms below 2^-26 of it: six matrix
+// before leave.  A product then is x0 y0 + (x0 y1 + x1 y0) + (x1 y1 + x0 y2 + x2 y0) and terms of up to 2^-24.2 of it (2^-27.5 rms): six matrix
 // instructions at 16 times the rate of the fp32 one.  A step of 32 indices is summed from zero, the small terms first, and
 // then added to the total, half as many additions as of 16 products each on the fp32 instruction: error against
 // binary64 (relative 2-norm) Y 2.4e-7 -> 1.9e-7, dX 2.8e-7 -> 2.2e-7, dW1 2.7e-7 -> 2.1e-7 on 24 classes of d = 328, f = 872,
@@ -1704,7 +1704,10 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_kernel(GemmParams p) {
 // fp32 number is a normal bf16 number and no part is lost, whatever stands beside it (16 multiplications per thread and step, backward
 // of the shape above up to 1 % longer; unscaled, values up to 2^-134 had no parts at all).  What leaves the range for it, infinities, NaN,
 // values from 2^104 and sums from 2^80 on, leaves a sum that is not finite, and the tile is computed once more on the fp32
-// instruction (f32_tile).
+// instruction (f32_tile).  Weight gradients of a class (or slot) with one or two rows are computed there alone: the terms left
+// out are more than the few additions save.  Relative 2-norm, 1e-8, fp32 instruction : split, 1 row 2.5 : 3.5 (largest 6.0 : 14.2), 2 rows 3.2 :
+// 3.4, 3 rows 3.6 : 3.4, 8 rows 5.3 : 3.5, 128 rows 9.2 : 6.0; backward of 24 classes of d = 328, f = 872, twelve with one row and twelve with 600,
+// 296 -> 304 us.
 // Tile of 64 x 64 (FWD1: 32 hidden units), four wavefronts of 32 x 32, three workgroups per compute unit that stay and
 // take one tile after the other.  A thread loads 16 values of a step into registers, two to three steps ahead, splits
 // them beside the matrix instructions of the step before and writes the planes to the other of two LDS stages; one barrier per step.
@@ -1718,6 +1721,8 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_kernel(GemmParams p) {
 // for (r >> 2) & 3; reduction-strided [k][64 columns] as loaded, 32-byte piece c of row k at c ^ (((k >> 1) & 1) + 2 ((k >> 3) & 1)), read transposing.
 constexpr int F32S_T = 64, F32S_BK = 32;   // tile edge, step
 constexpr float F32S_SCALE = 0x1p24f, F32S_BACK = 0x1p-48f;
+constexpr int F32S_FEW = 2;                // rows of a class up to which its gradients are the fp32 instruction's
+constexpr int F32S_FLAGS = 1024;           // words of flags: for 32768 tiles of a workgroup, some 400 GB of outputs
 
 // The tiles of a product that one workgroup computes, one after the other.  XCD x (workgroup number mod 8) takes an eighth of
 // the row tiles with all their columns, or of every class's tiles, the classes in order of decreasing row count.
@@ -1792,7 +1797,7 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
   constexpr int PL = T * F32S_BK * 2, ST = 6 * PL;           // bytes: a plane, a stage
   constexpr int EXACT = 2 * 4 * (F32_BM + 128) * 32;
   __shared__ __attribute__((aligned(1024))) char smem[2 * ST > EXACT ? 2 * ST : EXACT];
-  __shared__ unsigned redo[32];
+  __shared__ unsigned redo[F32S_FLAGS + 1];   // tiles for the fp32 instruction; any at all
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1, g4 = lane >> 4, jj = lane & 15;
@@ -1807,7 +1812,9 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
-  if (tid < 32) redo[tid] = 0;
+  for (int q = tid; q <= F32S_FLAGS; q += 256) redo[q] = 0;
+  meet();   // a tile without a split sum is flagged at once
+  auto summed = [](const F32Tile& tile) { return VARM || tile.K > F32S_FEW; };
 
   // ---- loads: two of the left operand, two of the right one per thread and step
   unsigned ls[4], vo[4];   // byte offsets inside a stage and in memory
@@ -1839,7 +1846,7 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
     while (lk >= lK && more) {
       const F32Tile t = nx;
       more = ahead.next(nx);
-      lK = t.K;
+      lK = summed(t) ? t.K : 0;
       lk = 0;
       const int n0 = t.bx * (MODE == FWD1 ? T / 2 : T);
       a0 = static_cast<const float*>(p.A) + (VARM ? (long long)t.row0 * lda : (long long)t.kbeg * lda + t.row0);
@@ -1982,15 +1989,18 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
       for (int j = 0; j < NJ; ++j) acc[i][j] = c[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
   };
   auto write_out = [&] {
-    bool bad = false;
+    bool bad = !summed(t) && t.K > 0;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int e = 0; e < 4; ++e) bad |= !(fabsf(acc[i][j][e]) <= 3.4e38f);
-    if (bad) atomicOr(&redo[(tiles >> 5) & 31], 1u << (tiles & 31));
-    if (!VARM && t.K == 0 && p.skip_empty) return;
+    if (bad) {
+      atomicOr(&redo[(tiles >> 5) & (F32S_FLAGS - 1)], 1u << (tiles & 31));
+      redo[F32S_FLAGS] = 1;
+    }
+    if (!summed(t) && (t.K > 0 || p.skip_empty)) return;
     const int n0 = t.bx * (MODE == FWD1 ? T / 2 : T);
     const long long rb0 = t.row0 + wm * WR;
     const int rows = t.row1 - (int)rb0, twof = 2 * p.f;
@@ -2051,7 +2061,7 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
       ++tiles;
       have = walk.next(t);
       clear();
-    } while (have && t.K == 0);
+    } while (have && !summed(t));
     k0 = 0;
   };
   auto last_step = [&]() -> bool {   // behind a step: the tile's sums are complete
@@ -2077,7 +2087,7 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
   clear();
 #pragma unroll
   for (int j = 0; j < NJ; ++j) fb[0][j] = fb[3][j] = bf16x8{};
-  while (have && t.K == 0) {
+  while (have && !summed(t)) {
     write_out();
     ++tiles;
     have = walk.next(t);
@@ -2109,16 +2119,13 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
     }
   }
 
-  // ---- tiles with a sum that is not finite: once more on the fp32 instruction
+  // ---- tiles with a sum that is not finite, and those without a split sum: on the fp32 instruction
   meet();
-  unsigned any = 0;
-#pragma unroll
-  for (int q = 0; q < 32; ++q) any |= redo[q];
-  if (__builtin_amdgcn_readfirstlane(any) == 0) return;
+  if (__builtin_amdgcn_readfirstlane(redo[F32S_FLAGS]) == 0) return;
   walk.i = 0;
   for (int n = 0; walk.next(t); ++n) {
-    // a workgroup's tiles beyond 1024 share their flags: a tile without a sum has none, and may not be written (skip_empty)
-    if (t.K == 0 || !(__builtin_amdgcn_readfirstlane(redo[(n >> 5) & 31]) >> (n & 31) & 1)) continue;
+    // a tile without rows has no flag; should tiles share their flags, it may not be written all the same (skip_empty)
+    if (t.K == 0 || !(__builtin_amdgcn_readfirstlane(redo[(n >> 5) & (F32S_FLAGS - 1)]) >> (n & 31) & 1)) continue;
     F32Operands<MODE> o;
     o.K = t.K;
     o.group = t.group;

@@ -72,3 +72,26 @@ def test_values_without_bf16_parts():
             assert float((s[names[0]][q].double() - want[names[0]][q]).norm()) <= 4e-7 * float(want[names[0]][q].norm()) + slack, q
             close(s[names[1]][q], want[names[1]][q], n, (names[1], q))
         assert min(float(t.abs().max()) for t in (s["dXp"][r[2]], s["dXp"][r[3]], s[names[0]][4], s[names[1]][5])) > 2.0 ** -112
+
+
+def test_classes_with_few_rows():
+    """Weight gradients of one and two rows among classes of hundreds: as exact as products rounded once each, class by class (in
+    the norm of a whole output they would not be seen)."""
+    d, f = 264, 328
+    rows = [1, 2, 200, 1, 3, 2, 0, 500] * 8
+    s = layer(rows, list(range(65)), d, f, seed=11)
+    s["Xp"][:, 0] = 1.0     # the first column of dW1 is the sum of du, dv
+    run(s)
+    b = (s["ctx"], s["dYp"], s["Xp"], s["UV"], s["H"], s["off"], s["first"], s["W1"], s["W2"], s["dXp"])
+    aW1, aW2 = torch.zeros_like(s["dW1"]), torch.zeros_like(s["dW2"])
+    symi.symi_expert_bwd_active(*b, aW1, aW2, s["ws"])
+    for gW1, gW2 in ((s["dW1"], s["dW2"]), (s["sW1"], s["sW2"]), (aW1, aW2)):
+        for e, n in enumerate(rows):
+            r = slice(s["offs"][e], s["offs"][e] + n)
+            dY, H, X = (s[t][r].double() for t in ("dYp", "H", "Xp"))
+            # n products and n - 1 additions of them, each rounded to 2^-24 of at most the sum of their magnitudes
+            err = (gW2[e].double() - dY.T @ H).abs()
+            assert bool((err <= n * 2.0 ** -24 * (dY.abs().T @ H.abs())).all()), (e, n)
+            if n == 1:
+                want = gW1[e].double()[:, :1] @ X
+                assert bool(((gW1[e].double() - want).abs() <= 2.0 ** -24 * want.abs()).all()), e

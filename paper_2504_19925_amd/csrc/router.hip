@@ -586,6 +586,11 @@ __global__ __launch_bounds__(256) void router_finish_kernel(RouterParams p, int 
 }
 
 // ---- fp32 configurations: plain FMAs
+// Workgroups in one row of up to 2^20 and as many rows as it takes: a dimension of a launch ends at 2^32 threads, which 2^20
+// tokens of d = 2048, E = 256 pass.  There are fewer than 2^32 workgroups of anything that fits the memory; those behind the last have no work.
+__device__ __forceinline__ unsigned flat_block() { return blockIdx.y * gridDim.x + blockIdx.x; }
+static dim3 flat_grid(long long n) { return n <= 1 << 20 ? dim3((unsigned)n) : dim3(1 << 20, cdiv(n, 1 << 20)); }
+
 // Eight lanes share the reductions of a token with four classes: pieces of eight indices dealt out in turn, 256 consecutive
 // bytes of X and of each row of Wr per load round, the eight sums added in a fixed tree.  Bound by latency: with one
 // thread per logit, a chain of d / 8 rounds, T = 139, E = 16, d = 288 took 11.5 us; error 1.4e-7 -> 0.6e-7.
@@ -594,7 +599,7 @@ __global__ __launch_bounds__(256) void router_fwd_f32_kernel(const float* __rest
                                                              const float* __restrict__ b,
                                                              float* __restrict__ logits, int T, int E, int d) {
   const int lane = threadIdx.x & 7, eq = (E + 3) / 4;
-  const long long g = (long long)blockIdx.x * 32 + (threadIdx.x >> 3);
+  const long long g = (long long)flat_block() * 32 + (threadIdx.x >> 3);
   const long long t = min(g / eq, (long long)T - 1);   // lanes behind the last token repeat it and store nothing
   const int e0 = (int)(g % eq) * 4;
   const float* const x = X + t * d;
@@ -685,12 +690,12 @@ __device__ __forceinline__ void router_dw_f32(const RouterParams& p, const int b
 // Weight gradient, dX and the first stage of the bias gradient in one launch.
 __global__ __launch_bounds__(64 * RF_WAVES) void router_bwd_f32_kernel(RouterParams p, unsigned ndx) {
   __shared__ __attribute__((aligned(16))) float red[RF_WAVES * RF_CLASSES * 64];
-  const unsigned dx = (p.d + 63) / 64, de = (p.E + RF_CLASSES - 1) / RF_CLASSES, ndw = dx * de * p.nchunk, b = blockIdx.x;
+  const unsigned dx = (p.d + 63) / 64, de = (p.E + RF_CLASSES - 1) / RF_CLASSES, ndw = dx * de * p.nchunk, b = flat_block();
   if (b < ndw) {
     router_dw_f32(p, b % dx, b / dx % de, b / (dx * de), red);
   } else if (b < ndw + ndx) {
     router_dx_f32(p, (long long)(b - ndw) * (64 * RF_WAVES) + threadIdx.x);
-  } else {
+  } else if ((int)(b - ndw - ndx) < p.nbias) {
     router_bias_partial(p.dl, p.T, p.E, b - ndw - ndx, p.bias, reinterpret_cast<double*>(red));
   }
 }
@@ -709,7 +714,7 @@ extern "C" int symi_router_fwd(const symi_ctx* ctx, const void* X, const void* W
   if (cfg->dtype == SYMI_BF16) {
     launch_router_fwd(ctx, X, Wr, b, logits, st);
   } else {
-    SYMI_TIMED(ctx, K_ROUTER_FWD, st, (router_fwd_f32_kernel<<<cdiv((long long)T * cdiv(E, 4), 32), 256, 0, st>>>(
+    SYMI_TIMED(ctx, K_ROUTER_FWD, st, (router_fwd_f32_kernel<<<flat_grid(cdiv((long long)T * cdiv(E, 4), 32)), 256, 0, st>>>(
         static_cast<const float*>(X), static_cast<const float*>(Wr), b, logits, T, E, d)));
   }
   SYMI_LAUNCH_CHECK("symi_router_fwd");
@@ -744,7 +749,8 @@ extern "C" int symi_router_bwd(const symi_ctx* ctx, const void* X, const void* W
     }
   } else if (T > 0) {
     const int ndx = cdiv((long long)T * d, 64 * RF_WAVES);
-    SYMI_TIMED(ctx, K_ROUTER_DX, st, (router_bwd_f32_kernel<<<cdiv(d, 64) * cdiv(E, RF_CLASSES) * p.nchunk + ndx + p.nbias, 64 * RF_WAVES, 0, st>>>(p, ndx)));
+    const long long all = (long long)cdiv(d, 64) * cdiv(E, RF_CLASSES) * p.nchunk + ndx + p.nbias;
+    SYMI_TIMED(ctx, K_ROUTER_DX, st, (router_bwd_f32_kernel<<<flat_grid(all), 64 * RF_WAVES, 0, st>>>(p, ndx)));
   }
   if (!once) {
     const int nred = cdiv((long long)E * d, 256);

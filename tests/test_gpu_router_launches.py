@@ -32,3 +32,37 @@ def test_against_binary64(dtype, E, d, T, bias):
                                ("dX", dX, dX0.double() + dld @ Wd, tol), ("db", db, dld.sum(0) if bias else torch.full_like(db, 7.0).double(), 4e-7)):
         err = float((got.double() - want).norm() / want.norm())
         assert err <= t, (name, err)
+
+
+def test_scores_beyond_the_threads_of_one_dimension():
+    """2^21 tokens of 1024 classes in fp32: 2^32 threads, more than one dimension of a launch takes."""
+    T, E, d = 1 << 21, 1024, 8
+    ctx, dev = symi.symi_create(symi.SymiCfg.make(T, E, 1, d, 8, E, 1, 0, "f32", 1)), "cuda"
+    X, Wr = torch.randn(T, d, device=dev), torch.randn(E, d, device=dev)
+    logits = torch.full((T, E), 7.0, device=dev)
+    symi.symi_router_fwd(ctx, X, Wr, None, logits)
+    for t in (0, 1 << 19, T - 512):
+        want = X[t:t + 512].double() @ Wr.double().T
+        assert float((logits[t:t + 512].double() - want).norm() / want.norm()) <= 4e-7, t
+
+
+def test_gradients_beyond_the_threads_of_one_dimension():
+    """2^20 tokens of d = 2048, E = 256 in fp32: 2^32 threads and some; 2^31 elements of X."""
+    T, E, d = 1 << 20, 256, 2048
+    cfg = symi.SymiCfg.make(T, E, 1, d, 8, E, 1, 0, "f32", 1)
+    ctx, dev = symi.symi_create(cfg), "cuda"
+    X, Wr, dl = torch.randn(T, d, device=dev), torch.randn(E, d, device=dev), torch.randn(T, E, device=dev)
+    dX, dWr, db = torch.ones(T, d, device=dev), torch.full((E, d), 7.0, device=dev), torch.full((E,), 7.0, device=dev)
+    ws = torch.empty(symi.symi_workspace_bytes(cfg), dtype=torch.uint8, device=dev)
+    symi.symi_router_bwd(ctx, X, Wr, dl, dWr, db, dX, ws)
+    wW, wb = torch.zeros(E, d, dtype=torch.float64, device=dev), torch.zeros(E, dtype=torch.float64, device=dev)
+    for t in range(0, T, 1 << 17):
+        r = slice(t, t + (1 << 17))
+        wW += dl[r].double().T @ X[r].double()
+        wb += dl[r].double().sum(0)
+        q = slice(t + (1 << 17) - 256, t + (1 << 17))
+        want = 1 + dl[q].double() @ Wr.double()
+        assert float((dX[q].double() - want).norm() / want.norm()) <= 4e-7, t
+    # sums of 2^20 terms: chunks of 512 and then 2048 chunks in ascending order, 2^-24 sqrt(2048) at most
+    assert float((dWr.double() - wW).norm() / wW.norm()) <= 3e-6
+    assert float((db.double() - wb).norm() / wb.norm()) <= 3e-6

@@ -1708,6 +1708,8 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_kernel(GemmParams p) {
 // out are more than the few additions save.  Relative 2-norm, 1e-8, fp32 instruction : split, 1 row 2.5 : 3.5 (largest 6.0 : 14.2), 2 rows 3.2 :
 // 3.4, 3 rows 3.6 : 3.4, 8 rows 5.3 : 3.5, 128 rows 9.2 : 6.0; backward of 24 classes of d = 328, f = 872, twelve with one row and twelve with 600,
 // 296 -> 304 us.
+// What that costs, 24 classes of 375 rows, no infinity / one / one in every 64 rows: forward 179 / 193 / 406 us, backward 344 / 361 / 859.  A
+// tile's values alone decide it, so a row's bits depend on the up to 63 rows beside it where one of them is out of the range.
 // Tile of 64 x 64 (FWD1: 32 hidden units), four wavefronts of 32 x 32, three workgroups per compute unit that stay and
 // take one tile after the other.  A thread loads 16 values of a step into registers, two to three steps ahead, splits
 // them beside the matrix instructions of the step before and writes the planes to the other of two LDS stages; one barrier per step.
@@ -1936,7 +1938,7 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_split_kernel(GemmParams p, in
   constexpr int NP = MI * NJ, PS = 5 * NP / 12;
   static_assert(MI + NJ <= NP && 12 * PS <= 5 * NP, "a phase has room for its reads, a step for its splits");
   // One step, stage S: six phases, each the product of two planes, the small ones first.  Beside them go the reads of the
-  // next phases' fragments, and in the first five the next step's splits into the other stage with the loads of the step
+  // next phases' fragments, and in the first three the next step's splits into the other stage with the loads of the step
   // after the next but one; in the last one the other stage is entered.
   auto phase = [&](auto sc, auto pc, auto qac, auto qbc) {
     constexpr int S = decltype(sc)::value, P = decltype(pc)::value, QA = decltype(qac)::value, QB = decltype(qbc)::value;

@@ -95,3 +95,84 @@ def test_classes_with_few_rows():
             if n == 1:
                 want = gW1[e].double()[:, :1] @ X
                 assert bool(((gW1[e].double() - want).abs() <= 2.0 ** -24 * want.abs()).all()), e
+
+
+def out_of_range(s, r):
+    """Infinities, NaN and values beyond what three bf16 parts hold, one kind to a slot: those of the forward in place, those of
+    the backward by the returned function."""
+    s["Xp"][r[1]][5, 7] = float("inf")
+    s["Xp"][r[2]][6, 3] = float("nan")
+    s["W1"][3][9, 11] = float("-inf")
+    s["W2"][4][5, 7] = float("inf")
+    s["W2"][5][2] = 1e33
+    s["Xp"][r[6]][70, 100] = 2e33
+    s["W1"][6] *= 1e-20
+
+    def later():
+        s["dYp"][r[8]][3, 3] = float("inf")
+        s["dYp"][r[9]] *= 1e33
+        s["H"][r[10]][12, 9] = float("nan")
+        s["H"][r[11]] *= 1e33
+        s["UV"][r[13]][1, 4] = float("inf")
+        s["UV"][r[14]][60, -3] = float("-inf")
+        s["Xp"][r[15]] *= 1e33
+        s["W2"][16][3, 4] = float("nan")
+        s["W1"][17][:, 5] = 1e33
+    return later
+
+
+def same(got, want, size, what):
+    """The same infinities and NaN, and finite results to 2e-5 of `size`, the sum of the magnitudes (32-bit sums of up to 1040 products,
+    rounded in turn, of values that are such sums themselves: 1040 2^-24 and less)."""
+    got, want = got.double(), want.float().double()     # beyond fp32: infinite
+    assert torch.equal(torch.isnan(got), torch.isnan(want)), what
+    assert torch.equal(torch.isinf(got), torch.isinf(want)) and torch.equal(got[torch.isinf(got)], want[torch.isinf(want)]), what
+    ok = torch.isfinite(want)
+    assert bool(((got - want).abs()[ok] <= 2e-5 * size[ok] + 1e-37).all()), what
+
+
+@pytest.mark.parametrize("d,f", [(264, 520), (328, 392)])
+def test_every_product_out_of_range(d, f):
+    """Six products, gradients per class, per slot and of the active classes, several tiles to a workgroup, remainders of rows and
+    columns and classes without rows: what 32-bit products give, in the tiles that are computed once more and in the others."""
+    rows = [100, 130, 64, 0, 77, 200] * 8
+    rows[3], rows[9], rows[15] = 70, 90, 80
+    first = [0, 1, 2, 3, 5, 8] + list(range(9, 49))
+    s = layer(rows, first, d, f, seed=13)
+    r = [slice(s["offs"][q], s["offs"][q + 1]) for q in range(48)]
+    later = out_of_range(s, r)
+    D, big = torch.float64, lambda t: t.double().abs().nan_to_num(0, 0, 0)
+    symi.symi_expert_fwd(s["ctx"], s["Xp"], s["off"], s["W1"], s["W2"], s["UV"], s["H"], s["Yp"], s["ws"])
+    for q in range(48):
+        X, W1, W2, H = s["Xp"][r[q]], s["W1"][q], s["W2"][q], s["H"][r[q]]
+        same(s["UV"][r[q]], X.to(D) @ W1.to(D).T, big(X) @ big(W1).T, ("UV", q))
+        same(s["Yp"][r[q]], H.to(D) @ W2.to(D).T, big(H) @ big(W2).T, ("Yp", q))
+    later()
+    dX, mX = torch.zeros_like(s["dXp"], dtype=D), torch.zeros_like(s["dXp"], dtype=D)
+    duv, mduv = torch.zeros_like(s["UV"], dtype=D), torch.zeros_like(s["UV"], dtype=D)
+    for q in range(48):
+        dY, W1, W2 = s["dYp"][r[q]], s["W1"][q], s["W2"][q]
+        u, v = s["UV"][r[q]][:, :f], s["UV"][r[q]][:, f:]
+        dh, mh, sg = (dY.to(D) @ W2.to(D)).float(), big(dY) @ big(W2), torch.sigmoid(u)
+        duv[r[q]] = torch.cat([dh * v * sg * (1 + u * (1 - sg)), dh * u * sg], 1).to(D)
+        mduv[r[q]] = torch.cat([mh * big(v * sg * (1 + u * (1 - sg))), mh * big(u * sg)], 1)
+        dX[r[q]], mX[r[q]] = duv[r[q]] @ W1.to(D), mduv[r[q]] @ big(W1)
+    b = (s["ctx"], s["dYp"], s["Xp"], s["UV"], s["H"], s["off"], s["first"], s["W1"], s["W2"], s["dXp"])
+    slots = [(q, q + 1) for q in range(48)]
+    for call, n1, n2, groups in ((symi.symi_expert_bwd, "dW1", "dW2", list(zip(first, first[1:]))),
+                                 (symi.symi_expert_bwd_active, "dW1", "dW2", list(zip(first, first[1:]))),
+                                 (symi.symi_expert_bwd_slots, "sW1", "sW2", slots)):
+        for t in ("dXp", n1, n2):
+            s[t].fill_(7.0)
+        call(*b, s[n1], s[n2], s["ws"])
+        for q in range(48):
+            same(s["dXp"][r[q]], dX[r[q]], mX[r[q]], ("dXp", call.__name__, q))
+        for g, (q0, q1) in enumerate(groups):
+            at = slice(s["offs"][q0], s["offs"][q1])
+            if at.start == at.stop:
+                kept = 7.0 if call is symi.symi_expert_bwd_active else 0.0
+                assert bool((s[n1][g] == kept).all()) and bool((s[n2][g] == kept).all()), (call.__name__, g)
+                continue
+            X, H, dY = s["Xp"][at], s["H"][at], s["dYp"][at]
+            same(s[n1][g], duv[at].T @ X.to(D), mduv[at].T @ big(X), (n1, call.__name__, g))
+            same(s[n2][g], dY.to(D).T @ H.to(D), big(dY).T @ big(H), (n2, call.__name__, g))

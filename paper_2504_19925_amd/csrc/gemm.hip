@@ -67,8 +67,9 @@ __device__ __forceinline__ float sigmoid_fast(float u) {
 
 // ---------------------------------------------------------------- m-tile table
 // map[0] = number of m-tiles, map[4 + 4i ..] = {first row, end row, slot} of m-tile i (TM = 256 rows), or
-// map[4 + 2i ..] = {first row, slot + 2^16 * (rows - 1)} (TM = FEW_BM: the fp32 products and the small-batch forward products; of these at most
-// 32 rows per slot on average make at most 1.5 S_tot tiles, which fit where 256-row tiles would be).
+// map[4 + 2i ..] = {first row, slot + 2^16 * (rows - 1)} (TM = FEW_BM: the fp32 products, whose workspace holds two words
+// for each 64-row tile, and the bf16 small-batch forward products, whose at most 32 rows per slot on average make at most 1.5 S_tot
+// tiles, which fit where 256-row tiles would be; TM = MID_BM: the 128 x 128 tile).
 // order[c] = the class with the c-th largest number of rows (ties: lower index first).
 constexpr int FEW_BM = 64, MID_BM = 128;
 
@@ -1351,7 +1352,7 @@ __global__ __launch_bounds__(GT, 2) void gemm_duo_kernel(GemmParams p) {
   wait_vmcnt0();
   __syncthreads();   // nobody's loads are in flight and nobody reads operands any more: the stages become the staging area
   if (idle) return;
-  SavedUV<4> saved[2];   // the hidden gradient's
+  SavedUV<4> saved[2];   // write_tile's, of the hidden gradient alone
   write_tile<MODE, 2, 4>(p, smem + wave * (NST * (SA + SB) / 4), acc, row0, row1, group, n0, wm, wn, lane, -1, saved);
 }
 
@@ -1714,7 +1715,7 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_kernel(GemmParams p) {
 // take one tile after the other.  A thread loads 16 values of a step into registers, two to three steps ahead, splits
 // them beside the matrix instructions of the step before and writes the planes to the other of two LDS stages; one barrier per step.
 // Bound by the vector instructions of the splits next to the matrix instructions (28 % of the matrix pipes' time is theirs
-// with 128 x 128 tiles), and where the tiles are few by the last round of them.  Step of the shape above 767 -> 598 us, forward of
+// with 128 x 128 tiles), and where the tiles are few by the last round of them.  Step of the shape above 767 -> 598 - 606 us, forward of
 // 24 classes of d = 256, f = 576, 18096 rows 154 -> 118, backward of 4 classes of d = 104, f = 896, 1412 rows 107 -> 78; 75 drawn
 // layers 1.10 (0.96 - 1.41).  Tried and dropped: 128 x 128 tiles with eight wavefronts (that step 620: fewer splits per product, but 273
 // tiles of the input gradient are two rounds of 256), half of the wavefronts loading and splitting for the other half (616 - 640), everything
@@ -2696,7 +2697,10 @@ static int expert_bwd_impl(const char* who, const symi_ctx* ctx, const void* dYp
   p.f = cfg->f;
   TileMaps maps = {};
   // The order of the classes matters to the gradients' last round only; short ones of a small batch go without it, and
-  // without a launch where no product reads a table (some 4 us: slot gradients of E = 16, d = 168, f = 584, 98 rows 44 -> 41 us).
+  // without a launch where no product reads a table (some 4 us: slot gradients of E = 16, d = 168, f = 584, 98 rows 44 -> 41 us).  Ordered : not, backward
+  // of drawn layers whose launch it is, by rows: up to 2560 1.05 (0.99 - 1.07), to 4096 1.02, the gain of 3 - 4 % where the classes are even, 0.89 - 0.98 in
+  // four of 40, with a few popular ones (64 classes of d = 368, f = 552, 4052 rows, the most popular with a quarter of them, 104 : 118 us), to 9200
+  // 1.01 (0.88 - 1.10): the launch is a smaller part, the late long reduction a larger one.
   bool ordered = !per_slot;
   if (cfg->dtype == SYMI_F32) {
     if (f32_table(ctx, {BWD_DH, BWD_DX, WGRAD2, WGRAD1}, per_slot)) maps.of64 = map;

@@ -11,7 +11,7 @@
 // the latency.
 // The weight gradient's reduction runs over all T tokens: it is cut into chunks (router_chunk) whose partial products
 // are summed by a second kernel in a fixed order; a single chunk's sums are the gradient.
-// The whole backward is one launch of products and bias sums and, beyond 128 tokens, one that adds the chunks up: as four to five
+// The whole backward is one launch of products and bias sums and, beyond one chunk, one that adds the chunks up: as four to five
 // launches small batches took some 4 us for each.  Gate network with the dispatch's backward, us: T = 636, E = 128, d = 208
 // 37 -> 19, 134, 48, 600 29 -> 21, 2261, 12, 1312 73 -> 62, 44033, 48, 152 95 -> 72, 65536, 128, 4096 1502 -> 1492; fp32 (with the logits' lane groups and the
 // weight gradient's loads without branches): 139, 4, 384 37 -> 13, 1769, 16, 512 57 -> 24, 4683, 24, 96 44 -> 23.

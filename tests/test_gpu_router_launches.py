@@ -66,3 +66,19 @@ def test_gradients_beyond_the_threads_of_one_dimension():
     # sums of 2^20 terms: chunks of 512 and then 2048 chunks in ascending order, 2^-24 sqrt(2048) at most
     assert float((dWr.double() - wW).norm() / wW.norm()) <= 3e-6
     assert float((db.double() - wb).norm() / wb.norm()) <= 3e-6
+
+
+@pytest.mark.parametrize("T", [100, 700])
+def test_fp32_buffers_at_any_element(T):
+    """fp32 buffers that begin 4 bytes behind a 16-byte boundary, as slices of a flat parameter buffer do: wide loads and stores."""
+    E, d, dev = 12, 136, "cuda"
+    cfg = symi.SymiCfg.make(T, E, 1, d, 8, E, 1, 0, "f32", 1)
+    ctx = symi.symi_create(cfg)
+    at = lambda *n: torch.randn(1 + torch.Size(n).numel() + 7, device=dev)[1:1 + torch.Size(n).numel()].view(*n)
+    X, Wr, dl, dX, dWr, logits = at(T, d), at(E, d), at(T, E), at(T, d), at(E, d), at(T, E)
+    dX0, ws = dX.double(), torch.empty(symi.symi_workspace_bytes(cfg), dtype=torch.uint8, device=dev)
+    symi.symi_router_fwd(ctx, X, Wr, None, logits)
+    symi.symi_router_bwd(ctx, X, Wr, dl, dWr, None, dX, ws)
+    for name, got, want in (("logits", logits, X.double() @ Wr.double().T), ("dWr", dWr, dl.double().T @ X.double()),
+                            ("dX", dX, dX0 + dl.double() @ Wr.double())):
+        assert float((got.double() - want).norm() / want.norm()) <= 4e-7, name
